@@ -253,27 +253,23 @@ int mra_align_batch(mra_ctx* ctx, const mra_stack* stacks, int32_t n);
 
 /* Tile configuration of a refset's correlation kernel (chosen by the
  * autotuner in paper_2011_05755_amd/autotune.py, or left at the default).
- *  corr_variant  -1: default for the geometry.  FP32: 0 = 8 waves with the
- *                particle operand held in registers (R4 = ceil(n_rings/4) <= 9),
- *                1 = 4 waves, operand in registers (R4 <= 12), 2 = 8 waves,
- *                operand streamed (any R4).  BF16/FP16: 0 = operand converted
- *                once per row tile and held in registers, 1 = operand re-read
- *                and converted per reference tile.  MRA_E_INVAL if the variant
- *                cannot serve the geometry.
+ *  corr_variant  tile configuration of the evaluation of every pair (prune = 0,
+ *                calls of few particles).  -1: default for the geometry.  FP32:
+ *                0 = 8 waves with the particle operand held in registers
+ *                (R4 = ceil(n_rings/4) <= 9), 1 = 4 waves, operand in registers
+ *                (R4 <= 12), 2 = 8 waves, operand streamed (any R4).  BF16/FP16:
+ *                0 = operand held in registers, 1 = operand re-read per reference
+ *                tile.  MRA_E_INVAL if the variant cannot serve the geometry.
  *  chunk_particles  particles per chunk (0: derived from the workspace cap);
  *                also caps the pieces mra_align_batch cuts the refset's stacks into.
- *  prune         -1 or 1: skip the inverse FFT over angle of every (particle
- *                row, reference) pair whose upper bound on the CC (from its
- *                spectrum: exact magnitudes of the 32 lowest frequency slots,
- *                Cauchy-Schwarz over the energy of the rest) lies below the
- *                best so far of the pair's row, or of any row of the same
- *                particle, so it cannot win; 0: evaluate every pair.
- *  run_tiles     consecutive 8-row tiles one correlation workgroup takes in
- *                order, carrying each particle's best from one tile to the
- *                next (longer runs prune more, shorter ones balance the
- *                launch better); 0: chosen from the launch size (up to 8
- *                while every CU gets 3 runs, up to 48 while it gets 20),
- *                else 1..64.
+ *  prune         -1 or 1: an upper bound of the CC over all angles and both
+ *                mirrors of every (particle row, reference) pair is taken from
+ *                16-bit products (for FP32 raised by what their rounding can
+ *                change), and only the pairs whose bound can still win are
+ *                evaluated, in the refset's precision, best bound first; 0:
+ *                evaluate every pair.  (A call of few particles, or with a
+ *                workspace too small for the bounds, evaluates every pair.)
+ *  run_tiles     0 .. 64, accepted and reported; no longer used.
  * Results do not depend on the tuning (bit for bit). */
 typedef struct mra_tuning {
   int32_t corr_variant;
@@ -298,9 +294,11 @@ int mra_debug_refs(mra_ctx* ctx, int32_t refset_id, float* qhat, double* norm);
 
 /* Kernel timing for measurement.  mra_profile(ctx, 1) clears and starts
  * recording a HIP event pair around every launch of the named kernel groups
- * ("polar", "corr", "merge", "rescore", "maxabs", "averages", "corr2" for
- * the runner-up pass of cc2, "rfa" for the fused K = 1 kernel and "refine"
- * for psi_frac) on the context's stream;
+ * ("polar", "bound", "tighten", "fine" and "fine2" for the resampling, the
+ * bounds, the FP16 tightening of FP32 bounds, the evaluation of the pairs that
+ * can win and its runner-up pass of cc2; "corr", "merge" and "corr2" where
+ * every pair is evaluated; "rescore", "averages", "rfa" for the fused K = 1
+ * kernel and "refine" for psi_frac) on the context's stream;
  * mra_profile(ctx, 0) stops.  mra_profile_read synchronises the stream and
  * returns the summed device time and the launch count of one group. */
 int mra_profile(mra_ctx* ctx, int enable);

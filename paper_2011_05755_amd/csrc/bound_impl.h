@@ -1,0 +1,321 @@
+// Upper bound of the CC of every (row, reference) pair over all 256 angles
+// and both mirrors, from a 16-bit contraction whose results never leave the
+// registers: the first half of the arg-max, which decides which pairs the
+// second half (fine_impl.h) has to evaluate.
+//
+// With the entries U of a pair's 16-bit products (see corr_impl.h), per mirror m,
+//   c_m(a) <= |g_0| + |g_128| + sum_{f=1}^{127} 2 |G_m,f|      (triangle inequality),
+//   2|G_0,f| = |(U00 + U11, U01 - U10)|, 2|G_1,f| = |(U01 + U10, U00 - U11)|.
+// The 16 lowest slots enter with these magnitudes; the others, in groups of
+// 2, 4 and 8 slots, through Cauchy-Schwarz over the group's energy:
+// sum 2|G_m,f| <= sqrt(n 2 sum U^2) for n slots (no exchange between lanes
+// and one square root per group; on 76 px, 100 references it leaves about a
+// quarter more pairs than all 128 magnitudes would).  The bound is raised by
+// 2^-12 of itself against its own rounding and that of the inverse FFT
+// (both below 10^-5 relative).
+//
+// FP32 alignment (ERR): the operands here are the FP32 ones rounded to FP16
+// (scaled by powers of two), so the bound is also raised by what that rounding
+// can change.  With |a - fl(a)| <= u |a| + eta (u = 2^-11; eta = 2^-14, the
+// smallest normal number, so that flushed subnormals are covered), per slot
+// |dU_pq| <= |da_p||b_q| + |a_p||db_q| + |da_p||db_q| over the rings, and
+//   sum_f |d(2 G_f)| <= sqrt(2) (Da Nb + Na Db + Da Db),
+// Na, Nb the norms of the row's and the reference's whole operand and Da =
+// u Na + eta sqrt(n), Db alike (n elements each).  That is about 0.5 % of a
+// particle's best CC at SNR 0.05.  A particle whose pixels do not scale into
+// FP16 (not finite, or within 2^9 of overflow) gets infinite bounds.
+//
+// One 8-wave workgroup holds the operand of NT row tiles (16 rows; 8 where
+// more than 48 rings leave no registers for two) in registers, wave w the
+// slots w + 8 i, and streams the reference operand once for all of them: the
+// stream from L2 is what bounds the kernel (160 KiB per reference tile at 35
+// rings), so two row tiles per read halve it.  The waves' partial bounds meet
+// in LDS every kBoundTiles reference tiles, in two alternating buffers: one
+// barrier per kBoundTiles.
+#pragma once
+
+#include "corr_impl.h"
+
+namespace mra {
+
+constexpr int kBoundTiles = 4;
+
+// Bound terms of one pair of lanes and row tile.  Lane q = ln & 1 gathers row
+// 2 (ln / 16) + q; with x, y its own entries of that row and u, v the partner
+// lane's, (x, y, u, v) = (U00, U10, U01, U11) in lane q = 0 and (U01, U11, U00,
+// U10) in lane q = 1: the two magnitudes come out with the mirrors swapped in
+// lane q = 1, which is undone once, when the sums are stored.
+struct BoundSum {
+  float b0, b1;  // exact magnitudes (swapped mirrors in odd lanes)
+  float c;       // group terms, the same for both mirrors
+  float e0, e1;  // energy of the running group: rows 2 (ln / 16) and 2 (ln / 16) + 1, this lane's column
+  __device__ __forceinline__ void clear() { b0 = b1 = c = e0 = e1 = 0.f; }
+  __device__ __forceinline__ void exact(const f32x4& acc, bool q, bool slot0) {
+    const float x = q ? acc[2] : acc[0], y = q ? acc[3] : acc[1];
+    const float u = swap_adjacent(q ? acc[0] : acc[2]), v = swap_adjacent(q ? acc[1] : acc[3]);
+    const float s = x + v, d = x - v, s2 = u + y, d2 = u - y;
+    float t0 = __builtin_amdgcn_sqrtf(fmaf(s, s, d2 * d2)), t1 = __builtin_amdgcn_sqrtf(fmaf(s2, s2, d * d));
+    if (slot0) t0 = t1 = 0.25f * (fabsf(s + s2) + fabsf(s - s2));  // |g_0| + |g_128|, the same for both mirrors
+    b0 += t0;
+    b1 += t1;
+  }
+  __device__ __forceinline__ void energy(const f32x4& acc) {
+    e0 = fmaf(acc[0], acc[0], fmaf(acc[1], acc[1], e0));
+    e1 = fmaf(acc[2], acc[2], fmaf(acc[3], acc[3], e1));
+  }
+  __device__ __forceinline__ void close_group(bool q, int n) {
+    const float own = q ? e1 : e0, other = swap_adjacent(q ? e0 : e1);
+    c += __builtin_amdgcn_sqrtf(2.f * n * (own + other));
+    e0 = e1 = 0.f;
+  }
+};
+
+// Squares of the lane's operand elements (FP16), for the row norms.
+__device__ __forceinline__ float dword_square(uint32_t d, float s) {
+  typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+  const f16x2 v = __builtin_bit_cast(f16x2, d);
+  return __builtin_amdgcn_fdot2(v, v, s, false);
+}
+
+// A row tile's operand in registers: per slot of the wave the steps held 8
+// wide, and the narrow last step (TD dwords per slot, where there is one)
+// of 4 / TD slots packed into one matrix-core operand.  The reference
+// operand that meets it holds its slot's dwords in the same place and zeros
+// elsewhere, so no slot's particle operand is padded (padded, two row tiles
+// would not fit the registers).
+template <class Con>
+struct BoundA {
+  static constexpr int NF = Con::NF, TD = Con::TD, SPQ = TD ? 4 / TD : 1;
+  u32x4 f[Con::SPW][NF];
+  u32x4 q[TD ? Con::SPW / SPQ : 1];
+  __device__ __forceinline__ void load(const Con& con, const CorrArgs& a, int tile, int w, int ln) {
+    con.read_a(a, tile, a_block_pos(ln & 15), w, ln, [&](int i, int d, uint32_t x) {
+      if (d < 4 * NF) f[i][d / 4][d % 4] = x;
+      else q[i / SPQ][(i % SPQ) * TD + d - 4 * NF] = x;
+    });
+  }
+};
+// One slot's reference operand; i is the slot's index in the wave.
+template <class Con>
+struct BoundB {
+  u32x4 f[Con::NF];
+  u32x4 q;
+  __device__ __forceinline__ void load(const Con& con, const CorrArgs& a, int kt, int slot, int i, int ln) {
+    typename Con::Frag b;
+    con.load_b(a, kt, slot, ln, b);
+#pragma unroll
+    for (int s = 0; s < Con::NF; ++s) f[s] = b.f[s];
+    if constexpr (Con::TD > 0) {
+      constexpr int SPQ = 4 / Con::TD;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) q[d] = d / Con::TD == i % SPQ ? b.t[d % Con::TD] : 0u;
+    }
+  }
+};
+// The slot's block of NT row tiles, the tiles' products interleaved: a step
+// that adds to the last one's result waits for it.
+template <int PREC, class Con, int NT>
+__device__ __forceinline__ void bound_products(const BoundA<Con> (&x)[NT], const BoundB<Con>& y, int i,
+                                               f32x4 (&acc)[NT]) {
+  typedef typename Con::V V;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < Con::NF; ++s)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      acc[t] = Op16<PREC>::mfma(__builtin_bit_cast(V, x[t].f[i][s]), __builtin_bit_cast(V, y.f[s]), acc[t]);
+  if constexpr (Con::TD > 0)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      acc[t] = Op16<PREC>::mfma(__builtin_bit_cast(V, x[t].q[i / (4 / Con::TD)]), __builtin_bit_cast(V, y.q), acc[t]);
+}
+
+template <int NT>
+struct BoundSmem {
+  float2* pp;   // [2][kBoundTiles][8 waves][NT][64] partial bounds of both mirrors
+  float* norm;  // [8 waves][NT * 8] partial squared row norms
+  unsigned long long* key;  // [NT * 8] each row's largest bound
+  __device__ __forceinline__ BoundSmem(float* smem) {
+    pp = reinterpret_cast<float2*>(smem);
+    norm = smem + 2 * kBoundTiles * 8 * NT * 64 * 2;
+    key = reinterpret_cast<unsigned long long*>(norm + 8 * NT * 8);
+  }
+  static constexpr size_t bytes() {
+    return (2 * kBoundTiles * 8 * NT * 64 * 2 + 8 * NT * 8 + 2 * NT * 8) * sizeof(float);
+  }
+};
+
+// What rounding both operands to FP16 can add to a pair's CC (see the file
+// comment), in their scaled units: sa = norm of the row's rounded operand,
+// nb = norm of the reference's (scaled) operand, R rings.
+__device__ __forceinline__ float fp16_error(float sa, float nb, int R) {
+  const float u = 1.f / 2048.f, eta = sqrtf(2.f * kSlots * R) / 16384.f;
+  const float Na = (sa + eta) * (1.f + 1.f / 1024.f), Da = u * Na + eta, Db = u * nb + eta;
+  return 1.41421363f * (1.f + 1.f / 64.f) * (Da * nb + Na * Db + Da * Db);
+}
+
+// Work item: row block item % blocks (NT tiles) against the reference tiles
+// of part item / blocks (a.kt_per_wg each).
+template <int PREC, int MAXR, int NT, bool ERR>
+__device__ __forceinline__ void bound_item(const CorrArgs& a, int item, float* smem) {
+  const BoundSmem<NT> sm(smem);
+  const int tid = threadIdx.x, ln = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int blocks = (a.n_row_tiles + NT - 1) / NT;
+  const int blk = item % blocks;
+  const int kt0 = item / blocks * a.kt_per_wg, kt1 = min(kt0 + a.kt_per_wg, a.n_ref_tiles);
+  typedef Half16Contract<PREC, 8, MAXR, false> Con;
+  constexpr int SPW = Con::SPW;
+  Con con;
+  BoundA<Con> A[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)  // (a tile past the last repeats it; its bounds are not stored)
+    A[t].load(con, a, min(blk * NT + t, a.n_row_tiles - 1), w, ln);
+  if constexpr (ERR) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      float s = 0.f;
+#pragma unroll
+      for (int i = 0; i < SPW; ++i) {
+#pragma unroll
+        for (int d = 0; d < 4 * Con::NF; ++d) s = dword_square(A[t].f[i][d / 4][d % 4], s);
+      }
+#pragma unroll
+      for (int d = 0; d < SPW * Con::TD; ++d) s = dword_square(A[t].q[d / 4][d % 4], s);
+      // lane's block row j = ln & 15 is (row j / 2, p = j % 2), ring group ln / 16
+      s += __shfl_xor(s, 1);
+      s += __shfl_xor(s, 16);
+      s += __shfl_xor(s, 32);
+      if (ln < 16 && !(ln & 1)) sm.norm[w * NT * 8 + t * 8 + (ln >> 1)] = s;
+    }
+  }
+  if (tid < NT * 8) sm.key[tid] = 0ull;
+  const int P = lane_pair(ln);
+  const bool q = ln & 1;
+  // the reference operand is kept D slots ahead, across reference tiles
+  // (one slot ahead, a slot takes a whole L2 latency); the sums of a slot are
+  // taken while the next one's products run
+  constexpr int D = Con::TD == 2 ? 2 : 4;
+  BoundB<Con> b[D];
+#pragma unroll
+  for (int i = 0; i < D; ++i) b[i].load(con, a, kt0, w + 8 * i, i, ln);
+  auto take = [&](BoundSum& s, const f32x4& acc, int i) {
+    if (i < 2) s.exact(acc, q, w == 0 && i == 0);
+    else s.energy(acc);
+    if (i == 3) s.close_group(q, 2);
+    if (i == 7) s.close_group(q, 4);
+    if (i == 15) s.close_group(q, 8);
+  };
+  int buf = 0;
+  for (int kb = kt0; kb < kt1; kb += kBoundTiles, buf ^= 1) {
+    const int nu = min(kBoundTiles, kt1 - kb);
+#pragma unroll 1
+    for (int u = 0; u < nu; ++u) {
+      const int kt = kb + u;
+      BoundSum bs[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) bs[t].clear();
+      const int ktn = kt + 1 < kt1 ? kt + 1 : kt0;
+      f32x4 acc[NT];
+#pragma unroll
+      for (int i = 0; i < SPW; ++i) {
+        f32x4 cur[NT];
+        bound_products<PREC>(A, b[i % D], i, cur);
+        b[i % D].load(con, a, i + D < SPW ? kt : ktn, w + 8 * ((i + D) % SPW), i + D, ln);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          if (i > 0) take(bs[t], acc[t], i - 1);
+          acc[t] = cur[t];
+        }
+        // one slot at a time: a schedule that runs further ahead holds more
+        // results and reference operands than there are registers
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) take(bs[t], acc[t], SPW - 1);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const float m0 = bs[t].b0 + bs[t].c, m1 = bs[t].b1 + bs[t].c;
+        sm.pp[(((buf * kBoundTiles + u) * 8 + w) * NT + t) * 64 + P] = q ? make_float2(m1, m0) : make_float2(m0, m1);
+      }
+    }
+    __syncthreads();
+    for (int i = tid; i < nu * NT * 64; i += 512) {
+      const int pr = i & 63, t = (i >> 6) % NT, u = i / (64 * NT);
+      float B0 = 0.f, B1 = 0.f;
+#pragma unroll
+      for (int w2 = 0; w2 < 8; ++w2) {
+        const float2 v = sm.pp[(((buf * kBoundTiles + u) * 8 + w2) * NT + t) * 64 + pr];
+        B0 += v.x;
+        B1 += v.y;
+      }
+      const int row = (blk * NT + t) * kRowTile + (pr >> 3), k = (kb + u) * kRefTile + (pr & 7);
+      if (row >= a.rows) continue;
+      // (1e-16: sums of squares below 1e-38 are lost)
+      float bound = (a.M == 2 ? fmaxf(B0, B1) : B0) * (1.f + 1.f / 4096.f) + 1e-16f;
+      if constexpr (ERR) {
+        float s = 0.f;
+#pragma unroll
+        for (int w2 = 0; w2 < 8; ++w2) s += sm.norm[w2 * NT * 8 + t * 8 + (pr >> 3)];
+        s = sqrtf(s);
+        const float mx = a.maxabs[row / a.S];
+        bound += fp16_error(s, k < a.K ? a.bnorm[k] * a.b_scale : 0.f, a.R);
+        bound = fp16_value(bound, mx, a.b_scale) + 1e-37f;  // (1e-37: what subnormals lose)
+        if (k == 0) a.rownorm[row] = s;
+        if (!(mx * 512.f < INFINITY)) bound = INFINITY;
+      }
+      a.ub[(size_t)row * a.ldu + k] = k < a.K ? bound : -INFINITY;
+      // the row's largest (NaN counts as infinite) over the tile's 8 references
+      unsigned long long key = k < a.K ? cand_key(bound == bound ? bound : INFINITY, k) : 0ull;
+#pragma unroll
+      for (int o = 4; o > 0; o >>= 1) {
+        const unsigned long long other = __shfl_xor(key, o);
+        key = other > key ? other : key;
+      }
+      if ((pr & 7) == 0) atomicMax(&sm.key[t * 8 + (pr >> 3)], key);
+    }
+  }
+  __syncthreads();
+  if (tid < NT * 8) {
+    const int row = blk * NT * kRowTile + tid;
+    if (row < a.rows) atomicMax(&a.rowkey[row], sm.key[tid]);
+  }
+}
+
+template <int PREC, int MAXR, int NT, bool ERR>
+__global__ __launch_bounds__(512) void k_bound(CorrArgs a) {
+  extern __shared__ float smem[];
+  bound_item<PREC, MAXR, NT, ERR>(a, blockIdx.x, smem);
+}
+
+// Batched form over the items of several stacks (start[p]: piece p's first).
+template <int PREC, int MAXR, int NT, bool ERR>
+__global__ __launch_bounds__(512) void k_bound_batch(CorrBatch b) {
+  extern __shared__ float smem[];
+  const int item = blockIdx.x;
+  if (item >= b.start[b.n]) return;
+  int p = 0;
+  while (p + 1 < b.n && b.start[p + 1] <= item) ++p;
+  bound_item<PREC, MAXR, NT, ERR>(b.piece[p], item - b.start[p], smem);
+}
+
+template <int PREC, int MAXR, int NT, bool ERR>
+inline void bound_go(const CorrArgs* a, const CorrBatch* b, int grid, hipStream_t st) {
+  const size_t lds = BoundSmem<NT>::bytes();
+  if (b) hipLaunchKernelGGL((k_bound_batch<PREC, MAXR, NT, ERR>), dim3(grid), dim3(512), lds, st, *b);
+  else hipLaunchKernelGGL((k_bound<PREC, MAXR, NT, ERR>), dim3(grid), dim3(512), lds, st, *a);
+}
+
+// Row tiles per workgroup of the ring count R4.
+constexpr int bound_row_tiles(int R4) { return R4 <= 12 ? 2 : 1; }
+
+template <int PREC, bool ERR>
+inline void bound_dispatch(int R4, const CorrArgs* a, const CorrBatch* b, int grid, hipStream_t st) {
+  if (R4 <= 8) return bound_go<PREC, 8, 2, ERR>(a, b, grid, st);
+  if (R4 <= 10) return bound_go<PREC, 10, 2, ERR>(a, b, grid, st);
+  if (R4 <= 12) return bound_go<PREC, 12, 2, ERR>(a, b, grid, st);
+  return bound_go<PREC, 16, 1, ERR>(a, b, grid, st);
+}
+
+}  // namespace mra

@@ -1,11 +1,13 @@
-// Ring-weighted correlation of every particle row with every reference
-// (Sec. 3: FFT(x)' x FFT(y) per ring, references on a second grid axis,
-// inverse FFT of the CC table, arg-max by reduction as in Fig. 2), fused so
-// that the CC table is never written to memory.
+// Ring-weighted correlation of particle rows with references (Sec. 3:
+// FFT(x)' x FFT(y) per ring, references on a second grid axis, inverse FFT of
+// the CC table, arg-max by reduction as in Fig. 2): the matrix-core
+// contraction of one 8-row x 8-reference tile, the inverse FFT over angle of
+// its pairs, and the kernel k_corr that evaluates every pair of a launch (CC
+// table, and alignment with pruning off).  The kernels that evaluate only the
+// pairs that can win are in bound_impl.h and fine_impl.h.
 //
-// A workgroup owns 8 particle rows (row = particle * S + shift) and loops
-// over all references in tiles of 8.  For each frequency slot f the matrix
-// cores compute the 16 x 16 block
+// A row is particle * S + shift.  For each frequency slot f the matrix cores
+// compute the 16 x 16 block
 //     U[(p,row), (q,ref)] = sum_r A_f[(p,row), r] * B_f[r, (q,ref)],
 //     A rows: p = 0 -> a - b, p = 1 -> a + b  (particle spectrum a + ib)
 //     B cols: q = 0 -> c - d, q = 1 -> c + d  (reference spectrum c + id,
@@ -14,17 +16,15 @@
 // c0 + i c1 (unmirrored CC + i * mirrored CC) at f and 256 - f (see
 // mra_fft.h).  The 128 slots of all 64 (row, ref) pairs sit in LDS (128 KiB);
 // then a 16 x 16 inverse FFT over angle (two passes through LDS) yields the
-// CC at all 256 angles for both mirrors, and the running maximum with the
-// smallest-flat-index tie rule is kept per row across reference tiles.
+// CC at all 256 angles for both mirrors.
 //
 // NW waves (8, or 4 in one FP32 variant): wave w owns slots w, w+NW, ... in
 // the contraction.  In the resident variants the particle operand A of
-// those slots is read from HBM once per row tile and kept in registers (FP32:
+// those slots is read once per row tile and kept in registers (FP32:
 // R4 <= 9 with 8 waves, R4 <= 12 with 4 waves; packed 16-bit for the BF16 /
 // FP16 forms) for all reference tiles; the streamed variants re-read it per
 // reference tile.  The reference operand B is streamed from L2 with a slot
-// prefetch.  Variants are tile configurations that an autotuner chooses
-// between; they do not change any result.
+// prefetch.  Variants are tile configurations; they do not change any result.
 #pragma once
 #include <type_traits>
 
@@ -38,8 +38,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kMaxBatch = kMaxBatchPieces;
 
 __device__ __forceinline__ float2 w256c(const float2* cs, int e) {
   float2 c = cs[e & 255];
@@ -128,9 +126,14 @@ __device__ __forceinline__ f32x2 a_pair(const CorrArgs& a, const float* ap, int 
   return r;
 }
 
-// Frequency slots below kLowSlots enter the pruning bound with their exact
-// magnitudes, the others through their summed energy.
-constexpr int kLowSlots = 32;
+// FP32 reference operand of reference k and slot `slot`: the lane's R4
+// elements (ring group ln / 16, q = ln & 1) are contiguous.
+__device__ __forceinline__ const float* b32_lane(const CorrArgs& a, int k, int slot, int ln) {
+  return a.B32 + ((size_t)(k * kSlots + slot) * 8 + (ln >> 4) * 2 + (ln & 1)) * b32_pitch(a.R4);
+}
+// 16-bit reference operand: place of the lane's elements (reference r of
+// the tile, ring group ln / 16, q = ln & 1) in each step of a slot's block.
+__device__ __forceinline__ int b16_lane(int r, int ln) { return (ln & 0x30) + 2 * r + (ln & 1); }
 
 // swap the values of neighbouring lanes (DPP quad_perm [1, 0, 3, 2]; every
 // lane is enabled, so no old value is needed)
@@ -138,35 +141,22 @@ __device__ __forceinline__ float swap_adjacent(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xb1, 0xf, 0xf, false));
 }
 
-// Block of slot `slot` -> the lane's pair (lane_pair(ln) = P): the four
-// entries U_pq gathered with one exchange between the two lanes of the
-// pair, stored as the state halves (U00, U01) and (U11, U10), and added to
-// the pair's pruning bound: a slot below kLowSlots (low) with the exact
-// magnitudes of its two spectrum values per mirror, a slot above through
-// its energy, the sum of the squares.
-__device__ __forceinline__ void pair_block(float2* stc, int slot, int ln, int P, f32x4 acc, bool low, float& b0,
-                                           float& b1, float& en) {
+// Block of one slot -> the lane's pair (lane_pair(ln)): the four entries U_pq
+// gathered with one exchange between the two lanes of the pair, as the state
+// halves (U00, U01) and (U11, U10).
+__device__ __forceinline__ void pair_gather(int ln, const f32x4& acc, float2& h0, float2& h1) {
   const bool q = ln & 1;
   // lane q = 0 holds (row 2g: U00, U10; row 2g + 1: U00, U10), lane q = 1
   // the same rows' U01, U11; each sends the entries of the other's row
   const float r0 = swap_adjacent(q ? acc[0] : acc[2]), r1 = swap_adjacent(q ? acc[1] : acc[3]);
-  const float u00 = q ? r0 : acc[0], u01 = q ? acc[2] : r0;
-  const float u10 = q ? r1 : acc[1], u11 = q ? acc[3] : r1;
-  stc[(slot * 2) * 64 + P] = make_float2(u00, u01);
-  stc[(slot * 2 + 1) * 64 + P] = make_float2(u11, u10);
-  const float s1 = u00 + u11, d1 = u00 - u11, s2 = u01 + u10, d2 = u01 - u10;
-  if (low) {
-    if (slot == 0) {  // |g_0| + |g_128|, the same for both mirrors
-      const float g = 0.25f * (fabsf(s1 + s2) + fabsf(s1 - s2));
-      b0 += g;
-      b1 += g;
-    } else {          // 2|G_0,f| = |(s1, d2)|, 2|G_1,f| = |(s2, d1)|
-      b0 += sqrtf(s1 * s1 + d2 * d2);
-      b1 += sqrtf(s2 * s2 + d1 * d1);
-    }
-  } else {
-    en = fmaf(u00, u00, fmaf(u01, u01, fmaf(u10, u10, fmaf(u11, u11, en))));
-  }
+  h0 = make_float2(q ? r0 : acc[0], q ? acc[2] : r0);
+  h1 = make_float2(q ? acc[3] : r1, q ? r1 : acc[1]);
+}
+__device__ __forceinline__ void pair_block(float2* stc, int slot, int ln, int P, f32x4 acc) {
+  float2 h0, h1;
+  pair_gather(ln, acc, h0, h1);
+  stc[(slot * 2) * 64 + P] = h0;
+  stc[(slot * 2 + 1) * 64 + P] = h1;
 }
 
 // Contraction of one reference tile with FP32 operands for the wave's
@@ -181,14 +171,13 @@ struct Fp32Contract {
   static constexpr int RX = EXACT ? MAXR : 0;
   static constexpr int LAYOUT = (NW == 8 && RES) ? kRingPerm : kSlotMajor;
   float areg[RES ? SPW : 1][RES ? MAXR : 1];
-  float bound0, bound1, energy;  // the lane's pair's pruning bound terms (pair_block)
 
   // the lane's reference operand of slot `slot` in reference tile kt
   __device__ __forceinline__ void load_b(const CorrArgs& a, int kt, int slot, int ln, float (&dst)[MAXR]) const {
     const int R4 = EXACT ? MAXR : a.R4;
-    const float* bp = a.B32 + ((size_t)(kt * kSlots + slot) * R4) * 64 + ln;
+    const float* bp = b32_lane(a, kt * kRefTile + ((ln >> 1) & 7), slot, ln);
 #pragma unroll
-    for (int t = 0; t < MAXR; ++t) dst[t] = bp[(t < R4 ? t : R4 - 1) * 64];  // unconditional
+    for (int t = 0; t < MAXR; ++t) dst[t] = bp[t < R4 ? t : R4 - 1];  // unconditional
   }
   // PRE (8 waves, resident operand, ring count exact): the reference
   // operand of the wave's first slot of reference tile kt is loaded before
@@ -200,7 +189,7 @@ struct Fp32Contract {
     if constexpr (PRE) load_b(a, kt, w, ln, bpre);
   }
 
-  __device__ __forceinline__ void load_a(const CorrArgs& a, int tile, int w, int ln) {
+  __device__ __forceinline__ void load_a(const CorrArgs& a, int tile, int /*k*/, int w, int ln) {
     if constexpr (RES) {
       if constexpr (LAYOUT == kRingPerm) {
         // the wave's slots w + 8 i sit at positions 16 w + i, in pairs
@@ -231,7 +220,6 @@ struct Fp32Contract {
   __device__ __forceinline__ void run(const CorrArgs& a, float2* stc, int tile, int kt, int w, int ln) {
     const int R4 = EXACT ? MAXR : a.R4;
     const int P = lane_pair(ln);
-    bound0 = bound1 = energy = 0.f;
     auto loadb = [&](int i, float (&dst)[MAXR]) { load_b(a, kt, w + NW * i, ln, dst); };
     if constexpr (RES) {
       // slots in pairs: two independent accumulation chains keep the matrix
@@ -256,8 +244,8 @@ struct Fp32Contract {
         }
         if (i + 2 < SPW) loadb(i + 2, b[(i + 2) % 4]);
         if (i + 3 < SPW) loadb(i + 3, b[(i + 3) % 4]);
-        pair_block(stc, w + NW * i, ln, P, acc0, i < kLowSlots / NW, bound0, bound1, energy);
-        pair_block(stc, w + NW * (i + 1), ln, P, acc1, i + 1 < kLowSlots / NW, bound0, bound1, energy);
+        pair_block(stc, w + NW * i, ln, P, acc0);
+        pair_block(stc, w + NW * (i + 1), ln, P, acc1);
       }
     } else {
       // both operands streamed, one slot ahead (explicit double buffer so
@@ -273,7 +261,7 @@ struct Fp32Contract {
 #pragma unroll
         for (int t = 0; t < MAXR; ++t)
           if (t < R4) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t], y[t], acc, 0, 0, 0);
-        pair_block(stc, slot, ln, P, acc, slot < kLowSlots, bound0, bound1, energy);
+        pair_block(stc, slot, ln, P, acc);
       };
       loadb(0, b0);
       loada(0, a0);
@@ -293,44 +281,38 @@ struct Fp32Contract {
 };
 
 // Contraction with 16-bit operands; NS = ceil(MAXR / 8) <= 2 steps of 8
-// rings per lane group, R4 <= MAXR (EXACT: every work item's R4 lies in the
-// bucket MAXR - 3 .. MAXR, or 1 .. 8 for MAXR = 8: ceil(R4 / 8) == NS, and at
-// MAXR = 16 the reference operand's last step is 8 wide).  With MAXR = 12 the second step holds at most 4 rings
-// per lane group (NARROW): the resident particle operand keeps 2 dwords of it
-// per slot instead of 4.  The particle operand
-// arrives rounded to the contraction's type (FP16 already scaled per
-// particle) in the 16-bit ring-major layout.  RES: it is read once per row
-// tile and kept packed in registers, two values per dword; otherwise it is
-// re-read per reference tile, one slot ahead.  The reference operand's last
-// step is stored as wide as its rings need (b16_tail_width) and read with
-// dword loads of that width.
-template <int PREC, int NW, int MAXR, bool EXACT, bool RES>
+// rings per lane group.  MAXR is the ring bucket of R4 (8: 1..8, 10: 9..10, 12:
+// 11..12, 16: 13..16), which fixes the step count and the width of the last
+// step: with MAXR = 10 or 12 it holds at most 2 or 4 rings per lane group
+// (NARROW), and the particle operand keeps 1 or 2 dwords of it per slot (TD)
+// instead of 4.  The particle operand arrives rounded to the contraction's type
+// (FP16 already scaled per particle) in the 16-bit ring-major layout.  RES: it
+// is read once per row tile and kept packed in registers, two values per
+// dword; otherwise it is re-read per reference tile, one slot ahead.  The
+// reference operand's last step is stored as wide as its rings need
+// (b16_tail_width: 2 TD elements, 8 where it is not narrow).
+template <int PREC, int NW, int MAXR, bool RES>
 struct Half16Contract {
   static constexpr int SPW = kSlots / NW;
   static constexpr int NS = (MAXR + 7) / 8;
   static_assert(NS <= 2, "at most two steps of 8 rings per lane group");
   static constexpr bool NARROW = NS == 2 && MAXR - 8 <= 4;
   static constexpr int NF = NARROW ? 1 : NS;  // steps held 8 wide
+  static constexpr int TD = NARROW ? (MAXR - 8 + 1) / 2 : 0;  // dwords of the narrow step
   typedef typename Op16<PREC>::T V;
   // one slot's operand of the lane: the steps held 8 wide, then (NARROW) the
-  // last step's 4 elements
+  // last step's elements (t[1] only with TD = 2)
   struct Frag {
     u32x4 f[NF];
     u32x2 t;
   };
   Frag areg[RES ? SPW : 1];
-  float bound0, bound1, energy;  // the lane's pair's pruning bound terms (pair_block)
   Frag bpre;                     // RES: reference operand of the wave's first slot, loaded ahead
 
   // Element t (ring (ln/16) R4 + t) of the lane's row for each t < MAXR is
-  // read unconditionally: the index is clamped into the row tile's rings,
-  // and elements t >= R4 and padding rings >= R are cleared by an AND with a
-  // mask the optimiser cannot see through.
-  __device__ __forceinline__ uint32_t keep_mask(const CorrArgs& a, int t, int ln) const {
-    uint32_t keep = (t < a.R4 && (ln >> 4) * a.R4 + t < a.R) ? ~0u : 0u;
-    asm("" : "+v"(keep));
-    return keep;
-  }
+  // read unconditionally, its index clamped into the row tile's rings: an
+  // element t >= R4 repeats the last one, and padding rings >= R hold zeros;
+  // the reference operand is zero at both.
   __device__ __forceinline__ const uint16_t* ring_block(const CorrArgs& a, int tile, int t, int ln) const {
     const int tt = t < a.R4 ? t : a.R4 - 1;
     return reinterpret_cast<const uint16_t*>(a.A) + ((size_t)(tile * 4 + (ln >> 4)) * a.R4 + tt) * kSlots * 16;
@@ -350,8 +332,7 @@ struct Half16Contract {
     for (int t = 0; t < 8 * NS; ++t) {
       if (t < MAXR) {
         const uint16_t* bp = ring_block(a, tile, t, ln) + idx;
-        const uint32_t x = nt ? (uint32_t)__builtin_nontemporal_load(bp) : (uint32_t)*bp;
-        v[t] = x & keep_mask(a, t, ln);
+        v[t] = nt ? (uint32_t)__builtin_nontemporal_load(bp) : (uint32_t)*bp;
       } else {
         v[t] = 0u;
       }
@@ -359,69 +340,72 @@ struct Half16Contract {
 #pragma unroll
     for (int d = 0; d < 4 * NF; ++d) dst.f[d / 4][d % 4] = v[2 * d] | (v[2 * d + 1] << 16);
     if constexpr (NARROW) {
-      dst.t[0] = v[8] | (v[9] << 16);
-      dst.t[1] = v[10] | (v[11] << 16);
+#pragma unroll
+      for (int d = 0; d < TD; ++d) dst.t[d] = v[8 + 2 * d] | (v[9 + 2 * d] << 16);
     }
   }
 
-  // RES: the operand of all the wave's slots w + 8 i.  Per element t, two
-  // 16-byte loads (the interleaved runs 2 w and 2 w + 1) give slots i < 8
-  // and i >= 8; the dwords are then regrouped per slot.
-  __device__ __forceinline__ void load_a(const CorrArgs& a, int tile, int w, int ln) {
-    if constexpr (RES) {
-      static_assert(NW == 8, "the interleaved runs hold 8 slots of each of 8 waves");
-      const int k = a_block_pos(ln & 15);
+  // The operand of all the wave's slots w + 8 i, of the lane's block row:
+  // element k (p * 8 + row % 8) of row tile `tile` (either may differ by lane).
+  // Per element t, one 16-byte load of the interleaved run 2 w + hh gives
+  // slots i = 8 hh .. 8 hh + 7; dword regroups them per slot: dword d (elements
+  // t = 2 d, 2 d + 1) of slot 8 hh + j.
+  __device__ __forceinline__ void load_run(const CorrArgs& a, int tile, int k, int w, int ln, int hh,
+                                           u32x4 (&u)[8 * NS]) const {
+    static_assert(NW == 8, "the interleaved runs hold 8 slots of each of 8 waves");
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        u32x4 u[8 * NS];
-#pragma unroll
-        for (int t = 0; t < 8 * NS; ++t) {
-          if (t < MAXR) {
-            const u32x4* bp = reinterpret_cast<const u32x4*>(ring_block(a, tile, t, ln) + a16_index(16 * w + 8 * hh, k));
-            u[t] = __builtin_nontemporal_load(bp) & keep_mask(a, t, ln);
-          } else {
-            u[t] = u32x4{0u, 0u, 0u, 0u};
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          Frag& f = areg[8 * hh + j];
-#pragma unroll
-          for (int d = 0; d < 4 * NF; ++d) f.f[d / 4][d % 4] = pick2(u[2 * d][j >> 1], u[2 * d + 1][j >> 1], j & 1);
-          if constexpr (NARROW) {
-            f.t[0] = pick2(u[8][j >> 1], u[9][j >> 1], j & 1);
-            f.t[1] = pick2(u[10][j >> 1], u[11][j >> 1], j & 1);
-          }
-        }
-      }
-    }
-  }
-
-  // the lane's reference operand of slot `slot` in reference tile kt.  Last-step
-  // dword j of the lane is read at index min(j, h - 1): a dword j >= h
-  // repeats stored values, which meet the particle operand's elements t >=
-  // R4, all zero, so it adds exact zeros (every stored value is finite).
-  // With ns == 1 the last-step address is step 0's, read and unused.
-  __device__ __forceinline__ void load_b(const CorrArgs& a, int kt, int slot, int ln, Frag& dst) const {
-    const int ns = EXACT ? NS : a.NS;
-    const int bt = a.BT;                          // last step: bt elements per lane
-    const int se = (ns - 1) * 512 + 64 * bt;      // elements per slot block
-    const int h = bt / 2;                         // dwords per lane in the last step
-    const uint16_t* bp = a.B16 + (size_t)(kt * kSlots + slot) * se;
-    dst.f[0] = *reinterpret_cast<const u32x4*>(bp + ln * 8);  // step 0 is always 8 wide
-    if constexpr (NS == 2) {
-      const uint32_t* tp = reinterpret_cast<const uint32_t*>(bp + (ns - 1) * 512 + ln * bt);
-      if constexpr (NARROW) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) dst.t[j] = tp[j < h ? j : h - 1];
-      } else if constexpr (EXACT) {
-        dst.f[1] = *reinterpret_cast<const u32x4*>(tp);  // 8 wide: one 16-byte load
+    for (int t = 0; t < 8 * NS; ++t) {
+      if (t < MAXR) {
+        const u32x4* bp = reinterpret_cast<const u32x4*>(ring_block(a, tile, t, ln) + a16_index(16 * w + 8 * hh, k));
+        u[t] = __builtin_nontemporal_load(bp);
       } else {
-        // (four 4-byte loads cost the address path four times one 16-byte
-        // load: batched launches keep the ring buckets apart to avoid this)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) dst.f[1][j] = tp[j < h ? j : h - 1];
+        u[t] = u32x4{0u, 0u, 0u, 0u};
       }
+    }
+  }
+  static __device__ __forceinline__ uint32_t dword(const u32x4 (&u)[8 * NS], int j, int d) {
+    return pick2(u[2 * d][j >> 1], u[2 * d + 1][j >> 1], j & 1);
+  }
+  // put(i, d, x) takes dword d of slot i
+  template <class Put>
+  __device__ __forceinline__ void read_a(const CorrArgs& a, int tile, int k, int w, int ln, Put put) const {
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 u[8 * NS];
+      load_run(a, tile, k, w, ln, hh, u);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+#pragma unroll
+        for (int d = 0; d < 4 * NF + TD; ++d) put(8 * hh + j, d, dword(u, j, d));
+      }
+    }
+  }
+  __device__ __forceinline__ void load_a(const CorrArgs& a, int tile, int k, int w, int ln) {
+    if constexpr (RES)
+      read_a(a, tile, k, w, ln, [&](int i, int d, uint32_t x) {
+        if (d < 4 * NF) areg[i].f[d / 4][d % 4] = x;
+        else areg[i].t[d - 4 * NF] = x;
+      });
+  }
+
+  // the lane's reference operand of slot `slot` in reference tile kt (elements
+  // t >= R4 are stored as zeros)
+  static constexpr int BT = NARROW ? 2 * TD : 8;         // last step: elements per lane
+  static constexpr int SE = (NS - 1) * 512 + 64 * BT;    // elements per slot block
+  __device__ __forceinline__ void load_b(const CorrArgs& a, int kt, int slot, int ln, Frag& dst) const {
+    load_b_at(a, kt, slot, ln, 0, dst);
+  }
+  // the same from the place pl (b16_lane) of a tile kt, `tile_off` elements
+  // further (per lane: any reference)
+  __device__ __forceinline__ void load_b_at(const CorrArgs& a, int kt, int slot, int pl, uint32_t tile_off,
+                                            Frag& dst) const {
+    const uint16_t* bp = a.B16 + (size_t)(kt * kSlots + slot) * SE;
+    dst.f[0] = *reinterpret_cast<const u32x4*>(bp + (tile_off + pl * 8));
+    if constexpr (NS == 2) {
+      const uint16_t* tp = bp + 512 + (tile_off + pl * BT);
+      if constexpr (!NARROW) dst.f[1] = *reinterpret_cast<const u32x4*>(tp);
+      else if constexpr (TD == 2) dst.t = *reinterpret_cast<const u32x2*>(tp);
+      else dst.t[0] = *reinterpret_cast<const uint32_t*>(tp);
     }
   }
   // RES: start loading the first slot of reference tile kt, which the next
@@ -430,32 +414,33 @@ struct Half16Contract {
     if constexpr (RES) load_b(a, kt, w, ln, bpre);
   }
 
-  __device__ __forceinline__ void run(const CorrArgs& a, float2* stc, int tile, int kt, int w, int ln) {
-    const int ns = EXACT ? NS : a.NS;
-    const int P = lane_pair(ln);
-    bound0 = bound1 = energy = 0.f;
-    auto loadb = [&](int i, Frag& dst) { load_b(a, kt, w + NW * i, ln, dst); };
-    auto chain = [&](const Frag& x, const Frag& y, int slot, bool low) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  // one slot's block: operand x of the particle rows, y of the references
+  __device__ __forceinline__ f32x4 product(const Frag& x, const Frag& y) const {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int s = 0; s < NF; ++s)
-        if (s < ns) acc = Op16<PREC>::mfma(__builtin_bit_cast(V, x.f[s]), __builtin_bit_cast(V, y.f[s]), acc);
-      if constexpr (NARROW) {
-        // the last step is a K = 32 product with elements 4..7 zero: a K = 16
-        // product accumulated straight onto the K = 32 one's result gave
-        // wrong sums on gfx950 when the two issued back to back
-        const u32x4 xa = {x.t[0], x.t[1], 0u, 0u}, yb = {y.t[0], y.t[1], 0u, 0u};
-        if (ns == NS) acc = Op16<PREC>::mfma(__builtin_bit_cast(V, xa), __builtin_bit_cast(V, yb), acc);
-      }
-      pair_block(stc, slot, ln, P, acc, low, bound0, bound1, energy);
-    };
+    for (int s = 0; s < NF; ++s)
+      acc = Op16<PREC>::mfma(__builtin_bit_cast(V, x.f[s]), __builtin_bit_cast(V, y.f[s]), acc);
+    if constexpr (NARROW) {
+      // the last step is a K = 32 product with the other elements zero: a K = 16
+      // product accumulated straight onto the K = 32 one's result gave
+      // wrong sums on gfx950 when the two issued back to back
+      const u32x4 xa = {x.t[0], TD > 1 ? x.t[1] : 0u, 0u, 0u}, yb = {y.t[0], TD > 1 ? y.t[1] : 0u, 0u, 0u};
+      acc = Op16<PREC>::mfma(__builtin_bit_cast(V, xa), __builtin_bit_cast(V, yb), acc);
+    }
+    return acc;
+  }
+
+  __device__ __forceinline__ void run(const CorrArgs& a, float2* stc, int tile, int kt, int w, int ln) {
+    const int P = lane_pair(ln);
+    auto loadb = [&](int i, Frag& dst) { load_b(a, kt, w + NW * i, ln, dst); };
+    auto chain = [&](const Frag& x, const Frag& y, int slot) { pair_block(stc, slot, ln, P, product(x, y)); };
     if constexpr (RES) {
       Frag b[2];
       b[0] = bpre;
 #pragma unroll
       for (int i = 0; i < SPW; ++i) {
         if (i + 1 < SPW) loadb(i + 1, b[(i + 1) % 2]);
-        chain(areg[RES ? i : 0], b[i % 2], w + NW * i, i < kLowSlots / NW);
+        chain(areg[RES ? i : 0], b[i % 2], w + NW * i);
         // keep each slot's store next to its products (a schedule that
         // defers them all holds 16 blocks of results and runs slower)
         __builtin_amdgcn_sched_barrier(0);
@@ -469,48 +454,14 @@ struct Half16Contract {
       for (int i = 0; i < SPW; i += 2) {
         loadb(i + 1, b1);
         fetch(a, tile, w + NW * (i + 1), ln, x1, false);
-        chain(x0, b0, w + NW * i, i < kLowSlots / NW);
+        chain(x0, b0, w + NW * i);
         if (i + 2 < SPW) {
           loadb(i + 2, b0);
           fetch(a, tile, w + NW * (i + 2), ln, x0, false);
         }
-        chain(x1, b1, w + NW * (i + 1), i + 1 < kLowSlots / NW);
+        chain(x1, b1, w + NW * (i + 1));
       }
     }
-  }
-};
-
-template <int NW>
-struct CorrSmem {
-  float* st;                // [128][2][64][2] spectra of the 64 (row, ref) pairs
-  float2* stc;
-  unsigned long long* key;  // [8] best candidate of each row so far (ordered key, 0 = none)
-  float4* pp;               // [2][NW][64] per (reference-tile parity, wave, pair): low-slot bound of
-                            // both mirrors, high-slot energy, unused
-  int* list;                // [NW][64] each wave's list of the pairs that need the inverse FFT
-  float* thr;               // [8] each row's best before this reference tile's inverse FFT
-  float* pt;                // [8] best over the rows of the row's particle (this tile and carried)
-  int* ppart;               // [8] particle of each row slot (-1 past the chunk)
-  float* carry_v;           // best of the particle that the run's next tile may continue
-  int* carry_p;             // that particle (-1: none)
-  float2* tw;               // exp(-2 pi i e / 256)
-  __device__ __forceinline__ CorrSmem(float* smem) {
-    st = smem;
-    stc = reinterpret_cast<float2*>(smem);
-    key = reinterpret_cast<unsigned long long*>(smem + kSlots * 2 * 64 * 2);
-    pp = reinterpret_cast<float4*>(key + 8);
-    list = reinterpret_cast<int*>(pp + 2 * NW * 64);
-    thr = reinterpret_cast<float*>(list + NW * 64);
-    pt = thr + 8;
-    ppart = reinterpret_cast<int*>(pt + 8);
-    carry_v = reinterpret_cast<float*>(ppart + 8);
-    carry_p = reinterpret_cast<int*>(carry_v + 2);
-    tw = reinterpret_cast<float2*>(carry_p + 2);
-  }
-  static constexpr size_t bytes() {
-    return (size_t)kSlots * 2 * 64 * 2 * sizeof(float) + 8 * sizeof(unsigned long long) +
-           2 * NW * 64 * sizeof(float4) + NW * 64 * sizeof(int) +
-           8 * sizeof(float) * 2 + 8 * sizeof(int) + 2 * sizeof(float) + 2 * sizeof(int) + kNphi * sizeof(float2);
   }
 };
 
@@ -537,321 +488,272 @@ __device__ __forceinline__ int key_index(unsigned long long k) {
   return k == 0ull ? 0x7fffffff : (int)(0x7fffffffu - (uint32_t)k);
 }
 
-// The pruning threshold a particle's best so far imposes on its rows: the
-// best itself, or (re-ranked 16-bit forms) margin * |best| below it, so that
-// every row within that margin of the particle's best keeps its exact best.
-__device__ __forceinline__ float part_thr(float best, float margin) {
-  return (margin > 0.f && best > -INFINITY) ? best - margin * fabsf(best) : best;
-}
-
-// Power-of-two FP16 scale of chunk row r: |a +- b| <= 2 * 256 * max|pixel|
-// of the row's particle is mapped below 2^14.
-__device__ __forceinline__ float fp16_scale(const CorrArgs& a, int r) {
-  return r >= a.rows ? 1.f : fp16_operand_scale(a.maxabs[r / a.S]);
-}
-
 // What a tile computes: the per-row arg-max, the full CC table (debug), or
 // the arg-max with one candidate per particle left out (the runner-up pass).
 constexpr int kArgmax = 0, kTable = 1, kRunnerUp = 2;
 
-// One 8-row tile against every reference tile (see the file comment).
+constexpr size_t kStateFloats = (size_t)kSlots * 2 * 64 * 2;  // spectra of the 64 (row, ref) pairs
+
+// The inverse FFT over angle of n_live pairs whose spectra the contraction
+// left in the state stc ([128 slots][2 halves][PS]; n_live the same in every
+// wave): done(i, n1, x) is called by one lane per (pair i, n1 < 16) with the
+// complex CC x[n2] (unmirrored + i mirrored) at the angles n1 + 16 n2.  With
+// PS = 64 pair i's entries are at list[i], otherwise at i.  Contains a workgroup
+// barrier; the caller has one between the contraction and this, and one
+// before the state is written again.
 //
-// Exact pruning (a.prune, not in table mode): after the contraction of a
-// reference tile, every (row, ref) pair gets an upper bound of its CC over
-// all angles, per mirror m,
-//   c_m[a] <= |g_0| + |g_128| + sum_{f=1}^{127} 2 |G_m,f|,
-// with the terms of slots below kLowSlots taken exactly from the spectra and
-// the rest bounded by Cauchy-Schwarz through the pairs' high-slot energy
-// (sum of 2|G_m,f| <= sqrt(2 * 96 * sum of the squared MFMA entries)).  A pair
-// whose bound, inflated by 2^-12 against rounding, is below the threshold of
-// its row cannot matter, so its inverse FFT and arg-max are skipped.  The
-// threshold is the larger of the row's own best over earlier reference tiles
-// (a tie with it loses on the flat index) and the best over every row of the
-// same particle seen so far, in this tile and in the earlier tiles of the
-// workgroup's run (part_thr: minus a.margin of it for the re-ranked 16-bit
-// forms).  A row's reported best is exact whenever it reaches that particle
-// threshold, so the particle's winner (and, with a margin, every row the
-// re-ranking considers) is the same with and without pruning.  Most pairs of
-// a particle's later tiles fall below it, and a reference tile with no live
-// pair skips the inverse FFT and its barriers altogether.
-template <int PREC, int NW, class Contract, int MODE, bool SPLIT>
-__device__ __forceinline__ void corr_tile(const CorrArgs& a, int tile, const CorrSmem<NW>& sm, Contract& con) {
-  constexpr int CPW = 16 / NW;  // inverse-FFT columns (pass 1) and rows (pass 2) per wave
-  // the lane index is opaque in every tile, so that nothing derived from it
-  // is hoisted out of the run's tile loop and kept live across it
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-  const int ln = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (tid < 8) {
-    const int row = tile * kRowTile + tid;
-    const int part = row < a.rows ? row / a.S : -1;
-    sm.key[tid] = 0ull;
-    sm.ppart[tid] = part;
-    sm.pt[tid] = (part >= 0 && part == *sm.carry_p) ? *sm.carry_v : -INFINITY;
-  }
-  // (FP16: each particle's operand rows come scaled by a power of two of its
-  // own, exact, so results do not depend on how particles are grouped)
-  con.load_a(a, tile, w, ln);
-  int* list = sm.list + w * 64;
-  // Pruning (not in table mode, and not with 4 waves, whose registers are
-  // full with the resident operand) stops for the rest of the row tile when a
-  // reference tile after the second still leaves more than 56 of its 64 pairs
-  // live: the bound then costs more than it saves (references that are
-  // themselves noisy images).
-  bool prune = MODE != kTable && NW == 8 && a.prune;
+// With CPWX columns (pass 1) and rows (pass 2) per wave, the working waves'
+// columns / rows are CPWX * w + c, c = 0 .. CPWX-1: lane group c (LPCX lanes)
+// takes column / row c for the live pairs list[n0 + ln % LPCX].  The first
+// waves hold rows below 8 and the others rows from 8 on, so that every wave's
+// pass-2 addresses share one shape (a lane base plus constant offsets).  At
+// most 16 live pairs fit 4 columns of 16 lanes per wave: then waves 0..3 (one
+// per SIMD) do the passes and the others wait at the barrier, so each SIMD
+// issues one wave's instructions instead of two.
+template <int NW, bool SPLIT, int PS, class Done>
+__device__ __forceinline__ void inverse_pairs(float2* stc, const float2* tw, const int* list, int n_live, int w, int ln,
+                                              Done done) {
+  auto passes = [&](auto cpw_c) {
+    constexpr int CPWX = decltype(cpw_c)::value, LPCX = 64 / CPWX;
+    const bool work = CPWX * w < 16;  // wave-uniform
 
-  for (int kt = 0; kt < a.n_ref_tiles; ++kt) {
-    const int par = kt & 1;  // energy and bound partials alternate, so a wave may write the next
-                             // tile's while another still reads this one's
-    // ---------------- contraction on the matrix cores ----------------
-    con.run(a, sm.stc, tile, kt, w, ln);
-    // the next reference tile's first operand (tile 0 again after the last:
-    // the run's next row tile starts there)
-    con.prefetch(a, kt + 1 < a.n_ref_tiles ? kt + 1 : 0, w, ln);
-    // the wave's share of each pair's bound (its slots' terms, gathered in
-    // the contraction by the pair's lanes)
-    if (prune) sm.pp[(par * NW + w) * 64 + lane_pair(ln)] = make_float4(con.bound0, con.bound1, con.energy, 0.f);
+    // ---------------- inverse FFT over angle, pass 1 ----------------
+    // H_j (j = 16 k1 + k2) of pair P: half 0 of slot j (j < 128) or half 1
+    // of slot 256 - j (j >= 128; slot 0 for j = 128)
+    if (work) {
+#pragma unroll 1
+      for (int n0 = 0; n0 < n_live; n0 += LPCX) {
+        // lane-derived values are recomputed here rather than kept live
+        // across the caller's loop, where the registers hold the operand
+        int lnx = ln;
+        asm volatile("" : "+v"(lnx));
+        const int lane_n = lnx % LPCX, k2 = CPWX * w + lnx / LPCX;
+        const bool act = n0 + lane_n < n_live;
+        const int A = PS == 64 ? list[act ? n0 + lane_n : 0] : (act ? n0 + lane_n : 0);
+        const int lo = k2 * 2 * PS + A, hi = A - k2 * 2 * PS;
+        const int mid = k2 == 0 ? PS + A : hi + 257 * PS;
+        auto at = [&](int k1) { return k1 < 8 ? lo + k1 * 32 * PS : (k1 == 8 ? mid : hi + (513 - 32 * k1) * PS); };
+        float2 x[16];
+#pragma unroll
+        for (int k1 = 0; k1 < 16; ++k1) x[k1] = stc[at(k1)];
+        inv_pass1(k2, x, [&](int e) { return tw[e & 255]; });
+        if (act) {
+#pragma unroll
+          for (int n1 = 0; n1 < 16; ++n1) stc[at(n1)] = x[n1];
+        }
+      }
+    }
     __syncthreads();
-    // each row's best before this tile's candidates arrive: candidates of this
-    // tile are recorded only above it (equal values of earlier tiles have
-    // smaller flat indices)
-    if (MODE != kTable && tid < 8) sm.thr[tid] = key_value(sm.key[tid]);
 
-    // ---------------- which pairs need the inverse FFT ----------------
-    uint64_t live = ~0ull;
-    if (prune) {
-      // (the lane index made opaque again, so that the addresses below are
-      // computed here rather than kept live across the contraction)
-      int P = ln;
-      asm volatile("" : "+v"(P));
-      float B0 = 0.f, B1 = 0.f, E = 0.f;
-#pragma unroll
-      for (int w2 = 0; w2 < NW; ++w2) {
-        const float4 b = sm.pp[(par * NW + w2) * 64 + P];
-        B0 += b.x;
-        B1 += b.y;
-        E += b.z;
-      }
-      const float bound = (a.M == 2 ? fmaxf(B0, B1) : B0) + sqrtf(2.f * (kSlots - kLowSlots) * E);
-      const int row_l = P >> 3, ref_l = P & 7;
-      const float thr = fmaxf(key_value(sm.key[row_l]), part_thr(sm.pt[row_l], a.margin));
-      const bool keep = tile * kRowTile + row_l < a.rows && kt * kRefTile + ref_l < a.K &&
-                        !(bound * (1.f + 1.f / 4096.f) < thr);
-      live = __ballot(keep);
-    }
-    const int n_live = __popcll(live);
-    if (prune && kt >= 2 && n_live > 56) prune = false;  // wave-uniform
-    if (n_live == 0) continue;  // workgroup-uniform: every wave read the same partials
-    {
-      const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0));
-      if ((live >> ln) & 1) list[rank] = ln;
-      lds_wave_sync();
-    }
-    // The inverse FFT of the live pairs.  With CPWX columns (pass 1) and
-    // rows (pass 2) per wave, the working waves' columns / rows are
-    // CPWX * w + c, c = 0 .. CPWX-1: lane group c (LPCX lanes) takes column /
-    // row c for the live pairs list[n0 + ln % LPCX].  The first waves hold
-    // rows below 8 and the others rows from 8 on, so that every wave's
-    // pass-2 addresses share one shape (a lane base plus constant offsets).
-    // At most 16 live pairs (most reference tiles) fit 4 columns of 16
-    // lanes per wave: then waves 0..3 (one per SIMD) do the passes and the
-    // others wait at the barriers, so each SIMD issues one wave's
-    // instructions instead of two.
-    auto passes = [&](auto cpw_c) {
-      constexpr int CPWX = decltype(cpw_c)::value, LPCX = 64 / CPWX;
-      const bool work = CPWX * w < 16;  // wave-uniform
-
-      // ---------------- inverse FFT over angle, pass 1 ----------------
-      // H_j (j = 16 k1 + k2) of pair P: half 0 of slot j (j < 128) or half 1
-      // of slot 256 - j (j >= 128; slot 0 for j = 128)
-      if (work) {
+    // ---------------- pass 2 ----------------
+    // Rows below 8 read upwards from slot 16 n1, the others downwards from
+    // slot 256 - 16 n1.  SPLIT: one loop per direction (each wave runs one),
+    // so that either keeps its 16 reads at constant offsets from one address
+    // (in one loop the compiler merges the two read sets into 31 per-element
+    // addresses); the 4-wave kernels, whose registers are full, keep one loop.
+    auto pass2 = [&](auto dir_c) {
+      constexpr int dir = decltype(dir_c)::value;  // 1 up, 2 down, 0 either (chosen per wave)
 #pragma unroll 1
-        for (int n0 = 0; n0 < n_live; n0 += LPCX) {
-          // lane-derived values are recomputed here rather than kept live
-          // across the reference loop, where the registers hold the operand
-          int lnx = ln;
-          asm volatile("" : "+v"(lnx));
-          const int lane_n = lnx % LPCX, k2 = CPWX * w + lnx / LPCX;
-          const bool act = n0 + lane_n < n_live;
-          const int P = list[act ? n0 + lane_n : 0];
-          const int lo = k2 * 128 + P, hi = P - k2 * 128;
-          const int mid = k2 == 0 ? 64 + P : hi + 257 * 64;
-          auto at = [&](int k1) { return k1 < 8 ? lo + k1 * 2048 : (k1 == 8 ? mid : hi + (513 - 32 * k1) * 64); };
-          float2 x[16];
+      for (int n0 = 0; n0 < n_live; n0 += LPCX) {
+        int lnx = ln;
+        asm volatile("" : "+v"(lnx));
+        const int lane_n = lnx % LPCX, c = lnx / LPCX, n1 = CPWX * w + c;
+        const bool act = n0 + lane_n < n_live;
+        const int i = act ? n0 + lane_n : 0, A = PS == 64 ? list[i] : i;
+        float2 x[16];
+        const bool low = dir == 1 || (dir == 0 && CPWX * w < 8);
+        if (low) {
+          const int base = n1 * 32 * PS + A;
 #pragma unroll
-          for (int k1 = 0; k1 < 16; ++k1) x[k1] = sm.stc[at(k1)];
-          inv_pass1(k2, x, [&](int e) { return sm.tw[e & 255]; });
-          if (act) {
+          for (int k2 = 0; k2 < 16; ++k2) x[k2] = stc[base + k2 * 2 * PS];
+        } else if constexpr (dir == 2) {
+          const int base = (513 - 32 * n1) * PS + A;  // k2 = 0; k2 steps go down by 2 PS
+          int top = base - 15 * 2 * PS;               // k2 = 15, the lowest address
+          asm volatile("" : "+v"(top));               // the base of the reads (not re-associated)
+          x[0] = stc[n1 == 8 ? PS + A : base];
 #pragma unroll
-            for (int n1 = 0; n1 < 16; ++n1) sm.stc[at(n1)] = x[n1];
-          }
-        }
-      }
-      __syncthreads();
-
-      // ---------------- pass 2 + arg-max ----------------
-      // Rows below 8 read upwards from slot 16 n1, the others downwards from
-      // slot 256 - 16 n1.  SPLIT: one loop per direction (each wave runs one),
-      // so that either keeps its 16 reads at constant offsets from one address
-      // (in one loop the compiler merges the two read sets into 31 per-element
-      // addresses); the 4-wave kernels, whose registers are full, keep one loop.
-      auto pass2 = [&](auto dir_c) {
-        constexpr int dir = decltype(dir_c)::value;  // 1 up, 2 down, 0 either (chosen per wave)
-#pragma unroll 1
-        for (int n0 = 0; n0 < n_live; n0 += LPCX) {
-          int lnx = ln;
-          asm volatile("" : "+v"(lnx));
-          const int lane_n = lnx % LPCX, c = lnx / LPCX, n1 = CPWX * w + c;
-          const bool act = n0 + lane_n < n_live;
-          const int P = list[act ? n0 + lane_n : 0];
-          const int row_l = P >> 3, ref_l = P & 7;
-          const int row = tile * kRowTile + row_l;
-          const int k = kt * kRefTile + ref_l;
-          float2 x[16];
-          const bool low = dir == 1 || (dir == 0 && CPWX * w < 8);
-          if (low) {
-            const int base = n1 * 2048 + P;
-#pragma unroll
-            for (int k2 = 0; k2 < 16; ++k2) x[k2] = sm.stc[base + k2 * 128];
-          } else if constexpr (dir == 2) {
-            const int base = (513 - 32 * n1) * 64 + P;  // k2 = 0; k2 steps go down by 128
-            int top = base - 15 * 128;                  // k2 = 15, the lowest address
-            asm volatile("" : "+v"(top));               // the base of the reads (not re-associated)
-            x[0] = sm.stc[n1 == 8 ? 64 + P : base];
-#pragma unroll
-            for (int k2 = 1; k2 < 16; ++k2) x[k2] = sm.stc[top + (15 - k2) * 128];
-          } else {
-            const int base = (513 - 32 * n1) * 64 + P;
-            x[0] = sm.stc[n1 == 8 ? 64 + P : base];
-#pragma unroll
-            for (int k2 = 1; k2 < 16; ++k2) x[k2] = sm.stc[base - k2 * 128];
-          }
-          inv_pass2(x);
-          if constexpr (MODE == kTable) {
-            if (act && row < a.rows && k < a.K) {
-              const int n = row / a.S, s = row - n * a.S;
-              const float unscale = PREC == kFP16 ? 1.f / (fp16_scale(a, row) * a.b_scale) : 1.f;
-              for (int m = 0; m < a.M; ++m) {
-                float* o = a.table + ((((size_t)n * a.K + k) * a.M + m) * a.S + s) * kNphi;
-#pragma unroll
-                for (int n2 = 0; n2 < 16; ++n2) o[n1 + 16 * n2] = (m ? x[n2].y : x[n2].x) * unscale;
-              }
-            }
-          } else {
-            // only values above the row's best of earlier reference tiles can
-            // win (a tie with an earlier tile loses: its flat index is smaller)
-            const float thr = sm.thr[row_l];
-            const bool valid = act && row < a.rows && k < a.K;
-            // the candidate left out of this pass (key m * 256 + angle of this
-            // lane's (row, ref)), or -1
-            int ex = -1;
-            if (MODE == kRunnerUp && valid) {
-              const int n = row / a.S, s = row - n * a.S;
-              const int e = a.excl[n];
-              if (e >= 0) {
-                const int rest = e >> 8, se = rest % a.S, km = rest / a.S;
-                if (se == s && km / a.M == k) ex = (km % a.M) * 256 + (e & 255);
-              }
-            }
-            float bv = -INFINITY;
-            int bi = 0x7fffffff;
-            float mx = -INFINITY;
-#pragma unroll
-            for (int n2 = 0; n2 < 16; ++n2) mx = fmaxf(mx, a.M == 2 ? fmaxf(x[n2].x, x[n2].y) : x[n2].x);
-            if (MODE == kArgmax && mx > thr) {
-              // the lane's best is mx; its key is the smallest among the
-              // candidates equal to it (keys grow with n2, mirror 1 after 0)
-              bv = mx;
-              if (a.M == 2) {
-#pragma unroll
-                for (int n2 = 15; n2 >= 0; --n2) bi = x[n2].y == mx ? 256 + n1 + 16 * n2 : bi;
-              }
-#pragma unroll
-              for (int n2 = 15; n2 >= 0; --n2) bi = x[n2].x == mx ? n1 + 16 * n2 : bi;
-            } else if (MODE == kRunnerUp && mx > thr) {
-#pragma unroll
-              for (int n2 = 0; n2 < 16; ++n2) {
-                const int ang = n1 + 16 * n2;
-                if (ang != ex && better(x[n2].x, ang, bv, bi)) { bv = x[n2].x; bi = ang; }
-                if (a.M == 2 && 256 + ang != ex && better(x[n2].y, 256 + ang, bv, bi)) {
-                  bv = x[n2].y;
-                  bi = 256 + ang;
-                }
-              }
-            }
-            if (valid && bi != 0x7fffffff && bv > thr) {
-              const int iota = ((k * a.M + (bi >> 8)) * a.S + row % a.S) * kNphi + (bi & 255);
-              atomicMax(&sm.key[row_l], cand_key(bv, iota));
-            }
-          }
-        }
-      };
-      if (work) {
-        if constexpr (SPLIT) {
-          if (CPWX * w < 8) pass2(std::integral_constant<int, 1>{});  // wave-uniform
-          else pass2(std::integral_constant<int, 2>{});
+          for (int k2 = 1; k2 < 16; ++k2) x[k2] = stc[top + (15 - k2) * 2 * PS];
         } else {
-          pass2(std::integral_constant<int, 0>{});
+          const int base = (513 - 32 * n1) * PS + A;
+          x[0] = stc[n1 == 8 ? PS + A : base];
+#pragma unroll
+          for (int k2 = 1; k2 < 16; ++k2) x[k2] = stc[base - k2 * 2 * PS];
         }
+        inv_pass2(x);
+        if (act) done(i, n1, x);
       }
     };
-    if constexpr (NW == 8) {
-      if (n_live <= 16) passes(std::integral_constant<int, 4>{});  // workgroup-uniform
-      else passes(std::integral_constant<int, 2>{});
-    } else {
-      passes(std::integral_constant<int, CPW>{});
+    if (work) {
+      if constexpr (SPLIT) {
+        if (CPWX * w < 8) pass2(std::integral_constant<int, 1>{});  // wave-uniform
+        else pass2(std::integral_constant<int, 2>{});
+      } else {
+        pass2(std::integral_constant<int, 0>{});
+      }
     }
-    __syncthreads();
-    // the particle bests of the rows, for the next reference tile's bound
-    if (MODE != kTable && tid < 8) {
-      float b = sm.pt[tid];
-      const int part = sm.ppart[tid];
-#pragma unroll
-      for (int r = 0; r < kRowTile; ++r)
-        if (sm.ppart[r] == part) b = fmaxf(b, key_value(sm.key[r]));
-      sm.pt[tid] = b;
-    }
+  };
+  if constexpr (NW == 8) {
+    if (n_live <= 16) passes(std::integral_constant<int, 4>{});  // workgroup-uniform
+    else passes(std::integral_constant<int, 2>{});
+  } else {
+    passes(std::integral_constant<int, 16 / NW>{});
   }
-  __syncthreads();
+}
+
+// The best of a lane's 16 angles n1 + 16 n2 and both mirrors (mirror search),
+// if it reaches thr: its value in bv and m * 256 + angle in bi (the smallest
+// of those equal to it), else bi = 2^31 - 1.  ex: the candidate left out
+// (runner-up pass), or -1.  -inf and NaN are never candidates.
+template <int MODE>
+__device__ __forceinline__ void pick_best(const float2 (&x)[16], int n1, int M, float thr, int ex, float& bv, int& bi) {
+  bv = -INFINITY;
+  bi = 0x7fffffff;
+  float mx = -INFINITY;
+#pragma unroll
+  for (int n2 = 0; n2 < 16; ++n2) mx = fmaxf(mx, M == 2 ? fmaxf(x[n2].x, x[n2].y) : x[n2].x);
+  if (!(mx >= thr) || mx == -INFINITY) return;
+  if (MODE == kArgmax) {
+    // the lane's best is mx; its key is the smallest among the candidates
+    // equal to it (keys grow with n2, mirror 1 after 0)
+    bv = mx;
+    if (M == 2) {
+#pragma unroll
+      for (int n2 = 15; n2 >= 0; --n2) bi = x[n2].y == mx ? 256 + n1 + 16 * n2 : bi;
+    }
+#pragma unroll
+    for (int n2 = 15; n2 >= 0; --n2) bi = x[n2].x == mx ? n1 + 16 * n2 : bi;
+  } else {
+#pragma unroll
+    for (int n2 = 0; n2 < 16; ++n2) {
+      const int ang = n1 + 16 * n2;
+      if (ang != ex && better(x[n2].x, ang, bv, bi)) { bv = x[n2].x; bi = ang; }
+      if (M == 2 && 256 + ang != ex && better(x[n2].y, 256 + ang, bv, bi)) {
+        bv = x[n2].y;
+        bi = 256 + ang;
+      }
+    }
+    if (!(bv >= thr) || bv == -INFINITY) bi = 0x7fffffff;
+  }
+}
+
+// The candidate m * 256 + angle left out of (reference k, shift s) when the
+// flat index e (or -1) lies in that pair, else -1.
+__device__ __forceinline__ int excluded_at(int e, int k, int s, int S, int M) {
+  if (e < 0) return -1;
+  const int rest = e >> 8, se = rest % S, km = rest / S;
+  return (se == s && km / M == k) ? (km % M) * 256 + (e & 255) : -1;
+}
+
+// Particle n's outputs from its best CC and flat index (2^31 - 1: none).
+__device__ __forceinline__ void write_result(const ResultArgs& a, int n, float best, int bi) {
+  const int64_t o = a.out_off + n;
+  if (a.runner_up) {  // second pass: the best over every candidate but the winner
+    a.cc2[o] = bi == 0x7fffffff ? NAN : best;
+    return;
+  }
+  if (a.win) a.win[n] = bi == 0x7fffffff ? -1 : bi;
+  if (bi == 0x7fffffff) {  // no ordered candidate (NaN input): report an invalid winner
+    a.ref[o] = -1;
+    a.mirror[o] = 0;
+    a.shift_x[o] = 0;
+    a.shift_y[o] = 0;
+    a.psi[o] = 0;
+    a.cc[o] = NAN;
+    if (a.flat) a.flat[o] = -1;
+    if (a.cc2) a.cc2[o] = NAN;
+    return;
+  }
+  const int ang = bi & 255;
+  int rest = bi >> 8;
+  const int s = rest % a.S;
+  rest /= a.S;
+  const int m = rest % a.M, k = rest / a.M;
+  a.ref[o] = k;
+  a.mirror[o] = m;
+  a.shift_x[o] = s % a.S1 - a.T;
+  a.shift_y[o] = s / a.S1 - a.T;
+  a.psi[o] = (kNphi - ang) & 255;
+  a.cc[o] = best;
+  if (a.flat) a.flat[o] = bi;
+  if (a.cc2) a.cc2[o] = NAN;
+}
+
+template <int NW>
+struct CorrSmem {
+  float2* stc;              // [128][2][64] spectra of the 64 (row, ref) pairs
+  unsigned long long* key;  // [8] best candidate of each row so far (ordered key, 0 = none)
+  int* list;                // [NW][64] each wave's list of the pairs of the inverse FFT
+  float2* tw;               // exp(-2 pi i e / 256)
+  __device__ __forceinline__ CorrSmem(float* smem) {
+    stc = reinterpret_cast<float2*>(smem);
+    key = reinterpret_cast<unsigned long long*>(smem + kStateFloats);
+    list = reinterpret_cast<int*>(key + 8);
+    tw = reinterpret_cast<float2*>(list + NW * 64);
+  }
+  static constexpr size_t bytes() {
+    return kStateFloats * sizeof(float) + 8 * sizeof(unsigned long long) + NW * 64 * sizeof(int) +
+           kNphi * sizeof(float2);
+  }
+};
+
+// One 8-row tile against the reference tiles kt0 .. kt1 - 1, every pair
+// evaluated; the rows' bests go to c.rowkey.
+template <int PREC, int NW, class Contract, int MODE, bool SPLIT>
+__device__ __forceinline__ void corr_tile(const CorrArgs& a, int tile, int kt0, int kt1, const CorrSmem<NW>& sm,
+                                          Contract& con) {
+  const int tid = threadIdx.x, ln = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid < 8) sm.key[tid] = 0ull;
+  con.prefetch(a, kt0, w, ln);
+  // (FP16: each particle's operand rows come scaled by a power of two of its
+  // own, exact, so results do not depend on how particles are grouped)
+  con.load_a(a, tile, a_block_pos(ln & 15), w, ln);
+  for (int kt = kt0; kt < kt1; ++kt) {
+    con.run(a, sm.stc, tile, kt, w, ln);
+    con.prefetch(a, kt + 1 < kt1 ? kt + 1 : kt0, w, ln);
+    __syncthreads();
+    const uint64_t live =
+        __ballot(tile * kRowTile + (ln >> 3) < a.rows && kt * kRefTile + (ln & 7) < a.K);
+    int* list = sm.list + w * 64;
+    if ((live >> ln) & 1)
+      list[__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0))] = ln;
+    lds_wave_sync();
+    inverse_pairs<NW, SPLIT, 64>(sm.stc, sm.tw, list, __popcll(live), w, ln, [&](int i, int n1, const float2(&x)[16]) {
+      const int P = list[i];
+      const int row = tile * kRowTile + (P >> 3), k = kt * kRefTile + (P & 7);
+      const int n = row / a.S, s = row - n * a.S;
+      if constexpr (MODE == kTable) {
+        // (FP16: the particle's operand and the refset's are scaled by powers of two)
+        auto value = [&](float v) { return PREC == kFP16 ? fp16_value(v, a.maxabs[n], a.b_scale) : v; };
+        for (int m = 0; m < a.M; ++m) {
+          float* o = a.table + ((((size_t)n * a.K + k) * a.M + m) * a.S + s) * kNphi;
+#pragma unroll
+          for (int n2 = 0; n2 < 16; ++n2) o[n1 + 16 * n2] = value(m ? x[n2].y : x[n2].x);
+        }
+      } else {
+        const int ex = MODE == kRunnerUp ? excluded_at(a.excl[n], k, s, a.S, a.M) : -1;
+        float bv;
+        int bi;
+        pick_best<MODE>(x, n1, a.M, key_value(sm.key[P >> 3]), ex, bv, bi);
+        if (bi != 0x7fffffff) {
+          const int iota = ((k * a.M + (bi >> 8)) * a.S + s) * kNphi + (bi & 255);
+          atomicMax(&sm.key[P >> 3], cand_key(bv, iota));
+        }
+      }
+    });
+    __syncthreads();
+  }
   if (MODE != kTable && tid < 8) {
     const int r = tile * kRowTile + tid;
-    if (r < a.rows) {
-      const unsigned long long kk = sm.key[tid];
-      const float unscale = PREC == kFP16 ? 1.f / (fp16_scale(a, r) * a.b_scale) : 1.f;
-      a.row_cc[r] = key_value(kk) * unscale;
-      a.row_idx[r] = key_index(kk);
-    }
-    // the particle of the last row continues into the run's next tile
-    float b = sm.pt[tid];
-    const int part = sm.ppart[tid];
-#pragma unroll
-    for (int r2 = 0; r2 < kRowTile; ++r2)
-      if (sm.ppart[r2] == part) b = fmaxf(b, key_value(sm.key[r2]));
-    if (tid == 7) {
-      *sm.carry_p = part;
-      *sm.carry_v = b;
-    }
+    if (r < a.rows) atomicMax(&a.rowkey[r], sm.key[tid]);
   }
 }
 
 template <int PREC, int NW, int MAXR, bool RES, bool EXACT>
 struct ContractFor {
   typedef typename std::conditional<PREC == kFP32, Fp32Contract<NW, MAXR, RES, EXACT>,
-                                    Half16Contract<PREC == kFP32 ? kBF16 : PREC, NW, MAXR, EXACT, RES>>::type type;
+                                    Half16Contract<PREC == kFP32 ? kBF16 : PREC, NW, MAXR, RES>>::type type;
 };
-
-// Row tiles of run `run` (a.tiles_per_run consecutive tiles), in order, so
-// that a particle's best carries from one of its tiles to the next.
-template <int PREC, int NW, class Contract, int MODE, bool SPLIT>
-__device__ __forceinline__ void corr_run(const CorrArgs& a, int run, const CorrSmem<NW>& sm, Contract& con) {
-  const int t0 = run * a.tiles_per_run;
-  const int t1 = min(t0 + a.tiles_per_run, a.n_row_tiles);
-  if (threadIdx.x == 0) *sm.carry_p = -1;
-  lds_wave_sync();
-  con.prefetch(a, 0, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
-  for (int t = t0; t < t1; ++t) corr_tile<PREC, NW, Contract, MODE, SPLIT>(a, t, sm, con);
-}
 
 template <int PREC, int NW, int MAXR, bool RES, bool EXACT, int MODE>
 __global__ __launch_bounds__(NW * 64) void k_corr(CorrArgs a) {
@@ -859,22 +761,9 @@ __global__ __launch_bounds__(NW * 64) void k_corr(CorrArgs a) {
   CorrSmem<NW> sm(smem);
   if (threadIdx.x < kNphi) sm.tw[threadIdx.x] = w256c(a.cs32, threadIdx.x);
   typename ContractFor<PREC, NW, MAXR, RES, EXACT>::type con;
-  corr_run<PREC, NW, decltype(con), MODE, NW == 8>(a, blockIdx.x, sm, con);
-}
-
-// Batched form over the runs of several stacks' row tiles: workgroup g takes
-// run g of the concatenated run list (run_start[p] is piece p's first).
-template <int PREC, int NW, int MAXR, bool RES, bool EXACT>
-__global__ __launch_bounds__(NW * 64) void k_corr_batch(CorrBatch b) {
-  extern __shared__ float smem[];
-  CorrSmem<NW> sm(smem);
-  if (threadIdx.x < kNphi) sm.tw[threadIdx.x] = w256c(b.piece[0].cs32, threadIdx.x);
-  typename ContractFor<PREC, NW, MAXR, RES, EXACT>::type con;
-  const int item = blockIdx.x;
-  if (item >= b.run_start[b.n]) return;
-  int p = 0;
-  while (p + 1 < b.n && b.run_start[p + 1] <= item) ++p;
-  corr_run<PREC, NW, decltype(con), kArgmax, NW == 8>(b.piece[p], item - b.run_start[p], sm, con);
+  const int part = blockIdx.x / a.n_row_tiles, kt0 = part * a.kt_per_wg;
+  corr_tile<PREC, NW, decltype(con), MODE, NW == 8>(a, blockIdx.x - part * a.n_row_tiles, kt0,
+                                                    min(kt0 + a.kt_per_wg, a.n_ref_tiles), sm, con);
 }
 
 template <int P_, int NW_, int MR_, bool RES_, bool EXACT_>
@@ -885,59 +774,32 @@ struct Cfg {
 
 template <class C, int MODE>
 inline void launch_mode(const CorrArgs& a, hipStream_t st) {
-  const int runs = (a.n_row_tiles + a.tiles_per_run - 1) / a.tiles_per_run;
-  hipLaunchKernelGGL((k_corr<C::P, C::NW, C::MR, C::RES, C::EXACT, MODE>), dim3(runs), dim3(C::NW * 64),
+  const int parts = (a.n_ref_tiles + a.kt_per_wg - 1) / a.kt_per_wg;
+  hipLaunchKernelGGL((k_corr<C::P, C::NW, C::MR, C::RES, C::EXACT, MODE>), dim3(a.n_row_tiles * parts), dim3(C::NW * 64),
                      CorrSmem<C::NW>::bytes(), st, a);
 }
 
+// Per-precision instantiation sets (one translation unit each): one launch
+// over a's row tiles; mode: kArgmax, kTable (write the CC table) or kRunnerUp.
+void corr_dispatch_fp32(int variant, const CorrArgs& a, int mode, hipStream_t st);
+void corr_dispatch_bf16(int variant, const CorrArgs& a, int mode, hipStream_t st);
+void corr_dispatch_fp16(int variant, const CorrArgs& a, int mode, hipStream_t st);
+
 template <class C>
-inline void launch_one(const CorrArgs& a, bool table, hipStream_t st) {
-  if (table) launch_mode<C, kTable>(a, st);
+inline void corr_go(const CorrArgs& a, int mode, hipStream_t st) {
+  if (mode == kTable) launch_mode<C, kTable>(a, st);
+  else if (mode == kRunnerUp) launch_mode<C, kRunnerUp>(a, st);
   else launch_mode<C, kArgmax>(a, st);
 }
 
-template <class C>
-inline void launch_one(const CorrBatch& b, int grid, hipStream_t st) {
-  (void)grid;
-  hipLaunchKernelGGL((k_corr_batch<C::P, C::NW, C::MR, C::RES, C::EXACT>), dim3(b.run_start[b.n]),
-                     dim3(C::NW * 64), CorrSmem<C::NW>::bytes(), st, b);
-}
-
-// Per-precision instantiation sets (one translation unit each).  `b` null:
-// one launch over a's row tiles (table: write the CC table); else the
-// persistent launch over b's pieces with `grid` workgroups.
-void corr_dispatch_fp32(int variant, int r4min, int r4max, const CorrArgs* a, bool table, const CorrBatch* b,
-                        int grid, hipStream_t st);
-void corr_dispatch_bf16(int variant, int r4min, int r4max, const CorrArgs* a, bool table, const CorrBatch* b,
-                        int grid, hipStream_t st);
-void corr_dispatch_fp16(int variant, int r4min, int r4max, const CorrArgs* a, bool table, const CorrBatch* b,
-                        int grid, hipStream_t st);
-
-// The runner-up pass (one instantiation per precision: the generic
-// streamed-operand configuration, any R4 <= 16).
-void corr_runner_up_fp32(const CorrArgs& a, hipStream_t st);
-void corr_runner_up_bf16(const CorrArgs& a, hipStream_t st);
-void corr_runner_up_fp16(const CorrArgs& a, hipStream_t st);
-
-template <class C>
-inline void corr_go(const CorrArgs* a, bool table, const CorrBatch* b, int grid, hipStream_t st) {
-  if (b) launch_one<C>(*b, grid, st);
-  else launch_one<C>(*a, table, st);
-}
-
-// 16-bit forms: operand ring bucket MAXR in {8, 12, 16} (R4 <= 8, 9..12,
-// 13..16); exact where every work item lies in the bucket (then the step
-// count is fixed, and at 16 the last step is 8 wide), else the run-time form.
+// 16-bit forms: operand ring bucket MAXR in {8, 10, 12, 16} (R4 <= 8, 9..10,
+// 11..12, 13..16).
 template <int PREC, bool RES>
-inline void corr_dispatch_16(int r4min, int r4max, const CorrArgs* a, bool table, const CorrBatch* b, int grid,
-                             hipStream_t st) {
-  if (r4max <= 8) return corr_go<Cfg<PREC, 8, 8, RES, true>>(a, table, b, grid, st);
-  if (r4max <= 12) {
-    if (r4min > 8) return corr_go<Cfg<PREC, 8, 12, RES, true>>(a, table, b, grid, st);
-    return corr_go<Cfg<PREC, 8, 12, RES, false>>(a, table, b, grid, st);
-  }
-  if (r4min > 12) return corr_go<Cfg<PREC, 8, 16, RES, true>>(a, table, b, grid, st);
-  return corr_go<Cfg<PREC, 8, 16, RES, false>>(a, table, b, grid, st);
+inline void corr_dispatch_16(int R4, const CorrArgs& a, int mode, hipStream_t st) {
+  if (R4 <= 8) return corr_go<Cfg<PREC, 8, 8, RES, true>>(a, mode, st);
+  if (R4 <= 10) return corr_go<Cfg<PREC, 8, 10, RES, true>>(a, mode, st);
+  if (R4 <= 12) return corr_go<Cfg<PREC, 8, 12, RES, true>>(a, mode, st);
+  return corr_go<Cfg<PREC, 8, 16, RES, true>>(a, mode, st);
 }
 
 }  // namespace mra

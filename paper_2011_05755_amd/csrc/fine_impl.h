@@ -1,0 +1,572 @@
+// Second half of the arg-max: with the upper bound of every (row, reference)
+// pair known (bound_impl.h), evaluate only the pairs that can still win.
+//
+// One workgroup takes a particle.  It orders the particle's rows (shifts) by
+// their largest bound and takes them in groups of up to eight, best first,
+// until the best CC found exceeds every bound that is left.  The first group
+// starts with each row's best reference, which settles the threshold for nearly all else;
+// after that the pairs of a group whose bound reaches it are collected and
+// evaluated 16 at a time, from up to 8 references picked freely.  On 76 px
+// particles with 100 references at SNR 0.05 about 12 of the 4900 pairs are
+// evaluated, in two to three such steps, so the kernel is bound by the latency
+// of a step's phases (operands, contraction, inverse FFT, each between
+// barriers), not by their arithmetic: the state holds 16 pairs and both
+// operands are streamed through the registers, so that several workgroups
+// share a CU (16-bit forms: 4 of 4 waves; FP32: 2 of 8, as the resampler).
+// Lanes of rows or references that a step does not need repeat those it does,
+// and load nothing more.
+//
+// The result is the arg-max over every pair: a pair that is never evaluated
+// has a bound below the best CC (part_thr: below it by the re-ranking margin
+// in the re-ranked 16-bit forms, so that every row within that margin keeps its
+// exact best).  Bounds that are not below it in every case, infinite and NaN
+// ones included, are evaluated, and ties are decided by the flat index in
+// cand_key, whatever the order of evaluation.
+//
+// 16-bit forms read the rows' operand as the resampler left it.  FP32
+// alignment makes the FP32 operand of the eight rows here (resampling and
+// ring FFTs as in the resampling kernel, the same arithmetic), in a scratch
+// tile per workgroup that stays in the caches, so the FP32 operand of all rows
+// never goes through HBM.  Before that (kFineTighten) the FP16 operand's own CC
+// of the live pairs replaces their bounds: it is within fp16_error of the FP32
+// one, which leaves 3 to 4 rows per particle instead of 10 to 13, one group of
+// eight instead of two.
+#pragma once
+
+#include "bound_impl.h"
+#include "polar_impl.h"
+
+namespace mra {
+
+constexpr int kFinePairs = 16;     // pairs evaluated at a time
+constexpr int kFineList = 512;     // entries of the list of live pairs
+constexpr int kFineRefs = kFineList / 8;  // references looked over at a time
+
+// The pruning threshold a particle's best so far imposes on its rows: the
+// best itself, or (re-ranked 16-bit forms) margin * |best| below it, so that
+// every row within that margin of the particle's best keeps its exact best.
+__device__ __forceinline__ float part_thr(float best, float margin) {
+  return (margin > 0.f && best > -INFINITY) ? best - margin * fabsf(best) : best;
+}
+
+// The rows and references of a step: block row pair (row j, p) takes row
+// rows[j], block column pair (reference d, q) reference refs[d]; pair P = j * 8
+// + d has the state index rank[P], or -1 if it is not evaluated.  One copy per
+// wave.
+struct FineStep {
+  int rank[64];
+  int refs[8];
+  int j[kFinePairs], k[kFinePairs];  // row and reference of each evaluated pair
+};
+
+__device__ __forceinline__ void store_live(float2* stc, int slot, int ln, const f32x4& acc, int rank) {
+  float2 h0, h1;
+  pair_gather(ln, acc, h0, h1);
+  if (rank >= 0) {
+    stc[(slot * 2) * kFinePairs + rank] = h0;
+    stc[(slot * 2 + 1) * kFinePairs + rank] = h1;
+  }
+}
+
+// Contractions of one step for the wave's slots, both operands streamed; the
+// products and their order are those of corr_impl.h.
+//
+// 16-bit forms, NW waves: the lane's block row is element k of row tile `tile`,
+// counted from the particle's first (c.A points there); ref is the lane's
+// reference.  Wave w takes the operand's runs 2 (w + NW i) + hh of 8 slots.
+template <int PREC, int MAXR, int NW>
+struct FineContract16 {
+  typedef Half16Contract<PREC, 8, MAXR, false> Base;
+  typedef typename Base::Frag Frag;
+  static constexpr int kSlotsPerWave = kSlots / NW;
+  // the wave's q-th slot, 8 of a run at a time: run index q / 8
+  static __device__ __forceinline__ int slot_of(int q, int w) {
+    const int run = q >> 3;  // (w8, hh) = (w + NW (run / 2), run % 2)
+    return w + NW * (run >> 1) + 8 * (8 * (run & 1) + (q & 7));
+  }
+  static __device__ __forceinline__ void run(const CorrArgs& c, float2* stc, int tile, int k, int ref, int w, int ln,
+                                             int rank) {
+    // opaque lane values: what is derived from them is computed here, not
+    // kept in registers across the caller's loops
+    asm volatile("" : "+v"(tile), "+v"(k), "+v"(ln), "+v"(rank), "+v"(ref));
+    ln &= 63;
+    Base con;
+    constexpr int D = 4;  // reference operand kept D slots ahead
+    Frag b[D];
+    const int pl = b16_lane(ref & 7, ln);
+    const uint32_t tile_off = (uint32_t)(ref >> 3) * (uint32_t)(kSlots * Base::SE);
+#pragma unroll
+    for (int i = 0; i < D; ++i) con.load_b_at(c, 0, slot_of(i, w), pl, tile_off, b[i]);
+    const uint32_t lane_off = (uint32_t)((tile * 4 + (ln >> 4)) * c.R4) * (kSlots * 16 * 2) + k * 16;
+#pragma unroll 1
+    for (int run = 0; run < kSlotsPerWave / 8; ++run) {
+      const int g = 2 * (w + NW * (run >> 1)) + (run & 1);
+      u32x4 u[8 * Base::NS];
+#pragma unroll
+      for (int t = 0; t < 8 * Base::NS; ++t) {
+        if (t < MAXR) {
+          const char* at = reinterpret_cast<const char*>(c.A) + (size_t)(t < c.R4 ? t : c.R4 - 1) * (kSlots * 16 * 2) +
+                           g * 256;  // the same for every lane
+          u[t] = *reinterpret_cast<const u32x4*>(at + lane_off);
+        } else {
+          u[t] = u32x4{0u, 0u, 0u, 0u};
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int q = 8 * run + j;
+        Frag x;
+#pragma unroll
+        for (int d = 0; d < 4 * Base::NF; ++d) x.f[d / 4][d % 4] = Base::dword(u, j, d);
+#pragma unroll
+        for (int d = 0; d < Base::TD; ++d) x.t[d] = Base::dword(u, j, 4 * Base::NF + d);
+        const f32x4 acc = con.product(x, b[j % D]);
+        // (past the last slot it reads the last one again)
+        con.load_b_at(c, 0, slot_of(q + D < kSlotsPerWave ? q + D : kSlotsPerWave - 1, w), pl, tile_off, b[j % D]);
+        store_live(stc, slot_of(q, w), ln, acc, rank);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+};
+
+// FP32, 8 waves: the operand is the scratch tile c.A (kRingPerm: the wave's
+// slots w + 8 i in pairs, one 8-byte load for two slots).
+template <int MAXR>
+struct FineContract32 {
+  static constexpr int M4 = (MAXR + 3) / 4;
+  struct Ops {
+    f32x2 a[MAXR];
+    f32x4 b0[M4], b1[M4];
+  };
+  static __device__ __forceinline__ void load(const CorrArgs& c, const float* ap, const float* bp, int i2, int ln,
+                                              Ops& o) {
+#pragma unroll
+    for (int t = 0; t < MAXR; ++t) o.a[t] = a_pair<0>(c, ap + 32 * i2, ln, t);
+    const int last = b32_pitch(c.R4) / 4 - 1;
+    const float* b0 = bp + (size_t)i2 * 16 * 8 * b32_pitch(c.R4);
+    const float* b1 = b0 + (size_t)8 * 8 * b32_pitch(c.R4);
+#pragma unroll
+    for (int t = 0; t < M4; ++t) {  // unconditional (see corr_impl.h)
+      o.b0[t] = *reinterpret_cast<const f32x4*>(b0 + 4 * (t < last ? t : last));
+      o.b1[t] = *reinterpret_cast<const f32x4*>(b1 + 4 * (t < last ? t : last));
+    }
+  }
+  static __device__ __forceinline__ void run(const CorrArgs& c, float2* stc, int, int, int ref, int w, int ln,
+                                             int rank) {
+    asm volatile("" : "+v"(ln), "+v"(rank), "+v"(ref));
+    ln &= 63;
+    const float* ap = c.A + ((size_t)(ln >> 4) * c.R4 * kSlots + 16 * w) * 16 + 2 * a_block_pos(ln & 15);
+    const float* bp = b32_lane(c, ref, w, ln);
+    auto mul = [&](int i2, const Ops& o) {
+      f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < MAXR; ++t) {
+        if (t < c.R4) {
+          acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(o.a[t].x, o.b0[t / 4][t % 4], acc0, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(o.a[t].y, o.b1[t / 4][t % 4], acc1, 0, 0, 0);
+        }
+      }
+      store_live(stc, w + 16 * i2, ln, acc0, rank);
+      store_live(stc, w + 16 * i2 + 8, ln, acc1, rank);
+    };
+    if constexpr (MAXR <= 9) {  // two slots ahead
+      Ops o[2];
+      load(c, ap, bp, 0, ln, o[0]);
+#pragma unroll 1
+      for (int i2 = 0; i2 < 8; i2 += 2) {
+        load(c, ap, bp, i2 + 1, ln, o[1]);
+        mul(i2, o[0]);
+        load(c, ap, bp, i2 + 2 < 8 ? i2 + 2 : 7, ln, o[0]);
+        mul(i2 + 1, o[1]);
+      }
+    } else {
+#pragma unroll 1
+      for (int i2 = 0; i2 < 8; ++i2) {
+        Ops o;
+        load(c, ap, bp, i2, ln, o);
+        mul(i2, o);
+      }
+    }
+  }
+};
+
+// LDS of a workgroup: S rows, NW waves.
+struct FineSmem {
+  unsigned long long* key;    // [S] best candidate of each row (0 = none)
+  unsigned long long* pbest;  // best of the particle
+  float2* tw;                 // exp(-2 pi i e / 256)
+  float* rowmax;              // [S] largest bound of each row
+  int* rowarg;                // [S] its reference
+  int* order;                 // [S] rows by falling rowmax
+  int* taken;                 // [S] 16-bit forms: the row has been in a group
+  int* shift;                 // [8] the group's rows
+  int* count;                 // entries of the list
+  uint32_t* pmax;             // [kFinePairs] tighten: largest CC of each pair (ordered bits)
+  uint32_t* live;             // [kFineList] live pairs: reference * 8 + row of the group
+  FineStep* step;             // [NW]
+  float* work;                // the pairs' state; between steps (FP32) the image, scratch and cos/sin
+  static constexpr int pad(int S) { return (S + 3) & ~3; }
+  __device__ __forceinline__ FineSmem(float* smem, int S, int NW) {
+    const int P = pad(S);
+    key = reinterpret_cast<unsigned long long*>(smem);
+    pbest = key + P;
+    tw = reinterpret_cast<float2*>(pbest + 2);
+    live = reinterpret_cast<uint32_t*>(tw + kNphi);
+    rowmax = reinterpret_cast<float*>(live + kFineList);
+    rowarg = reinterpret_cast<int*>(rowmax + P);
+    order = rowarg + P;
+    taken = order + P;
+    shift = taken + P;
+    count = shift + 8;
+    pmax = reinterpret_cast<uint32_t*>(count + 4);
+    step = reinterpret_cast<FineStep*>(pmax + kFinePairs);
+    work = reinterpret_cast<float*>(step + NW);
+  }
+  static constexpr size_t fixed_bytes(int S, int NW) {
+    return (size_t)(pad(S) + 2) * 8 + kNphi * sizeof(float2) + kFineList * sizeof(uint32_t) + 4 * (size_t)pad(S) * 4 +
+           (8 + 4 + kFinePairs) * 4 + NW * sizeof(FineStep);
+  }
+};
+static_assert(sizeof(FineStep) % 16 == 0 && FineSmem::fixed_bytes(49, 4) % 16 == 0, "the work area is 16-byte aligned");
+
+// FP32: the operand of the group's rows (shifts sh[0 .. 7]) into the scratch
+// tile, one ring per wave at a time (8 waves).
+__device__ __forceinline__ void fine_operand(const FineArgs& a, int n, const int* sh, float* work, float* tile) {
+  float* img = work;
+  float2* scr = reinterpret_cast<float2*>(work + ((a.Lp * a.Lp + 3) & ~3));
+  CosSin* cs = reinterpret_cast<CosSin*>(scr + kPolarWaves * 64 * 9);
+  stage_image(img, a.parts + (size_t)n * a.L * a.L, a.L, a.Lp, a.pad);
+  stage_cs(cs, a.cs64);
+  __syncthreads();
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ln_ = threadIdx.x & 63;
+  const int l_ = ln_ >> 3, r_ = ln_ & 7;
+  float2* my = scr + w * 64 * 9;
+  float* stage = reinterpret_cast<float*>(my);
+  const int base = (a.cx + a.pad) * a.Lp + (a.cx + a.pad);
+  const int s1m = (65536 + a.m.S1 - 1) / a.m.S1;
+  const int o4 = 4 * (base + shift_offset(sh[r_], a.m.S1, s1m, a.m.T, a.Lp));
+#pragma unroll 1
+  for (int ring = w; ring < a.c.R; ring += 8) {
+    // opaque lane indices: addresses are recomputed per ring instead of
+    // being held in registers across the loop
+    int l = l_, r = r_, ln = ln_;
+    asm volatile("" : "+v"(l), "+v"(r), "+v"(ln));
+    l &= 7;
+    r &= 7;
+    ln &= 63;
+    int k1a, k1b;
+    fwd_cols(l, k1a, k1b);
+    float v[32];
+    float2 Za[8], Zb[8];
+    sample_ring(img, cs, my, (float)(a.r_min + ring), l, r, o4, 4 * a.Lp, v);
+    fft_ring(cs, my, l, r, k1a, k1b, v, Za, Zb);
+    RingSlots rs;
+    ring_slots(cs, l, Za, Zb, rs);
+    float* dst = tile + (size_t)ring * kSlots * 16;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      stage_slots(stage, h, r, rs);
+      wave_sync();
+      write_f32_half(stage, dst, h, ln, true, 16, 0, 8);
+      wave_sync();
+    }
+  }
+}
+
+template <int PREC, int NW, class Contract, int MODE>
+__device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int n, float* smem) {
+  constexpr int kThreads = 64 * NW;
+  const FineSmem sm(smem, c.S, NW);
+  const int tid = threadIdx.x, ln = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int S = c.S, row0 = n * S;
+  float* ub = c.ub + (size_t)row0 * c.ldu;
+  if (PREC != kFP32)  // the particle's first row tile
+    c.A = reinterpret_cast<const float*>(reinterpret_cast<const uint16_t*>(c.A) +
+                                         (size_t)(row0 >> 3) * (kSlots * c.R4 * 64));
+  float2* stc = reinterpret_cast<float2*>(sm.work);
+  FineStep& st = sm.step[w];
+  const int ex0 = MODE == kRunnerUp ? c.excl[n] : -1;
+  auto value = [&](float v) { return PREC == kFP16 ? fp16_value(v, c.maxabs[n], c.b_scale) : v; };
+  // (infinite bounds: the particle does not scale into FP16)
+  if (MODE == kFineTighten && !(c.maxabs[n] * 512.f < INFINITY)) return;
+
+  for (int i = tid; i < kNphi; i += kThreads) sm.tw[i] = w256c(c.cs32, i);
+  for (int s = tid; s < S; s += kThreads) {
+    const unsigned long long kk = c.rowkey[row0 + s];
+    const int k = key_index(kk);
+    sm.rowmax[s] = key_value(kk);
+    sm.rowarg[s] = k < c.K ? k : 0;
+    sm.key[s] = 0ull;
+    sm.taken[s] = 0;
+  }
+  if (tid == 0) *sm.pbest = 0ull;
+  if (tid < kFinePairs) sm.pmax[tid] = 0u;
+  __syncthreads();
+  for (int s = tid; s < S; s += kThreads) {
+    const float m = sm.rowmax[s];
+    int rank = 0;
+#pragma unroll 8
+    for (int t = 0; t < S; ++t) {
+      const float v = sm.rowmax[t];
+      rank += (v > m || (v == m && t < s)) ? 1 : 0;
+    }
+    sm.order[rank] = s;
+  }
+  __syncthreads();
+
+  auto threshold = [&]() { return part_thr(key_value(*sm.pbest), a.margin); };
+  bool first_group = true;
+  for (int g0 = 0; g0 < S; first_group = false) {
+    // the next group: up to eight live rows.  FP32, which makes their operand
+    // here, takes the next eight in order; the 16-bit forms those in the row
+    // tile of the next one, whose operand shares cache lines.  (Every wave
+    // reads the same values here: the last update of *pbest and of taken lies
+    // before a barrier, so all take the same way.)
+    const float thr0 = threshold();
+    const int top = sm.order[g0];
+    if (sm.rowmax[top] < thr0) break;
+    int nrow;
+    if constexpr (PREC == kFP32) {
+      const int i = g0 + (ln & 7);
+      const bool live = i < S && !(sm.rowmax[sm.order[i < S ? i : 0]] < thr0);
+      nrow = __popc((uint32_t)__ballot(live) & 0xffu);  // a prefix: rowmax falls
+      // rows past the live ones repeat the first
+      if (tid < 8) sm.shift[tid] = sm.order[g0 + (tid < nrow ? tid : 0)];
+      g0 += 8;
+    } else {
+      const int s = (((row0 + top) >> 3) << 3) + (ln & 7) - row0;
+      const bool live = ln < 8 && s >= 0 && s < S && !sm.taken[s] && !(sm.rowmax[s] < thr0);
+      const uint32_t m = (uint32_t)__ballot(live);
+      nrow = __popc(m);
+      __syncthreads();
+      if (tid < 8) {
+        if (live) {
+          sm.shift[__popc(m & ((1u << ln) - 1u))] = s;
+          sm.taken[s] = 1;
+        }
+        if (ln >= nrow) sm.shift[ln] = top;
+      }
+    }
+    __syncthreads();
+    if constexpr (PREC != kFP32)
+      while (g0 < S && sm.taken[sm.order[g0]]) ++g0;
+    if constexpr (PREC == kFP32) {
+      fine_operand(a, n, sm.shift, sm.work, const_cast<float*>(c.A));
+      __syncthreads();  // the tile is written and the work area is free for the state
+    }
+
+    // the references in windows of kFineRefs; before the first window of the
+    // first group (base = -kFineRefs) each row's best reference
+    for (int base = first_group ? -kFineRefs : 0; base < c.K; base += kFineRefs) {
+      int cnt = nrow;
+      if (base >= 0) {
+        if (tid == 0) *sm.count = 0;
+        __syncthreads();
+        const float thr = threshold();
+        for (int i = tid; i < 8 * kFineRefs; i += kThreads) {
+          const int j = i / kFineRefs, k = base + i % kFineRefs;
+          if (j >= nrow || k >= c.K) continue;
+          const int s = sm.shift[j];
+          const float u = ub[(size_t)s * c.ldu + k];
+          if (!(u < thr) && !(first_group && k == sm.rowarg[s])) sm.live[atomicAdd(sm.count, 1)] = (uint32_t)(k * 8 + j);
+        }
+        __syncthreads();
+        cnt = *sm.count;
+      }
+#pragma unroll 1
+      for (int i0 = 0; i0 < cnt;) {
+        // the next step: entries i0 .. i0 + 15 that are still live, up to the
+        // first whose reference would be the ninth (lane i < 16: entry i0 + i;
+        // every wave does the same)
+        bool on = ln < kFinePairs && i0 + ln < cnt;
+        int j = 0, k = 0;
+        if (on) {
+          if (base >= 0) {
+            const uint32_t e = sm.live[i0 + ln];
+            k = (int)(e >> 3);
+            j = (int)(e & 7u);
+            // (a long list: the threshold may have passed it since)
+            if (i0 > 0) on = !(ub[(size_t)sm.shift[j] * c.ldu + k] < threshold());
+          } else {
+            j = ln;
+            k = sm.rowarg[sm.shift[ln]];
+          }
+        }
+        uint32_t m = (uint32_t)__ballot(on);
+        int first = ln;  // the first entry with this one's reference
+#pragma unroll
+        for (int e = kFinePairs - 1; e >= 0; --e)
+          if (((m >> e) & 1) && __builtin_amdgcn_readlane(k, e) == k && e < first) first = e;
+        const uint32_t fm = (uint32_t)__ballot(on && first == ln);
+        const int d = __popc(fm & ((1u << (first & 31)) - 1u));
+        const uint32_t over = (uint32_t)__ballot(on && d >= 8);
+        const int take = over ? __ffs(over) - 1 : kFinePairs;
+        i0 += take;
+        m &= (1u << take) - 1u;
+        if (m == 0) continue;  // the same in every wave
+        const int np = __popc(m), e0 = __ffs(m) - 1;
+        const int ka = __builtin_amdgcn_readlane(k, e0), ja = __builtin_amdgcn_readlane(j, e0);
+        lds_wave_sync();  // the wave is done with its last step
+        st.rank[ln] = -1;
+        if (ln < 8) st.refs[ln] = ka;
+        lds_wave_sync();
+        if (ln < kFinePairs && ((m >> ln) & 1)) {
+          const int r = __popc(m & ((1u << ln) - 1u));
+          st.rank[j * 8 + d] = r;
+          if (first == ln) st.refs[d] = k;
+          st.j[r] = j;
+          st.k[r] = k;
+        }
+        lds_wave_sync();
+        {
+          // rows without a pair repeat the first pair's
+          const int jr = (ln & 15) >> 1;
+          bool used = false;
+#pragma unroll
+          for (int r = 0; r < 8; ++r) used |= st.rank[jr * 8 + r] >= 0;
+          const int row = row0 + sm.shift[used ? jr : ja];
+          Contract::run(c, stc, (row >> 3) - (row0 >> 3), (ln & 1) * 8 + (row & 7), st.refs[(ln >> 1) & 7], w, ln,
+                        st.rank[lane_pair(ln)]);
+        }
+        __syncthreads();
+        inverse_pairs<NW, true, kFinePairs>(stc, sm.tw, nullptr, np, w, ln, [&](int i, int n1, const float2(&x)[16]) {
+          if constexpr (MODE == kFineTighten) {
+            float mx = -INFINITY;
+            bool nan = false;
+#pragma unroll
+            for (int n2 = 0; n2 < 16; ++n2) {
+              mx = fmaxf(mx, c.M == 2 ? fmaxf(x[n2].x, x[n2].y) : x[n2].x);
+              nan |= !(x[n2].x == x[n2].x) || !(x[n2].y == x[n2].y);
+            }
+            atomicMax(&sm.pmax[i], (uint32_t)(cand_key(nan ? INFINITY : mx, 0) >> 32));
+          } else {
+            const int s = sm.shift[st.j[i]], k = st.k[i];
+            const int ex = MODE == kRunnerUp ? excluded_at(ex0, k, s, S, c.M) : -1;
+            float bv;
+            int bi;
+            pick_best<MODE == kRunnerUp ? kRunnerUp : kArgmax>(x, n1, c.M, key_value(sm.key[s]), ex, bv, bi);
+            if (bi != 0x7fffffff) {
+              const unsigned long long key = cand_key(bv, ((k * c.M + (bi >> 8)) * S + s) * kNphi + (bi & 255));
+              atomicMax(&sm.key[s], key);
+              atomicMax(sm.pbest, key);
+            }
+          }
+        });
+        __syncthreads();
+        if constexpr (MODE == kFineTighten) {
+          // the FP16 CC is within the rounding error of the FP32 one, and of
+          // its own evaluation (2^-12 of the bound)
+          if (tid < np) {
+            const int s = sm.shift[st.j[tid]], k = st.k[tid];
+            const float cc = key_value((unsigned long long)sm.pmax[tid] << 32);
+            float* u = ub + (size_t)s * c.ldu + k;
+            const float err = fp16_error(c.rownorm[row0 + s], c.bnorm[k] * c.b_scale, c.R) + 1e-16f;
+            const float own = *u * (1.f / 4096.f), mx = c.maxabs[n];
+            const float hi = fp16_value(cc + err, mx, c.b_scale) + own + 1e-37f;
+            const float lo = fp16_value(cc - err, mx, c.b_scale) - own - 1e-37f;
+            if (hi < *u) *u = hi;
+            if (lo > -INFINITY && lo < INFINITY) atomicMax(sm.pbest, cand_key(lo, 0));
+            sm.pmax[tid] = 0u;
+          }
+          __syncthreads();
+        }
+      }
+      if (base >= 0) __syncthreads();  // before the list is written again
+    }
+  }
+  if constexpr (MODE == kFineTighten) {
+    // the largest bound of the rows looked at
+    for (int s = w; s < S; s += NW) {
+      if (!sm.taken[s]) continue;
+      unsigned long long best = 0ull;
+      for (int k = ln; k < c.K; k += 64) {
+        const float v = ub[(size_t)s * c.ldu + k];
+        const unsigned long long key = cand_key(v == v ? v : INFINITY, k);
+        best = key > best ? key : best;
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long other = __shfl_xor(best, o);
+        best = other > best ? other : best;
+      }
+      if (ln == 0) c.rowkey[row0 + s] = best;
+    }
+  } else {
+    if (c.row_cc)
+      for (int s = tid; s < S; s += kThreads) {
+        c.row_cc[(size_t)row0 + s] = value(key_value(sm.key[s]));
+        c.row_idx[(size_t)row0 + s] = key_index(sm.key[s]);
+      }
+    if (tid == 0) write_result(a.m, n, value(key_value(*sm.pbest)), key_index(*sm.pbest));
+  }
+  __syncthreads();  // before the next particle's keys
+}
+
+// 16-bit operands: 4 waves, FP32: 8 (as the resampler)
+constexpr int fine_waves(int prec) { return prec == kFP32 ? 8 : 4; }
+template <int PREC, int MAXR>
+struct FineContract {
+  typedef typename std::conditional<
+      PREC == kFP32, FineContract32<MAXR>,
+      FineContract16<PREC == kFP32 ? kBF16 : PREC, MAXR, fine_waves(kBF16)>>::type type;
+};
+
+// at most 128 registers: four waves per SIMD
+template <int PREC, int MAXR, int MODE>
+__global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine(FineArgs a) {
+  extern __shared__ float smem[];
+  CorrArgs c = a.c;
+  if (PREC == kFP32) c.A += (size_t)blockIdx.x * a.scratch_floats;
+  for (int n = blockIdx.x; n < a.m.n_part; n += gridDim.x)
+    fine_particle<PREC, fine_waves(PREC), typename FineContract<PREC, MAXR>::type, MODE>(a, c, n, smem);
+}
+
+// Batched form over the particles of several stacks.
+template <int PREC, int MAXR, int MODE>
+__global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine_batch(FineBatch b) {
+  extern __shared__ float smem[];
+  for (int item = blockIdx.x; item < b.start[b.n]; item += gridDim.x) {
+    int p = 0;
+    while (p + 1 < b.n && b.start[p + 1] <= item) ++p;
+    CorrArgs c = b.piece[p].c;
+    if (PREC == kFP32) c.A += (size_t)blockIdx.x * b.piece[p].scratch_floats;
+    fine_particle<PREC, fine_waves(PREC), typename FineContract<PREC, MAXR>::type, MODE>(b.piece[p], c,
+                                                                                        item - b.start[p], smem);
+  }
+}
+
+template <int PREC, int MAXR, int MODE>
+inline void fine_mode(const FineArgs* a, const FineBatch* b, int grid, size_t lds, hipStream_t st) {
+  const dim3 g(grid), t(64 * fine_waves(PREC));
+  if (b) hipLaunchKernelGGL((k_fine_batch<PREC, MAXR, MODE>), g, t, lds, st, *b);
+  else hipLaunchKernelGGL((k_fine<PREC, MAXR, MODE>), g, t, lds, st, *a);
+}
+// TIGHTEN: only the tightening of FP32 bounds, else every other mode
+template <int PREC, int MAXR, bool TIGHTEN>
+inline void fine_go(FineMode mode, const FineArgs* a, const FineBatch* b, int grid, size_t lds, hipStream_t st) {
+  if constexpr (TIGHTEN) return fine_mode<PREC, MAXR, kFineTighten>(a, b, grid, lds, st);
+  else if (mode == kFineRunnerUp) return fine_mode<PREC, MAXR, kRunnerUp>(a, b, grid, lds, st);
+  else return fine_mode<PREC, MAXR, kArgmax>(a, b, grid, lds, st);
+}
+
+// R4max: the largest ring count of the launch's pieces (one ring bucket).
+void fine_dispatch_fp32(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
+                        hipStream_t st);
+void fine_dispatch_bf16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
+                        hipStream_t st);
+void fine_dispatch_fp16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
+                        hipStream_t st);
+void fine_dispatch_tighten(int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds, hipStream_t st);
+
+template <int PREC, bool TIGHTEN>
+inline void fine_dispatch_16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
+                             hipStream_t st) {
+  if (R4max <= 8) return fine_go<PREC, 8, TIGHTEN>(mode, a, b, grid, lds, st);
+  if (R4max <= 10) return fine_go<PREC, 10, TIGHTEN>(mode, a, b, grid, lds, st);
+  if (R4max <= 12) return fine_go<PREC, 12, TIGHTEN>(mode, a, b, grid, lds, st);
+  return fine_go<PREC, 16, TIGHTEN>(mode, a, b, grid, lds, st);
+}
+
+}  // namespace mra

@@ -21,106 +21,55 @@ int corr_default_variant(int prec, int R4) {
   return 0;
 }
 
-static void dispatch(int prec, int variant, int r4min, int r4max, const CorrArgs* a, bool table,
-                     const CorrBatch* b, int grid, hipStream_t st) {
-  if (prec == kFP32) corr_dispatch_fp32(variant, r4min, r4max, a, table, b, grid, st);
-  else if (prec == kBF16) corr_dispatch_bf16(variant, r4min, r4max, a, table, b, grid, st);
-  else corr_dispatch_fp16(variant, r4min, r4max, a, table, b, grid, st);
+static hipError_t launch(int prec, int variant, int mode, const CorrArgs& a, hipStream_t st) {
+  if (a.n_row_tiles <= 0) return hipSuccess;
+  if (!corr_variant_ok(prec, variant, a.R4) || a.a_layout != a_layout_for(prec, variant) || a.kt_per_wg < 1 ||
+      (mode != kTable && !a.rowkey))
+    return hipErrorInvalidValue;
+  if (prec == kFP32) corr_dispatch_fp32(variant, a, mode, st);
+  else if (prec == kBF16) corr_dispatch_bf16(variant, a, mode, st);
+  else corr_dispatch_fp16(variant, a, mode, st);
+  return hipGetLastError();
 }
 
 hipError_t launch_corr(int prec, int variant, bool table, const CorrArgs& a, hipStream_t st) {
-  if (a.n_row_tiles <= 0) return hipSuccess;
   if (table) variant = prec == kFP32 ? 2 : 0;  // any R4 (the host writes the operand for this form)
-  if (!corr_variant_ok(prec, variant, a.R4)) return hipErrorInvalidValue;
-  dispatch(prec, variant, a.R4, a.R4, &a, table, nullptr, 0, st);
-  return hipGetLastError();
+  return launch(prec, variant, table ? kTable : kArgmax, a, st);
 }
 
-hipError_t launch_corr_runner_up(int prec, const CorrArgs& a, hipStream_t st) {
-  if (a.n_row_tiles <= 0) return hipSuccess;
-  if (a.R4 < 1 || a.R4 > 16 || !a.excl) return hipErrorInvalidValue;
-  if (prec == kFP32) corr_runner_up_fp32(a, st);
-  else if (prec == kBF16) corr_runner_up_bf16(a, st);
-  else corr_runner_up_fp16(a, st);
-  return hipGetLastError();
+hipError_t launch_corr_runner_up(int prec, int variant, const CorrArgs& a, hipStream_t st) {
+  if (!a.excl) return hipErrorInvalidValue;
+  return launch(prec, variant, kRunnerUp, a, st);
 }
 
-hipError_t launch_corr_batch(int prec, int variant, const CorrBatch& b, int grid, hipStream_t st) {
-  if (b.n <= 0 || grid <= 0) return hipSuccess;
-  int r4min = 1 << 30, r4max = 0;
-  for (int i = 0; i < b.n; ++i) {
-    r4max = b.piece[i].R4 > r4max ? b.piece[i].R4 : r4max;
-    r4min = b.piece[i].R4 < r4min ? b.piece[i].R4 : r4min;
+// Per-particle merge of its S row bests (the keys order them as the tie rule
+// does) and decoding of the flat index into alignment parameters; one wave
+// per particle.
+__global__ __launch_bounds__(256) void k_merge(MergeArgs m) {
+  const ResultArgs& a = m.r;
+  const int n = (blockIdx.x * 256 + threadIdx.x) >> 6, ln = threadIdx.x & 63;
+  if (n >= a.n_part) return;
+  auto value = [&](float v) { return m.maxabs ? fp16_value(v, m.maxabs[n], m.b_scale) : v; };
+  unsigned long long best = 0ull;
+  for (int s = ln; s < a.S; s += 64) {
+    const unsigned long long k = m.rowkey[(size_t)n * a.S + s];
+    if (m.row_cc) {
+      m.row_cc[(size_t)n * a.S + s] = value(key_value(k));
+      m.row_idx[(size_t)n * a.S + s] = key_index(k);
+    }
+    best = k > best ? k : best;
   }
-  if (!corr_variant_ok(prec, variant, r4max)) return hipErrorInvalidValue;
-  dispatch(prec, variant, r4min, r4max, nullptr, false, &b, grid, st);
-  return hipGetLastError();
-}
-
-// Per-particle merge of its S row results (arg-max over shifts with the
-// same tie rule) and decoding of the flat index into alignment parameters.
-__device__ __forceinline__ void merge_particle(const MergeArgs& a, int n) {
-  float best = -INFINITY;
-  int bi = 0x7fffffff;
-  for (int s = 0; s < a.S; ++s) {
-    const float v = a.row_cc[(size_t)n * a.S + s];
-    const int i = a.row_idx[(size_t)n * a.S + s];
-    if (better(v, i, best, bi)) { best = v; bi = i; }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long other = __shfl_xor(best, o);
+    best = other > best ? other : best;
   }
-  const int64_t o = a.out_off + n;
-  if (a.runner_up) {  // second pass: the best over every candidate but the winner
-    a.cc2[o] = bi == 0x7fffffff ? NAN : best;
-    return;
-  }
-  if (a.win) a.win[n] = bi == 0x7fffffff ? -1 : bi;
-  if (bi == 0x7fffffff) {  // no ordered candidate (NaN input): report an invalid winner
-    a.ref[o] = -1;
-    a.mirror[o] = 0;
-    a.shift_x[o] = 0;
-    a.shift_y[o] = 0;
-    a.psi[o] = 0;
-    a.cc[o] = NAN;
-    if (a.flat) a.flat[o] = -1;
-    if (a.cc2) a.cc2[o] = NAN;
-    return;
-  }
-  const int ang = bi & 255;
-  int rest = bi >> 8;
-  const int s = rest % a.S;
-  rest /= a.S;
-  const int m = rest % a.M, k = rest / a.M;
-  a.ref[o] = k;
-  a.mirror[o] = m;
-  a.shift_x[o] = s % a.S1 - a.T;
-  a.shift_y[o] = s / a.S1 - a.T;
-  a.psi[o] = (kNphi - ang) & 255;
-  a.cc[o] = best;
-  if (a.flat) a.flat[o] = bi;
-  if (a.cc2) a.cc2[o] = NAN;
-}
-
-__global__ __launch_bounds__(256) void k_merge(MergeArgs a) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n < a.n_part) merge_particle(a, n);
-}
-
-__global__ __launch_bounds__(256) void k_merge_batch(MergeBatch b) {
-  const int item = blockIdx.x * blockDim.x + threadIdx.x;
-  if (item >= b.start[b.n]) return;
-  int p = 0;
-  while (p + 1 < b.n && b.start[p + 1] <= item) ++p;
-  merge_particle(b.piece[p], item - b.start[p]);
+  if (ln == 0) write_result(a, n, value(key_value(best)), key_index(best));
 }
 
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
-  if (a.n_part <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_merge, dim3((a.n_part + 255) / 256), dim3(256), 0, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_merge_batch(const MergeBatch& b, hipStream_t st) {
-  if (b.n <= 0 || b.start[b.n] <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_merge_batch, dim3((b.start[b.n] + 255) / 256), dim3(256), 0, st, b);
+  if (a.r.n_part <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_merge, dim3((a.r.n_part + 3) / 4), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -3,16 +3,11 @@
 
 namespace mra {
 
-// variant 0: particle operand converted once per row tile and resident;
-// 1: re-read and converted per reference tile.
-void corr_dispatch_fp16(int variant, int r4min, int r4max, const CorrArgs* a, bool table, const CorrBatch* b,
-                        int grid, hipStream_t st) {
-  if (variant == 0) corr_dispatch_16<kFP16, true>(r4min, r4max, a, table, b, grid, st);
-  else corr_dispatch_16<kFP16, false>(r4min, r4max, a, table, b, grid, st);
-}
-
-void corr_runner_up_fp16(const CorrArgs& a, hipStream_t st) {
-  launch_mode<Cfg<kFP16, 8, 16, true, false>, kRunnerUp>(a, st);  // operand resident, R4 <= 16
+// variant 0: particle operand read once per row tile and resident; 1: re-read
+// per reference tile (the runner-up pass: resident).
+void corr_dispatch_fp16(int variant, const CorrArgs& a, int mode, hipStream_t st) {
+  if (variant == 0 || mode == kRunnerUp) corr_dispatch_16<kFP16, true>(a.R4, a, mode, st);
+  else corr_dispatch_16<kFP16, false>(a.R4, a, mode, st);
 }
 
 }  // namespace mra

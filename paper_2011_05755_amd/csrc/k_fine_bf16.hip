@@ -1,0 +1,11 @@
+// BF16 instantiations of the evaluation kernel.
+#include "fine_impl.h"
+
+namespace mra {
+
+void fine_dispatch_bf16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
+                        hipStream_t st) {
+  fine_dispatch_16<kBF16, false>(mode, R4max, a, b, grid, lds, st);
+}
+
+}  // namespace mra

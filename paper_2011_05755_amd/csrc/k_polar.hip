@@ -1,6 +1,6 @@
 // Shift + polar resampling and per-ring FFT of particle images (Algorithm 1:
 // each shifted particle resampled to polar coordinates and transformed per
-// ring), the FP32 re-score of a winning candidate, and the per-particle max |pixel|.
+// ring) and the FP32 re-score of a winning candidate.
 //
 // One 8-wave workgroup per particle (about 68 KB of LDS at L = 76, so two
 // workgroups share a CU: 16 waves, against 12 with three 4-wave groups, which
@@ -33,13 +33,6 @@ __device__ __forceinline__ int xcd_item() {
   return (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
 }
 
-// lane J's value of each group of 8 consecutive lanes, to all 8
-// (ds_swizzle bit-mask mode: source lane = (lane & 0x18) | J within 32)
-template <int J>
-__device__ __forceinline__ int group_bcast(int v) {
-  return __builtin_amdgcn_ds_swizzle(v, 0x18 | (J << 5));
-}
-
 // Operand element type written in mode 0: FP32 (kRingPerm or kSlotMajor,
 // chosen at run time), or BF16 / FP16 in kRingPerm16.
 enum PolarOut { kOutF32 = 0, kOutBF16 = 1, kOutFP16 = 2 };
@@ -60,7 +53,7 @@ __device__ __forceinline__ uint32_t pack16(float x, float y) {
 }
 
 template <int MODE, int OUT>
-__device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, float* smem) {
+__device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, int part, float* smem) {
   float* img = smem;
   float2* scr = reinterpret_cast<float2*>(smem + ((a.Lp * a.Lp + 3) & ~3));
   CosSin* cs = reinterpret_cast<CosSin*>(scr + kPolarWaves * 64 * 9);
@@ -70,6 +63,21 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, float*
 
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ln = threadIdx.x & 63;
   const int l = ln >> 3, rl = ln & 7;
+  if (a.rowkey && part == 0)
+    for (int i = threadIdx.x; i < a.S; i += kPolarThreads) a.rowkey[(size_t)n * a.S + i] = 0ull;
+  float hscale = 1.f;
+  if constexpr (OUT == kOutFP16) {
+    // max |pixel| of the particle, from the staged image (its border is zero)
+    float* red = reinterpret_cast<float*>(cs + kNphi);
+    float m = 0.f;
+    for (int i = threadIdx.x; i < a.Lp * a.Lp; i += kPolarThreads) m = fmaxf(m, fabsf(img[i]));
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if (ln == 0) red[w] = m;
+    __syncthreads();
+    for (int i = 0; i < kPolarWaves; ++i) m = fmaxf(m, red[i]);
+    if (threadIdx.x == 0) a.maxabs[n] = m;
+    hscale = fp16_operand_scale(m);
+  }
   float2* my = scr + w * 64 * 9;                // per-wave scratch: 64 lanes x 9 float2
   float* stage = reinterpret_cast<float*>(my);  // [64 slots][16] in each staging round
   const int base = (a.cx + a.pad) * a.Lp + (a.cx + a.pad);
@@ -80,10 +88,22 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, float*
   const int q0 = row0 >> 3;
   const int ngrp = ((row0 + a.S - 1) >> 3) - q0 + 1;
 
+  if constexpr (MODE == 0 && OUT != kOutF32) {
+    // padding rings of the 16-bit operand are read with the others: zeros
+    // (16-byte chunks of one row each)
+    const int pad_rings = 4 * a.R4 - a.R, chunks = pad_rings * 256;
+    for (int i = part * kPolarThreads + threadIdx.x; i < ngrp * chunks; i += kPolarThreads * a.split) {
+      const int grp = i / chunks, c = i - grp * chunks;
+      const int tile = q0 + grp, row = tile * 8 + (c & 7) - row0;
+      if (row >= 0 && row < a.S)
+        reinterpret_cast<uint4*>(a.out)[((size_t)(tile * 4 * a.R4 + a.R) * 256) + c] = make_uint4(0u, 0u, 0u, 0u);
+    }
+  }
+
   // (ring, row group) items in contiguous blocks per wave (balanced)
   const int n_items = a.R * ngrp;
-  const int per_wave = (n_items + kPolarWaves - 1) / kPolarWaves;
-  const int it0 = w * per_wave, it1 = min(n_items, it0 + per_wave);
+  const int per_wave = (n_items + kPolarWaves * a.split - 1) / (kPolarWaves * a.split);
+  const int it0 = (part * kPolarWaves + w) * per_wave, it1 = min(n_items, it0 + per_wave);
   for (int item = it0; item < it1; ++item) {
     const int ring = item / ngrp, grp = item - ring * ngrp;
     // FP32 operand: the shift and lane indices are made opaque here, so that
@@ -108,43 +128,8 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, float*
     const int sc = s < 0 ? 0 : (s < a.S ? s : a.S - 1);
     const int o4 = 4 * (base + shift_offset(sc, a.S1, s1m, a.T, a.Lp));
 
-    // 32 bilinear samples v[i] = p[16 n1 + 2 l + e] (i = 2 n1 + e) of this
-    // lane's shift, the positions taken from the staged cos/sin (no memory
-    // loads in the loop).  Positions and weights do not depend on the shift:
-    // lane rx of group l takes them for the angles i = rx (mod 8) and
-    // samples those at all 8 shifts of the item; a transpose through the
-    // wave's scratch, in two halves of 16 angles, hands each lane its own
-    // shift's samples.
-    const float rr = (float)(a.r_min + ring);
-    const CosSin* cp = cs + 2 * lx;
-    // byte offsets of the item's 8 shifts (lane j of the group computed shift j's)
-    const int o4s[8] = {group_bcast<0>(o4), group_bcast<1>(o4), group_bcast<2>(o4), group_bcast<3>(o4),
-                        group_bcast<4>(o4), group_bcast<5>(o4), group_bcast<6>(o4), group_bcast<7>(o4)};
-    float* tr = reinterpret_cast<float*>(my);  // [64 (l, shift)][17]: row pitch 17 spreads the banks
     float v[32];
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-      float smp[2][8];
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int i = 16 * hf + 8 * b + rx;
-        const CosSin c = cp[16 * (i >> 1) + (i & 1)];
-        const int off = polar_offset(rr, c, Lp4);
-        float w00, w10, w01, w11;
-        polar_weights(rr, c, w00, w10, w01, w11);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) smp[b][j] = bilin4w(img, o4s[j] + off, Lp4, w00, w10, w01, w11);
-      }
-      wave_sync();  // the scratch's earlier readers are done
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) tr[(lx * 8 + j) * 17 + 8 * b + rx] = smp[b][j];
-      wave_sync();
-#pragma unroll
-      for (int q = 0; q < 16; ++q) v[16 * hf + q] = tr[(lx * 8 + rx) * 17 + q];
-    }
-    wave_sync();  // before the FFT's transposes reuse the scratch
+    sample_ring(img, cs, my, (float)(a.r_min + ring), lx, rx, o4, Lp4, v);
 
     if (MODE == 1) {
       if (valid) {
@@ -155,95 +140,28 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, float*
       continue;
     }
 
-    float2 z[16];
-#pragma unroll
-    for (int n1 = 0; n1 < 16; ++n1) z[n1] = make_float2(v[2 * n1], v[2 * n1 + 1]);
-    dft16<-1>(z);
-#pragma unroll
-    for (int k1 = 1; k1 < 16; ++k1) z[k1] = cmul(z[k1], twid(cs, 2 * ((lx * k1) & 127)));
-    // transpose through the scratch in two halves: lane l's first column
-    // k1a lies in 0..7, its second k1b in 8..15.  Entries are ordered
-    // (l, shift) with the shift fastest, which spreads a wave's accesses
-    // over the banks better than (shift, l).
     float2 Za[8], Zb[8];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-      for (int k1 = 0; k1 < 8; ++k1) my[(lx * 8 + rx) * 9 + k1] = z[8 * h + k1];
-      wave_sync();
-#pragma unroll
-      for (int n2 = 0; n2 < 8; ++n2) {
-        if (h == 0) Za[n2] = my[(n2 * 8 + rx) * 9 + k1a];
-        else Zb[n2] = my[(n2 * 8 + rx) * 9 + k1b - 8];
-      }
-      wave_sync();
-    }
-    dft8<-1>(Za);
-    dft8<-1>(Zb);
+    fft_ring(cs, my, lx, rx, k1a, k1b, v, Za, Zb);
 
     if (MODE == 0) {
-      // Every real split yields one slot below 64 and one above (128 - f, or
-      // lane 0's 0 and 64): keep both, then stage [slot][p*8 + row] for the
-      // 64 low slots and then the 64 high ones, and write the 64-byte
-      // (ring, slot) segments of the tile with 16-byte stores, each store
-      // instruction covering whole 128-byte lines.  The four
-      // 16-byte chunks of a slot are XOR-swizzled by slot & 3, so the eight
-      // lanes l that write at once hit distinct banks.
-      int lo_s[8], hi_s[8];
-      float lo_a[8], lo_b[8], hi_a[8], hi_b[8];
-      int e = 0, s0 = 0;
-      float a0 = 0.f, b0 = 0.f;
-      fwd_emit(lx, Za, Zb, [&](int f) { return twid(cs, f & 255); },
-               [&](int slot, float re, float im) {
-                 const int k = e >> 1;
-                 if ((e++ & 1) == 0) {
-                   s0 = slot; a0 = re - im; b0 = re + im;
-                 } else {
-                   const bool first_low = s0 < slot;
-                   lo_s[k] = first_low ? s0 : slot;
-                   hi_s[k] = first_low ? slot : s0;
-                   lo_a[k] = first_low ? a0 : re - im;
-                   lo_b[k] = first_low ? b0 : re + im;
-                   hi_a[k] = first_low ? re - im : a0;
-                   hi_b[k] = first_low ? re + im : b0;
-                 }
-               });
+      // The slots are staged as [slot][p*8 + row], the 64 low ones and then the
+      // 64 high ones, and written so that each store instruction covers whole
+      // 128-byte lines of the tile.
+      RingSlots rs;
+      ring_slots(cs, lx, Za, Zb, rs);
       const int tile = q0 + grp;
       const int first = row0 - tile * 8;            // rows of this tile before the particle
       const int last = row0 + a.S - tile * 8;       // first row after the particle
-      // otherwise the lane's segment of slot s = 64 h + 16 it + j (j = lane /
-      // 4), slot stride ss: a per-lane part computed once per item and a
-      // uniform offset
       const bool slot_major = a.a_layout == kSlotMajor, perm = a.a_layout == kRingPerm;
       // 16-bit operand: each value rounded once, as the contraction's matrix
       // cores take it (FP16 scaled by the particle's power of two)
       constexpr bool half = OUT != kOutF32;
-      const float hscale = OUT == kOutFP16 ? fp16_operand_scale(a.maxabs[n]) : 1.f;
       const int ss = slot_major ? a.R4 * 64 : 16;
       float* dst = a.out + (slot_major ? (size_t)tile * kSlots * a.R4 * 64 + ring * 16
                                        : ((size_t)tile * 4 * a.R4 + ring) * kSlots * 16);
-      const int part = lnx & 3;                       // rows (part & 1) * 4 .. +3 of p = part >> 1
-      const int r0 = (part & 1) * 4;
-      const bool full = r0 >= first && r0 + 4 <= last;
-      const int j = lnx >> 2;
-      float* const lane_dst = dst + (size_t)__mul24(j, ss) + part * 4;
-      // kRingPerm: lane (pp = lane / 8, c = lane % 8) writes elements 2c, 2c+1
-      // (rows rp, rp + 1) of the position pair 16 it + 4 h + lp, whose slots
-      // are 64 h + sp and 64 h + sp + 8, interleaved by element
-      const int pp = lnx >> 3, c = lnx & 7;
-      const int lp = 8 * (pp >> 2) + (pp & 3), sp = (pp >> 2) + 16 * (pp & 3);
-      const int rp = 2 * (c & 3);
-      const bool full_p = rp >= first && rp + 2 <= last;
-      float* const pair_dst = dst + 32 * lp + 4 * c;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int sl = h ? hi_s[k] - 64 : lo_s[k];
-          const int sw = (sl & 3) << 2;
-          stage[sl * 16 + (rx ^ sw)] = h ? hi_a[k] : lo_a[k];
-          stage[sl * 16 + ((8 + rx) ^ sw)] = h ? hi_b[k] : lo_b[k];
-        }
+        stage_slots(stage, h, rx, rs);
         wave_sync();
         if constexpr (half) {
           // kRingPerm16: the staged slots 64 h + sl are positions 16 (sl % 8)
@@ -272,33 +190,7 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, float*
           }
           wave_sync();
         } else {
-#pragma unroll
-          for (int it = 0; it < 4; ++it) {
-            if (perm) {
-              const int s0 = 2 * it + sp, s1 = s0 + 8, sw = (s0 & 3) << 2;  // s1 & 3 == s0 & 3
-              const float2 v0 = *reinterpret_cast<const float2*>(stage + s0 * 16 + ((2 * c) ^ sw));
-              const float2 v1 = *reinterpret_cast<const float2*>(stage + s1 * 16 + ((2 * c) ^ sw));
-              float* o = pair_dst + 32 * (16 * it + 4 * h);
-              if (full_p) {
-                *reinterpret_cast<float4*>(o) = make_float4(v0.x, v1.x, v0.y, v1.y);
-              } else {
-                if (rp >= first && rp < last) { o[0] = v0.x; o[1] = v1.x; }
-                if (rp + 1 >= first && rp + 1 < last) { o[2] = v0.y; o[3] = v1.y; }
-              }
-              continue;
-            }
-            const int sl = it * 16 + (lnx >> 2);
-            const float4 val = *reinterpret_cast<const float4*>(stage + sl * 16 + ((part ^ (sl & 3)) << 2));
-            float* o = lane_dst + (size_t)(64 * h + 16 * it) * ss;
-            if (full) {
-              *reinterpret_cast<float4*>(o) = val;
-            } else {
-              if (r0 + 0 >= first && r0 + 0 < last) o[0] = val.x;
-              if (r0 + 1 >= first && r0 + 1 < last) o[1] = val.y;
-              if (r0 + 2 >= first && r0 + 2 < last) o[2] = val.z;
-              if (r0 + 3 >= first && r0 + 3 < last) o[3] = val.w;
-            }
-          }
+          write_f32_half(stage, dst, h, lnx, perm, ss, first, last);
           wave_sync();
         }
       }
@@ -322,9 +214,9 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, float*
 template <int MODE, int OUT>
 __global__ __launch_bounds__(kPolarThreads) void k_polar_fft(PolarArgs a) {
   extern __shared__ float smem[];
-  const int n = xcd_item();
+  const int i = xcd_item(), n = i / a.split;
   if (n >= a.n_part) return;
-  polar_particle<MODE, OUT>(a, n, smem);
+  polar_particle<MODE, OUT>(a, n, i - n * a.split, smem);
 }
 
 // every piece of a batch writes the same operand type
@@ -335,16 +227,17 @@ __global__ __launch_bounds__(kPolarThreads) void k_polar_batch(PolarBatch b) {
   if (item >= b.start[b.n]) return;
   int p = 0;
   while (p + 1 < b.n && b.start[p + 1] <= item) ++p;
-  polar_particle<0, OUT>(b.piece[p], item - b.start[p], smem);
+  const int i = item - b.start[p], n = i / b.piece[p].split;
+  polar_particle<0, OUT>(b.piece[p], n, i - n * b.piece[p].split, smem);
 }
 
 static int polar_out(const PolarArgs& a) {
-  return a.a_layout != kRingPerm16 ? kOutF32 : (a.prec == kFP16 ? kOutFP16 : kOutBF16);
+  return a.a_layout != kRingPerm16 ? kOutF32 : (a.prec == kBF16 ? kOutBF16 : kOutFP16);
 }
 
 size_t polar_lds_bytes(int Lp) {
   return (size_t)((Lp * Lp + 3) & ~3) * sizeof(float) + (size_t)kPolarWaves * 64 * 9 * sizeof(float2) +
-         (size_t)kNphi * sizeof(CosSin);
+         (size_t)kNphi * sizeof(CosSin) + kPolarWaves * sizeof(float);
 }
 
 hipError_t launch_polar_batch(const PolarBatch& b, hipStream_t st) {
@@ -367,8 +260,9 @@ hipError_t launch_polar_batch(const PolarBatch& b, hipStream_t st) {
 
 hipError_t launch_polar(int mode, const PolarArgs& a, hipStream_t st) {
   if (a.n_part <= 0) return hipSuccess;
+  if (a.split < 1) return hipErrorInvalidValue;
   const size_t lds = polar_lds_bytes(a.Lp);
-  dim3 grid((a.n_part + 7) / 8 * 8), block(kPolarThreads);
+  dim3 grid(((unsigned)a.n_part * a.split + 7) / 8 * 8), block(kPolarThreads);
   switch (mode) {
     case 0:
       switch (polar_out(a)) {
@@ -393,7 +287,7 @@ hipError_t launch_polar(int mode, const PolarArgs& a, hipStream_t st) {
 // whose 16-bit best lies more than a.margin of the particle's 16-bit
 // best below it are left out (they cannot win at 16-bit accuracy).
 constexpr int kMaxRescoreRows = 8;
-constexpr int kMaxRows = 289;  // shifts per particle at the largest search range (+-8)
+
 constexpr int kRescoreRed = 24;  // reduction slots: 4 waves x 3 lags x up to 2 candidates
 
 // FP32 CC of (ref k, shift soff, mirror m) at the lags lag0 + d, d < ND, for
@@ -565,7 +459,7 @@ __device__ __forceinline__ void rescore_particle(const RescoreArgs& a, int n, fl
   // index) of the rows not yet taken across the wave.  Rows without a
   // candidate (index 2^31 - 1) and NaN values never count.
   if (threadIdx.x < 64) {
-    constexpr int kPer = (kMaxRows + 63) / 64;
+    constexpr int kPer = (kMaxShifts + 63) / 64;
     const int l = threadIdx.x;
     float lv[kPer];
     int li[kPer];
@@ -704,25 +598,6 @@ __global__ __launch_bounds__(256) void k_refine(RescoreArgs a) {
 hipError_t launch_refine(const RescoreArgs& a, hipStream_t st) {
   if (a.n_part <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_refine, dim3(a.n_part), dim3(256), rescore_lds_bytes(a.Lp), st, a);
-  return hipGetLastError();
-}
-
-// max |pixel| of each particle image (the FP16 operand scale): one
-// workgroup per particle, out[n] for n < n_part.
-__global__ __launch_bounds__(256) void k_part_maxabs(const float* x, int LL, float* out) {
-  __shared__ float red[4];
-  const float* img = x + (size_t)blockIdx.x * LL;
-  float m = 0.f;
-  for (int i = threadIdx.x; i < LL; i += 256) m = fmaxf(m, fabsf(img[i]));
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) out[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-
-hipError_t launch_part_maxabs(const float* x, int n_part, int L, float* out, hipStream_t st) {
-  if (n_part <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_part_maxabs, dim3(n_part), dim3(256), 0, st, x, L * L, out);
   return hipGetLastError();
 }
 

@@ -4,9 +4,10 @@
 //   nu_k       weighted ring norm sqrt(sum_r w_r sum_j q^2),
 //   Q_k[r][f]  per-ring DFT (direct sum), times w_r / (nu_k * 256),
 // then packed into the operand layouts of the correlation kernel:
-//   FP32  [ref tile][slot][t < R4][64], lane = g*16 + 2*(ref%8) + q, ring = g*R4 + t
-//   16-bit [ref tile][slot][s < NS - 1][64][8] (the same lanes), ring = g*R4 + 8 s + e,
-//          then the last step [64][BT] (BT = 2, 4 or 8: as wide as its rings need)
+//   FP32  [ref, padded to whole tiles][slot][2 g + q][t, padded to 16 bytes], ring = g*R4 + t, t < R4
+//   16-bit [ref tile][slot][s < NS - 1][64][8], lane = 16 g + 2 (ref%8) + q, ring = g*R4 + 8 s + e,
+//          then the last step [64][BT] (BT = 2, 4 or 8: as wide as its rings need);
+//          an FP32 refset holds an FP16 one too, for the bounds
 // with q = 0 -> c - d and q = 1 -> c + d for c + id = Q_f (slot f = 1..127)
 // and c = Q_0, d = Q_128 in slot 0; with one reference also
 //   single [ring][slot] (c - d, c + d) for the fused single-reference kernel.
@@ -79,12 +80,9 @@ __global__ void k_ref_qhat(RefArgs a) {
   a.qhat32[i] = (float)(a.q64[i] * a.inv[k]);
 }
 
-__device__ __forceinline__ double packed_value(const RefArgs& a, int kt, int slot, int lane, int t) {
-  // lane = 16 g + 2 ref + q: ring group g, column (ref, q) of the contraction's block
-  const int g = lane >> 4, n = lane & 15;
-  const int q = n & 1, ref = kt * kRefTile + (n >> 1);
-  const int ring = g * a.R4 + t;
-  if (t >= a.R4 || ring >= a.R || ref >= a.K) return 0.0;
+// element of reference ref (q, slot) at ring `ring`
+__device__ __forceinline__ double packed_value(const RefArgs& a, int ref, int slot, int q, int ring) {
+  if (ring >= a.R || ref >= a.K) return 0.0;
   const double2* Q = a.Qs + (size_t)ref * 129 * a.R;
   double c, d;
   if (slot == 0) {
@@ -98,25 +96,25 @@ __device__ __forceinline__ double packed_value(const RefArgs& a, int kt, int slo
 }
 
 __global__ void k_ref_bmax(RefArgs a) {
-  const int64_t total = (int64_t)a.n_ref_tiles * kSlots * a.R4 * 64;
+  const int64_t total = (int64_t)a.K * kSlots * a.R * 2;
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   float m = 0.f;
   if (i < total) {
-    const int lane = i % 64, t = (i / 64) % a.R4;
-    const int slot = (i / (64 * (int64_t)a.R4)) % kSlots, kt = i / (64 * (int64_t)a.R4 * kSlots);
-    m = (float)fabs(packed_value(a, kt, slot, lane, t));
+    const int ring = i % a.R, q = (i / a.R) & 1, slot = (i / (2 * a.R)) % kSlots;
+    m = (float)fabs(packed_value(a, (int)(i / ((int64_t)2 * a.R * kSlots)), slot, q, ring));
   }
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
   if ((threadIdx.x & 63) == 0) atomicMax(reinterpret_cast<unsigned int*>(a.bmax), __float_as_uint(m));
 }
 
 __global__ void k_ref_pack32(RefArgs a) {
-  const int64_t total = (int64_t)a.n_ref_tiles * kSlots * a.R4 * 64;
+  const int pitch = b32_pitch(a.R4);
+  const int64_t total = (int64_t)a.n_ref_tiles * kRefTile * kSlots * 8 * pitch;
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= total) return;
-  const int lane = i % 64, t = (i / 64) % a.R4;
-  const int slot = (i / (64 * (int64_t)a.R4)) % kSlots, kt = i / (64 * (int64_t)a.R4 * kSlots);
-  a.B32[i] = (float)packed_value(a, kt, slot, lane, t);
+  const int t = i % pitch, gq = (i / pitch) & 7, slot = (i / (8 * pitch)) % kSlots;
+  const int ref = i / ((int64_t)8 * pitch * kSlots);
+  a.B32[i] = t < a.R4 ? (float)packed_value(a, ref, slot, gq & 1, (gq >> 1) * a.R4 + t) : 0.f;
 }
 
 __global__ void k_ref_pack16(RefArgs a) {
@@ -135,7 +133,9 @@ __global__ void k_ref_pack16(RefArgs a) {
     lane = (off - full) / bt;
     t = 8 * (a.NS - 1) + (off - full) % bt;
   }
-  const double v = packed_value(a, kt, slot, lane, t) * a.b_scale;
+  // lane = 16 ring group + 2 reference + q
+  const int g = lane >> 4;
+  const double v = t < a.R4 ? packed_value(a, kt * kRefTile + ((lane >> 1) & 7), slot, lane & 1, g * a.R4 + t) * a.b_scale : 0.0;
   if (a.prec == kBF16) {
     __bf16 h = (__bf16)(float)v;
     a.B16[i] = __builtin_bit_cast(uint16_t, h);
@@ -162,6 +162,23 @@ __global__ void k_ref_pack_single(RefArgs a) {
   a.G1[i] = make_float2((float)(c - d), (float)(c + d));
 }
 
+// Norm of each reference's packed operand, 2 sum |Q|^2 over its slots and
+// rings (the imaginary parts of f = 0 and 128, zero up to rounding, only
+// raise it), rounded up.
+__global__ __launch_bounds__(256) void k_ref_bnorm(RefArgs a) {
+  __shared__ double red[4];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < 129 * a.R; i += 256) {
+    const double2 q = a.Qs[(size_t)blockIdx.x * 129 * a.R + i];
+    s += 2.0 * (q.x * q.x + q.y * q.y);
+  }
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    a.bnorm[blockIdx.x] = (float)(sqrt(((red[0] + red[1]) + red[2]) + red[3]) * (1.0 + 1e-6));
+}
+
 static inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
 hipError_t launch_ref_stage1(const RefArgs& a, hipStream_t st) {
@@ -171,7 +188,7 @@ hipError_t launch_ref_stage1(const RefArgs& a, hipStream_t st) {
   const int64_t ns = (int64_t)a.K * 129 * a.R;
   hipLaunchKernelGGL(k_ref_spectra, dim3(blocks_for(ns, 256)), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_ref_qhat, dim3(blocks_for(nq, 256)), dim3(256), 0, st, a);
-  const int64_t nb = (int64_t)a.n_ref_tiles * kSlots * a.R4 * 64;
+  const int64_t nb = (int64_t)a.K * kSlots * a.R * 2;
   hipLaunchKernelGGL(k_ref_bmax, dim3(blocks_for(nb, 256)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
@@ -179,12 +196,12 @@ hipError_t launch_ref_stage1(const RefArgs& a, hipStream_t st) {
 hipError_t launch_ref_stage2(const RefArgs& a, hipStream_t st) {
   if (a.G1) hipLaunchKernelGGL(k_ref_pack_single, dim3(blocks_for((int64_t)a.R * kSlots, 256)), dim3(256), 0, st, a);
   if (a.prec == kFP32) {
-    const int64_t n = (int64_t)a.n_ref_tiles * kSlots * a.R4 * 64;
+    const int64_t n = (int64_t)a.n_ref_tiles * kRefTile * kSlots * 8 * b32_pitch(a.R4);
     hipLaunchKernelGGL(k_ref_pack32, dim3(blocks_for(n, 256)), dim3(256), 0, st, a);
-  } else {
-    const int64_t n = (int64_t)a.n_ref_tiles * kSlots * b16_slot_elems(a.R4);
-    hipLaunchKernelGGL(k_ref_pack16, dim3(blocks_for(n, 256)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_ref_bnorm, dim3(a.K), dim3(256), 0, st, a);
   }
+  const int64_t n = (int64_t)a.n_ref_tiles * kSlots * b16_slot_elems(a.R4);
+  hipLaunchKernelGGL(k_ref_pack16, dim3(blocks_for(n, 256)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -42,7 +42,8 @@ struct Refset {
   mra_geom g{};
   int K = 0, R = 0, R4 = 0, NS = 0, n_kt = 0;
   float* B32 = nullptr;
-  uint16_t* B16 = nullptr;
+  uint16_t* B16 = nullptr;  // the 16-bit forms' operand; FP32: the FP16 one of the bounds
+  float* bnorm = nullptr;   // FP32: norm of each reference's operand
   float2* G1 = nullptr;    // K = 1: spectrum table of the fused single-reference kernel
   float* qhat = nullptr;
   double* norm = nullptr;
@@ -51,8 +52,8 @@ struct Refset {
   int dmin = 0, dmax = 0;  // range of stencil floor offsets
   int variant = 0;         // correlation kernel tile configuration
   int chunk = 0;           // particles per chunk (0: from the workspace cap)
-  int prune = 1;           // exact pruning of the inverse FFT in the correlation kernel
-  int run_tiles = 0;       // row tiles per correlation workgroup (0: from the launch size)
+  int prune = 1;           // evaluate only the pairs whose bound can win (0: every pair)
+  int run_tiles = 0;       // accepted and reported, no longer used
 };
 
 struct Fail {
@@ -157,7 +158,7 @@ void clear_profile(mra_ctx* c) {
 }
 
 void free_refset(Refset& r) {
-  for (void* p : {(void*)r.B32, (void*)r.B16, (void*)r.G1, (void*)r.qhat, (void*)r.norm, (void*)r.stencil})
+  for (void* p : {(void*)r.B32, (void*)r.B16, (void*)r.bnorm, (void*)r.G1, (void*)r.qhat, (void*)r.norm, (void*)r.stencil})
     if (p) (void)hipFree(p);
   r = Refset{};
 }
@@ -263,78 +264,139 @@ void check_result(const mra_result* r) {
     throw Fail{MRA_E_INVAL, "result arrays must be non-NULL (cc2, flat_index may be NULL)"};
 }
 
-// bytes of the correlation operand A per particle row (one eighth of a tile)
-// the operand's element size: 16-bit for the 16-bit contractions
-size_t a_elem(const Refset& rs) { return a_elem_bytes(a_layout_for(rs.g.precision, rs.variant)); }
-size_t a_bytes_per_row(const Refset& rs) { return (size_t)kSlots * rs.R4 * 64 * a_elem(rs) / kRowTile; }
-
-int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p) {
-  if (rs.chunk > 0) return rs.chunk;
-  const uint64_t budget = c->cap / 2;
-  const uint64_t per = (uint64_t)p.S * a_bytes_per_row(rs);
-  int64_t n = (int64_t)(budget / per);
-  return std::max<int64_t>(n, 1);
+// The two ways through a chunk.  Pruned: the 16-bit operand of every row
+// (FP16 for FP32 alignment), a bound of every (row, reference) pair, then the
+// evaluation of the pairs that can win; FP32 makes the FP32 operand of the
+// rows it evaluates in a scratch tile per workgroup.  Unpruned (prune = 0, the
+// debug CC table, or a workspace too small for the bounds): the operand of
+// every row in the contraction's own type, every pair evaluated.
+int operand_layout(const Refset& rs, bool pruned) {
+  return pruned ? (int)kRingPerm16 : a_layout_for(rs.g.precision, rs.variant);
 }
+size_t tile_bytes_of(const Refset& rs, bool pruned) {
+  return (size_t)kSlots * rs.R4 * 64 * a_elem_bytes(operand_layout(rs, pruned));
+}
+size_t scratch_tile_bytes(const Refset& rs) { return (size_t)kSlots * rs.R4 * 64 * sizeof(float); }
+int ub_pitch(const Refset& rs) { return rs.n_kt * kRefTile; }
+// the operand's FP16 scale is kept per particle
+bool scaled_operand(const Refset& rs, bool pruned) {
+  return rs.g.precision == kFP16 || (pruned && rs.g.precision == kFP32);
+}
+// row results are written out for the re-ranking
+bool row_results(const Refset& rs) { return rs.g.precision != kFP32 && rs.g.rescore_rows >= 2; }
 
 // Device buffers of one alignment chunk of nc particles.
 struct ChunkBufs {
-  float* A = nullptr;       // particle operand, ceil(nc S / 8) row tiles
-  float* rcc = nullptr;     // [nc S] best CC per row
-  int* ridx = nullptr;      // [nc S] its flat index
-  float* maxabs = nullptr;  // FP16: [nc] max |pixel|
-  int32_t* win = nullptr;   // cc2: [nc] chunk-local winner copy
+  float* A = nullptr;        // particle operand, ceil(nc S / 8) row tiles
+  float* ub = nullptr;       // pruned: [nc S][ub_pitch] bounds
+  unsigned long long* rowkey = nullptr;  // [nc S] largest bound (pruned) or best CC per row
+  float* rownorm = nullptr;  // pruned FP32: [nc S] norm of the row's operand
+  float* scratch = nullptr;  // pruned FP32: one operand tile per evaluation workgroup
+  int grid = 0;              // evaluation workgroups
+  float* rcc = nullptr;      // [nc S] best CC per row
+  int* ridx = nullptr;       // [nc S] its flat index
+  float* maxabs = nullptr;   // FP16 operand: [nc] max |pixel|
+  int32_t* win = nullptr;    // cc2: [nc] chunk-local winner copy
 };
 
-size_t tile_bytes_of(const Refset& rs) { return (size_t)kSlots * rs.R4 * 64 * a_elem(rs); }
+// Calls take(name, bytes) for every buffer of an nc-particle chunk.
+template <class Take>
+ChunkBufs layout_chunk(const Refset& rs, const Plan& p, int64_t nc, bool pruned, bool cc2, int n_cu, Take take) {
+  ChunkBufs b;
+  const size_t rows = (size_t)nc * p.S;
+  const size_t tiles = (rows + kRowTile - 1) / kRowTile;
+  b.A = (float*)take("A", tiles * tile_bytes_of(rs, pruned));
+  if (pruned) {
+    b.grid = fine_grid(rs.g.precision, nc, n_cu);
+    b.ub = (float*)take("ub", rows * ub_pitch(rs) * sizeof(float));
+    if (rs.g.precision == kFP32) {
+      b.rownorm = (float*)take("rownorm", rows * sizeof(float));
+      b.scratch = (float*)take("scratch", b.grid * scratch_tile_bytes(rs));
+    }
+  }
+  b.rowkey = (unsigned long long*)take("rowkey", (rows + 1) * sizeof(unsigned long long));
+  if (row_results(rs)) {
+    b.rcc = (float*)take("row_cc", rows * sizeof(float));
+    b.ridx = (int*)take("row_idx", rows * sizeof(int));
+  }
+  if (scaled_operand(rs, pruned)) b.maxabs = (float*)take("maxabs", (size_t)nc * sizeof(float));
+  if (cc2) b.win = (int32_t*)take("win", (size_t)nc * sizeof(int32_t));
+  return b;
+}
 
 // Lays the buffers of an nc-particle chunk out from `base` (256-byte
 // aligned pieces); returns the bytes used.  base = nullptr only measures.
-size_t carve_chunk(const Refset& rs, const Plan& p, int64_t nc, bool fp16, bool cc2, char* base, ChunkBufs* b) {
-  const size_t rows = (size_t)nc * p.S;
-  const size_t tiles = (rows + kRowTile - 1) / kRowTile;
+size_t carve_chunk(const Refset& rs, const Plan& p, int64_t nc, bool pruned, bool cc2, int n_cu, char* base,
+                   ChunkBufs* b) {
   size_t off = 0;
-  auto take = [&](size_t bytes) {
+  const ChunkBufs got = layout_chunk(rs, p, nc, pruned, cc2, n_cu, [&](const char*, size_t bytes) -> void* {
     char* q = base ? base + off : nullptr;
     off += (bytes + 255) & ~(size_t)255;
     return q;
-  };
-  char* A = take(tiles * tile_bytes_of(rs));
-  char* rcc = take(rows * sizeof(float));
-  char* ridx = take(rows * sizeof(int));
-  char* mx = fp16 ? take((size_t)nc * sizeof(float)) : nullptr;
-  char* win = cc2 ? take((size_t)nc * sizeof(int32_t)) : nullptr;
-  if (b) {
-    b->A = (float*)A;
-    b->rcc = (float*)rcc;
-    b->ridx = (int*)ridx;
-    b->maxabs = (float*)mx;
-    b->win = (int32_t*)win;
-  }
+  });
+  if (b) *b = got;
   return off;
 }
 
 // Buffers of a chunk from the context's workspace (grown on demand).
-ChunkBufs ws_chunk(mra_ctx* c, const Refset& rs, const Plan& p, int nc, const mra_result* out) {
-  ChunkBufs b;
-  const size_t rows = (size_t)nc * p.S;
-  const size_t tiles = (rows + kRowTile - 1) / kRowTile;
-  b.A = (float*)ws_get(c, "A", tiles * tile_bytes_of(rs));
-  b.rcc = (float*)ws_get(c, "row_cc", rows * sizeof(float));
-  b.ridx = (int*)ws_get(c, "row_idx", rows * sizeof(int));
-  if (rs.g.precision == kFP16) b.maxabs = (float*)ws_get(c, "maxabs", (size_t)nc * sizeof(float));
-  if (out && out->cc2) b.win = (int32_t*)ws_get(c, "win", (size_t)nc * sizeof(int32_t));
-  return b;
+ChunkBufs ws_chunk(mra_ctx* c, const Refset& rs, const Plan& p, int64_t nc, bool pruned, const mra_result* out) {
+  return layout_chunk(rs, p, nc, pruned, out && out->cc2, c->n_cu,
+                      [&](const char* name, size_t bytes) { return ws_get(c, name, bytes); });
+}
+
+// Workspace held by buffers that a chunk does not use (and so cannot reuse).
+uint64_t ws_other(mra_ctx* c) {
+  uint64_t total = 0;
+  for (const auto& kv : c->ws) {
+    bool chunk_buf = false;
+    for (const char* n : {"A", "ub", "rowkey", "rownorm", "scratch", "row_cc", "row_idx", "maxabs", "win"}) chunk_buf |= kv.first == n;
+    if (!chunk_buf) total += kv.second.bytes;
+  }
+  return total;
+}
+
+// bytes of operand and bounds per particle
+uint64_t particle_bytes(const Refset& rs, const Plan& p, bool pruned) {
+  const uint64_t row = tile_bytes_of(rs, pruned) / kRowTile + (pruned ? ub_pitch(rs) * sizeof(float) : 0);
+  return (uint64_t)p.S * row;
+}
+
+int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned) {
+  if (rs.chunk > 0) return rs.chunk;
+  const uint64_t budget = c->cap / 2;
+  return std::max<int64_t>(1, (int64_t)(budget / particle_bytes(rs, p, pruned)));
+}
+
+// A call of few particles takes the unpruned way: with every pair of a few
+// row and reference tiles spread over the CUs it ends before the pruned way's
+// chain of dependent steps does.  At 76 px, 100 references, +-3 (91 tile pairs
+// per particle, 256 CUs), unpruned against pruned: FP32 1 particle 64 / 317
+// us, 16 particles 288 / 382, 32 particles 510 / 387; BF16 1 particle 56 / 177
+// us, 32 particles 162 / 217, 64 particles 256 / 431; at 90 px, +-2 BF16 64
+// particles (10 tile pairs per CU) 167 / 161.
+bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N) {
+  const int64_t tiles = (N * p.S + kRowTile - 1) / kRowTile * rs.n_kt;
+  return tiles <= (rs.g.precision == kFP32 ? 5 : 12) * (int64_t)c->n_cu;
+}
+
+// Particles per chunk within the workspace cap on the pruned path, or 0 when
+// its bounds and scratch do not fit (the call then takes the unpruned one).
+int64_t pruned_chunk(mra_ctx* c, const Refset& rs, const Plan& p, int64_t N, bool cc2) {
+  if (!rs.prune || few_pairs(c, rs, p, N)) return 0;
+  int64_t n = std::min<int64_t>({chunk_particles(c, rs, p, true), (int64_t)(INT32_MAX / p.S / 2), N});
+  const uint64_t other = ws_other(c);
+  while (n > 0 && other + carve_chunk(rs, p, n, true, cc2, c->n_cu, nullptr, nullptr) > c->cap) n /= 2;
+  return n;
 }
 
 // Largest chunk whose buffers fit `bytes` of scratch (0 if not one particle).
-int64_t scratch_chunk(const Refset& rs, const Plan& p, bool cc2, size_t bytes) {
-  const bool fp16 = rs.g.precision == kFP16;
-  if (carve_chunk(rs, p, 1, fp16, cc2, nullptr, nullptr) > bytes) return 0;
+int64_t scratch_chunk(const Refset& rs, const Plan& p, bool pruned, bool cc2, int n_cu, size_t bytes) {
+  if (carve_chunk(rs, p, 1, pruned, cc2, n_cu, nullptr, nullptr) > bytes) return 0;
   // the buffers grow with the chunk: bisect for the largest that fits
   int64_t lo = 1, hi = std::min<int64_t>(INT32_MAX / p.S / 2, (int64_t)(bytes / ((size_t)p.S * 8)) + 1);
   while (lo < hi) {
     const int64_t mid = lo + (hi - lo + 1) / 2;
-    if (carve_chunk(rs, p, mid, fp16, cc2, nullptr, nullptr) <= bytes) lo = mid;
+    if (carve_chunk(rs, p, mid, pruned, cc2, n_cu, nullptr, nullptr) <= bytes) lo = mid;
     else hi = mid - 1;
   }
   return lo;
@@ -361,106 +423,188 @@ void refine_chunk(mra_ctx* c, const Refset& rs, const Plan& p, const float* part
   }
 }
 
-// One chunk of the alignment pass: resample + FFT -> correlation -> merge
-// (-> FP32 re-score for 16-bit contractions).  mode 0 = production,
-// mode 3 = debug CC table into `table`.
-void run_chunk(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, int64_t n0, int nc,
-               const mra_result* out, float* table, const ChunkBufs& bufs) {
-  hipStream_t st = c->stream;
-  const int L = rs.g.L;
-  const int rows = nc * p.S;
-  const int tiles = (rows + kRowTile - 1) / kRowTile;
-  const size_t tile_bytes = tile_bytes_of(rs);
-  float* A = bufs.A;
-  float* rcc = bufs.rcc;
-  int* ridx = bufs.ridx;
-  // rows past the chunk in its last tile are read as zeros
-  if (rows % kRowTile)
-    hip_check(c, launch_fill_zero((char*)A + (size_t)(tiles - 1) * tile_bytes, tile_bytes, st), "fill");
-  const float* src = parts + (size_t)n0 * L * L;
-
-  float* maxabs = nullptr;
-  if (rs.g.precision == kFP16) {
-    maxabs = bufs.maxabs;
-    timed(c, "maxabs", [&] { hip_check(c, launch_part_maxabs(src, nc, L, maxabs, st), "maxabs"); });
-  }
-
+// Arguments of the launches over particles n0 .. n0 + nc - 1 of a stack.
+PolarArgs polar_args(mra_ctx* c, const Refset& rs, const Plan& p, const float* src, int nc) {
   PolarArgs pa{};
   pa.parts = src;
   pa.n_part = nc;
-  pa.L = L; pa.R = rs.R; pa.R4 = rs.R4; pa.T = p.T; pa.S1 = p.S1; pa.S = p.S;
+  pa.L = rs.g.L; pa.R = rs.R; pa.R4 = rs.R4; pa.T = p.T; pa.S1 = p.S1; pa.S = p.S;
   pa.Lp = p.Lp; pa.pad = p.pad; pa.cx = p.cx;
   pa.r_min = rs.g.r_min;
-  // the CC table is written by the form launch_corr picks for it
-  pa.a_layout = a_layout_for(rs.g.precision, table ? (rs.g.precision == kFP32 ? 2 : 0) : rs.variant);
   pa.prec = rs.g.precision;
-  pa.maxabs = maxabs;
   pa.cs64 = c->cs64;
-  pa.out = A;
-  timed(c, "polar", [&] { hip_check(c, launch_polar(0, pa, st), "polar"); });
+  // (a particle's rows touch up to S / 8 + 1 row groups)
+  pa.split = polar_split(nc, rs.R * (p.S / kRowTile + 1), c->n_cu);
+  return pa;
+}
 
+CorrArgs corr_args(mra_ctx* c, const Refset& rs, const Plan& p, int nc, int layout, const ChunkBufs& b) {
   CorrArgs ca{};
-  ca.A = A;
-  ca.a_layout = pa.a_layout;
-  ca.n_row_tiles = tiles;
-  ca.rows = rows;
+  ca.A = b.A;
+  ca.a_layout = layout;
+  ca.rows = nc * p.S;
+  ca.n_row_tiles = (ca.rows + kRowTile - 1) / kRowTile;
   ca.B32 = rs.B32;
   ca.B16 = rs.B16;
-  ca.R = rs.R; ca.R4 = rs.R4; ca.NS = rs.NS; ca.BT = b16_tail_width(rs.R4); ca.n_ref_tiles = rs.n_kt; ca.K = rs.K; ca.S = p.S; ca.M = p.M;
-  ca.maxabs = maxabs;
+  ca.R = rs.R; ca.R4 = rs.R4; ca.n_ref_tiles = rs.n_kt;
+  ca.K = rs.K; ca.S = p.S; ca.M = p.M;
+  ca.maxabs = b.maxabs;
   ca.b_scale = rs.b_scale;
+  ca.bnorm = rs.bnorm;
   ca.cs32 = c->cs32;
-  ca.row_cc = rcc;
-  ca.row_idx = ridx;
-  ca.table = table;
-  ca.prune = rs.prune;
-  ca.tiles_per_run = table ? 1 : (rs.run_tiles > 0 ? rs.run_tiles : corr_tiles_per_run(tiles, c->n_cu));
-  ca.margin = rs.g.rescore_rows >= 2 ? rerank_margin(rs.g.precision) : 0.f;
-  timed(c, "corr", [&] { hip_check(c, launch_corr(rs.g.precision, rs.variant, table != nullptr, ca, st), "corr"); });
-  if (table) return;
+  ca.row_cc = b.rcc;
+  ca.row_idx = b.ridx;
+  ca.ub = b.ub;
+  ca.rowkey = b.rowkey;
+  ca.rownorm = b.rownorm;
+  ca.ldu = ub_pitch(rs);
+  return ca;
+}
 
-  MergeArgs ma{};
-  ma.row_cc = rcc; ma.row_idx = ridx;
-  ma.n_part = nc; ma.S = p.S; ma.S1 = p.S1; ma.T = p.T; ma.M = p.M;
-  ma.out_off = n0;
-  ma.ref = out->ref; ma.shift_x = out->shift_x; ma.shift_y = out->shift_y;
-  ma.psi = out->psi; ma.mirror = out->mirror; ma.flat = out->flat_index;
-  ma.cc = out->cc; ma.cc2 = out->cc2;
-  int32_t* win = out->cc2 ? bufs.win : nullptr;
-  ma.win = win;
-  timed(c, "merge", [&] { hip_check(c, launch_merge(ma, st), "merge"); });
+ResultArgs result_args(const Plan& p, int64_t n0, int nc, const mra_result* out, const ChunkBufs& b) {
+  ResultArgs ra{};
+  ra.n_part = nc; ra.S = p.S; ra.S1 = p.S1; ra.T = p.T; ra.M = p.M;
+  ra.out_off = n0;
+  ra.ref = out->ref; ra.shift_x = out->shift_x; ra.shift_y = out->shift_y;
+  ra.psi = out->psi; ra.mirror = out->mirror; ra.flat = out->flat_index;
+  ra.cc = out->cc; ra.cc2 = out->cc2;
+  ra.win = out->cc2 ? b.win : nullptr;
+  return ra;
+}
 
-  if (rs.g.precision != kFP32) {
-    RescoreArgs ra{};
-    ra.parts = src;
-    ra.n_part = nc;
-    ra.out_off = n0;
-    ra.L = L; ra.R = rs.R; ra.r_min = rs.g.r_min; ra.Lp = p.Lp_r; ra.pad = p.pad_r; ra.cx = p.cx;
-    ra.K = rs.K; ra.T = p.T;
-    ra.stencil = rs.stencil;
-    ra.qhat = rs.qhat;
-    ra.ref = out->ref; ra.shift_x = out->shift_x; ra.shift_y = out->shift_y;
-    ra.psi = out->psi; ra.mirror = out->mirror;
-    ra.cc = out->cc;
-    ra.rows = rs.g.rescore_rows;
-    ra.margin = rerank_margin(rs.g.precision);
-    ra.S1 = p.S1; ra.S = p.S; ra.M = p.M;
-    ra.row_cc = rcc; ra.row_idx = ridx;
-    ra.ref_w = out->ref; ra.shift_x_w = out->shift_x; ra.shift_y_w = out->shift_y;
-    ra.psi_w = out->psi; ra.mirror_w = out->mirror; ra.flat_w = out->flat_index;
-    ra.win = win;
-    timed(c, "rescore", [&] { hip_check(c, launch_rescore(ra, st), "rescore"); });
+RescoreArgs rescore_args(const Refset& rs, const Plan& p, const float* src, int64_t n0, int nc,
+                         const mra_result* out, const ChunkBufs& b) {
+  RescoreArgs ra{};
+  ra.parts = src;
+  ra.n_part = nc;
+  ra.out_off = n0;
+  ra.L = rs.g.L; ra.R = rs.R; ra.r_min = rs.g.r_min; ra.Lp = p.Lp_r; ra.pad = p.pad_r; ra.cx = p.cx;
+  ra.K = rs.K; ra.T = p.T;
+  ra.stencil = rs.stencil;
+  ra.qhat = rs.qhat;
+  ra.ref = out->ref; ra.shift_x = out->shift_x; ra.shift_y = out->shift_y;
+  ra.psi = out->psi; ra.mirror = out->mirror;
+  ra.cc = out->cc;
+  ra.rows = rs.g.rescore_rows;
+  ra.margin = rerank_margin(rs.g.precision);
+  ra.S1 = p.S1; ra.S = p.S; ra.M = p.M;
+  ra.row_cc = b.rcc; ra.row_idx = b.ridx;
+  ra.ref_w = out->ref; ra.shift_x_w = out->shift_x; ra.shift_y_w = out->shift_y;
+  ra.psi_w = out->psi; ra.mirror_w = out->mirror; ra.flat_w = out->flat_index;
+  ra.win = out->cc2 ? b.win : nullptr;
+  return ra;
+}
+
+// Evaluation of a chunk from its operand and bounds (ca, with b's buffers).
+FineArgs fine_args(mra_ctx* c, const Refset& rs, const Plan& p, const CorrArgs& ca, const float* src, int64_t n0,
+                   int nc, const mra_result* out, const ChunkBufs& b) {
+  FineArgs fa{};
+  fa.c = ca;
+  if (rs.g.precision == kFP32) {
+    fa.c.A = b.scratch;
+    fa.scratch_floats = (int)(scratch_tile_bytes(rs) / sizeof(float));
   }
+  fa.m = result_args(p, n0, nc, out, b);
+  fa.margin = rs.g.rescore_rows >= 2 ? rerank_margin(rs.g.precision) : 0.f;
+  fa.parts = src;
+  fa.L = rs.g.L; fa.Lp = p.Lp; fa.pad = p.pad; fa.cx = p.cx; fa.r_min = rs.g.r_min;
+  fa.cs64 = c->cs64;
+  return fa;
+}
 
+// Whether FP32 bounds are tightened before the evaluation of n particles.  It
+// saves the evaluation's second group of rows, whose resampling keeps the
+// CUs busy; when the particles do not fill the CUs' workgroups, its own
+// latency costs more.
+bool tighten(const mra_ctx* c, const Refset& rs, int64_t n) {
+  return rs.g.precision == kFP32 && n > fine_grid(kFP32, INT32_MAX, c->n_cu);
+}
+
+// One chunk of the alignment pass, pruned: resample + FFT -> bounds ->
+// evaluation (-> FP32 re-score for 16-bit contractions).
+void run_chunk(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, int64_t n0, int nc,
+               const mra_result* out, const ChunkBufs& b) {
+  hipStream_t st = c->stream;
+  const int prec = rs.g.precision;
+  const float* src = parts + (size_t)n0 * rs.g.L * rs.g.L;
+  PolarArgs pa = polar_args(c, rs, p, src, nc);
+  pa.a_layout = kRingPerm16;
+  pa.maxabs = b.maxabs;
+  pa.rowkey = b.rowkey;
+  pa.out = b.A;
+  timed(c, "polar", [&] { hip_check(c, launch_polar(0, pa, st), "polar"); });
+  CorrArgs ca = corr_args(c, rs, p, nc, kRingPerm16, b);
+  const int items = bound_items(ca, c->n_cu);
+  timed(c, "bound", [&] { hip_check(c, launch_bound(prec, ca, items, st), "bound"); });
+  FineArgs fa = fine_args(c, rs, p, ca, src, n0, nc, out, b);
+  if (tighten(c, rs, nc)) {
+    FineArgs ta = fa;
+    ta.c.A = b.A;
+    timed(c, "tighten", [&] {
+      hip_check(c, launch_fine(prec, kFineTighten, ta, fine_grid(kFP16, nc, c->n_cu), st), "tighten");
+    });
+  }
+  timed(c, "fine", [&] { hip_check(c, launch_fine(prec, kFineArgmax, fa, b.grid, st), "fine"); });
+  if (prec != kFP32)
+    timed(c, "rescore", [&] { hip_check(c, launch_rescore(rescore_args(rs, p, src, n0, nc, out, b), st), "rescore"); });
+  if (out->cc2) {
+    // runner-up: the same bounds, the best over every candidate but the winner
+    fa.c.excl = b.win;
+    fa.c.row_cc = nullptr;
+    fa.m.win = nullptr;
+    fa.m.runner_up = 1;
+    fa.margin = 0.f;
+    timed(c, "fine2", [&] { hip_check(c, launch_fine(prec, kFineRunnerUp, fa, b.grid, st), "fine2"); });
+  }
+  if (out->psi_frac) refine_chunk(c, rs, p, parts, n0, nc, out);
+}
+
+// One chunk with every pair evaluated: resample + FFT -> correlation ->
+// merge (-> FP32 re-score); table != nullptr: the debug CC table only.
+void run_chunk_unpruned(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, int64_t n0, int nc,
+                        const mra_result* out, float* table, const ChunkBufs& b) {
+  hipStream_t st = c->stream;
+  const int prec = rs.g.precision;
+  const float* src = parts + (size_t)n0 * rs.g.L * rs.g.L;
+  // (the CC table is written by the form launch_corr picks for it)
+  const int layout = a_layout_for(prec, table ? (prec == kFP32 ? 2 : 0) : rs.variant);
+  CorrArgs ca = corr_args(c, rs, p, nc, layout, b);
+  // rows past the chunk in its last tile are read as zeros
+  const size_t tile_bytes = tile_bytes_of(rs, false);
+  if (ca.rows % kRowTile)
+    hip_check(c, launch_fill_zero((char*)b.A + (size_t)(ca.n_row_tiles - 1) * tile_bytes, tile_bytes, st), "fill");
+  PolarArgs pa = polar_args(c, rs, p, src, nc);
+  pa.a_layout = layout;
+  pa.maxabs = b.maxabs;
+  pa.rowkey = b.rowkey;
+  pa.out = b.A;
+  timed(c, "polar", [&] { hip_check(c, launch_polar(0, pa, st), "polar"); });
+  ca.table = table;
+  ca.kt_per_wg = (rs.n_kt + corr_parts(ca.n_row_tiles, rs.n_kt, c->n_cu) - 1) /
+                 corr_parts(ca.n_row_tiles, rs.n_kt, c->n_cu);
+  timed(c, "corr", [&] { hip_check(c, launch_corr(prec, rs.variant, table != nullptr, ca, st), "corr"); });
+  if (table) return;
+  MergeArgs ma{};
+  ma.r = result_args(p, n0, nc, out, b);
+  ma.rowkey = b.rowkey;
+  ma.maxabs = prec == kFP16 ? b.maxabs : nullptr;
+  ma.b_scale = rs.b_scale;
+  ma.row_cc = b.rcc;
+  ma.row_idx = b.ridx;
+  timed(c, "merge", [&] { hip_check(c, launch_merge(ma, st), "merge"); });
+  if (prec != kFP32)
+    timed(c, "rescore", [&] { hip_check(c, launch_rescore(rescore_args(rs, p, src, n0, nc, out, b), st), "rescore"); });
   if (out->cc2) {
     // runner-up: the same contraction with each particle's winner left out;
     // the best that remains is the best over every other candidate
-    ca.excl = win;
-    timed(c, "corr2", [&] { hip_check(c, launch_corr_runner_up(rs.g.precision, ca, st), "corr2"); });
-    MergeArgs m2 = ma;
-    m2.win = nullptr;
-    m2.runner_up = 1;
-    timed(c, "merge", [&] { hip_check(c, launch_merge(m2, st), "merge"); });
+    ca.excl = b.win;
+    const size_t key_bytes = ((size_t)ca.rows * sizeof(unsigned long long) + 15) & ~(size_t)15;
+    hip_check(c, launch_fill_zero(b.rowkey, key_bytes, st), "fill");
+    timed(c, "corr2", [&] { hip_check(c, launch_corr_runner_up(prec, rs.variant, ca, st), "corr2"); });
+    ma.r.win = nullptr;
+    ma.row_cc = nullptr;
+    ma.r.runner_up = 1;
+    timed(c, "merge", [&] { hip_check(c, launch_merge(ma, st), "merge"); });
   }
   if (out->psi_frac) refine_chunk(c, rs, p, parts, n0, nc, out);
 }
@@ -488,6 +632,23 @@ void run_single(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts,
   if (out->psi_frac) refine_chunk(c, rs, p, parts, 0, N, out);
 }
 
+// A stack chunk by chunk, in the context's workspace.
+void align_stack(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, int64_t N, const mra_result* out,
+                 float* table) {
+  int64_t step = table ? 0 : pruned_chunk(c, rs, p, N, out->cc2 != nullptr);
+  const bool pruned = step > 0;
+  if (!pruned) step = std::min<int64_t>(chunk_particles(c, rs, p, false), (int64_t)(INT32_MAX / p.S / 2));
+  for (int64_t n0 = 0; n0 < N; n0 += step) {
+    const int nc = (int)std::min<int64_t>(step, N - n0);
+    const ChunkBufs b = ws_chunk(c, rs, p, nc, pruned, out);
+    if (pruned)
+      run_chunk(c, rs, p, parts, n0, nc, out, b);
+    else
+      run_chunk_unpruned(c, rs, p, parts, n0, nc, out,
+                         table ? table + (size_t)n0 * rs.K * p.M * p.S * kNphi : nullptr, b);
+  }
+}
+
 // noalloc: the chunk buffers come from the device scratch array instead of
 // the workspace, so nothing is allocated (the path of mra_align_noalloc).
 void align_impl(mra_ctx* c, int32_t id, const float* parts, int64_t N, int T, const mra_result* out,
@@ -502,21 +663,23 @@ void align_impl(mra_ctx* c, int32_t id, const float* parts, int64_t N, int T, co
     run_single(c, rs, p, parts, N, out);
     return;
   }
-  int64_t step = std::min<int64_t>(chunk_particles(c, rs, p), (int64_t)(INT32_MAX / p.S / 2));
-  if (noalloc) {
-    step = scratch_chunk(rs, p, out && out->cc2, kScratchBytes);
-    if (step < 1)
-      throw Fail{MRA_E_INVAL, "one particle's operand exceeds the " + std::to_string(kScratchBytes >> 20) +
-                                  " MiB no-allocation scratch"};
-    if (!c->scratch) throw Fail{MRA_E_DEVICE, "no-allocation scratch not resolved on this device"};
+  if (!noalloc) {
+    align_stack(c, rs, p, parts, N, out, table);
+    return;
   }
+  if (!c->scratch) throw Fail{MRA_E_DEVICE, "no-allocation scratch not resolved on this device"};
+  int64_t step = rs.prune && !few_pairs(c, rs, p, N) ? scratch_chunk(rs, p, true, out->cc2 != nullptr, c->n_cu, kScratchBytes) : 0;
+  const bool pruned = step > 0;
+  if (!pruned) step = scratch_chunk(rs, p, false, out->cc2 != nullptr, c->n_cu, kScratchBytes);
+  if (step < 1)
+    throw Fail{MRA_E_INVAL, "one particle's operand exceeds the " + std::to_string(kScratchBytes >> 20) +
+                                " MiB no-allocation scratch"};
   for (int64_t n0 = 0; n0 < N; n0 += step) {
     const int nc = (int)std::min<int64_t>(step, N - n0);
-    float* tab = table ? table + (size_t)n0 * rs.K * p.M * p.S * kNphi : nullptr;
     ChunkBufs b;
-    if (noalloc) carve_chunk(rs, p, nc, rs.g.precision == kFP16, out && out->cc2, (char*)c->scratch, &b);
-    else b = ws_chunk(c, rs, p, nc, out);
-    run_chunk(c, rs, p, parts, n0, nc, out, tab, b);
+    carve_chunk(rs, p, nc, pruned, out->cc2 != nullptr, c->n_cu, (char*)c->scratch, &b);
+    if (pruned) run_chunk(c, rs, p, parts, n0, nc, out, b);
+    else run_chunk_unpruned(c, rs, p, parts, n0, nc, out, nullptr, b);
   }
 }
 
@@ -527,122 +690,107 @@ struct Piece {
   Plan p;
   int64_t n0;
   int nc;
-  size_t a_off;  // first byte of the piece in the wave's A buffer
-  size_t row0;   // first row in the wave's row-result buffers
 };
 
-void launch_wave(mra_ctx* c, const mra_stack* stacks, std::vector<Piece>& w) {
+void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& w) {
   hipStream_t st = c->stream;
   if (w.size() == 1) {  // one piece fills the chip by itself: the plain per-chunk launches
     const Piece& pc = w[0];
     const mra_stack& sk = stacks[pc.stack];
-    run_chunk(c, *pc.rs, pc.p, sk.parts, pc.n0, pc.nc, &sk.out, nullptr, ws_chunk(c, *pc.rs, pc.p, pc.nc, &sk.out));
+    run_chunk(c, *pc.rs, pc.p, sk.parts, pc.n0, pc.nc, &sk.out, ws_chunk(c, *pc.rs, pc.p, pc.nc, true, &sk.out));
     return;
   }
-  const Refset& rs0 = *w[0].rs;
-  const int prec = rs0.g.precision, variant = rs0.variant;
-  size_t a_bytes = 0, rows = 0, part_total = 0;
-  for (Piece& pc : w) {
-    part_total += pc.nc;
-    pc.a_off = a_bytes;
-    pc.row0 = rows;
+  const int prec = w[0].rs->g.precision, np = (int)w.size();
+  size_t a_bytes = 0, ub_floats = 0, rows = 0, parts = 0, tile = 0;
+  for (const Piece& pc : w) {
     const size_t r = (size_t)pc.nc * pc.p.S;
-    a_bytes += (r + kRowTile - 1) / kRowTile * tile_bytes_of(*pc.rs);
+    a_bytes += (r + kRowTile - 1) / kRowTile * tile_bytes_of(*pc.rs, true);
+    ub_floats += r * ub_pitch(*pc.rs);
     rows += r;
+    parts += pc.nc;
+    tile = std::max(tile, scratch_tile_bytes(*pc.rs));
   }
+  const int grid = fine_grid(prec, (int64_t)parts, c->n_cu);
   char* A = (char*)ws_get(c, "A", a_bytes);
-  float* rcc = (float*)ws_get(c, "row_cc", rows * sizeof(float));
-  int* ridx = (int*)ws_get(c, "row_idx", rows * sizeof(int));
-  float* maxabs = prec == kFP16 ? (float*)ws_get(c, "maxabs", (size_t)part_total * sizeof(float)) : nullptr;
+  float* ub = (float*)ws_get(c, "ub", ub_floats * sizeof(float));
+  unsigned long long* rowkey = (unsigned long long*)ws_get(c, "rowkey", (rows + 1) * sizeof(unsigned long long));
+  float* rownorm = prec == kFP32 ? (float*)ws_get(c, "rownorm", rows * sizeof(float)) : nullptr;
+  float* scratch = prec == kFP32 ? (float*)ws_get(c, "scratch", grid * tile) : nullptr;
+  float* rcc = prec != kFP32 ? (float*)ws_get(c, "row_cc", rows * sizeof(float)) : nullptr;
+  int* ridx = prec != kFP32 ? (int*)ws_get(c, "row_idx", rows * sizeof(int)) : nullptr;
+  float* maxabs = prec != kBF16 ? (float*)ws_get(c, "maxabs", parts * sizeof(float)) : nullptr;
 
   PolarBatch pb{};
   CorrBatch cb{};
-  MergeBatch mb{};
+  FineBatch fb{};
   RescoreBatch rb{};
-  pb.n = cb.n = mb.n = rb.n = (int)w.size();
-  int part = 0, run = 0;
-  for (size_t i = 0; i < w.size(); ++i) {
+  pb.n = cb.n = fb.n = rb.n = np;
+  int part = 0, items = 0, pitems = 0;
+  for (int i = 0; i < np; ++i) {
     const Piece& pc = w[i];
     const Refset& rs = *pc.rs;
     const mra_stack& sk = stacks[pc.stack];
-    const int L = rs.g.L;
-    const int prow = pc.nc * pc.p.S;
-    const int ptiles = (prow + kRowTile - 1) / kRowTile;
-    const size_t tile_bytes = tile_bytes_of(rs);
-    float* Ap = (float*)(A + pc.a_off);
-    const float* src = sk.parts + (size_t)pc.n0 * L * L;
-    if (prow % kRowTile)
-      hip_check(c, launch_fill_zero((char*)Ap + (size_t)(ptiles - 1) * tile_bytes, tile_bytes, st), "fill");
-    float* mx = nullptr;
-    if (maxabs) {
-      mx = maxabs + part;
-      timed(c, "maxabs", [&] { hip_check(c, launch_part_maxabs(src, pc.nc, L, mx, st), "maxabs"); });
+    const size_t r = (size_t)pc.nc * pc.p.S;
+    const float* src = sk.parts + (size_t)pc.n0 * rs.g.L * rs.g.L;
+    ChunkBufs b;
+    b.A = (float*)A;
+    b.ub = ub;
+    b.rowkey = rowkey;
+    b.rownorm = rownorm;
+    b.scratch = scratch;
+    b.grid = grid;
+    b.maxabs = maxabs ? maxabs + part : nullptr;
+    if (row_results(rs)) {
+      b.rcc = rcc;
+      b.ridx = ridx;
     }
-    PolarArgs& pa = pb.piece[i];
-    pa.parts = src; pa.n_part = pc.nc;
-    pa.L = L; pa.R = rs.R; pa.R4 = rs.R4; pa.T = pc.p.T; pa.S1 = pc.p.S1; pa.S = pc.p.S;
-    pa.Lp = pc.p.Lp; pa.pad = pc.p.pad; pa.cx = pc.p.cx; pa.r_min = rs.g.r_min; pa.cs64 = c->cs64; pa.out = Ap;
-    pa.a_layout = a_layout_for(prec, variant);
-    pa.prec = prec;
-    pa.maxabs = mx;
-    pb.start[i] = part;
-
-    CorrArgs& ca = cb.piece[i];
-    ca.A = Ap; ca.a_layout = pa.a_layout; ca.n_row_tiles = ptiles; ca.rows = prow;
-    ca.B32 = rs.B32; ca.B16 = rs.B16;
-    ca.R = rs.R; ca.R4 = rs.R4; ca.NS = rs.NS; ca.BT = b16_tail_width(rs.R4); ca.n_ref_tiles = rs.n_kt; ca.K = rs.K; ca.S = pc.p.S; ca.M = pc.p.M;
-    ca.maxabs = mx; ca.b_scale = rs.b_scale; ca.cs32 = c->cs32;
-    ca.row_cc = rcc + pc.row0; ca.row_idx = ridx + pc.row0; ca.table = nullptr; ca.prune = rs.prune;
-    ca.tiles_per_run = rs.run_tiles > 0 ? rs.run_tiles : corr_tiles_per_run(ptiles, c->n_cu);
-    ca.margin = rs.g.rescore_rows >= 2 ? rerank_margin(prec) : 0.f;
-    cb.run_start[i] = run;
-
-    MergeArgs& ma = mb.piece[i];
-    ma.row_cc = rcc + pc.row0; ma.row_idx = ridx + pc.row0;
-    ma.n_part = pc.nc; ma.S = pc.p.S; ma.S1 = pc.p.S1; ma.T = pc.p.T; ma.M = pc.p.M; ma.out_off = pc.n0;
-    ma.ref = sk.out.ref; ma.shift_x = sk.out.shift_x; ma.shift_y = sk.out.shift_y; ma.psi = sk.out.psi;
-    ma.mirror = sk.out.mirror; ma.flat = sk.out.flat_index; ma.cc = sk.out.cc; ma.cc2 = sk.out.cc2;
-    mb.start[i] = part;
-
-    RescoreArgs& ra = rb.piece[i];
-    ra.parts = src; ra.n_part = pc.nc; ra.out_off = pc.n0;
-    ra.L = L; ra.R = rs.R; ra.r_min = rs.g.r_min; ra.Lp = pc.p.Lp_r; ra.pad = pc.p.pad_r; ra.cx = pc.p.cx;
-    ra.K = rs.K; ra.T = pc.p.T; ra.stencil = rs.stencil; ra.qhat = rs.qhat;
-    ra.ref = sk.out.ref; ra.shift_x = sk.out.shift_x; ra.shift_y = sk.out.shift_y; ra.psi = sk.out.psi;
-    ra.mirror = sk.out.mirror; ra.cc = sk.out.cc;
-    ra.rows = rs.g.rescore_rows; ra.margin = rerank_margin(prec); ra.S1 = pc.p.S1; ra.S = pc.p.S; ra.M = pc.p.M;
-    ra.row_cc = rcc + pc.row0; ra.row_idx = ridx + pc.row0;
-    ra.ref_w = sk.out.ref; ra.shift_x_w = sk.out.shift_x; ra.shift_y_w = sk.out.shift_y;
-    ra.psi_w = sk.out.psi; ra.mirror_w = sk.out.mirror; ra.flat_w = sk.out.flat_index;
-    ra.win = nullptr;
-    rb.start[i] = part;
-
+    pb.piece[i] = polar_args(c, rs, pc.p, src, pc.nc);
+    pb.piece[i].split = polar_split((int)parts, rs.R * (pc.p.S / kRowTile + 1), c->n_cu);
+    pb.piece[i].a_layout = kRingPerm16;
+    pb.piece[i].maxabs = b.maxabs;
+    pb.piece[i].rowkey = b.rowkey;
+    pb.piece[i].out = b.A;
+    cb.piece[i] = corr_args(c, rs, pc.p, pc.nc, kRingPerm16, b);
+    cb.start[i] = items;
+    items += bound_items(cb.piece[i], 0);
+    fb.piece[i] = fine_args(c, rs, pc.p, cb.piece[i], src, pc.n0, pc.nc, &sk.out, b);
+    if (scratch) fb.piece[i].scratch_floats = (int)(tile / sizeof(float));
+    rb.piece[i] = rescore_args(rs, pc.p, src, pc.n0, pc.nc, &sk.out, b);
+    pb.start[i] = pitems;
+    pitems += pc.nc * pb.piece[i].split;
+    fb.start[i] = rb.start[i] = part;
+    A += (r + kRowTile - 1) / kRowTile * tile_bytes_of(rs, true);
+    ub += r * ub_pitch(rs);
+    rowkey += r;
+    if (rownorm) rownorm += r;
+    if (rcc) {
+      rcc += r;
+      ridx += r;
+    }
     part += pc.nc;
-    run += (ptiles + ca.tiles_per_run - 1) / ca.tiles_per_run;
   }
-  pb.start[w.size()] = mb.start[w.size()] = rb.start[w.size()] = part;
-  cb.run_start[w.size()] = run;
+  pb.start[np] = pitems;
+  fb.start[np] = rb.start[np] = part;
+  cb.start[np] = items;
   timed(c, "polar", [&] { hip_check(c, launch_polar_batch(pb, st), "polar batch"); });
-  const int grid = run;
-  timed(c, "corr", [&] { hip_check(c, launch_corr_batch(prec, variant, cb, grid, st), "corr batch"); });
-  timed(c, "merge", [&] { hip_check(c, launch_merge_batch(mb, st), "merge batch"); });
+  timed(c, "bound", [&] { hip_check(c, launch_bound_batch(prec, cb, st), "bound batch"); });
+  if (tighten(c, *w[0].rs, (int64_t)parts)) {
+    FineBatch tb = fb;
+    for (int i = 0; i < np; ++i) tb.piece[i].c.A = cb.piece[i].A;
+    const int tgrid = fine_grid(kFP16, (int64_t)parts, c->n_cu);
+    timed(c, "tighten", [&] { hip_check(c, launch_fine_batch(prec, kFineTighten, tb, tgrid, st), "tighten batch"); });
+  }
+  timed(c, "fine", [&] { hip_check(c, launch_fine_batch(prec, kFineArgmax, fb, grid, st), "fine batch"); });
   if (prec != kFP32) timed(c, "rescore", [&] { hip_check(c, launch_rescore_batch(rb, st), "rescore batch"); });
 }
 
 void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Plan>& plans) {
   const uint64_t budget = c->cap / 2;
-  // stacks that share a correlation instantiation (precision, tile variant,
-  // and the ring bucket: for the 16-bit forms R4 <= 8, 9..12 or 13..16, for
-  // the FP32 resident 8-wave variant the exact R4; launches that mix them
-  // take the kernel's slower run-time form) are packed into the same waves;
-  // within a group the caller's order holds
+  // stacks that share the kernels' instantiations (precision and ring bucket)
+  // are packed into the same waves; within a group the caller's order holds
   std::vector<int> order(n);
   for (int i = 0; i < n; ++i) order[i] = i;
-  auto group = [](const Refset& rs) {
-    const int bucket = rs.g.precision == kFP32 ? (rs.variant == 0 ? rs.R4 : 0)
-                                               : (rs.R4 <= 8 ? 0 : (rs.R4 <= 12 ? 1 : 2));
-    return (rs.g.precision * 16 + rs.variant) * 32 + bucket;
-  };
+  auto group = [](const Refset& rs) { return rs.g.precision * 4 + ring_bucket(rs.R4); };
   auto key = [&](int i) {
     if (stacks[i].N <= 0) return 0;
     return group(get_refset(c, stacks[i].refset_id));
@@ -650,6 +798,11 @@ void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Pla
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return key(x) < key(y); });
   std::vector<Piece> wave;
   uint64_t used = 0;
+  auto flush = [&] {
+    if (!wave.empty()) launch_wave(c, stacks, wave);
+    wave.clear();
+    used = 0;
+  };
   for (int i : order) {
     const mra_stack& s = stacks[i];
     if (s.N <= 0) continue;
@@ -659,31 +812,28 @@ void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Pla
       run_single(c, rs, p, s.parts, s.N, &s.out);
       continue;
     }
-    if (s.out.cc2 || s.out.psi_frac) {  // runner-up or refinement: the per-chunk path
-      const int64_t step = std::min<int64_t>(chunk_particles(c, rs, p), (int64_t)(INT32_MAX / p.S / 2));
-      for (int64_t n0 = 0; n0 < s.N; n0 += step) {
-        const int nc = (int)std::min<int64_t>(step, s.N - n0);
-        run_chunk(c, rs, p, s.parts, n0, nc, &s.out, nullptr, ws_chunk(c, rs, p, nc, &s.out));
-      }
+    // runner-up, refinement, no pruning, or a workspace too small for what a
+    // wave holds besides its operand and bounds (FP32: the scratch tiles, at
+    // most a quarter of it): the per-chunk path
+    if (s.out.cc2 || s.out.psi_frac || !rs.prune ||
+        (rs.g.precision == kFP32 && fine_grid(kFP32, INT32_MAX, c->n_cu) * scratch_tile_bytes(rs) > c->cap / 4) ||
+        ws_other(c) > c->cap / 8 || particle_bytes(rs, p, true) > budget / 2) {
+      align_stack(c, rs, p, s.parts, s.N, &s.out, nullptr);
       continue;
     }
-    const uint64_t per = (uint64_t)p.S * a_bytes_per_row(rs);
+    const uint64_t per = particle_bytes(rs, p, true);
     const int64_t cap_n = rs.chunk > 0 ? rs.chunk : std::max<int64_t>(1, (int64_t)(budget / per));
     for (int64_t n0 = 0; n0 < s.N;) {
       const bool compatible = wave.empty() || group(*wave[0].rs) == group(rs);
-      if (!compatible || (int)wave.size() == kMaxBatchPieces || used + per > budget) {
-        if (!wave.empty()) launch_wave(c, stacks, wave);
-        wave.clear();
-        used = 0;
-      }
+      if (!compatible || (int)wave.size() == kMaxBatchPieces || used + per > budget) flush();
       const int64_t room = std::max<int64_t>(1, (int64_t)((budget - used) / per));
       const int nc = (int)std::min<int64_t>({s.N - n0, room, cap_n, (int64_t)(INT32_MAX / p.S / 2)});
-      wave.push_back(Piece{i, &rs, p, n0, nc, 0, 0});
-      used += (uint64_t)nc * per + (uint64_t)kRowTile * a_bytes_per_row(rs);
+      wave.push_back(Piece{i, &rs, p, n0, nc});
+      used += (uint64_t)nc * per + tile_bytes_of(rs, true);
       n0 += nc;
     }
   }
-  if (!wave.empty()) launch_wave(c, stacks, wave);
+  flush();
 }
 
 void load_refs_impl(mra_ctx* c, int32_t id, const float* refs, int32_t K, const mra_geom* g) {
@@ -749,14 +899,16 @@ void load_refs_impl(mra_ctx* c, int32_t id, const float* refs, int32_t K, const 
         if (!(norms[k] > 0.0))
           throw Fail{MRA_E_DEGENERATE, "reference " + std::to_string(k) + " has zero weighted ring norm"};
     rs.b_scale = 1.f;
-    if (g->precision == kFP16 && bmax > 0.f) rs.b_scale = std::ldexp(1.f, 14 - (int)std::ceil(std::log2(bmax)));
+    if (g->precision != kBF16 && bmax > 0.f && std::isfinite(bmax)) rs.b_scale = std::ldexp(1.f, 14 - (int)std::ceil(std::log2(bmax)));
     ra.b_scale = rs.b_scale;
-    if (g->precision == kFP32)
-      rs.B32 = (float*)alloc(c, (size_t)rs.n_kt * kSlots * rs.R4 * 64 * sizeof(float), "B32");
-    else
-      rs.B16 = (uint16_t*)alloc(c, (size_t)rs.n_kt * kSlots * b16_slot_elems(rs.R4) * sizeof(uint16_t), "B16");
+    if (g->precision == kFP32) {
+      rs.B32 = (float*)alloc(c, (size_t)rs.n_kt * kRefTile * kSlots * 8 * b32_pitch(rs.R4) * sizeof(float), "B32");
+      rs.bnorm = (float*)alloc(c, (size_t)K * sizeof(float), "bnorm");
+    }
+    rs.B16 = (uint16_t*)alloc(c, (size_t)rs.n_kt * kSlots * b16_slot_elems(rs.R4) * sizeof(uint16_t), "B16");
     ra.B32 = rs.B32;
     ra.B16 = rs.B16;
+    ra.bnorm = rs.bnorm;
     if (K == 1) rs.G1 = (float2*)alloc(c, (size_t)rs.R * kSlots * sizeof(float2), "G1");
     ra.G1 = rs.G1;
     hip_check(c, launch_ref_stage2(ra, st), "ref stage 2");
@@ -1062,6 +1214,7 @@ int mra_debug_polar(mra_ctx* c, int32_t id, const float* parts, int64_t N, float
     pa.parts = parts; pa.n_part = (int)N;
     pa.L = rs.g.L; pa.R = rs.R; pa.R4 = rs.R4; pa.T = p.T; pa.S1 = p.S1; pa.S = p.S;
     pa.Lp = p.Lp; pa.pad = p.pad; pa.cx = p.cx; pa.r_min = rs.g.r_min; pa.cs64 = c->cs64; pa.out = out;
+    pa.split = 1;
     hip_check(c, launch_polar(1, pa, c->stream), "polar");
   });
 }
@@ -1075,6 +1228,7 @@ int mra_debug_spectra(mra_ctx* c, int32_t id, const float* parts, int64_t N, flo
     pa.parts = parts; pa.n_part = (int)N;
     pa.L = rs.g.L; pa.R = rs.R; pa.R4 = rs.R4; pa.T = p.T; pa.S1 = p.S1; pa.S = p.S;
     pa.Lp = p.Lp; pa.pad = p.pad; pa.cx = p.cx; pa.r_min = rs.g.r_min; pa.cs64 = c->cs64; pa.out = out;
+    pa.split = 1;
     hip_check(c, launch_polar(2, pa, c->stream), "polar");
   });
 }

@@ -12,13 +12,13 @@ constexpr int kNphi = 256;          // angles per ring (the paper's workloads)
 constexpr int kSlots = 128;         // frequency slots: f = 1..127, slot 0 = (f 0, f 128)
 
 constexpr int kRowTile = 8;         // particle rows (shift, particle) per correlation tile
+constexpr int kMaxShifts = 289;     // shifts per particle at the largest search range (+-8)
 constexpr int kRefTile = 8;         // references per correlation tile
 constexpr int kPolarWaves = 8;      // resampling workgroup: 8 waves, 8 shifts x 8 FFT lanes each
 constexpr int kPolarThreads = 64 * kPolarWaves;
 constexpr int kMaxBatchPieces = 12; // stack pieces per batched launch (kernel-argument table)
 constexpr int kAvgChunk = 32;       // particles per partial class sum
 constexpr int kAvgThreads = 256;
-constexpr int kMaxRunTiles = 48;    // consecutive row tiles per correlation workgroup (a run), at most
 
 enum Prec { kFP32 = 0, kBF16 = 1, kFP16 = 2 };
 
@@ -71,11 +71,22 @@ __host__ __device__ constexpr int b16_tail_width(int R4) {
 // 16-bit elements per (reference tile, slot) block
 __host__ __device__ constexpr int b16_slot_elems(int R4) { return (((R4 + 7) / 8 - 1) * 8 + b16_tail_width(R4)) * 64; }
 
+// FP32 reference operand: [reference (padded to whole tiles)][slot][ring group
+// * 2 + q][b32_pitch]: a lane's R4 elements contiguous, padded to 16 bytes
+__host__ __device__ constexpr int b32_pitch(int R4) { return (R4 + 3) & ~3; }
+
 // Power-of-two FP16 scale of a particle's operand: |a +- b| <= 2 * 256 *
 // max|pixel| is mapped below 2^14.
 __device__ __forceinline__ float fp16_operand_scale(float maxabs) {
   const float m = fmaxf(maxabs * 512.f, 1e-30f);
   return ldexpf(1.f, 14 - (int)ceilf(log2f(m)));
+}
+
+// A value in the scaled units of a particle with max |pixel| mx against a
+// refset of scale b_scale, in its own: one power of two at a time (their
+// product may leave the float range).
+__device__ __forceinline__ float fp16_value(float v, float mx, float b_scale) {
+  return v * (1.f / fp16_operand_scale(mx)) * (1.f / b_scale);
 }
 
 // Entry of the particle sampling stencil for ring r and angle j (FP64
@@ -100,53 +111,86 @@ struct PolarArgs {
   int Lp, pad, cx;     // LDS image side (with zero border), border width, centre
   int r_min;           // radius of ring 0
   int a_layout;        // mode 0: ALayout of the operand
+  int split;           // mode 0: workgroups per particle
   int prec;            // kRingPerm16: kBF16 or kFP16
-  const float* maxabs; // kFP16: max |pixel| of each particle of the chunk (operand scale)
+  float* maxabs;       // kFP16: out, max |pixel| of each particle of the chunk (operand scale)
   const double2* cs64; // (cos, sin)(2 pi j / 256)
+  unsigned long long* rowkey;  // zeroed for the particle's rows, or null
   float* out;          // (mode 0, kRingPerm16: 16-bit elements)
 };
 
-// Fused contraction + inverse FFT over angle + arg-max.
+// Contraction, bounds and evaluation of a chunk's rows against a refset.
 struct CorrArgs {
   const float* A;        // [row tiles][...] in layout a_layout (ALayout; 16-bit elements for kRingPerm16)
   int a_layout;
   int n_row_tiles;
   int rows;              // valid rows in the chunk (n * S)
-  const float* B32;      // [ref tiles][128][R4][64]
-  const uint16_t* B16;   // [ref tiles][128][b16_slot_elems(R4)]: NS - 1 steps [64][8], then [64][BT]
-  int R, R4, NS, n_ref_tiles, K, S, M;
-  int BT;                // b16_tail_width(R4)
-  const float* maxabs;   // FP16: max |pixel| of each particle of the chunk (A scale), else null
-  float b_scale;         // FP16: power-of-two scale folded into B16
+  const float* B32;      // [n_ref_tiles * 8][128][8][b32_pitch(R4)]
+  const uint16_t* B16;   // [ref tiles][128][b16_slot_elems(R4)]: NS - 1 steps [64][8], then [64][BT],
+                         // the 64 ordered ring group, reference, q
+  int R, R4, n_ref_tiles, K, S, M;
+  const float* maxabs;   // FP16 operand: max |pixel| of each particle of the chunk (A scale), else null
+  float b_scale;         // FP16 operand: power-of-two scale folded into B16
+  const float* bnorm;    // FP32 alignment: norm of each reference's operand (bound error)
   const float2* cs32;
-  float* row_cc;         // [rows] best CC of the row
-  int* row_idx;          // [rows] flat index of the row's best
+  float* row_cc;         // evaluation: [rows] best CC of the row and its flat index, or null
+  int* row_idx;
   float* table;          // debug: [n][K][M][S][256], else null
   const int* excl;       // per particle of the chunk: flat index left out of the arg-max, or null
-  int prune;             // 1: skip the inverse FFT of pairs whose CC bound is below the row's threshold
-  int tiles_per_run;     // consecutive row tiles per workgroup (>= 1)
-  float margin;          // particle threshold: best - margin * |best| (0: the best itself)
+  float* ub;             // [rows][ldu] upper bound of each pair's CC (-inf past K)
+  int ldu;               // 8 * n_ref_tiles
+  unsigned long long* rowkey;  // [rows] each row's largest bound and its reference, or (every pair evaluated) its
+                               // best CC and flat index, in cand_key order; zeroed by the resampler
+  float* rownorm;        // FP32 alignment: [rows] norm of the row's operand (FP16, scaled; bound error)
+  int kt_per_wg;         // reference tiles per workgroup (bounds, and the correlation of every pair)
 };
 
-// Batched correlation: pieces of several stacks in one launch, one
-// workgroup per run of row tiles.  run_start[i] is the first run of piece i;
-// run_start[n] the total.
+// Batched form: work item i of the launch is item i - start[p] of piece p
+// with start[p] <= i < start[p + 1].
 struct CorrBatch {
   int n;
-  int run_start[kMaxBatchPieces + 1];
+  int start[kMaxBatchPieces + 1];
   CorrArgs piece[kMaxBatchPieces];
 };
 
-struct MergeArgs {
-  const float* row_cc;
-  const int* row_idx;
+// Where a chunk's particles' results go.
+struct ResultArgs {
   int n_part, S, S1, T, M;
+  int runner_up;         // 1: the values are bests without the winner; write only cc2
   int64_t out_off;
   int32_t *ref, *shift_x, *shift_y, *psi, *mirror, *flat;
   float *cc, *cc2;
   int32_t* win;          // chunk-local copy of each winner's flat index, or null
-  int runner_up;         // 1: rows hold the best without the winner; write only cc2
 };
+
+// Merge of the rows' bests, every pair having been evaluated.
+struct MergeArgs {
+  ResultArgs r;
+  const unsigned long long* rowkey;  // [n_part * S]
+  const float* maxabs;   // FP16: with b_scale, the scale of the rows' values, else null
+  float b_scale;
+  float* row_cc;         // out, for the re-ranking, or null
+  int* row_idx;
+};
+
+// Evaluation of the pairs that can win, one workgroup per particle at a time.
+struct FineArgs {
+  CorrArgs c;            // A: the rows' operand (16-bit forms) or the scratch tiles (FP32)
+  ResultArgs m;          // the particle's outputs
+  float margin;          // rows within this fraction of the particle's best keep their exact best
+  // FP32: the operand of the rows evaluated is made here, in one scratch tile
+  // per workgroup (blockIdx.x * scratch_floats)
+  int scratch_floats;
+  const float* parts;    // first particle of the chunk
+  int L, Lp, pad, cx, r_min;
+  const double2* cs64;
+};
+struct FineBatch {
+  int n;
+  int start[kMaxBatchPieces + 1];
+  FineArgs piece[kMaxBatchPieces];
+};
+static_assert(sizeof(FineBatch) <= 4096, "kernel arguments");
 
 struct RescoreArgs {
   const float* parts;
@@ -176,11 +220,6 @@ struct PolarBatch {
   int start[kMaxBatchPieces + 1];
   PolarArgs piece[kMaxBatchPieces];
 };
-struct MergeBatch {
-  int n;
-  int start[kMaxBatchPieces + 1];
-  MergeArgs piece[kMaxBatchPieces];
-};
 struct RescoreBatch {
   int n;
   int start[kMaxBatchPieces + 1];
@@ -205,29 +244,36 @@ struct RfaArgs {
 hipError_t launch_polar(int mode, const PolarArgs& a, hipStream_t st);
 size_t polar_lds_bytes(int Lp);
 hipError_t launch_corr(int prec, int variant, bool table, const CorrArgs& a, hipStream_t st);
-hipError_t launch_corr_runner_up(int prec, const CorrArgs& a, hipStream_t st);
-hipError_t launch_corr_batch(int prec, int variant, const CorrBatch& b, int grid, hipStream_t st);
-// row tiles per correlation run for a launch of `tiles` tiles on n_cu CUs:
-// long runs carry each particle's best across its tiles (fewer tiles start
-// without a threshold), enough runs keep every CU busy to the launch's end.
-// Runs of up to 8 tiles as long as every CU gets 3 runs; longer ones (up to
-// kMaxRunTiles) while every CU still gets 20, which measured best on the
-// 100k workload at 32 and 128 GiB workspaces.
-inline int corr_tiles_per_run(int tiles, int n_cu) {
-  const int cu = n_cu > 0 ? n_cu : 1;
-  const int a = tiles / (3 * cu), b = tiles / (20 * cu);
-  const int g = b > (a < 8 ? a : 8) ? b : (a < 8 ? a : 8);
-  return g < 1 ? 1 : (g > kMaxRunTiles ? kMaxRunTiles : g);
+hipError_t launch_corr_runner_up(int prec, int variant, const CorrArgs& a, hipStream_t st);
+// 16-bit ring buckets (R4 <= 8, 9..10, 11..12, 13..16): the pieces of a batched launch share one
+constexpr int ring_bucket(int R4) { return R4 <= 8 ? 0 : (R4 <= 10 ? 1 : (R4 <= 12 ? 2 : 3)); }
+// work items of a bound launch over a's rows; sets a.kt_per_wg
+int bound_items(CorrArgs& a, int n_cu);
+hipError_t launch_bound(int prec, const CorrArgs& a, int n_items, hipStream_t st);
+hipError_t launch_bound_batch(int prec, const CorrBatch& b, hipStream_t st);
+// workgroups of an evaluation launch over n particles (FP32: also its scratch tiles)
+int fine_grid(int prec, int64_t n, int n_cu);
+enum FineMode { kFineArgmax = 0, kFineRunnerUp = 2, kFineTighten = 3 };
+hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, int grid, hipStream_t st);
+hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, int grid, hipStream_t st);
+// launches of few particles: workgroups per particle (of n_items 8-row ring
+// items) that fill n_cu CUs twice, and reference parts of a launch of `tiles`
+// row tiles that give every CU a workgroup
+inline int polar_split(int n_part, int n_items, int n_cu) {
+  const int want = n_part > 0 ? 2 * n_cu / n_part : 1, most = (n_items + kPolarWaves - 1) / kPolarWaves;
+  return want < 1 ? 1 : (want > most ? most : want);
+}
+inline int corr_parts(int tiles, int n_ref_tiles, int n_cu) {
+  const int want = tiles > 0 ? n_cu / tiles : 1;
+  return want < 1 ? 1 : (want > n_ref_tiles ? n_ref_tiles : want);
 }
 bool corr_variant_ok(int prec, int variant, int R4);
 int corr_default_variant(int prec, int R4);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st);
 hipError_t launch_rescore(const RescoreArgs& a, hipStream_t st);
 hipError_t launch_polar_batch(const PolarBatch& b, hipStream_t st);
-hipError_t launch_merge_batch(const MergeBatch& b, hipStream_t st);
 hipError_t launch_rescore_batch(const RescoreBatch& b, hipStream_t st);
 hipError_t launch_refine(const RescoreArgs& a, hipStream_t st);  // psi_frac from the final parameters
-hipError_t launch_part_maxabs(const float* x, int n_part, int L, float* out, hipStream_t st);
 hipError_t launch_rfa(const RfaArgs& a, hipStream_t st);
 // zero `bytes` (a multiple of 16) at p (16-byte aligned) with a kernel
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
@@ -249,6 +295,7 @@ struct RefArgs {
   float2* G1;        // K = 1: [R][128] (c - d, c + d) per slot, else null
   float* bmax;       // device scalar: max |B| (for the FP16 scale)
   float b_scale;
+  float* bnorm;      // FP32: [K] norm of each reference's operand (rounded up), else null
 };
 hipError_t launch_ref_stage1(const RefArgs& a, hipStream_t st);  // polar, norm, spectra, qhat, bmax
 hipError_t launch_ref_stage2(const RefArgs& a, hipStream_t st);  // pack B32 / B16

@@ -51,14 +51,29 @@ constexpr float kC1 = 0.92387953251128675613f;  // cos(pi/8)
 constexpr float kS1 = 0.38268343236508977173f;  // sin(pi/8)
 constexpr float kR2 = 0.70710678118654752440f;  // cos(pi/4)
 
+// a * cos(pi/4) (-1 - i): both parts take the same two products, and which one
+// is rounded before the sum is written out (BY_X: that of a.x).  Left to the
+// compiler it depends on the code around, and kernels that share the ring
+// transform would differ in the last bit.
+template <bool BY_X>
+MRA_HD float2 mul_e3(float2 a) {
+  if (BY_X) {
+    const float m = -kR2 * a.x;
+    return make_float2(fmaf(a.y, kR2, m), fmaf(a.y, -kR2, m));
+  }
+  const float m = -kR2 * a.y;
+  return make_float2(fmaf(a.x, -kR2, -m), fmaf(a.x, -kR2, m));
+}
+
 // 8-point DFT in place: radix 4 over even/odd inputs, then one radix-2 pass.
-template <int SIGN>
+// BY_X: see mul_e3 (SIGN = -1).
+template <int SIGN, bool BY_X = true>
 MRA_HD void dft8(float2 (&v)[8]) {
   dft4<SIGN>(v[0], v[2], v[4], v[6]);   // a[0][n1] in v[2 n1]
   dft4<SIGN>(v[1], v[3], v[5], v[7]);   // a[1][n1] in v[2 n1 + 1]
   v[3] = cmul(v[3], make_float2(kR2, SIGN * kR2));
   v[5] = mul_i<SIGN>(v[5]);
-  v[7] = cmul(v[7], make_float2(-kR2, SIGN * kR2));
+  v[7] = SIGN < 0 ? mul_e3<BY_X>(v[7]) : cmul(v[7], make_float2(-kR2, SIGN * kR2));
   float2 o[8];
 #pragma unroll
   for (int n1 = 0; n1 < 4; ++n1) {

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "mra_common.h"
+#include "mra_fft.h"
 
 namespace mra {
 
@@ -117,6 +118,172 @@ __device__ __forceinline__ float bilin(const float* img, int o, int Lp, float fx
   const float top = i00 + fx * (i10 - i00);
   const float bot = i01 + fx * (i11 - i01);
   return top + fy * (bot - top);
+}
+
+// lane J's value of each group of 8 consecutive lanes, to all 8
+// (ds_swizzle bit-mask mode: source lane = (lane & 0x18) | J within 32)
+template <int J>
+__device__ __forceinline__ int group_bcast(int v) {
+  return __builtin_amdgcn_ds_swizzle(v, 0x18 | (J << 5));
+}
+
+// One ring at 8 shifts: the 32 bilinear samples v[i] = p[16 n1 + 2 l + e]
+// (i = 2 n1 + e) of the lane's shift.  Lane (l, r) of the wave: group l of
+// the FFT, shift r; o4 is the byte offset of that shift's centre pixel.
+// Positions and weights do not depend on the shift: lane r of group l takes
+// them for the angles i = r (mod 8), from the staged cos/sin (no memory
+// loads), and samples those at all 8 shifts; a transpose through the wave's
+// scratch `my` (64 x 9 float2), in two halves of 16 angles, hands each lane
+// its own shift's samples.
+__device__ __forceinline__ void sample_ring(const float* img, const CosSin* cs, float2* my, float rr, int l, int r,
+                                            int o4, int Lp4, float (&v)[32]) {
+  const CosSin* cp = cs + 2 * l;
+  const int o4s[8] = {group_bcast<0>(o4), group_bcast<1>(o4), group_bcast<2>(o4), group_bcast<3>(o4),
+                      group_bcast<4>(o4), group_bcast<5>(o4), group_bcast<6>(o4), group_bcast<7>(o4)};
+  float* tr = reinterpret_cast<float*>(my);  // [64 (l, shift)][17]: row pitch 17 spreads the banks
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) {
+    float smp[2][8];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int i = 16 * hf + 8 * b + r;
+      const CosSin c = cp[16 * (i >> 1) + (i & 1)];
+      const int off = polar_offset(rr, c, Lp4);
+      float w00, w10, w01, w11;
+      polar_weights(rr, c, w00, w10, w01, w11);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) smp[b][j] = bilin4w(img, o4s[j] + off, Lp4, w00, w10, w01, w11);
+    }
+    wave_sync();  // the scratch's earlier readers are done
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) tr[(l * 8 + j) * 17 + 8 * b + r] = smp[b][j];
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[16 * hf + q] = tr[(l * 8 + r) * 17 + q];
+  }
+  wave_sync();  // before the FFT's transposes reuse the scratch
+}
+
+// Ring FFT of the lane's samples: the two columns fwd_emit takes
+// (k1a, k1b = fwd_cols(l)).
+__device__ __forceinline__ void fft_ring(const CosSin* cs, float2* my, int l, int r, int k1a, int k1b,
+                                         const float (&v)[32], float2 (&Za)[8], float2 (&Zb)[8]) {
+  float2 z[16];
+#pragma unroll
+  for (int n1 = 0; n1 < 16; ++n1) z[n1] = make_float2(v[2 * n1], v[2 * n1 + 1]);
+  dft16<-1>(z);
+#pragma unroll
+  for (int k1 = 1; k1 < 16; ++k1) z[k1] = cmul(z[k1], twid(cs, 2 * ((l * k1) & 127)));
+  // transpose through the scratch in two halves: lane l's first column
+  // k1a lies in 0..7, its second k1b in 8..15.  Entries are ordered
+  // (l, shift) with the shift fastest, which spreads a wave's accesses
+  // over the banks better than (shift, l).
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int k1 = 0; k1 < 8; ++k1) my[(l * 8 + r) * 9 + k1] = z[8 * h + k1];
+    wave_sync();
+#pragma unroll
+    for (int n2 = 0; n2 < 8; ++n2) {
+      if (h == 0) Za[n2] = my[(n2 * 8 + r) * 9 + k1a];
+      else Zb[n2] = my[(n2 * 8 + r) * 9 + k1b - 8];
+    }
+    wave_sync();
+  }
+  dft8<-1>(Za);
+  dft8<-1, false>(Zb);
+}
+
+// The lane's 16 spectrum values as operand entries (a - b, a + b).  Every
+// real split yields one slot below 64 and one above (128 - f, or lane 0's 0
+// and 64): both are kept, so that the 64 low and the 64 high slots can be
+// staged one after the other.
+struct RingSlots {
+  int lo_s[8], hi_s[8];
+  float lo_a[8], lo_b[8], hi_a[8], hi_b[8];
+};
+__device__ __forceinline__ void ring_slots(const CosSin* cs, int l, const float2 (&Za)[8], const float2 (&Zb)[8],
+                                           RingSlots& o) {
+  int e = 0, s0 = 0;
+  float a0 = 0.f, b0 = 0.f;
+  fwd_emit(l, Za, Zb, [&](int f) { return twid(cs, f & 255); },
+           [&](int slot, float re, float im) {
+             const int k = e >> 1;
+             if ((e++ & 1) == 0) {
+               s0 = slot; a0 = re - im; b0 = re + im;
+             } else {
+               const bool first_low = s0 < slot;
+               o.lo_s[k] = first_low ? s0 : slot;
+               o.hi_s[k] = first_low ? slot : s0;
+               o.lo_a[k] = first_low ? a0 : re - im;
+               o.lo_b[k] = first_low ? b0 : re + im;
+               o.hi_a[k] = first_low ? re - im : a0;
+               o.hi_b[k] = first_low ? re + im : b0;
+             }
+           });
+}
+
+// Stages the low (h = 0) or high (h = 1) slots as [64 slots][16] floats
+// (entry p * 8 + shift), the four 16-byte chunks of a slot XOR-swizzled by
+// slot & 3, so the eight lanes l that write at once hit distinct banks.
+__device__ __forceinline__ void stage_slots(float* stage, int h, int r, const RingSlots& o) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int sl = h ? o.hi_s[k] - 64 : o.lo_s[k];
+    const int sw = (sl & 3) << 2;
+    stage[sl * 16 + (r ^ sw)] = h ? o.hi_a[k] : o.lo_a[k];
+    stage[sl * 16 + ((8 + r) ^ sw)] = h ? o.hi_b[k] : o.lo_b[k];
+  }
+}
+
+// FP32 operand: writes one ring's staged slots of half h to the row tile
+// block.  kRingPerm (perm): dst = the ring's [position][16] block; lane
+// (pp = lane / 8, c = lane % 8) writes elements 2c, 2c+1 (rows rp, rp + 1) of
+// the position pair 16 it + 4 h + lp, whose slots are 64 h + sp and
+// 64 h + sp + 8, interleaved by element.  Otherwise slot s goes to dst + s ss,
+// in 16-byte pieces: the lane's piece of slot 64 h + 16 it + lane / 4.  Only
+// rows first <= row < last of the tile are written.
+__device__ __forceinline__ void write_f32_half(const float* stage, float* dst, int h, int ln, bool perm, int ss,
+                                               int first, int last) {
+  const int part = ln & 3;                       // rows (part & 1) * 4 .. +3 of p = part >> 1
+  const int r0 = (part & 1) * 4;
+  const bool full = r0 >= first && r0 + 4 <= last;
+  const int j = ln >> 2;
+  float* const lane_dst = dst + (size_t)__mul24(j, ss) + part * 4;
+  const int pp = ln >> 3, c = ln & 7;
+  const int lp = 8 * (pp >> 2) + (pp & 3), sp = (pp >> 2) + 16 * (pp & 3);
+  const int rp = 2 * (c & 3);
+  const bool full_p = rp >= first && rp + 2 <= last;
+  float* const pair_dst = dst + 32 * lp + 4 * c;
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    if (perm) {
+      const int s0 = 2 * it + sp, s1 = s0 + 8, sw = (s0 & 3) << 2;  // s1 & 3 == s0 & 3
+      const float2 v0 = *reinterpret_cast<const float2*>(stage + s0 * 16 + ((2 * c) ^ sw));
+      const float2 v1 = *reinterpret_cast<const float2*>(stage + s1 * 16 + ((2 * c) ^ sw));
+      float* o = pair_dst + 32 * (16 * it + 4 * h);
+      if (full_p) {
+        *reinterpret_cast<float4*>(o) = make_float4(v0.x, v1.x, v0.y, v1.y);
+      } else {
+        if (rp >= first && rp < last) { o[0] = v0.x; o[1] = v1.x; }
+        if (rp + 1 >= first && rp + 1 < last) { o[2] = v0.y; o[3] = v1.y; }
+      }
+      continue;
+    }
+    const int sl = it * 16 + (ln >> 2);
+    const float4 val = *reinterpret_cast<const float4*>(stage + sl * 16 + ((part ^ (sl & 3)) << 2));
+    float* o = lane_dst + (size_t)(64 * h + 16 * it) * ss;
+    if (full) {
+      *reinterpret_cast<float4*>(o) = val;
+    } else {
+      if (r0 + 0 >= first && r0 + 0 < last) o[0] = val.x;
+      if (r0 + 1 >= first && r0 + 1 < last) o[1] = val.y;
+      if (r0 + 2 >= first && r0 + 2 < last) o[2] = val.z;
+      if (r0 + 3 >= first && r0 + 3 < last) o[3] = val.w;
+    }
+  }
 }
 
 }  // namespace mra
