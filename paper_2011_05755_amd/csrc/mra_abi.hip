@@ -9,6 +9,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "mra.h"
@@ -70,6 +71,8 @@ struct mra_ctx {
   bool failed = false;
   std::string err;
   std::map<int32_t, Refset> refs;
+  Refset spare;                  // buffers of a replaced refset, for the next load of its sizes
+  mra::RefInfo* ref_info = nullptr;  // pinned
   double2* cs64 = nullptr;
   float2* cs32 = nullptr;
   std::map<std::string, DevBuf> ws;
@@ -103,9 +106,21 @@ void* scratch_ptr(mra_ctx* c) {
   return p;
 }
 
+void free_refset(Refset& r) {
+  for (void* p : {(void*)r.B32, (void*)r.B16, (void*)r.bnorm, (void*)r.G1, (void*)r.qhat, (void*)r.norm, (void*)r.stencil})
+    if (p) (void)hipFree(p);
+  r = Refset{};
+}
+
 void* alloc(mra_ctx* c, size_t bytes, const char* what) {
   void* p = nullptr;
   hipError_t e = hipMalloc(&p, bytes < 16 ? 16 : bytes);
+  if (e == hipErrorOutOfMemory && c->spare.stencil) {  // a replaced refset's buffers are given back first
+    (void)hipGetLastError();
+    hip_check(c, hipStreamSynchronize(c->stream), "sync");
+    free_refset(c->spare);
+    e = hipMalloc(&p, bytes < 16 ? 16 : bytes);
+  }
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
     throw Fail{MRA_E_NOMEM, std::string("out of device memory allocating ") + what};
@@ -157,12 +172,6 @@ void clear_profile(mra_ctx* c) {
   c->prof.clear();
 }
 
-void free_refset(Refset& r) {
-  for (void* p : {(void*)r.B32, (void*)r.B16, (void*)r.bnorm, (void*)r.G1, (void*)r.qhat, (void*)r.norm, (void*)r.stencil})
-    if (p) (void)hipFree(p);
-  r = Refset{};
-}
-
 // cos / sin of 2 pi j / n built from the first octant so that the table is
 // exactly symmetric (cos even, sin odd, quarter turns exact).
 void build_cs(int n, std::vector<double>& c, std::vector<double>& s) {
@@ -199,21 +208,6 @@ void check_geom(const mra_geom* g) {
   if (g->precision < 0 || g->precision > 2) bad("precision must be MRA_FP32, MRA_BF16 or MRA_FP16");
   if (g->normalize != 0 && g->normalize != 1) bad("normalize must be 0 or 1");
   if (g->rescore_rows < 0 || g->rescore_rows > 8) bad("rescore_rows must be in [0, 8]");
-}
-
-// Range of the floor offsets of the polar stencil (r cos, r sin) over the
-// rings of g: the pixels a zero shift touches lie in [c + dmin, c + dmax + 1].
-void stencil_range(const mra_geom& g, int& dmin, int& dmax) {
-  std::vector<double> cs, sn;
-  build_cs(kNphi, cs, sn);
-  dmin = 0;
-  dmax = 0;
-  for (int r = g.r_min; r <= g.r_max; ++r)
-    for (int j = 0; j < kNphi; ++j) {
-      const int fx = (int)std::floor(r * cs[j]), fy = (int)std::floor(r * sn[j]);
-      dmin = std::min({dmin, fx, fy});
-      dmax = std::max({dmax, fx, fy});
-    }
 }
 
 // The flat candidate index iota = (((k M + m) S1 + sy) S1 + sx) n_phi + a is
@@ -836,6 +830,37 @@ void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Pla
   flush();
 }
 
+// The buffers of one replaced refset are kept (up to kSpareBytes) for the next
+// set of the same sizes: a program that replaces its references on every pass
+// then allocates and frees nothing.  What was enqueued against the old set
+// comes first on the same stream.
+constexpr uint64_t kSpareBytes = 256ull << 20;
+
+uint64_t refset_bytes(const Refset& r) {
+  return (uint64_t)r.R * kNphi * (sizeof(Stencil) + r.K * sizeof(float)) +
+         (r.B32 ? (uint64_t)r.n_kt * kRefTile * kSlots * 8 * b32_pitch(r.R4) * sizeof(float) : 0) +
+         (r.B16 ? (uint64_t)r.n_kt * kSlots * b16_slot_elems(r.R4) * sizeof(uint16_t) : 0);
+}
+
+void keep_spare(mra_ctx* c, Refset& old) {
+  Refset gone = refset_bytes(old) <= kSpareBytes ? c->spare : old;
+  if (refset_bytes(old) <= kSpareBytes) c->spare = old;
+  if (gone.stencil) {
+    hip_check(c, hipStreamSynchronize(c->stream), "sync");
+    free_refset(gone);
+  }
+}
+
+// rs (sizes set, no buffers yet) takes the spare set's buffers if they fit.
+bool take_spare(mra_ctx* c, Refset& rs) {
+  Refset& o = c->spare;
+  if (!o.stencil || o.K != rs.K || o.R != rs.R || o.g.precision != rs.g.precision) return false;
+  rs.stencil = o.stencil; rs.norm = o.norm; rs.qhat = o.qhat;
+  rs.B32 = o.B32; rs.B16 = o.B16; rs.bnorm = o.bnorm; rs.G1 = o.G1;
+  o = Refset{};
+  return true;
+}
+
 void load_refs_impl(mra_ctx* c, int32_t id, const float* refs, int32_t K, const mra_geom* g) {
   check_geom(g);
   if (K < 1) throw Fail{MRA_E_INVAL, "K must be >= 1"};
@@ -851,29 +876,16 @@ void load_refs_impl(mra_ctx* c, int32_t id, const float* refs, int32_t K, const 
   rs.variant = corr_default_variant(g->precision, rs.R4);
   hipStream_t st = c->stream;
   try {
-    // particle sampling stencil, exactly symmetric in j <-> 256 - j
-    std::vector<double> cs, sn;
-    build_cs(kNphi, cs, sn);
-    std::vector<Stencil> sten((size_t)rs.R * kNphi);
-    rs.dmin = 0;
-    rs.dmax = 0;
-    for (int r = 0; r < rs.R; ++r)
-      for (int j = 0; j < kNphi; ++j) {
-        const double rr = g->r_min + r;
-        const double x = rr * cs[j], y = rr * sn[j];
-        const double fx = std::floor(x), fy = std::floor(y);
-        Stencil s;
-        s.bx = 4 * (int)fx;
-        s.dy = (int)fy;
-        s.fx = (float)(x - fx);
-        s.fy = (float)(y - fy);
-        sten[(size_t)r * kNphi + j] = s;
-        rs.dmin = std::min({rs.dmin, (int)fx, (int)fy});
-        rs.dmax = std::max({rs.dmax, (int)fx, (int)fy});
-      }
-    rs.stencil = (Stencil*)alloc(c, sten.size() * sizeof(Stencil), "stencil");
-    hip_check(c, hipMemcpyAsync(rs.stencil, sten.data(), sten.size() * sizeof(Stencil), hipMemcpyHostToDevice, st), "memcpy");
-
+    // floor offsets of the sampling positions r (cos, sin): the table holds the
+    // quarter turns exactly, so the rings reach from -r_max to r_max
+    rs.dmin = -g->r_max;
+    rs.dmax = g->r_max;
+    // a set of the same sizes that another load replaced lends its buffers
+    const bool reuse = take_spare(c, rs);
+    auto buf = [&](auto*& ptr, size_t bytes, const char* what) {
+      if (!reuse) ptr = (std::remove_reference_t<decltype(ptr)>)alloc(c, bytes, what);
+    };
+    buf(rs.stencil, (size_t)rs.R * kNphi * sizeof(Stencil), "stencil");
     RefArgs ra{};
     ra.refs = refs;
     ra.K = K; ra.L = g->L; ra.r_min = g->r_min; ra.R = rs.R; ra.R4 = rs.R4; ra.NS = rs.NS;
@@ -882,34 +894,31 @@ void load_refs_impl(mra_ctx* c, int32_t id, const float* refs, int32_t K, const 
     ra.q64 = (double*)ws_get(c, "ref_q64", (size_t)K * rs.R * kNphi * sizeof(double));
     ra.inv = (double*)ws_get(c, "ref_inv", (size_t)K * sizeof(double));
     ra.Qs = (double2*)ws_get(c, "ref_Qs", (size_t)K * 129 * rs.R * sizeof(double2));
-    ra.bmax = (float*)ws_get(c, "ref_bmax", 256);
-    rs.norm = (double*)alloc(c, (size_t)K * sizeof(double), "norm");
-    rs.qhat = (float*)alloc(c, (size_t)K * rs.R * kNphi * sizeof(float), "qhat");
+    ra.info = (RefInfo*)ws_get(c, "ref_info", 256);
+    buf(rs.norm, (size_t)K * sizeof(double), "norm");
+    buf(rs.qhat, (size_t)K * rs.R * kNphi * sizeof(float), "qhat");
     ra.norm = rs.norm;
     ra.qhat32 = rs.qhat;
-    hip_check(c, hipMemsetAsync(ra.bmax, 0, sizeof(float), st), "memset");
+    ra.stencil = rs.stencil;
     hip_check(c, launch_ref_stage1(ra, st), "ref stage 1");
-    std::vector<double> norms(K);
-    float bmax = 0.f;
-    hip_check(c, hipMemcpyAsync(norms.data(), rs.norm, K * sizeof(double), hipMemcpyDeviceToHost, st), "memcpy");
-    hip_check(c, hipMemcpyAsync(&bmax, ra.bmax, sizeof(float), hipMemcpyDeviceToHost, st), "memcpy");
+    hip_check(c, hipMemcpyAsync(c->ref_info, ra.info, sizeof(RefInfo), hipMemcpyDeviceToHost, st), "memcpy");
     hip_check(c, hipStreamSynchronize(st), "sync");
-    if (g->normalize)
-      for (int k = 0; k < K; ++k)
-        if (!(norms[k] > 0.0))
-          throw Fail{MRA_E_DEGENERATE, "reference " + std::to_string(k) + " has zero weighted ring norm"};
+    const float bmax = c->ref_info->bmax;
+    if (g->normalize && c->ref_info->bad < K)
+      throw Fail{MRA_E_DEGENERATE,
+                 "reference " + std::to_string(c->ref_info->bad) + " has zero weighted ring norm"};
     rs.b_scale = 1.f;
     if (g->precision != kBF16 && bmax > 0.f && std::isfinite(bmax)) rs.b_scale = std::ldexp(1.f, 14 - (int)std::ceil(std::log2(bmax)));
     ra.b_scale = rs.b_scale;
-    if (g->precision == kFP32) {
-      rs.B32 = (float*)alloc(c, (size_t)rs.n_kt * kRefTile * kSlots * 8 * b32_pitch(rs.R4) * sizeof(float), "B32");
-      rs.bnorm = (float*)alloc(c, (size_t)K * sizeof(float), "bnorm");
-    }
-    rs.B16 = (uint16_t*)alloc(c, (size_t)rs.n_kt * kSlots * b16_slot_elems(rs.R4) * sizeof(uint16_t), "B16");
+    // (FP32 with one reference: the fused kernel and the CC table need no bounds)
+    if (g->precision == kFP32) buf(rs.B32, (size_t)rs.n_kt * kRefTile * kSlots * 8 * b32_pitch(rs.R4) * sizeof(float), "B32");
+    if (g->precision == kFP32 && K > 1) buf(rs.bnorm, (size_t)K * sizeof(float), "bnorm");
+    if (g->precision != kFP32 || K > 1)
+      buf(rs.B16, (size_t)rs.n_kt * kSlots * b16_slot_elems(rs.R4) * sizeof(uint16_t), "B16");
     ra.B32 = rs.B32;
     ra.B16 = rs.B16;
     ra.bnorm = rs.bnorm;
-    if (K == 1) rs.G1 = (float2*)alloc(c, (size_t)rs.R * kSlots * sizeof(float2), "G1");
+    if (K == 1) buf(rs.G1, (size_t)rs.R * kSlots * sizeof(float2), "G1");
     ra.G1 = rs.G1;
     hip_check(c, launch_ref_stage2(ra, st), "ref stage 2");
   } catch (...) {
@@ -918,8 +927,7 @@ void load_refs_impl(mra_ctx* c, int32_t id, const float* refs, int32_t K, const 
   }
   auto it = c->refs.find(id);
   if (it != c->refs.end()) {
-    hip_check(c, hipStreamSynchronize(st), "sync");
-    free_refset(it->second);
+    keep_spare(c, it->second);
     c->refs.erase(it);
   }
   c->refs[id] = rs;
@@ -1078,12 +1086,14 @@ int mra_create(mra_ctx** out, int device, void* hip_stream, uint64_t workspace_c
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && ncu > 0)
       c->n_cu = ncu;
     c->scratch = scratch_ptr(c);
+    hip_check(c, hipHostMalloc((void**)&c->ref_info, sizeof(RefInfo), hipHostMallocDefault), "hipHostMalloc");
     c->cs64 = (double2*)alloc(c, kNphi * sizeof(double2), "cs64");
     c->cs32 = (float2*)alloc(c, kNphi * sizeof(float2), "cs32");
     hip_check(c, hipMemcpy(c->cs64, h64.data(), kNphi * sizeof(double2), hipMemcpyHostToDevice), "memcpy");
     hip_check(c, hipMemcpy(c->cs32, h32.data(), kNphi * sizeof(float2), hipMemcpyHostToDevice), "memcpy");
   });
   if (rc != MRA_OK) {
+    if (c->ref_info) (void)hipHostFree(c->ref_info);
     delete c;
     return rc;
   }
@@ -1097,6 +1107,8 @@ int mra_destroy(mra_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   clear_profile(c);
   for (auto& kv : c->refs) free_refset(kv.second);
+  free_refset(c->spare);
+  if (c->ref_info) (void)hipHostFree(c->ref_info);
   for (auto& kv : c->ws)
     if (kv.second.p) (void)hipFree(kv.second.p);
   if (c->cs64) (void)hipFree(c->cs64);
@@ -1119,7 +1131,8 @@ int mra_check_geom(const mra_geom* g, int32_t K, int32_t shift_max) {
     Refset rs;
     rs.g = *g;
     rs.K = K;
-    stencil_range(*g, rs.dmin, rs.dmax);
+    rs.dmin = -g->r_max;
+    rs.dmax = g->r_max;
     (void)plan_for(rs, T);
     return MRA_OK;
   } catch (const Fail& f) {
@@ -1134,6 +1147,7 @@ int mra_unload_refs(mra_ctx* c, int32_t id) {
     Refset& rs = get_refset(c, id);
     hip_check(c, hipStreamSynchronize(c->stream), "sync");
     free_refset(rs);
+    free_refset(c->spare);
     c->refs.erase(id);
   });
 }

@@ -281,6 +281,10 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 hipError_t launch_count_changed(const int32_t* cls, int32_t* prev, int n, int* count, hipStream_t st);
 
 // reference preparation
+struct RefInfo {     // read back by the host
+  float bmax;        // largest |packed value|
+  int bad;           // first reference without a positive norm, or 2^31 - 1
+};
 struct RefArgs {
   const float* refs;
   int K, L, r_min, R, R4, NS, n_ref_tiles, normalize, prec;
@@ -293,7 +297,8 @@ struct RefArgs {
   float* B32;
   uint16_t* B16;
   float2* G1;        // K = 1: [R][128] (c - d, c + d) per slot, else null
-  float* bmax;       // device scalar: max |B| (for the FP16 scale)
+  RefInfo* info;
+  Stencil* stencil;  // out: [R][256]
   float b_scale;
   float* bnorm;      // FP32: [K] norm of each reference's operand (rounded up), else null
 };
