@@ -258,9 +258,11 @@ __device__ __forceinline__ void fine_operand(const FineArgs& a, int n, const int
     int k1a, k1b;
     fwd_cols(l, k1a, k1b);
     float v[32];
-    float2 Za[8], Zb[8];
+    float2 z[16], Za[8], Zb[8];
     sample_ring(img, cs, my, (float)(a.r_min + ring), l, r, o4, 4 * a.Lp, v);
-    fft_ring(cs, my, l, r, k1a, k1b, v, Za, Zb);
+#pragma unroll
+    for (int n1 = 0; n1 < 16; ++n1) z[n1] = make_float2(v[2 * n1], v[2 * n1 + 1]);
+    fft_ring(cs, my, l, r, k1a, k1b, z, Za, Zb);
     RingSlots rs;
     ring_slots(cs, l, Za, Zb, rs);
     float* dst = tile + (size_t)ring * kSlots * 16;

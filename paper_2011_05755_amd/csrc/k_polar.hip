@@ -2,9 +2,10 @@
 // each shifted particle resampled to polar coordinates and transformed per
 // ring) and the FP32 re-score of a winning candidate.
 //
-// One 8-wave workgroup per particle (about 68 KB of LDS at L = 76, so two
-// workgroups share a CU: 16 waves, against 12 with three 4-wave groups, which
-// ran 10 % slower).  The image is staged once in LDS with a zero
+// One workgroup per particle (a part of one where there are few), 8 waves
+// and two to a CU where the LDS holds two images (16 waves, against 12 with
+// three 4-wave groups, which ran 10 % slower), else up to 16 waves.  The
+// window of the image that the samples read is staged once in LDS with a zero
 // border (coalesced HBM read), beside a float-float cos/sin table; the
 // (ring, 8-row group) items of the particle are split between the waves.
 // In an item, lane (l, row) needs the 32 samples p[16 n1 + 2l + e] of shift
@@ -13,17 +14,30 @@
 // angles (from the table: the item loop issues no memory loads) and samples
 // them at all 8 shifts, and a transpose through LDS regroups the samples by
 // shift.
+// What bounds it (20 000 particles of 76 px, 7 x 7 shifts, 35 rings, BF16):
+// LDS, busy 92 % of the time before taps were shared and half of that bank
+// conflicts, and the vector units, busy 83 %.  The 16-bit forms therefore read
+// each column of taps once for all rows that share it, write their samples
+// to the transpose from the branch that takes them, stage each spectrum value
+// already rounded, and spread a wave's taps over the circle and over a row
+// pitch that collides little: 10.67 -> 9.3 ms (and 128 px, 9 x 9 shifts, 62
+// rings, 1200 particles: 2.25 -> 1.79 ms).  The FP32 form serves only the
+// unpruned path.
 // The 256-point real FFT runs as a 16 x 8 complex FFT across the eight
 // lanes l of a shift, with a transpose through a per-wave LDS scratch, and
 // the spectra are staged there again so that an item's 128 slots of one
 // ring are written as one contiguous 8 KB run of the operand (the kernel is
 // bound by its HBM writes, and runs of 64-byte pieces scattered over the
 // tile write far slower).
+#include <algorithm>
+
 #include "mra_common.h"
 #include "mra_fft.h"
 #include "polar_impl.h"
 
 namespace mra {
+
+constexpr int kPolarMaxWaves = 16;
 
 // Workgroup -> item: consecutive items on the same XCD (workgroups are dealt
 // to the 8 XCDs round-robin), so row tiles shared by neighbouring particles
@@ -33,48 +47,30 @@ __device__ __forceinline__ int xcd_item() {
   return (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
 }
 
-// Operand element type written in mode 0: FP32 (kRingPerm or kSlotMajor,
-// chosen at run time), or BF16 / FP16 in kRingPerm16.
-enum PolarOut { kOutF32 = 0, kOutBF16 = 1, kOutFP16 = 2 };
-
-// Two values in the contraction's 16-bit type, each rounded to nearest
-// (even) once, packed with x in the low half.
-template <int OUT>
-__device__ __forceinline__ uint32_t pack16(float x, float y) {
-  typedef float f32x2v __attribute__((ext_vector_type(2)));
-  const f32x2v v = {x, y};
-  if constexpr (OUT == kOutBF16) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-  } else {
-    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
-  }
-}
-
 template <int MODE, int OUT>
 __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, int part, float* smem) {
-  float* img = smem;
-  float2* scr = reinterpret_cast<float2*>(smem + ((a.Lp * a.Lp + 3) & ~3));
-  CosSin* cs = reinterpret_cast<CosSin*>(scr + kPolarWaves * 64 * 9);
-  stage_image(img, a.parts + (size_t)n * a.L * a.L, a.L, a.Lp, a.pad);
+  const int NT = blockDim.x, NW = NT >> 6;
+  float* img = smem;  // (first: its tap addresses take no base)
+  CosSin* cs = reinterpret_cast<CosSin*>(smem + ((a.rows * a.Lp + 3) & ~3));
+  float2* scr = reinterpret_cast<float2*>(cs + kNphi);
+  float* red = reinterpret_cast<float*>(scr + NW * 64 * 9);
+  const float peak = stage_window(img, a.parts + (size_t)n * a.L * a.L, a.L, a.Lp, a.rows, a.pad, OUT == kOutFP16);
   stage_cs(cs, a.cs64);
+  if constexpr (OUT == kOutFP16) {
+    float m = peak;
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  }
   __syncthreads();
 
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ln = threadIdx.x & 63;
   const int l = ln >> 3, rl = ln & 7;
   if (a.rowkey && part == 0)
-    for (int i = threadIdx.x; i < a.S; i += kPolarThreads) a.rowkey[(size_t)n * a.S + i] = 0ull;
+    for (int i = threadIdx.x; i < a.S; i += NT) a.rowkey[(size_t)n * a.S + i] = 0ull;
   float hscale = 1.f;
   if constexpr (OUT == kOutFP16) {
-    // max |pixel| of the particle, from the staged image (its border is zero)
-    float* red = reinterpret_cast<float*>(cs + kNphi);
-    float m = 0.f;
-    for (int i = threadIdx.x; i < a.Lp * a.Lp; i += kPolarThreads) m = fmaxf(m, fabsf(img[i]));
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if (ln == 0) red[w] = m;
-    __syncthreads();
-    for (int i = 0; i < kPolarWaves; ++i) m = fmaxf(m, red[i]);
+    float m = 0.f;  // max |pixel| of the particle
+    for (int i = 0; i < NW; ++i) m = fmaxf(m, red[i]);
     if (threadIdx.x == 0) a.maxabs[n] = m;
     hscale = fp16_operand_scale(m);
   }
@@ -92,7 +88,7 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, int pa
     // padding rings of the 16-bit operand are read with the others: zeros
     // (16-byte chunks of one row each)
     const int pad_rings = 4 * a.R4 - a.R, chunks = pad_rings * 256;
-    for (int i = part * kPolarThreads + threadIdx.x; i < ngrp * chunks; i += kPolarThreads * a.split) {
+    for (int i = part * NT + threadIdx.x; i < ngrp * chunks; i += NT * a.split) {
       const int grp = i / chunks, c = i - grp * chunks;
       const int tile = q0 + grp, row = tile * 8 + (c & 7) - row0;
       if (row >= 0 && row < a.S)
@@ -102,8 +98,8 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, int pa
 
   // (ring, row group) items in contiguous blocks per wave (balanced)
   const int n_items = a.R * ngrp;
-  const int per_wave = (n_items + kPolarWaves * a.split - 1) / (kPolarWaves * a.split);
-  const int it0 = (part * kPolarWaves + w) * per_wave, it1 = min(n_items, it0 + per_wave);
+  const int per_wave = (n_items + NW * a.split - 1) / (NW * a.split);
+  const int it0 = (part * NW + w) * per_wave, it1 = min(n_items, it0 + per_wave);
   for (int item = it0; item < it1; ++item) {
     const int ring = item / ngrp, grp = item - ring * ngrp;
     // FP32 operand: the shift and lane indices are made opaque here, so that
@@ -122,74 +118,64 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, int pa
     }
     int k1a, k1b;
     fwd_cols(lx, k1a, k1b);
-    const int row = (q0 + grp) * 8 + rx;
-    const int s = row - row0;
+    const int s = (q0 + grp) * 8 + rx - row0;
     const bool valid = s >= 0 && s < a.S;
-    const int sc = s < 0 ? 0 : (s < a.S ? s : a.S - 1);
-    const int o4 = 4 * (base + shift_offset(sc, a.S1, s1m, a.T, a.Lp));
 
-    float v[32];
-    sample_ring(img, cs, my, (float)(a.r_min + ring), lx, rx, o4, Lp4, v);
+    float2 z[16];
+    if constexpr (OUT != kOutF32) {
+      sample_runs(img, cs, my, (float)(a.r_min + ring), lx, rx, (q0 + grp) * 8 - row0, a.S1, s1m, a.T, 4 * base, Lp4, z);
+    } else {
+      const int sc = s < 0 ? 0 : (s < a.S ? s : a.S - 1);
+      const int o4 = 4 * (base + shift_offset(sc, a.S1, s1m, a.T, a.Lp));
+      float v[32];
+      sample_ring(img, cs, my, (float)(a.r_min + ring), lx, rx, o4, Lp4, v);
+#pragma unroll
+      for (int n1 = 0; n1 < 16; ++n1) z[n1] = make_float2(v[2 * n1], v[2 * n1 + 1]);
+    }
 
     if (MODE == 1) {
       if (valid) {
         float* o = a.out + (((size_t)n * a.S + s) * a.R + ring) * kNphi;
 #pragma unroll
-        for (int i = 0; i < 32; ++i) o[16 * (i >> 1) + 2 * lx + (i & 1)] = v[i];
+        for (int n1 = 0; n1 < 16; ++n1) {
+          o[16 * n1 + 2 * lx] = z[n1].x;
+          o[16 * n1 + 2 * lx + 1] = z[n1].y;
+        }
       }
       continue;
     }
 
     float2 Za[8], Zb[8];
-    fft_ring(cs, my, lx, rx, k1a, k1b, v, Za, Zb);
+    fft_ring(cs, my, lx, rx, k1a, k1b, z, Za, Zb);
 
     if (MODE == 0) {
-      // The slots are staged as [slot][p*8 + row], the 64 low ones and then the
-      // 64 high ones, and written so that each store instruction covers whole
-      // 128-byte lines of the tile.
-      RingSlots rs;
-      ring_slots(cs, lx, Za, Zb, rs);
+      // The slots are staged, the 64 low ones and then the 64 high ones, and
+      // written so that each store instruction covers whole 128-byte lines of
+      // the tile.
       const int tile = q0 + grp;
       const int first = row0 - tile * 8;            // rows of this tile before the particle
       const int last = row0 + a.S - tile * 8;       // first row after the particle
-      const bool slot_major = a.a_layout == kSlotMajor, perm = a.a_layout == kRingPerm;
-      // 16-bit operand: each value rounded once, as the contraction's matrix
-      // cores take it (FP16 scaled by the particle's power of two)
-      constexpr bool half = OUT != kOutF32;
-      const int ss = slot_major ? a.R4 * 64 : 16;
-      float* dst = a.out + (slot_major ? (size_t)tile * kSlots * a.R4 * 64 + ring * 16
-                                       : ((size_t)tile * 4 * a.R4 + ring) * kSlots * 16);
+      if constexpr (OUT != kOutF32) {
+        RingHalves rs;
+        ring_halves<OUT>(cs, lx, Za, Zb, hscale, rs);
+        uint16_t* blk = reinterpret_cast<uint16_t*>(a.out) + (size_t)(tile * 4 * a.R4 + ring) * kSlots * 16;
+        const bool row_in = rx >= first && rx < last;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        stage_slots(stage, h, rx, rs);
-        wave_sync();
-        if constexpr (half) {
-          // kRingPerm16: the staged slots 64 h + sl are positions 16 (sl % 8)
-          // + 8 h + sl / 8, i.e. the runs G = 2 w + h (w = sl % 8); lane
-          // (w, k) of chunk c = lane + 64 q writes element k of the 8
-          // positions of run G as one 16-byte store (one row, so a chunk is
-          // written whole or not at all)
-          uint16_t* blk = reinterpret_cast<uint16_t*>(a.out) + (size_t)(tile * 4 * a.R4 + ring) * kSlots * 16;
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const int cix = lnx + 64 * q, w = cix >> 4, k = cix & 15, row = k & 7;
-            uint32_t u[4];
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-              const int sl0 = w + 16 * jj, sl1 = sl0 + 8;  // positions 2 jj, 2 jj + 1 of the run
-              float v0 = stage[sl0 * 16 + (k ^ ((sl0 & 3) << 2))];
-              float v1 = stage[sl1 * 16 + (k ^ ((sl1 & 3) << 2))];
-              if constexpr (OUT == kOutFP16) {
-                v0 *= hscale;
-                v1 *= hscale;
-              }
-              u[jj] = pack16<OUT>(v0, v1);
-            }
-            if (row >= first && row < last)
-              *reinterpret_cast<uint4*>(blk + a16_index(16 * w + 8 * h, k)) = make_uint4(u[0], u[1], u[2], u[3]);
-          }
+        for (int h = 0; h < 2; ++h) {
+          write_half(reinterpret_cast<uint32_t*>(my), blk, h, lx, rx, row_in, rs);
           wave_sync();
-        } else {
+        }
+      } else {
+        RingSlots rs;
+        ring_slots(cs, lx, Za, Zb, rs);
+        const bool slot_major = a.a_layout == kSlotMajor, perm = a.a_layout == kRingPerm;
+        const int ss = slot_major ? a.R4 * 64 : 16;
+        float* dst = a.out + (slot_major ? (size_t)tile * kSlots * a.R4 * 64 + ring * 16
+                                         : ((size_t)tile * 4 * a.R4 + ring) * kSlots * 16);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          stage_slots(stage, h, rx, rs);
+          wave_sync();
           write_f32_half(stage, dst, h, lnx, perm, ss, first, last);
           wave_sync();
         }
@@ -212,7 +198,7 @@ __device__ __forceinline__ void polar_particle(const PolarArgs& a, int n, int pa
 }
 
 template <int MODE, int OUT>
-__global__ __launch_bounds__(kPolarThreads) void k_polar_fft(PolarArgs a) {
+__global__ __launch_bounds__(64 * kPolarMaxWaves, 4) void k_polar_fft(PolarArgs a) {
   extern __shared__ float smem[];
   const int i = xcd_item(), n = i / a.split;
   if (n >= a.n_part) return;
@@ -221,7 +207,7 @@ __global__ __launch_bounds__(kPolarThreads) void k_polar_fft(PolarArgs a) {
 
 // every piece of a batch writes the same operand type
 template <int OUT>
-__global__ __launch_bounds__(kPolarThreads) void k_polar_batch(PolarBatch b) {
+__global__ __launch_bounds__(64 * kPolarMaxWaves, 4) void k_polar_batch(PolarBatch b) {
   extern __shared__ float smem[];
   const int item = xcd_item();
   if (item >= b.start[b.n]) return;
@@ -240,16 +226,50 @@ size_t polar_lds_bytes(int Lp) {
          (size_t)kNphi * sizeof(CosSin) + kPolarWaves * sizeof(float);
 }
 
+constexpr size_t kLdsCu = 160 * 1024;
+static size_t polar_lds(int rows, int Lp, int waves) {
+  return (size_t)((rows * Lp + 3) & ~3) * sizeof(float) + (size_t)waves * 64 * 9 * sizeof(float2) + (size_t)kNphi * sizeof(CosSin) +
+         kPolarMaxWaves * sizeof(float);
+}
+
+// The LDS image of the pixels lo .. hi (either axis) that a particle's samples
+// read.  Row pitch: the taps of a wave lie on half a circle, and how they fall
+// on the 32 banks depends on the pitch modulo 32; over radii up to 15, 30, 35,
+// 46 and 62 the pitches 6, 10, 22 and 26 (mod 32) take 3.9, 4.6, 4.9, 5.0 and
+// 5.4 LDS cycles per read of 64 taps (2 without conflicts), within 3 % of the
+// best of any pitch; a multiple of 32 takes 7, an 80-pixel window's own side 5.4
+// (kernel, 76 px BF16: 9.41 ms at pitch 86, 9.60 at 80).  The window's own side where the wider rows would cost
+// the CU a workgroup.
+void polar_window(PolarArgs& a, int lo, int hi) {
+  a.pad = -lo;
+  a.rows = hi - lo + 1;
+  int P = a.rows;
+  while (P % 32 != 6 && P % 32 != 10 && P % 32 != 22 && P % 32 != 26) ++P;
+  const size_t wide = polar_lds(a.rows, P, kPolarWaves), own = polar_lds(a.rows, a.rows, kPolarWaves);
+  a.Lp = wide > kLdsCu || (wide > kLdsCu / 2 && own <= kLdsCu / 2) ? a.rows : P;
+}
+
+// Waves per workgroup: 8, two workgroups to a CU; where the image leaves room
+// for only one, as many as its LDS holds, up to 16 (128 px, 9 x 9 shifts, BF16,
+// 1200 particles: 1.79 ms with 16 waves, 1.99 with 8).
+int polar_waves(const PolarArgs& a) {
+  if (polar_lds(a.rows, a.Lp, kPolarWaves) <= kLdsCu / 2) return kPolarWaves;
+  int w = kPolarMaxWaves;
+  while (w > 1 && polar_lds(a.rows, a.Lp, w) > kLdsCu) --w;
+  return w;
+}
+
 hipError_t launch_polar_batch(const PolarBatch& b, hipStream_t st) {
   if (b.n <= 0 || b.start[b.n] <= 0) return hipSuccess;
-  int lp = 0;
   const int out = polar_out(b.piece[0]);
+  int waves = kPolarMaxWaves;
   for (int i = 0; i < b.n; ++i) {
-    lp = b.piece[i].Lp > lp ? b.piece[i].Lp : lp;
+    waves = std::min(waves, polar_waves(b.piece[i]));
     if (polar_out(b.piece[i]) != out) return hipErrorInvalidValue;
   }
-  const dim3 grid((b.start[b.n] + 7) / 8 * 8), block(kPolarThreads);
-  const size_t lds = polar_lds_bytes(lp);
+  size_t lds = 0;
+  for (int i = 0; i < b.n; ++i) lds = std::max(lds, polar_lds(b.piece[i].rows, b.piece[i].Lp, waves));
+  const dim3 grid((b.start[b.n] + 7) / 8 * 8), block(64 * waves);
   switch (out) {
     case kOutF32: hipLaunchKernelGGL(k_polar_batch<kOutF32>, grid, block, lds, st, b); break;
     case kOutBF16: hipLaunchKernelGGL(k_polar_batch<kOutBF16>, grid, block, lds, st, b); break;
@@ -261,8 +281,10 @@ hipError_t launch_polar_batch(const PolarBatch& b, hipStream_t st) {
 hipError_t launch_polar(int mode, const PolarArgs& a, hipStream_t st) {
   if (a.n_part <= 0) return hipSuccess;
   if (a.split < 1) return hipErrorInvalidValue;
-  const size_t lds = polar_lds_bytes(a.Lp);
-  dim3 grid(((unsigned)a.n_part * a.split + 7) / 8 * 8), block(kPolarThreads);
+  const int waves = polar_waves(a);
+  const size_t lds = polar_lds(a.rows, a.Lp, waves);
+  if (lds > kLdsCu) return hipErrorInvalidValue;
+  dim3 grid(((unsigned)a.n_part * a.split + 7) / 8 * 8), block(64 * waves);
   switch (mode) {
     case 0:
       switch (polar_out(a)) {

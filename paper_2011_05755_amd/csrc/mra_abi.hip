@@ -228,6 +228,7 @@ Refset& get_refset(mra_ctx* c, int32_t id) {
 
 struct Plan {
   int T, S1, S, M, pad, Lp, cx;
+  int lo, hi;       // lowest and highest pixel index the single-precision resamplers touch
   int pad_r, Lp_r;  // border and side for the kernels that sample with the FP64 stencil table
 };
 
@@ -246,7 +247,9 @@ Plan plan_for(const Refset& rs, int T) {
   const int hi = p.cx + T + rs.dmax + 1;
   p.pad_r = std::max(0, std::max(-lo, hi - (rs.g.L - 1)));
   p.Lp_r = rs.g.L + 2 * p.pad_r;
-  p.pad = std::max(0, std::max(-(lo - 1), hi + 1 - (rs.g.L - 1)));
+  p.lo = lo - 1;
+  p.hi = hi + 1;
+  p.pad = std::max(0, std::max(-p.lo, p.hi - (rs.g.L - 1)));
   p.Lp = rs.g.L + 2 * p.pad;
   if (polar_lds_bytes(p.Lp) > kLdsMax)
     throw Fail{MRA_E_INVAL, "box plus search range too large for the LDS-staged resampler"};
@@ -423,12 +426,13 @@ PolarArgs polar_args(mra_ctx* c, const Refset& rs, const Plan& p, const float* s
   pa.parts = src;
   pa.n_part = nc;
   pa.L = rs.g.L; pa.R = rs.R; pa.R4 = rs.R4; pa.T = p.T; pa.S1 = p.S1; pa.S = p.S;
-  pa.Lp = p.Lp; pa.pad = p.pad; pa.cx = p.cx;
+  pa.cx = p.cx;
+  polar_window(pa, p.lo, p.hi);
   pa.r_min = rs.g.r_min;
   pa.prec = rs.g.precision;
   pa.cs64 = c->cs64;
   // (a particle's rows touch up to S / 8 + 1 row groups)
-  pa.split = polar_split(nc, rs.R * (p.S / kRowTile + 1), c->n_cu);
+  pa.split = polar_split(nc, rs.R * (p.S / kRowTile + 1), c->n_cu, polar_waves(pa));
   return pa;
 }
 
@@ -739,7 +743,7 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
       b.ridx = ridx;
     }
     pb.piece[i] = polar_args(c, rs, pc.p, src, pc.nc);
-    pb.piece[i].split = polar_split((int)parts, rs.R * (pc.p.S / kRowTile + 1), c->n_cu);
+    pb.piece[i].split = polar_split((int)parts, rs.R * (pc.p.S / kRowTile + 1), c->n_cu, polar_waves(pb.piece[i]));
     pb.piece[i].a_layout = kRingPerm16;
     pb.piece[i].maxabs = b.maxabs;
     pb.piece[i].rowkey = b.rowkey;
@@ -1227,7 +1231,8 @@ int mra_debug_polar(mra_ctx* c, int32_t id, const float* parts, int64_t N, float
     PolarArgs pa{};
     pa.parts = parts; pa.n_part = (int)N;
     pa.L = rs.g.L; pa.R = rs.R; pa.R4 = rs.R4; pa.T = p.T; pa.S1 = p.S1; pa.S = p.S;
-    pa.Lp = p.Lp; pa.pad = p.pad; pa.cx = p.cx; pa.r_min = rs.g.r_min; pa.cs64 = c->cs64; pa.out = out;
+    pa.cx = p.cx; pa.r_min = rs.g.r_min; pa.cs64 = c->cs64; pa.out = out;
+    polar_window(pa, p.lo, p.hi);
     pa.split = 1;
     hip_check(c, launch_polar(1, pa, c->stream), "polar");
   });
@@ -1241,7 +1246,8 @@ int mra_debug_spectra(mra_ctx* c, int32_t id, const float* parts, int64_t N, flo
     PolarArgs pa{};
     pa.parts = parts; pa.n_part = (int)N;
     pa.L = rs.g.L; pa.R = rs.R; pa.R4 = rs.R4; pa.T = p.T; pa.S1 = p.S1; pa.S = p.S;
-    pa.Lp = p.Lp; pa.pad = p.pad; pa.cx = p.cx; pa.r_min = rs.g.r_min; pa.cs64 = c->cs64; pa.out = out;
+    pa.cx = p.cx; pa.r_min = rs.g.r_min; pa.cs64 = c->cs64; pa.out = out;
+    polar_window(pa, p.lo, p.hi);
     pa.split = 1;
     hip_check(c, launch_polar(2, pa, c->stream), "polar");
   });

@@ -108,7 +108,10 @@ struct PolarArgs {
   const float* parts;  // first particle of the chunk, [n][L][L]
   int n_part;
   int L, R, R4, T, S1, S;
-  int Lp, pad, cx;     // LDS image side (with zero border), border width, centre
+  // LDS image: rows x rows pixels of row pitch Lp; image pixel (y, x) at
+  // (y + pad, x + pad) (pad < 0: pixels outside are not staged), zeros outside
+  // the image; cx: the centre pixel
+  int Lp, rows, pad, cx;
   int r_min;           // radius of ring 0
   int a_layout;        // mode 0: ALayout of the operand
   int split;           // mode 0: workgroups per particle
@@ -242,7 +245,9 @@ struct RfaArgs {
 
 // ---- launchers (one .hip file each) ----
 hipError_t launch_polar(int mode, const PolarArgs& a, hipStream_t st);
-size_t polar_lds_bytes(int Lp);
+size_t polar_lds_bytes(int Lp);  // a resampler of 8 waves beside an Lp x Lp image
+void polar_window(PolarArgs& a, int lo, int hi);
+int polar_waves(const PolarArgs& a);
 hipError_t launch_corr(int prec, int variant, bool table, const CorrArgs& a, hipStream_t st);
 hipError_t launch_corr_runner_up(int prec, int variant, const CorrArgs& a, hipStream_t st);
 // 16-bit ring buckets (R4 <= 8, 9..10, 11..12, 13..16): the pieces of a batched launch share one
@@ -256,11 +261,11 @@ int fine_grid(int prec, int64_t n, int n_cu);
 enum FineMode { kFineArgmax = 0, kFineRunnerUp = 2, kFineTighten = 3 };
 hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, int grid, hipStream_t st);
 hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, int grid, hipStream_t st);
-// launches of few particles: workgroups per particle (of n_items 8-row ring
-// items) that fill n_cu CUs twice, and reference parts of a launch of `tiles`
+// launches of few particles: workgroups of `waves` waves per particle (of
+// n_items 8-row ring items) that fill n_cu CUs with 16 waves each, and reference parts of a launch of `tiles`
 // row tiles that give every CU a workgroup
-inline int polar_split(int n_part, int n_items, int n_cu) {
-  const int want = n_part > 0 ? 2 * n_cu / n_part : 1, most = (n_items + kPolarWaves - 1) / kPolarWaves;
+inline int polar_split(int n_part, int n_items, int n_cu, int waves) {
+  const int want = n_part > 0 ? 2 * kPolarWaves * n_cu / waves / n_part : 1, most = (n_items + waves - 1) / waves;
   return want < 1 ? 1 : (want > most ? most : want);
 }
 inline int corr_parts(int tiles, int n_ref_tiles, int n_cu) {

@@ -3,6 +3,8 @@
 // twiddles and a wave-level barrier.
 #pragma once
 
+#include <type_traits>
+
 #include "mra_common.h"
 #include "mra_fft.h"
 
@@ -58,6 +60,34 @@ __device__ __forceinline__ void stage_image(float* img, const float* src, int L,
       if (i < n) img[i] = v[b];
     }
   }
+}
+
+// The window of PolarArgs (rows x rows pixels at pitch Lp).  peak: the whole
+// image is read, also where the window is smaller, and the thread's largest
+// |pixel| returned.
+__device__ __forceinline__ float stage_window(float* img, const float* src, int L, int Lp, int rows, int pad, bool peak) {
+  constexpr int kB = 8;
+  const int lo = peak ? min(0, -pad) : -pad, side = (peak ? max(L, rows - pad) : rows - pad) - lo;
+  const int n = side * side;
+  float m = 0.f;
+  for (int i0 = threadIdx.x; i0 < n; i0 += kB * blockDim.x) {
+    float v[kB];
+    int at[kB];
+#pragma unroll
+    for (int b = 0; b < kB; ++b) {
+      const int i = i0 + b * blockDim.x;
+      const int q = i / side, yy = q + lo, xx = i - q * side + lo;
+      v[b] = (i < n && yy >= 0 && yy < L && xx >= 0 && xx < L) ? src[yy * L + xx] : 0.f;
+      const int wy = yy + pad, wx = xx + pad;
+      at[b] = i < n && wy >= 0 && wy < rows && wx >= 0 && wx < rows ? wy * Lp + wx : -1;
+    }
+#pragma unroll
+    for (int b = 0; b < kB; ++b) {
+      if (at[b] >= 0) img[at[b]] = v[b];
+      m = fmaxf(m, fabsf(v[b]));
+    }
+  }
+  return m;
 }
 
 // The same taps for a byte offset o4 of the top-left pixel and the row pitch
@@ -166,13 +196,115 @@ __device__ __forceinline__ void sample_ring(const float* img, const CosSin* cs, 
   wave_sync();  // before the FFT's transposes reuse the scratch
 }
 
+// One angle at the rows (shifts) J0 .. J1 - 1 of 8, consecutive in an image
+// row: the taps of one shift are the left taps of the next, so the run reads
+// J1 - J0 + 1 columns instead of twice their number.  at: byte address of the
+// first shift's top-left tap.  Row j's sample goes to tr[17 j] (written here:
+// handed back, the values are copied where the patterns' branches meet).
+template <int J0, int J1>
+__device__ __forceinline__ void sample_run(const char* at, int Lp4, float w00, float w10, float w01, float w11, float* tr) {
+  constexpr int n = J1 - J0;
+  const float* p0 = reinterpret_cast<const float*>(at);
+  const float* p1 = reinterpret_cast<const float*>(at + Lp4);
+  float t0[n + 1], t1[n + 1];
+#pragma unroll
+  for (int i = 0; i <= n; ++i) {
+    t0[i] = p0[i];
+    t1[i] = p1[i];
+  }
+#pragma unroll
+  for (int i = 0; i < n; ++i)
+    tr[17 * (J0 + i)] = fmaf(w11, t1[i + 1], fmaf(w01, t1[i], fmaf(w10, t0[i + 1], w00 * t0[i])));
+}
+// One angle at 8 consecutive rows: they wrap to the next image row of the
+// search grid after A rows and every S further ones.  at: byte address of the
+// angle's top-left tap at shift offset 0; o[k] the offset of run k's first shift.
+template <int A, int S>
+__device__ __forceinline__ void sample_pattern(const char* at, const int (&o)[4], int Lp4, float w00, float w10, float w01,
+                                               float w11, float* tr) {
+  constexpr int e0 = A < 8 ? A : 8, e1 = A + S < 8 ? A + S : 8, e2 = A + 2 * S < 8 ? A + 2 * S : 8;
+  static_assert(A + 3 * S >= 8, "at most four runs");
+  sample_run<0, e0>(at + o[0], Lp4, w00, w10, w01, w11, tr);
+  if constexpr (e0 < 8) sample_run<e0, e1>(at + o[1], Lp4, w00, w10, w01, w11, tr);
+  if constexpr (e1 < 8) sample_run<e1, e2>(at + o[2], Lp4, w00, w10, w01, w11, tr);
+  if constexpr (e2 < 8) sample_run<e2, 8>(at + o[3], Lp4, w00, w10, w01, w11, tr);
+}
+
+// As sample_ring for 8 consecutive rows s0 .. s0 + 7 of the search grid (s =
+// sy S1 + sx; rows outside it take shifts of its first or last grid row and
+// are not used), z[n1] = (p[16 n1 + 2 l], p[16 n1 + 2 l + 1]).  Lane r of group
+// l takes the angles of n1 = 2 r + hf, both of the pair, in half hf: a wave's
+// taps spread over the whole circle, which collides less in the banks than n1
+// = r and 8 + r, half a circle each (76 px BF16: 9.41 against 9.60 ms).  base4: byte
+// offset of the image centre.  What the resampler spends most LDS time on is
+// the taps: with shared columns they are 40 to 48 two-word reads per ring and
+// 8 rows, 64 without.  s0 and all but the lane indices are wave-uniform.
+__device__ __forceinline__ void sample_runs(const float* img, const CosSin* cs, float2* my, float rr, int l, int r, int s0,
+                                            int S1, int s1m, int T, int base4, int Lp4, float2 (&z)[16]) {
+  const int sy0 = (((s0 + 8 * S1) * s1m) >> 16) - 8, sx0 = s0 - sy0 * S1, a = S1 - sx0;
+  int o[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    int sy = sy0 + k;
+    sy = sy < 0 ? 0 : (sy < S1 ? sy : S1 - 1);
+    o[k] = base4 + (sy - T) * Lp4 + 4 * ((k == 0 ? sx0 : 0) - T);
+  }
+  // 8 S + A of sample_pattern; grids of more than 7 columns wrap as S = 7 does
+  const int pattern = S1 == 1 ? 0 : (a >= 8 ? 64 : 8 * (S1 < 7 ? S1 : 7) + a);
+  const CosSin* cp = cs + 2 * l;
+  float* tr = reinterpret_cast<float*>(my);  // [64 (l, row)][17]: row pitch 17 spreads the banks
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) {
+    wave_sync();  // the scratch's earlier readers are done
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const CosSin c = cp[16 * (2 * r + hf) + e];
+      const char* at = reinterpret_cast<const char*>(img) + polar_offset(rr, c, Lp4);
+      float w00, w10, w01, w11;
+      polar_weights(rr, c, w00, w10, w01, w11);
+      float* out = tr + l * 8 * 17 + 8 * e + r;
+      auto take = [&](auto a_c, auto s_c) {
+        sample_pattern<decltype(a_c)::value, decltype(s_c)::value>(at, o, Lp4, w00, w10, w01, w11, out);
+      };
+      switch (pattern) {  // wave-uniform
+        case 0: {  // one shift: the particle's own row is one of the 8, all take its sample
+          const float v = bilin4w(reinterpret_cast<const float*>(at + base4), 0, Lp4, w00, w10, w01, w11);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) out[17 * j] = v;
+          break;
+        }
+        case 25: take(std::integral_constant<int, 1>{}, std::integral_constant<int, 3>{}); break;
+        case 26: take(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{}); break;
+        case 27: take(std::integral_constant<int, 3>{}, std::integral_constant<int, 3>{}); break;
+        case 41: take(std::integral_constant<int, 1>{}, std::integral_constant<int, 5>{}); break;
+        case 42: take(std::integral_constant<int, 2>{}, std::integral_constant<int, 5>{}); break;
+        case 43: take(std::integral_constant<int, 3>{}, std::integral_constant<int, 5>{}); break;
+        case 44: take(std::integral_constant<int, 4>{}, std::integral_constant<int, 5>{}); break;
+        case 45: take(std::integral_constant<int, 5>{}, std::integral_constant<int, 5>{}); break;
+        case 57: take(std::integral_constant<int, 1>{}, std::integral_constant<int, 7>{}); break;
+        case 58: take(std::integral_constant<int, 2>{}, std::integral_constant<int, 7>{}); break;
+        case 59: take(std::integral_constant<int, 3>{}, std::integral_constant<int, 7>{}); break;
+        case 60: take(std::integral_constant<int, 4>{}, std::integral_constant<int, 7>{}); break;
+        case 61: take(std::integral_constant<int, 5>{}, std::integral_constant<int, 7>{}); break;
+        case 62: take(std::integral_constant<int, 6>{}, std::integral_constant<int, 7>{}); break;
+        case 63: take(std::integral_constant<int, 7>{}, std::integral_constant<int, 7>{}); break;
+        default: take(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
+      }
+    }
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const float* t = tr + (l * 8 + r) * 17 + q;
+      z[2 * q + hf] = make_float2(t[0], t[8]);
+    }
+  }
+  wave_sync();  // before the FFT's transposes reuse the scratch
+}
+
 // Ring FFT of the lane's samples: the two columns fwd_emit takes
 // (k1a, k1b = fwd_cols(l)).
-__device__ __forceinline__ void fft_ring(const CosSin* cs, float2* my, int l, int r, int k1a, int k1b,
-                                         const float (&v)[32], float2 (&Za)[8], float2 (&Zb)[8]) {
-  float2 z[16];
-#pragma unroll
-  for (int n1 = 0; n1 < 16; ++n1) z[n1] = make_float2(v[2 * n1], v[2 * n1 + 1]);
+__device__ __forceinline__ void fft_ring(const CosSin* cs, float2* my, int l, int r, int k1a, int k1b, float2 (&z)[16],
+                                         float2 (&Za)[8], float2 (&Zb)[8]) {
   dft16<-1>(z);
 #pragma unroll
   for (int k1 = 1; k1 < 16; ++k1) z[k1] = cmul(z[k1], twid(cs, 2 * ((l * k1) & 127)));
@@ -223,6 +355,85 @@ __device__ __forceinline__ void ring_slots(const CosSin* cs, int l, const float2
                o.hi_b[k] = first_low ? re + im : b0;
              }
            });
+}
+
+// Operand element type written in mode 0: FP32 (kRingPerm or kSlotMajor,
+// chosen at run time), or BF16 / FP16 in kRingPerm16.
+enum PolarOut { kOutF32 = 0, kOutBF16 = 1, kOutFP16 = 2 };
+
+// Two values in the contraction's 16-bit type, each rounded to nearest
+// (even) once, packed with x in the low half.
+template <int OUT>
+__device__ __forceinline__ uint32_t pack16(float x, float y) {
+  typedef float f32x2v __attribute__((ext_vector_type(2)));
+  const f32x2v v = {x, y};
+  if constexpr (OUT == kOutBF16) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+  } else {
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+  }
+}
+
+// The lane's spectrum values in the contraction's 16-bit type, (a - b) in the
+// low half and (a + b) in the high half of a dword per slot; each value
+// rounded once (FP16 scaled by the particle's power of two).
+struct RingHalves {
+  int lo_s[8], hi_s[8];
+  uint32_t lo[8], hi[8];
+};
+template <int OUT>
+__device__ __forceinline__ void ring_halves(const CosSin* cs, int l, const float2 (&Za)[8], const float2 (&Zb)[8],
+                                            float scale, RingHalves& o) {
+  int e = 0, s0 = 0;
+  uint32_t v0 = 0;
+  fwd_emit(l, Za, Zb, [&](int f) { return twid(cs, f & 255); },
+           [&](int slot, float re, float im) {
+             const int k = e >> 1;
+             float a = re - im, b = re + im;
+             if constexpr (OUT == kOutFP16) {
+               a *= scale;
+               b *= scale;
+             }
+             const uint32_t v = pack16<OUT>(a, b);
+             if ((e++ & 1) == 0) {
+               s0 = slot; v0 = v;
+             } else {
+               const bool first_low = s0 < slot;
+               o.lo_s[k] = first_low ? s0 : slot;
+               o.hi_s[k] = first_low ? slot : s0;
+               o.lo[k] = first_low ? v0 : v;
+               o.hi[k] = first_low ? v : v0;
+             }
+           });
+}
+
+// 16-bit operand (kRingPerm16): the low (h = 0) or high slots of one ring and 8
+// rows, staged as [64 slots][8 rows] dwords (lanes write and read consecutive
+// dwords).  The slots 64 h + w + 8 i are the run G = 2 w + h; lane (w, row)
+// writes the two elements k = row and 8 + row of its 8 positions as one
+// 16-byte store each, the 8 rows of a run together whole 128-byte lines.
+__device__ __forceinline__ void write_half(uint32_t* stage, uint16_t* blk, int h, int w, int row, bool row_in,
+                                           const RingHalves& o) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) stage[(h ? o.hi_s[k] - 64 : o.lo_s[k]) * 8 + row] = h ? o.hi[k] : o.lo[k];
+  wave_sync();
+  uint32_t x[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) x[i] = stage[(w + 8 * i) * 8 + row];
+  uint32_t u[2][4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    u[0][d] = __builtin_amdgcn_perm(x[2 * d + 1], x[2 * d], 0x05040100u);
+    u[1][d] = __builtin_amdgcn_perm(x[2 * d + 1], x[2 * d], 0x07060302u);
+  }
+  if (row_in) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+      *reinterpret_cast<uint4*>(blk + a16_index(16 * w + 8 * h, 8 * p + row)) =
+          make_uint4(u[p][0], u[p][1], u[p][2], u[p][3]);
+  }
 }
 
 // Stages the low (h = 0) or high (h = 1) slots as [64 slots][16] floats
