@@ -25,13 +25,17 @@
 // particle's best CC at SNR 0.05.  A particle whose pixels do not scale into
 // FP16 (not finite, or within 2^9 of overflow) gets infinite bounds.
 //
-// One 8-wave workgroup holds the operand of NT row tiles (16 rows; 8 where
-// more than 48 rings leave no registers for two) in registers, wave w the
-// slots w + 8 i, and streams the reference operand once for all of them: the
-// stream from L2 is what bounds the kernel (160 KiB per reference tile at 35
-// rings), so two row tiles per read halve it.  The waves' partial bounds meet
-// in LDS every kBoundTiles reference tiles, in two alternating buffers: one
-// barrier per kBoundTiles.
+// A 4-wave workgroup holds half the slots (0 .. 63 or 64 .. 127) of the
+// operand of NT row tiles (16 rows; 8 where more than 48 rings leave no registers
+// for two) in registers and streams the reference operand once for all of
+// them: two row tiles per read halve the stream from L2 (160 KiB per reference
+// tile at 35 rings).  Two workgroups share a CU and run independently, so one
+// multiplies while the other waits for its operand from HBM, meets its
+// waves or writes; one workgroup of 8 waves over all slots left the CU waiting
+// about a quarter of the time (@@).  The waves' partial
+// bounds meet in LDS every kBoundTiles reference tiles, in two alternating
+// buffers: one barrier per kBoundTiles.  The halves' bounds are added, and
+// each row's largest found, by k_bound_sum.
 #pragma once
 
 #include "corr_impl.h"
@@ -88,18 +92,38 @@ struct BoundA {
   static constexpr int NF = Con::NF, TD = Con::TD, SPQ = TD ? 4 / TD : 1;
   u32x4 f[Con::SPW][NF];
   u32x4 q[TD ? Con::SPW / SPQ : 1];
-  __device__ __forceinline__ void load(const Con& con, const CorrArgs& a, int tile, int w, int ln) {
-    con.read_a(a, tile, a_block_pos(ln & 15), w, ln, [&](int i, int d, uint32_t x) {
-      if (d < 4 * NF) f[i][d / 4][d % 4] = x;
-      else q[i / SPQ][(i % SPQ) * TD + d - 4 * NF] = x;
-    });
+  // the runs of waves w and w + 4 of 8 in half h
+  __device__ __forceinline__ void load(const Con& con, const CorrArgs& a, int tile, int w, int h, int ln) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      u32x4 u[8 * Con::NS];
+      con.load_run(a, tile, a_block_pos(ln & 15), w + 4 * r, ln, h, u);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int i = 8 * r + j;
+#pragma unroll
+        for (int d = 0; d < 4 * NF + TD; ++d) {
+          const uint32_t x = Con::dword(u, j, d);
+          if (d < 4 * NF) f[i][d / 4][d % 4] = x;
+          else q[i / SPQ][(i % SPQ) * TD + d - 4 * NF] = x;
+        }
+      }
+    }
   }
 };
-// One slot's reference operand; i is the slot's index in the wave.
+// One slot's reference operand; i is the slot's index in the wave.  An object
+// takes slots of one place i % SPQ only, so the zeros beside it are written
+// once (they are hidden from the compiler, which would write them again
+// with every load).
 template <class Con>
 struct BoundB {
   u32x4 f[Con::NF];
   u32x4 q;
+  __device__ __forceinline__ void clear() {
+    uint32_t z = 0;
+    asm("" : "+v"(z));
+    q = u32x4{z, z, z, z};
+  }
   __device__ __forceinline__ void load(const Con& con, const CorrArgs& a, int kt, int slot, int i, int ln) {
     typename Con::Frag b;
     con.load_b(a, kt, slot, ln, b);
@@ -108,7 +132,7 @@ struct BoundB {
     if constexpr (Con::TD > 0) {
       constexpr int SPQ = 4 / Con::TD;
 #pragma unroll
-      for (int d = 0; d < 4; ++d) q[d] = d / Con::TD == i % SPQ ? b.t[d % Con::TD] : 0u;
+      for (int d = 0; d < Con::TD; ++d) q[i % SPQ * Con::TD + d] = b.t[d];
     }
   }
 };
@@ -131,19 +155,19 @@ __device__ __forceinline__ void bound_products(const BoundA<Con> (&x)[NT], const
       acc[t] = Op16<PREC>::mfma(__builtin_bit_cast(V, x[t].q[i / (4 / Con::TD)]), __builtin_bit_cast(V, y.q), acc[t]);
 }
 
+constexpr int kBoundWaves = 4, kBoundThreads = 64 * kBoundWaves;
 template <int NT>
 struct BoundSmem {
-  float2* pp;   // [2][kBoundTiles][8 waves][NT][64] partial bounds of both mirrors
-  float* norm;  // [8 waves][NT * 8] partial squared row norms
-  unsigned long long* key;  // [NT * 8] each row's largest bound
+  // partial bounds of both mirrors, [2][kBoundTiles][waves][NT][64]; 16 more
+  // per tile spread the banks of the sums
+  static constexpr int kTile = kBoundWaves * NT * 64 + 16;
+  float2* pp;
+  float* norm;  // [waves][NT * 8] partial squared row norms
   __device__ __forceinline__ BoundSmem(float* smem) {
     pp = reinterpret_cast<float2*>(smem);
-    norm = smem + 2 * kBoundTiles * 8 * NT * 64 * 2;
-    key = reinterpret_cast<unsigned long long*>(norm + 8 * NT * 8);
+    norm = smem + 2 * kBoundTiles * kTile * 2;
   }
-  static constexpr size_t bytes() {
-    return (2 * kBoundTiles * 8 * NT * 64 * 2 + 8 * NT * 8 + 2 * NT * 8) * sizeof(float);
-  }
+  static constexpr size_t bytes() { return (2 * kBoundTiles * kTile * 2 + kBoundWaves * NT * 8) * sizeof(float); }
 };
 
 // What rounding both operands to FP16 can add to a pair's CC (see the file
@@ -155,23 +179,26 @@ __device__ __forceinline__ float fp16_error(float sa, float nb, int R) {
   return 1.41421363f * (1.f + 1.f / 64.f) * (Da * nb + Na * Db + Da * Db);
 }
 
-// Work item: row block item % blocks (NT tiles) against the reference tiles
-// of part item / blocks (a.kt_per_wg each).
-template <int PREC, int MAXR, int NT, bool ERR>
-__device__ __forceinline__ void bound_item(const CorrArgs& a, int item, float* smem) {
+// Row blocks of a launch, padded so that every XCD gets both halves.
+__device__ __forceinline__ int bound_blocks(const CorrArgs& a, int nt) {
+  return ((a.n_row_tiles + nt - 1) / nt + 7) & ~7;
+}
+
+// Half H of the slots of row block blk (NT tiles) against the reference tiles
+// of part `part` (a.kt_per_wg each); H = 0: with 16 slots of magnitudes.
+template <int PREC, int MAXR, int NT, bool ERR, int H>
+__device__ __forceinline__ void bound_item(const CorrArgs& a, int blk, int part, float* smem) {
   const BoundSmem<NT> sm(smem);
   const int tid = threadIdx.x, ln = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int blocks = (a.n_row_tiles + NT - 1) / NT;
-  const int blk = item % blocks;
-  const int kt0 = item / blocks * a.kt_per_wg, kt1 = min(kt0 + a.kt_per_wg, a.n_ref_tiles);
+  const int kt0 = part * a.kt_per_wg, kt1 = min(kt0 + a.kt_per_wg, a.n_ref_tiles);
   typedef Half16Contract<PREC, 8, MAXR, false> Con;
   constexpr int SPW = Con::SPW;
   Con con;
   BoundA<Con> A[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)  // (a tile past the last repeats it; its bounds are not stored)
-    A[t].load(con, a, min(blk * NT + t, a.n_row_tiles - 1), w, ln);
+    A[t].load(con, a, min(blk * NT + t, a.n_row_tiles - 1), w, H, ln);
   if constexpr (ERR) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -190,22 +217,26 @@ __device__ __forceinline__ void bound_item(const CorrArgs& a, int item, float* s
       if (ln < 16 && !(ln & 1)) sm.norm[w * NT * 8 + t * 8 + (ln >> 1)] = s;
     }
   }
-  if (tid < NT * 8) sm.key[tid] = 0ull;
   const int P = lane_pair(ln);
   const bool q = ln & 1;
+  // slot i of the wave: i = 8 r + j is slot j of the run of wave w + 4 r
+  auto slot = [&](int i) { return 64 * H + w + 4 * (i >> 3) + 8 * (i & 7); };
   // the reference operand is kept D slots ahead, across reference tiles
   // (one slot ahead, a slot takes a whole L2 latency); the sums of a slot are
   // taken while the next one's products run
   constexpr int D = Con::TD == 2 ? 2 : 4;
   BoundB<Con> b[D];
 #pragma unroll
-  for (int i = 0; i < D; ++i) b[i].load(con, a, kt0, w + 8 * i, i, ln);
+  for (int i = 0; i < D; ++i) {
+    b[i].clear();
+    b[i].load(con, a, kt0, slot(i), i, ln);
+  }
   auto take = [&](BoundSum& s, const f32x4& acc, int i) {
-    if (i < 2) s.exact(acc, q, w == 0 && i == 0);
+    const int j = i & 7;
+    if (H == 0 && j < 2) s.exact(acc, q, w == 0 && i == 0);
     else s.energy(acc);
-    if (i == 3) s.close_group(q, 2);
-    if (i == 7) s.close_group(q, 4);
-    if (i == 15) s.close_group(q, 8);
+    if (H == 0 && j == 3) s.close_group(q, 2);
+    if (j == 7) s.close_group(q, H == 0 ? 4 : 8);
   };
   int buf = 0;
   for (int kb = kt0; kb < kt1; kb += kBoundTiles, buf ^= 1) {
@@ -222,7 +253,7 @@ __device__ __forceinline__ void bound_item(const CorrArgs& a, int item, float* s
       for (int i = 0; i < SPW; ++i) {
         f32x4 cur[NT];
         bound_products<PREC>(A, b[i % D], i, cur);
-        b[i % D].load(con, a, i + D < SPW ? kt : ktn, w + 8 * ((i + D) % SPW), i + D, ln);
+        b[i % D].load(con, a, i + D < SPW ? kt : ktn, slot((i + D) % SPW), i + D, ln);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           if (i > 0) take(bs[t], acc[t], i - 1);
@@ -237,74 +268,70 @@ __device__ __forceinline__ void bound_item(const CorrArgs& a, int item, float* s
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const float m0 = bs[t].b0 + bs[t].c, m1 = bs[t].b1 + bs[t].c;
-        sm.pp[(((buf * kBoundTiles + u) * 8 + w) * NT + t) * 64 + P] = q ? make_float2(m1, m0) : make_float2(m0, m1);
+        sm.pp[(buf * kBoundTiles + u) * sm.kTile + (w * NT + t) * 64 + P] =
+            q ? make_float2(m1, m0) : make_float2(m0, m1);
       }
     }
     __syncthreads();
-    for (int i = tid; i < nu * NT * 64; i += 512) {
-      const int pr = i & 63, t = (i >> 6) % NT, u = i / (64 * NT);
+    // 4 tiles' references side by side: whole lines of a row's bounds
+    for (int i = tid; i < NT * 64 * kBoundTiles; i += kBoundThreads) {
+      const int u = (i >> 3) % kBoundTiles, lr = i / (8 * kBoundTiles), t = lr >> 3, pr = (lr & 7) * 8 + (i & 7);
+      const int row = blk * NT * kRowTile + lr;
+      if (u >= nu || row >= a.rows) continue;
       float B0 = 0.f, B1 = 0.f;
 #pragma unroll
-      for (int w2 = 0; w2 < 8; ++w2) {
-        const float2 v = sm.pp[(((buf * kBoundTiles + u) * 8 + w2) * NT + t) * 64 + pr];
+      for (int w2 = 0; w2 < kBoundWaves; ++w2) {
+        const float2 v = sm.pp[(buf * kBoundTiles + u) * sm.kTile + (w2 * NT + t) * 64 + pr];
         B0 += v.x;
         B1 += v.y;
       }
-      const int row = (blk * NT + t) * kRowTile + (pr >> 3), k = (kb + u) * kRefTile + (pr & 7);
-      if (row >= a.rows) continue;
-      // (1e-16: sums of squares below 1e-38 are lost)
-      float bound = (a.M == 2 ? fmaxf(B0, B1) : B0) * (1.f + 1.f / 4096.f) + 1e-16f;
-      if constexpr (ERR) {
+      (H ? a.ub_hi : a.ub)[(size_t)row * a.ldu + (kb + u) * kRefTile + (i & 7)] = a.M == 2 ? fmaxf(B0, B1) : B0;
+    }
+    if constexpr (ERR) {
+      const int row = blk * NT * kRowTile + tid;
+      if (kb == 0 && tid < NT * kRowTile && row < a.rows) {
         float s = 0.f;
 #pragma unroll
-        for (int w2 = 0; w2 < 8; ++w2) s += sm.norm[w2 * NT * 8 + t * 8 + (pr >> 3)];
-        s = sqrtf(s);
-        const float mx = a.maxabs[row / a.S];
-        bound += fp16_error(s, k < a.K ? a.bnorm[k] * a.b_scale : 0.f, a.R);
-        bound = fp16_value(bound, mx, a.b_scale) + 1e-37f;  // (1e-37: what subnormals lose)
-        if (k == 0) a.rownorm[row] = s;
-        if (!(mx * 512.f < INFINITY)) bound = INFINITY;
+        for (int w2 = 0; w2 < kBoundWaves; ++w2) s += sm.norm[w2 * NT * 8 + tid];
+        a.rownorm[H * a.rows + row] = s;
       }
-      a.ub[(size_t)row * a.ldu + k] = k < a.K ? bound : -INFINITY;
-      // the row's largest (NaN counts as infinite) over the tile's 8 references
-      unsigned long long key = k < a.K ? cand_key(bound == bound ? bound : INFINITY, k) : 0ull;
-#pragma unroll
-      for (int o = 4; o > 0; o >>= 1) {
-        const unsigned long long other = __shfl_xor(key, o);
-        key = other > key ? other : key;
-      }
-      if ((pr & 7) == 0) atomicMax(&sm.key[t * 8 + (pr >> 3)], key);
     }
-  }
-  __syncthreads();
-  if (tid < NT * 8) {
-    const int row = blk * NT * kRowTile + tid;
-    if (row < a.rows) atomicMax(&a.rowkey[row], sm.key[tid]);
   }
 }
 
+// Work item of a piece: half (r / 8) % 2 of row block (r / 16) 8 + r % 8, r the
+// item in its reference part.
 template <int PREC, int MAXR, int NT, bool ERR>
-__global__ __launch_bounds__(512) void k_bound(CorrArgs a) {
+__device__ __forceinline__ void bound_dispatch_item(const CorrArgs& a, int item, float* smem) {
+  const int per_part = 2 * bound_blocks(a, NT);
+  const int part = item / per_part, r = item - part * per_part, blk = (r >> 4) * 8 + (r & 7);
+  if (blk * NT >= a.n_row_tiles) return;
+  if (r & 8) bound_item<PREC, MAXR, NT, ERR, 1>(a, blk, part, smem);
+  else bound_item<PREC, MAXR, NT, ERR, 0>(a, blk, part, smem);
+}
+
+template <int PREC, int MAXR, int NT, bool ERR>
+__global__ __launch_bounds__(kBoundThreads, 2) void k_bound(CorrArgs a) {
   extern __shared__ float smem[];
-  bound_item<PREC, MAXR, NT, ERR>(a, blockIdx.x, smem);
+  bound_dispatch_item<PREC, MAXR, NT, ERR>(a, blockIdx.x, smem);
 }
 
 // Batched form over the items of several stacks (start[p]: piece p's first).
 template <int PREC, int MAXR, int NT, bool ERR>
-__global__ __launch_bounds__(512) void k_bound_batch(CorrBatch b) {
+__global__ __launch_bounds__(kBoundThreads, 2) void k_bound_batch(CorrBatch b) {
   extern __shared__ float smem[];
   const int item = blockIdx.x;
   if (item >= b.start[b.n]) return;
   int p = 0;
   while (p + 1 < b.n && b.start[p + 1] <= item) ++p;
-  bound_item<PREC, MAXR, NT, ERR>(b.piece[p], item - b.start[p], smem);
+  bound_dispatch_item<PREC, MAXR, NT, ERR>(b.piece[p], item - b.start[p], smem);
 }
 
 template <int PREC, int MAXR, int NT, bool ERR>
 inline void bound_go(const CorrArgs* a, const CorrBatch* b, int grid, hipStream_t st) {
   const size_t lds = BoundSmem<NT>::bytes();
-  if (b) hipLaunchKernelGGL((k_bound_batch<PREC, MAXR, NT, ERR>), dim3(grid), dim3(512), lds, st, *b);
-  else hipLaunchKernelGGL((k_bound<PREC, MAXR, NT, ERR>), dim3(grid), dim3(512), lds, st, *a);
+  if (b) hipLaunchKernelGGL((k_bound_batch<PREC, MAXR, NT, ERR>), dim3(grid), dim3(kBoundThreads), lds, st, *b);
+  else hipLaunchKernelGGL((k_bound<PREC, MAXR, NT, ERR>), dim3(grid), dim3(kBoundThreads), lds, st, *a);
 }
 
 // Row tiles per workgroup of the ring count R4.

@@ -286,8 +286,9 @@ bool row_results(const Refset& rs) { return rs.g.precision != kFP32 && rs.g.resc
 struct ChunkBufs {
   float* A = nullptr;        // particle operand, ceil(nc S / 8) row tiles
   float* ub = nullptr;       // pruned: [nc S][ub_pitch] bounds
+  float* ub_hi = nullptr;    // pruned: a half of them before they are added
   unsigned long long* rowkey = nullptr;  // [nc S] largest bound (pruned) or best CC per row
-  float* rownorm = nullptr;  // pruned FP32: [nc S] norm of the row's operand
+  float* rownorm = nullptr;  // pruned FP32: [2][nc S] norm of the row's operand
   float* scratch = nullptr;  // pruned FP32: one operand tile per evaluation workgroup
   int grid = 0;              // evaluation workgroups
   float* rcc = nullptr;      // [nc S] best CC per row
@@ -306,8 +307,9 @@ ChunkBufs layout_chunk(const Refset& rs, const Plan& p, int64_t nc, bool pruned,
   if (pruned) {
     b.grid = fine_grid(rs.g.precision, nc, n_cu);
     b.ub = (float*)take("ub", rows * ub_pitch(rs) * sizeof(float));
+    b.ub_hi = (float*)take("ub_hi", rows * ub_pitch(rs) * sizeof(float));
     if (rs.g.precision == kFP32) {
-      b.rownorm = (float*)take("rownorm", rows * sizeof(float));
+      b.rownorm = (float*)take("rownorm", 2 * rows * sizeof(float));
       b.scratch = (float*)take("scratch", b.grid * scratch_tile_bytes(rs));
     }
   }
@@ -346,7 +348,7 @@ uint64_t ws_other(mra_ctx* c) {
   uint64_t total = 0;
   for (const auto& kv : c->ws) {
     bool chunk_buf = false;
-    for (const char* n : {"A", "ub", "rowkey", "rownorm", "scratch", "row_cc", "row_idx", "maxabs", "win"}) chunk_buf |= kv.first == n;
+    for (const char* n : {"A", "ub", "ub_hi", "rowkey", "rownorm", "scratch", "row_cc", "row_idx", "maxabs", "win"}) chunk_buf |= kv.first == n;
     if (!chunk_buf) total += kv.second.bytes;
   }
   return total;
@@ -354,7 +356,7 @@ uint64_t ws_other(mra_ctx* c) {
 
 // bytes of operand and bounds per particle
 uint64_t particle_bytes(const Refset& rs, const Plan& p, bool pruned) {
-  const uint64_t row = tile_bytes_of(rs, pruned) / kRowTile + (pruned ? ub_pitch(rs) * sizeof(float) : 0);
+  const uint64_t row = tile_bytes_of(rs, pruned) / kRowTile + (pruned ? 2 * ub_pitch(rs) * sizeof(float) : 0);
   return (uint64_t)p.S * row;
 }
 
@@ -453,6 +455,7 @@ CorrArgs corr_args(mra_ctx* c, const Refset& rs, const Plan& p, int nc, int layo
   ca.row_cc = b.rcc;
   ca.row_idx = b.ridx;
   ca.ub = b.ub;
+  ca.ub_hi = b.ub_hi;
   ca.rowkey = b.rowkey;
   ca.rownorm = b.rownorm;
   ca.ldu = ub_pitch(rs);
@@ -528,7 +531,6 @@ void run_chunk(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, 
   PolarArgs pa = polar_args(c, rs, p, src, nc);
   pa.a_layout = kRingPerm16;
   pa.maxabs = b.maxabs;
-  pa.rowkey = b.rowkey;
   pa.out = b.A;
   timed(c, "polar", [&] { hip_check(c, launch_polar(0, pa, st), "polar"); });
   CorrArgs ca = corr_args(c, rs, p, nc, kRingPerm16, b);
@@ -711,8 +713,9 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
   const int grid = fine_grid(prec, (int64_t)parts, c->n_cu);
   char* A = (char*)ws_get(c, "A", a_bytes);
   float* ub = (float*)ws_get(c, "ub", ub_floats * sizeof(float));
+  float* ub_hi = (float*)ws_get(c, "ub_hi", ub_floats * sizeof(float));
   unsigned long long* rowkey = (unsigned long long*)ws_get(c, "rowkey", (rows + 1) * sizeof(unsigned long long));
-  float* rownorm = prec == kFP32 ? (float*)ws_get(c, "rownorm", rows * sizeof(float)) : nullptr;
+  float* rownorm = prec == kFP32 ? (float*)ws_get(c, "rownorm", 2 * rows * sizeof(float)) : nullptr;
   float* scratch = prec == kFP32 ? (float*)ws_get(c, "scratch", grid * tile) : nullptr;
   float* rcc = prec != kFP32 ? (float*)ws_get(c, "row_cc", rows * sizeof(float)) : nullptr;
   int* ridx = prec != kFP32 ? (int*)ws_get(c, "row_idx", rows * sizeof(int)) : nullptr;
@@ -733,6 +736,7 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     ChunkBufs b;
     b.A = (float*)A;
     b.ub = ub;
+    b.ub_hi = ub_hi;
     b.rowkey = rowkey;
     b.rownorm = rownorm;
     b.scratch = scratch;
@@ -746,7 +750,6 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     pb.piece[i].split = polar_split((int)parts, rs.R * (pc.p.S / kRowTile + 1), c->n_cu, polar_waves(pb.piece[i]));
     pb.piece[i].a_layout = kRingPerm16;
     pb.piece[i].maxabs = b.maxabs;
-    pb.piece[i].rowkey = b.rowkey;
     pb.piece[i].out = b.A;
     cb.piece[i] = corr_args(c, rs, pc.p, pc.nc, kRingPerm16, b);
     cb.start[i] = items;
@@ -759,8 +762,9 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     fb.start[i] = rb.start[i] = part;
     A += (r + kRowTile - 1) / kRowTile * tile_bytes_of(rs, true);
     ub += r * ub_pitch(rs);
+    ub_hi += r * ub_pitch(rs);
     rowkey += r;
-    if (rownorm) rownorm += r;
+    if (rownorm) rownorm += 2 * r;
     if (rcc) {
       rcc += r;
       ridx += r;

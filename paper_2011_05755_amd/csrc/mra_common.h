@@ -141,10 +141,13 @@ struct CorrArgs {
   float* table;          // debug: [n][K][M][S][256], else null
   const int* excl;       // per particle of the chunk: flat index left out of the arg-max, or null
   float* ub;             // [rows][ldu] upper bound of each pair's CC (-inf past K)
+  float* ub_hi;          // [rows][ldu] scratch: the bounds' part of slots 64 .. 127
   int ldu;               // 8 * n_ref_tiles
   unsigned long long* rowkey;  // [rows] each row's largest bound and its reference, or (every pair evaluated) its
-                               // best CC and flat index, in cand_key order; zeroed by the resampler
-  float* rownorm;        // FP32 alignment: [rows] norm of the row's operand (FP16, scaled; bound error)
+                               // best CC and flat index, in cand_key order; every pair evaluated: zeroed by
+                               // the resampler
+  float* rownorm;        // FP32 alignment: [2][rows], first the norm of the row's operand (FP16, scaled; bound
+                         // error); scratch of the bounds: the halves' squares
   int kt_per_wg;         // reference tiles per workgroup (bounds, and the correlation of every pair)
 };
 
