@@ -30,9 +30,15 @@
 // for two) in registers and streams the reference operand once for all of
 // them: two row tiles per read halve the stream from L2 (160 KiB per reference
 // tile at 35 rings).  Two workgroups share a CU and run independently, so one
-// multiplies while the other waits for its operand from HBM, meets its
-// waves or writes; one workgroup of 8 waves over all slots left the CU waiting
-// about a quarter of the time (@@).  The waves' partial
+// multiplies while the other waits for its operand from HBM, meets its waves or
+// writes.  20 000 x 49 rows, 100 references, 35 rings, BF16: 8.8 ms with the sum
+// of the halves, 9.1 with one 8-wave workgroup over all slots; 3001 x 49 rows,
+// 50 references, 36 rings, FP16: 0.86 and 0.97 ms.  What bounds it: matrix and
+// vector instructions, 39 and 43 % of the time and hardly at once with two
+// waves per SIMD; without the reference loads it runs 16 % shorter, with
+// nothing but loads 26 %.  (No faster: 8 slots ahead instead of 4; the products
+// of a slot in one run, also at raised priority; 32 rows per workgroup, which
+// halves what L2 delivers.)  The waves' partial
 // bounds meet in LDS every kBoundTiles reference tiles, in two alternating
 // buffers: one barrier per kBoundTiles.  The halves' bounds are added, and
 // each row's largest found, by k_bound_sum.

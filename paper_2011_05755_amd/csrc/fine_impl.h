@@ -30,8 +30,17 @@
 // never goes through HBM.  Before that (kFineTighten) the FP16 operand's own CC
 // of the live pairs replaces their bounds: it is within fp16_error of the FP32
 // one, which leaves 3 to 4 rows per particle instead of 10 to 13, one group of
-// eight instead of two.
+// eight instead of two (76 px, 100 references, tightening and evaluation against
+// evaluation alone: 64 particles 254 against 420 us, 512: 517 against 1325).
+//
+// A particle that has not come to its end after some steps is left to the
+// whole chip (k_fine_over): the pairs of its row tiles and references are
+// units of work for every workgroup, the bests meet in memory, and k_fine_done
+// writes the result, or after tightening the rows' largest bounds.  The
+// arg-max is over the same pairs and more, so the result is the same.
 #pragma once
+
+#include <climits>
 
 #include "bound_impl.h"
 #include "polar_impl.h"
@@ -276,8 +285,167 @@ __device__ __forceinline__ void fine_operand(const FineArgs& a, int n, const int
   }
 }
 
+// Where a particle is, for the functions below.
+struct FineAt {
+  int n, row0, S;
+  int ex0;             // runner-up: the excluded flat index
+  const float* ub;     // the particle's bounds
+};
+
+// Evaluates the group's pairs from i0 on, up to 16 a step: the cnt entries of
+// the list (listed), or rows 0 .. cnt - 1 with their best reference.  At most
+// `steps` steps (counted down); false if entries are left.
 template <int PREC, int NW, class Contract, int MODE>
-__device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int n, float* smem) {
+__device__ __forceinline__ bool fine_steps(const FineArgs& a, const CorrArgs& c, const FineSmem& sm, const FineAt& at,
+                                           int cnt, bool listed, int& i0, int& steps) {
+  const int tid = threadIdx.x, ln = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = at.n, row0 = at.row0, S = at.S, ex0 = at.ex0;
+  float* ub = const_cast<float*>(at.ub);
+  float2* stc = reinterpret_cast<float2*>(sm.work);
+  FineStep& st = sm.step[w];
+  auto threshold = [&]() { return part_thr(key_value(*sm.pbest), a.margin); };
+#pragma unroll 1
+  while (i0 < cnt) {
+    if (steps <= 0) return false;
+    // the next step: entries i0 .. i0 + 15 that are still live, up to the
+    // first whose reference would be the ninth (lane i < 16: entry i0 + i;
+    // every wave does the same)
+    bool on = ln < kFinePairs && i0 + ln < cnt;
+    int j = 0, k = 0;
+    if (on) {
+      if (listed) {
+        const uint32_t e = sm.live[i0 + ln];
+        k = (int)(e >> 3);
+        j = (int)(e & 7u);
+        // (a long list: the threshold may have passed it since)
+        if (i0 > 0) on = !(ub[(size_t)sm.shift[j] * c.ldu + k] < threshold());
+      } else {
+        j = ln;
+        k = sm.rowarg[sm.shift[ln]];
+      }
+    }
+    uint32_t m = (uint32_t)__ballot(on);
+    int first = ln;  // the first entry with this one's reference
+#pragma unroll
+    for (int e = kFinePairs - 1; e >= 0; --e)
+      if (((m >> e) & 1) && __builtin_amdgcn_readlane(k, e) == k && e < first) first = e;
+    const uint32_t fm = (uint32_t)__ballot(on && first == ln);
+    const int d = __popc(fm & ((1u << (first & 31)) - 1u));
+    const uint32_t over = (uint32_t)__ballot(on && d >= 8);
+    const int take = over ? __ffs(over) - 1 : kFinePairs;
+    i0 += take;
+    m &= (1u << take) - 1u;
+    if (m == 0) continue;  // the same in every wave
+    --steps;
+    const int np = __popc(m), e0 = __ffs(m) - 1;
+    const int ka = __builtin_amdgcn_readlane(k, e0), ja = __builtin_amdgcn_readlane(j, e0);
+    lds_wave_sync();  // the wave is done with its last step
+    st.rank[ln] = -1;
+    if (ln < 8) st.refs[ln] = ka;
+    lds_wave_sync();
+    if (ln < kFinePairs && ((m >> ln) & 1)) {
+      const int r = __popc(m & ((1u << ln) - 1u));
+      st.rank[j * 8 + d] = r;
+      if (first == ln) st.refs[d] = k;
+      st.j[r] = j;
+      st.k[r] = k;
+    }
+    lds_wave_sync();
+    {
+      // rows without a pair repeat the first pair's
+      const int jr = (ln & 15) >> 1;
+      bool used = false;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) used |= st.rank[jr * 8 + r] >= 0;
+      const int row = row0 + sm.shift[used ? jr : ja];
+      Contract::run(c, stc, (row >> 3) - (row0 >> 3), (ln & 1) * 8 + (row & 7), st.refs[(ln >> 1) & 7], w, ln,
+                    st.rank[lane_pair(ln)]);
+    }
+    __syncthreads();
+    inverse_pairs<NW, true, kFinePairs>(stc, sm.tw, nullptr, np, w, ln, [&](int i, int n1, const float2(&x)[16]) {
+      if constexpr (MODE == kFineTighten) {
+        float mx = -INFINITY;
+        bool nan = false;
+#pragma unroll
+        for (int n2 = 0; n2 < 16; ++n2) {
+          mx = fmaxf(mx, c.M == 2 ? fmaxf(x[n2].x, x[n2].y) : x[n2].x);
+          nan |= !(x[n2].x == x[n2].x) || !(x[n2].y == x[n2].y);
+        }
+        atomicMax(&sm.pmax[i], (uint32_t)(cand_key(nan ? INFINITY : mx, 0) >> 32));
+      } else {
+        const int s = sm.shift[st.j[i]], k = st.k[i];
+        const int ex = MODE == kRunnerUp ? excluded_at(ex0, k, s, S, c.M) : -1;
+        float bv;
+        int bi;
+        pick_best<MODE == kRunnerUp ? kRunnerUp : kArgmax>(x, n1, c.M, key_value(sm.key[s]), ex, bv, bi);
+        if (bi != 0x7fffffff) {
+          const unsigned long long key = cand_key(bv, ((k * c.M + (bi >> 8)) * S + s) * kNphi + (bi & 255));
+          atomicMax(&sm.key[s], key);
+          atomicMax(sm.pbest, key);
+        }
+      }
+    });
+    __syncthreads();
+    if constexpr (MODE == kFineTighten) {
+      // the FP16 CC is within the rounding error of the FP32 one, and of
+      // its own evaluation (2^-12 of the bound)
+      if (tid < np) {
+        const int s = sm.shift[st.j[tid]], k = st.k[tid];
+        const float cc = key_value((unsigned long long)sm.pmax[tid] << 32);
+        float* u = ub + (size_t)s * c.ldu + k;
+        const float err = fp16_error(c.rownorm[row0 + s], c.bnorm[k] * c.b_scale, c.R) + 1e-16f;
+        const float own = *u * (1.f / 4096.f), mx = c.maxabs[n];
+        const float hi = fp16_value(cc + err, mx, c.b_scale) + own + 1e-37f;
+        const float lo = fp16_value(cc - err, mx, c.b_scale) - own - 1e-37f;
+        if (hi < *u) *u = hi;
+        if (lo > -INFINITY && lo < INFINITY) atomicMax(sm.pbest, cand_key(lo, 0));
+        sm.pmax[tid] = 0u;
+      }
+      __syncthreads();
+    }
+  }
+  return true;
+}
+
+// A row's largest bound, after some have been tightened: one wave.
+__device__ __forceinline__ void largest_bound(const CorrArgs& c, int row, int ln) {
+  const float* ub = c.ub + (size_t)row * c.ldu;
+  unsigned long long best = 0ull;
+  for (int k = ln; k < c.K; k += 64) {
+    const float v = ub[k];
+    const unsigned long long key = cand_key(v == v ? v : INFINITY, k);
+    best = key > best ? key : best;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long other = __shfl_xor(best, o);
+    best = other > best ? other : best;
+  }
+  if (ln == 0) c.rowkey[row] = best;
+}
+
+// A particle with many live pairs, left to the whole chip: its bests so far
+// and its number go to the list, unless the list is full.
+__device__ __forceinline__ bool fine_spill(const FineSmem& sm, const FineOver& over, int item, int S) {
+  __syncthreads();  // every wave has read the list's length
+  if (threadIdx.x == 0) *sm.count = atomicAdd(over.count, 1);
+  __syncthreads();
+  const int e = *sm.count;
+  __syncthreads();
+  if (e >= over.cap) return false;
+  if (threadIdx.x == 0) {
+    over.item[e] = item;
+    over.best[e] = *sm.pbest;
+  }
+  for (int s = threadIdx.x; s < S; s += blockDim.x) over.row[(size_t)e * over.pitch + s] = sm.key[s];
+  __syncthreads();  // before the next particle's keys
+  return true;
+}
+
+template <int PREC, int NW, class Contract, int MODE>
+__device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int n, const FineOver& over, int item,
+                                              float* smem) {
   constexpr int kThreads = 64 * NW;
   const FineSmem sm(smem, c.S, NW);
   const int tid = threadIdx.x, ln = tid & 63;
@@ -287,9 +455,8 @@ __device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int
   if (PREC != kFP32)  // the particle's first row tile
     c.A = reinterpret_cast<const float*>(reinterpret_cast<const uint16_t*>(c.A) +
                                          (size_t)(row0 >> 3) * (kSlots * c.R4 * 64));
-  float2* stc = reinterpret_cast<float2*>(sm.work);
-  FineStep& st = sm.step[w];
-  const int ex0 = MODE == kRunnerUp ? c.excl[n] : -1;
+  const FineAt at{n, row0, S, MODE == kRunnerUp ? c.excl[n] : -1, ub};
+  int steps = over.cap > 0 ? over.steps : INT_MAX;
   auto value = [&](float v) { return PREC == kFP16 ? fp16_value(v, c.maxabs[n], c.b_scale) : v; };
   // (infinite bounds: the particle does not scale into FP16)
   if (MODE == kFineTighten && !(c.maxabs[n] * 512.f < INFINITY)) return;
@@ -377,124 +544,17 @@ __device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int
         __syncthreads();
         cnt = *sm.count;
       }
-#pragma unroll 1
-      for (int i0 = 0; i0 < cnt;) {
-        // the next step: entries i0 .. i0 + 15 that are still live, up to the
-        // first whose reference would be the ninth (lane i < 16: entry i0 + i;
-        // every wave does the same)
-        bool on = ln < kFinePairs && i0 + ln < cnt;
-        int j = 0, k = 0;
-        if (on) {
-          if (base >= 0) {
-            const uint32_t e = sm.live[i0 + ln];
-            k = (int)(e >> 3);
-            j = (int)(e & 7u);
-            // (a long list: the threshold may have passed it since)
-            if (i0 > 0) on = !(ub[(size_t)sm.shift[j] * c.ldu + k] < threshold());
-          } else {
-            j = ln;
-            k = sm.rowarg[sm.shift[ln]];
-          }
-        }
-        uint32_t m = (uint32_t)__ballot(on);
-        int first = ln;  // the first entry with this one's reference
-#pragma unroll
-        for (int e = kFinePairs - 1; e >= 0; --e)
-          if (((m >> e) & 1) && __builtin_amdgcn_readlane(k, e) == k && e < first) first = e;
-        const uint32_t fm = (uint32_t)__ballot(on && first == ln);
-        const int d = __popc(fm & ((1u << (first & 31)) - 1u));
-        const uint32_t over = (uint32_t)__ballot(on && d >= 8);
-        const int take = over ? __ffs(over) - 1 : kFinePairs;
-        i0 += take;
-        m &= (1u << take) - 1u;
-        if (m == 0) continue;  // the same in every wave
-        const int np = __popc(m), e0 = __ffs(m) - 1;
-        const int ka = __builtin_amdgcn_readlane(k, e0), ja = __builtin_amdgcn_readlane(j, e0);
-        lds_wave_sync();  // the wave is done with its last step
-        st.rank[ln] = -1;
-        if (ln < 8) st.refs[ln] = ka;
-        lds_wave_sync();
-        if (ln < kFinePairs && ((m >> ln) & 1)) {
-          const int r = __popc(m & ((1u << ln) - 1u));
-          st.rank[j * 8 + d] = r;
-          if (first == ln) st.refs[d] = k;
-          st.j[r] = j;
-          st.k[r] = k;
-        }
-        lds_wave_sync();
-        {
-          // rows without a pair repeat the first pair's
-          const int jr = (ln & 15) >> 1;
-          bool used = false;
-#pragma unroll
-          for (int r = 0; r < 8; ++r) used |= st.rank[jr * 8 + r] >= 0;
-          const int row = row0 + sm.shift[used ? jr : ja];
-          Contract::run(c, stc, (row >> 3) - (row0 >> 3), (ln & 1) * 8 + (row & 7), st.refs[(ln >> 1) & 7], w, ln,
-                        st.rank[lane_pair(ln)]);
-        }
-        __syncthreads();
-        inverse_pairs<NW, true, kFinePairs>(stc, sm.tw, nullptr, np, w, ln, [&](int i, int n1, const float2(&x)[16]) {
-          if constexpr (MODE == kFineTighten) {
-            float mx = -INFINITY;
-            bool nan = false;
-#pragma unroll
-            for (int n2 = 0; n2 < 16; ++n2) {
-              mx = fmaxf(mx, c.M == 2 ? fmaxf(x[n2].x, x[n2].y) : x[n2].x);
-              nan |= !(x[n2].x == x[n2].x) || !(x[n2].y == x[n2].y);
-            }
-            atomicMax(&sm.pmax[i], (uint32_t)(cand_key(nan ? INFINITY : mx, 0) >> 32));
-          } else {
-            const int s = sm.shift[st.j[i]], k = st.k[i];
-            const int ex = MODE == kRunnerUp ? excluded_at(ex0, k, s, S, c.M) : -1;
-            float bv;
-            int bi;
-            pick_best<MODE == kRunnerUp ? kRunnerUp : kArgmax>(x, n1, c.M, key_value(sm.key[s]), ex, bv, bi);
-            if (bi != 0x7fffffff) {
-              const unsigned long long key = cand_key(bv, ((k * c.M + (bi >> 8)) * S + s) * kNphi + (bi & 255));
-              atomicMax(&sm.key[s], key);
-              atomicMax(sm.pbest, key);
-            }
-          }
-        });
-        __syncthreads();
-        if constexpr (MODE == kFineTighten) {
-          // the FP16 CC is within the rounding error of the FP32 one, and of
-          // its own evaluation (2^-12 of the bound)
-          if (tid < np) {
-            const int s = sm.shift[st.j[tid]], k = st.k[tid];
-            const float cc = key_value((unsigned long long)sm.pmax[tid] << 32);
-            float* u = ub + (size_t)s * c.ldu + k;
-            const float err = fp16_error(c.rownorm[row0 + s], c.bnorm[k] * c.b_scale, c.R) + 1e-16f;
-            const float own = *u * (1.f / 4096.f), mx = c.maxabs[n];
-            const float hi = fp16_value(cc + err, mx, c.b_scale) + own + 1e-37f;
-            const float lo = fp16_value(cc - err, mx, c.b_scale) - own - 1e-37f;
-            if (hi < *u) *u = hi;
-            if (lo > -INFINITY && lo < INFINITY) atomicMax(sm.pbest, cand_key(lo, 0));
-            sm.pmax[tid] = 0u;
-          }
-          __syncthreads();
-        }
+      int i0 = 0;
+      while (!fine_steps<PREC, NW, Contract, MODE>(a, c, sm, at, cnt, base >= 0, i0, steps)) {
+        if (fine_spill(sm, over, item, S)) return;
+        steps = INT_MAX;
       }
       if (base >= 0) __syncthreads();  // before the list is written again
     }
   }
   if constexpr (MODE == kFineTighten) {
-    // the largest bound of the rows looked at
-    for (int s = w; s < S; s += NW) {
-      if (!sm.taken[s]) continue;
-      unsigned long long best = 0ull;
-      for (int k = ln; k < c.K; k += 64) {
-        const float v = ub[(size_t)s * c.ldu + k];
-        const unsigned long long key = cand_key(v == v ? v : INFINITY, k);
-        best = key > best ? key : best;
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long other = __shfl_xor(best, o);
-        best = other > best ? other : best;
-      }
-      if (ln == 0) c.rowkey[row0 + s] = best;
-    }
+    for (int s = w; s < S; s += NW)
+      if (sm.taken[s]) largest_bound(c, row0 + s, ln);  // the rows looked at
   } else {
     if (c.row_cc)
       for (int s = tid; s < S; s += kThreads) {
@@ -506,6 +566,85 @@ __device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int
   __syncthreads();  // before the next particle's keys
 }
 
+constexpr int kOverRefs = 32;
+// One unit of a particle left to the whole chip (entry e of the list): the
+// pairs of its g-th row tile and kOverRefs references that reach the
+// particle's best so far.
+template <int PREC, int NW, class Contract, int MODE>
+__device__ __forceinline__ void fine_unit(const FineArgs& a, CorrArgs c, int n, const FineOver& over, int e, int unit,
+                                          float* smem) {
+  static_assert(PREC != kFP32 && 8 * kOverRefs <= 64 * NW, "a pair per thread");
+  const FineSmem sm(smem, c.S, NW);
+  const int tid = threadIdx.x, ln = tid & 63;
+  const int S = c.S, row0 = n * S, nw = (c.K + kOverRefs - 1) / kOverRefs;
+  const int g = unit / nw, base = (unit - g * nw) * kOverRefs;
+  const int first = ((row0 >> 3) + g) * 8 - row0;
+  if (first >= S) return;
+  const float* ub = c.ub + (size_t)row0 * c.ldu;
+  c.A = reinterpret_cast<const float*>(reinterpret_cast<const uint16_t*>(c.A) +
+                                       (size_t)(row0 >> 3) * (kSlots * c.R4 * 64));
+  const FineAt at{n, row0, S, MODE == kRunnerUp ? c.excl[n] : -1, ub};
+  if (tid == 0) {
+    // (the best of other workgroups: any earlier value only leaves more pairs)
+    *sm.pbest = __hip_atomic_load(&over.best[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *sm.count = 0;
+  }
+  __syncthreads();
+  const float thr = part_thr(key_value(*sm.pbest), a.margin);
+  const int s = first + (ln & 7);
+  const bool live = ln < 8 && s >= 0 && s < S && !(key_value(c.rowkey[row0 + (s >= 0 && s < S ? s : 0)]) < thr);
+  const uint32_t m = (uint32_t)__ballot(live);
+  const int nrow = __popc(m);
+  if (nrow == 0) {  // (the same in every wave)
+    __syncthreads();  // every wave has read the best
+    return;
+  }
+  const int top = first + __ffs(m) - 1;
+  if (tid < 8) {
+    if (live) {
+      sm.shift[__popc(m & ((1u << ln) - 1u))] = s;
+      sm.key[s] = 0ull;
+    }
+    if (ln >= nrow) sm.shift[ln] = top;  // rows past the live ones repeat the first
+  }
+  __syncthreads();
+  if (tid < 8 * kOverRefs) {
+    const int j = tid / kOverRefs, k = base + tid % kOverRefs;
+    if (j < nrow && k < c.K && !(ub[(size_t)sm.shift[j] * c.ldu + k] < thr))
+      sm.live[atomicAdd(sm.count, 1)] = (uint32_t)(k * 8 + j);
+  }
+  __syncthreads();
+  const int cnt = *sm.count;
+  if (cnt > 0) {
+    int i0 = 0, steps = INT_MAX;
+    fine_steps<PREC, NW, Contract, MODE>(a, c, sm, at, cnt, true, i0, steps);
+    if (tid < nrow) {
+      const unsigned long long key = sm.key[sm.shift[tid]];
+      if (key) atomicMax(&over.row[(size_t)e * over.pitch + sm.shift[tid]], key);
+    }
+    if (tid == 0) atomicMax(&over.best[e], *sm.pbest);
+  }
+  __syncthreads();  // before the next unit's lists
+}
+
+// The results of entry e, particle n: one wave.
+template <int PREC, int MODE>
+__device__ __forceinline__ void fine_finish(const FineArgs& a, int n, const FineOver& over, int e, int ln) {
+  const CorrArgs& c = a.c;
+  if (MODE == kFineTighten) {
+    for (int s = 0; s < c.S; ++s) largest_bound(c, n * c.S + s, ln);
+    return;
+  }
+  auto value = [&](float v) { return PREC == kFP16 ? fp16_value(v, c.maxabs[n], c.b_scale) : v; };
+  if (c.row_cc)
+    for (int s = ln; s < c.S; s += 64) {
+      const unsigned long long key = over.row[(size_t)e * over.pitch + s];
+      c.row_cc[(size_t)n * c.S + s] = value(key_value(key));
+      c.row_idx[(size_t)n * c.S + s] = key_index(key);
+    }
+  if (ln == 0) write_result(a.m, n, value(key_value(over.best[e])), key_index(over.best[e]));
+}
+
 // 16-bit operands: 4 waves, FP32: 8 (as the resampler)
 constexpr int fine_waves(int prec) { return prec == kFP32 ? 8 : 4; }
 template <int PREC, int MAXR>
@@ -515,60 +654,111 @@ struct FineContract {
       FineContract16<PREC == kFP32 ? kBF16 : PREC, MAXR, fine_waves(kBF16)>>::type type;
 };
 
-// at most 128 registers: four waves per SIMD
-template <int PREC, int MAXR, int MODE>
-__global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine(FineArgs a) {
-  extern __shared__ float smem[];
-  CorrArgs c = a.c;
-  if (PREC == kFP32) c.A += (size_t)blockIdx.x * a.scratch_floats;
-  for (int n = blockIdx.x; n < a.m.n_part; n += gridDim.x)
-    fine_particle<PREC, fine_waves(PREC), typename FineContract<PREC, MAXR>::type, MODE>(a, c, n, smem);
-}
-
-// Batched form over the particles of several stacks.
-template <int PREC, int MAXR, int MODE>
-__global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine_batch(FineBatch b) {
-  extern __shared__ float smem[];
-  for (int item = blockIdx.x; item < b.start[b.n]; item += gridDim.x) {
+// Item -> piece and particle.
+struct FineOne {
+  FineArgs a;
+  __device__ __forceinline__ int items() const { return a.m.n_part; }
+  __device__ __forceinline__ const FineArgs& find(int item, int& n) const {
+    n = item;
+    return a;
+  }
+};
+static_assert(sizeof(FineBatch) + sizeof(FineOver) <= 4096, "kernel arguments");
+struct FineMany {
+  FineBatch b;
+  __device__ __forceinline__ int items() const { return b.start[b.n]; }
+  __device__ __forceinline__ const FineArgs& find(int item, int& n) const {
     int p = 0;
     while (p + 1 < b.n && b.start[p + 1] <= item) ++p;
-    CorrArgs c = b.piece[p].c;
-    if (PREC == kFP32) c.A += (size_t)blockIdx.x * b.piece[p].scratch_floats;
-    fine_particle<PREC, fine_waves(PREC), typename FineContract<PREC, MAXR>::type, MODE>(b.piece[p], c,
-                                                                                        item - b.start[p], smem);
+    n = item - b.start[p];
+    return b.piece[p];
+  }
+};
+
+// at most 128 registers: four waves per SIMD
+template <int PREC, int MAXR, int MODE, class Items>
+__global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine(Items it, FineOver over) {
+  extern __shared__ float smem[];
+  for (int item = blockIdx.x; item < it.items(); item += gridDim.x) {
+    int n;
+    const FineArgs& a = it.find(item, n);
+    CorrArgs c = a.c;
+    if (PREC == kFP32) c.A += (size_t)blockIdx.x * a.scratch_floats;
+    fine_particle<PREC, fine_waves(PREC), typename FineContract<PREC, MAXR>::type, MODE>(a, c, n, over, item, smem);
   }
 }
 
+// The particles left over, each spread over over.units workgroups.
+template <int PREC, int MAXR, int MODE, class Items>
+__global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine_over(Items it, FineOver over) {
+  extern __shared__ float smem[];
+  const int cnt = min(*over.count, over.cap);
+  if (cnt == 0) return;
+  int last = -1;
+  for (int u = blockIdx.x; u < cnt * over.units; u += gridDim.x) {
+    const int e = u % cnt;
+    int n;
+    const FineArgs& a = it.find(over.item[e], n);
+    CorrArgs c = a.c;
+    if (c.S != last) {  // the places of the table and of pmax depend on S
+      const FineSmem sm(smem, c.S, fine_waves(PREC));
+      if (threadIdx.x < kFinePairs) sm.pmax[threadIdx.x] = 0u;
+      for (int i = threadIdx.x; i < kNphi; i += 64 * fine_waves(PREC)) sm.tw[i] = w256c(c.cs32, i);
+      last = c.S;
+      __syncthreads();
+    }
+    fine_unit<PREC, fine_waves(PREC), typename FineContract<PREC, MAXR>::type, MODE>(a, c, n, over, e, u / cnt, smem);
+  }
+}
+template <int PREC, int MODE, class Items>
+__global__ __launch_bounds__(64) void k_fine_done(Items it, FineOver over) {
+  const int e = blockIdx.x;
+  if (e >= min(*over.count, over.cap)) return;
+  int n;
+  const FineArgs& a = it.find(over.item[e], n);
+  fine_finish<PREC, MODE>(a, n, over, e, threadIdx.x);
+}
+
+template <int PREC, int MAXR, int MODE, class Items>
+inline void fine_launch(const Items& it, const FineOver& over, int grid, size_t lds, hipStream_t st) {
+  const dim3 t(64 * fine_waves(PREC));
+  hipLaunchKernelGGL((k_fine<PREC, MAXR, MODE, Items>), dim3(grid), t, lds, st, it, over);
+  if constexpr (PREC != kFP32) {
+    if (over.cap > 0) {
+      hipLaunchKernelGGL((k_fine_over<PREC, MAXR, MODE, Items>), dim3(over.grid), t, lds, st, it, over);
+      hipLaunchKernelGGL((k_fine_done<PREC, MODE, Items>), dim3(over.cap), dim3(64), 0, st, it, over);
+    }
+  }
+}
 template <int PREC, int MAXR, int MODE>
-inline void fine_mode(const FineArgs* a, const FineBatch* b, int grid, size_t lds, hipStream_t st) {
-  const dim3 g(grid), t(64 * fine_waves(PREC));
-  if (b) hipLaunchKernelGGL((k_fine_batch<PREC, MAXR, MODE>), g, t, lds, st, *b);
-  else hipLaunchKernelGGL((k_fine<PREC, MAXR, MODE>), g, t, lds, st, *a);
+inline void fine_mode(const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds, hipStream_t st) {
+  if (b) fine_launch<PREC, MAXR, MODE>(FineMany{*b}, over, grid, lds, st);
+  else fine_launch<PREC, MAXR, MODE>(FineOne{*a}, over, grid, lds, st);
 }
 // TIGHTEN: only the tightening of FP32 bounds, else every other mode
 template <int PREC, int MAXR, bool TIGHTEN>
-inline void fine_go(FineMode mode, const FineArgs* a, const FineBatch* b, int grid, size_t lds, hipStream_t st) {
-  if constexpr (TIGHTEN) return fine_mode<PREC, MAXR, kFineTighten>(a, b, grid, lds, st);
-  else if (mode == kFineRunnerUp) return fine_mode<PREC, MAXR, kRunnerUp>(a, b, grid, lds, st);
-  else return fine_mode<PREC, MAXR, kArgmax>(a, b, grid, lds, st);
+inline void fine_go(FineMode mode, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds, hipStream_t st) {
+  if constexpr (TIGHTEN) return fine_mode<PREC, MAXR, kFineTighten>(a, b, over, grid, lds, st);
+  else if (mode == kFineRunnerUp) return fine_mode<PREC, MAXR, kRunnerUp>(a, b, over, grid, lds, st);
+  else return fine_mode<PREC, MAXR, kArgmax>(a, b, over, grid, lds, st);
 }
 
 // R4max: the largest ring count of the launch's pieces (one ring bucket).
-void fine_dispatch_fp32(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
+void fine_dispatch_fp32(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds,
                         hipStream_t st);
-void fine_dispatch_bf16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
+void fine_dispatch_bf16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds,
                         hipStream_t st);
-void fine_dispatch_fp16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
+void fine_dispatch_fp16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds,
                         hipStream_t st);
-void fine_dispatch_tighten(int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds, hipStream_t st);
+void fine_dispatch_tighten(int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds, hipStream_t st);
 
 template <int PREC, bool TIGHTEN>
-inline void fine_dispatch_16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
+inline void fine_dispatch_16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds,
                              hipStream_t st) {
-  if (R4max <= 8) return fine_go<PREC, 8, TIGHTEN>(mode, a, b, grid, lds, st);
-  if (R4max <= 10) return fine_go<PREC, 10, TIGHTEN>(mode, a, b, grid, lds, st);
-  if (R4max <= 12) return fine_go<PREC, 12, TIGHTEN>(mode, a, b, grid, lds, st);
-  return fine_go<PREC, 16, TIGHTEN>(mode, a, b, grid, lds, st);
+  if (R4max <= 8) return fine_go<PREC, 8, TIGHTEN>(mode, a, b, over, grid, lds, st);
+  if (R4max <= 10) return fine_go<PREC, 10, TIGHTEN>(mode, a, b, over, grid, lds, st);
+  if (R4max <= 12) return fine_go<PREC, 12, TIGHTEN>(mode, a, b, over, grid, lds, st);
+  return fine_go<PREC, 16, TIGHTEN>(mode, a, b, over, grid, lds, st);
 }
 
 }  // namespace mra

@@ -17,11 +17,11 @@ static size_t lds_bytes(int prec, int S, int Lp) {
 }
 
 static void dispatch(int prec, FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
-                     hipStream_t st) {
-  if (mode == kFineTighten) fine_dispatch_tighten(R4max, a, b, grid, lds, st);
-  else if (prec == kFP32) fine_dispatch_fp32(mode, R4max, a, b, grid, lds, st);
-  else if (prec == kBF16) fine_dispatch_bf16(mode, R4max, a, b, grid, lds, st);
-  else fine_dispatch_fp16(mode, R4max, a, b, grid, lds, st);
+                     const FineOver& over, hipStream_t st) {
+  if (mode == kFineTighten) fine_dispatch_tighten(R4max, a, b, over, grid, lds, st);
+  else if (prec == kFP32) fine_dispatch_fp32(mode, R4max, a, b, over, grid, lds, st);
+  else if (prec == kBF16) fine_dispatch_bf16(mode, R4max, a, b, over, grid, lds, st);
+  else fine_dispatch_fp16(mode, R4max, a, b, over, grid, lds, st);
 }
 
 static bool accepts(int prec, FineMode mode, const FineArgs& a) {
@@ -31,16 +31,42 @@ static bool accepts(int prec, FineMode mode, const FineArgs& a) {
          (mode != kFineTighten || (a.c.rownorm && a.c.bnorm && a.c.maxabs)) && (mode != kFineRunnerUp || a.c.excl);
 }
 
-hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, int grid, hipStream_t st) {
+int fine_units(int S, int K) { return (S / kRowTile + 2) * ((K + kOverRefs - 1) / kOverRefs); }
+
+// Steps after which a launch over n particles leaves one of them to the whole
+// chip.  One particle in 64 or so (76 px, 100 references, SNR 0.05) has hundreds
+// of live pairs, and alone takes 0.4 to 1 ms after the others are done; left
+// over, its rows go round once more, spread over all workgroups.  In a launch of
+// few rounds of workgroups an early end matters most: BF16 (us, evaluation)
+// 300 particles 434 -> 196, 1000: 964 -> 455, 4000: 1581 -> 1030, 8000: 2627 ->
+// 1850; FP32 (tightening) 64: 190 -> 179, 256: 1092 -> 358, 4000: 1885 -> 1193.
+// In one of more rounds the list holds the fewer, longest ones: after 24 steps
+// 20 000 particles BF16 4.70 -> 4.31 ms (after 8: 4.63), 10 000 FP32 3.31 -> 2.69
+// (after 8: 4.10).  In a launch that leaves half the workgroups without a
+// particle, a particle of few units (5 at 20 references, +-2) is spread out at
+// once, after 2 steps: FP32, 64 px, SNR 0.05 (whole call) 50 particles 231 -> 202
+// us, 300 of 10 references 367 -> 330; of 20 units (100 references) it is not: 64
+// particles 204 against 218.
+int fine_over_steps(int64_t n, int units, int n_cu) {
+  const int64_t grid = fine_grid(kFP16, INT32_MAX, n_cu);
+  return 2 * n <= grid && units <= 16 ? 2 : (n <= 8 * grid ? 8 : 24);
+}
+
+static bool sound(const FineOver& o) {
+  return o.cap == 0 || (o.cap > 0 && o.count && o.item && o.best && o.row && o.pitch >= 1 && o.units >= 1 && o.grid >= 1);
+}
+
+hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, const FineOver& over, int grid, hipStream_t st) {
   if (a.m.n_part <= 0) return hipSuccess;
-  if (grid < 1 || !accepts(prec, mode, a)) return hipErrorInvalidValue;
-  dispatch(prec, mode, a.c.R4, &a, nullptr, grid, lds_bytes(mode == kFineTighten ? kFP16 : prec, a.c.S, a.Lp), st);
+  if (grid < 1 || !accepts(prec, mode, a) || !sound(over)) return hipErrorInvalidValue;
+  dispatch(prec, mode, a.c.R4, &a, nullptr, grid, lds_bytes(mode == kFineTighten ? kFP16 : prec, a.c.S, a.Lp), over, st);
   return hipGetLastError();
 }
 
-hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, int grid, hipStream_t st) {
+hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, const FineOver& over, int grid,
+                             hipStream_t st) {
   if (b.n <= 0 || b.start[b.n] <= 0) return hipSuccess;
-  if (grid < 1) return hipErrorInvalidValue;
+  if (grid < 1 || !sound(over)) return hipErrorInvalidValue;
   size_t lds = 0;
   int r4 = 0;
   for (int i = 0; i < b.n; ++i) {
@@ -51,7 +77,7 @@ hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, int gr
     const size_t need = lds_bytes(mode == kFineTighten ? kFP16 : prec, b.piece[i].c.S, b.piece[i].Lp);
     lds = need > lds ? need : lds;
   }
-  dispatch(prec, mode, r4, nullptr, &b, grid, lds, st);
+  dispatch(prec, mode, r4, nullptr, &b, grid, lds, over, st);
   return hipGetLastError();
 }
 

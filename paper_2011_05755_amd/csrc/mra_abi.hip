@@ -291,11 +291,32 @@ struct ChunkBufs {
   float* rownorm = nullptr;  // pruned FP32: [2][nc S] norm of the row's operand
   float* scratch = nullptr;  // pruned FP32: one operand tile per evaluation workgroup
   int grid = 0;              // evaluation workgroups
+  FineOver over{};           // the particles left to the whole chip
   float* rcc = nullptr;      // [nc S] best CC per row
   int* ridx = nullptr;       // [nc S] its flat index
   float* maxabs = nullptr;   // FP16 operand: [nc] max |pixel|
   int32_t* win = nullptr;    // cc2: [nc] chunk-local winner copy
 };
+
+// The list of particles that an evaluation of nc particles (of at most S shifts
+// and `units` units of work each) leaves to the whole chip.
+template <class Take>
+FineOver take_over(int64_t nc, int S, int units, int n_cu, Take take) {
+  FineOver o{};
+  o.cap = (int)std::min<int64_t>(nc, kFineOverCap);
+  o.steps = fine_over_steps(nc, units, n_cu);
+  o.pitch = S;
+  o.units = units;
+  o.grid = fine_grid(kFP16, INT32_MAX, n_cu);
+  const size_t keys = (size_t)o.cap * (1 + S) * sizeof(unsigned long long);
+  char* p = (char*)take("over", keys + (size_t)(o.cap + 2) * sizeof(int));
+  if (!p) return o;  // (only measured)
+  o.best = (unsigned long long*)p;
+  o.row = o.best + o.cap;
+  o.item = (int*)(p + keys);
+  o.count = o.item + o.cap;
+  return o;
+}
 
 // Calls take(name, bytes) for every buffer of an nc-particle chunk.
 template <class Take>
@@ -312,6 +333,7 @@ ChunkBufs layout_chunk(const Refset& rs, const Plan& p, int64_t nc, bool pruned,
       b.rownorm = (float*)take("rownorm", 2 * rows * sizeof(float));
       b.scratch = (float*)take("scratch", b.grid * scratch_tile_bytes(rs));
     }
+    b.over = take_over(nc, p.S, fine_units(p.S, rs.K), n_cu, take);
   }
   b.rowkey = (unsigned long long*)take("rowkey", (rows + 1) * sizeof(unsigned long long));
   if (row_results(rs)) {
@@ -348,7 +370,8 @@ uint64_t ws_other(mra_ctx* c) {
   uint64_t total = 0;
   for (const auto& kv : c->ws) {
     bool chunk_buf = false;
-    for (const char* n : {"A", "ub", "ub_hi", "rowkey", "rownorm", "scratch", "row_cc", "row_idx", "maxabs", "win"}) chunk_buf |= kv.first == n;
+    for (const char* n : {"A", "ub", "ub_hi", "rowkey", "rownorm", "scratch", "row_cc", "row_idx", "maxabs", "over", "win"})
+      chunk_buf |= kv.first == n;
     if (!chunk_buf) total += kv.second.bytes;
   }
   return total;
@@ -369,10 +392,10 @@ int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned
 // A call of few particles takes the unpruned way: with every pair of a few
 // row and reference tiles spread over the CUs it ends before the pruned way's
 // chain of dependent steps does.  At 76 px, 100 references, +-3 (91 tile pairs
-// per particle, 256 CUs), unpruned against pruned: FP32 1 particle 64 / 317
-// us, 16 particles 288 / 382, 32 particles 510 / 387; BF16 1 particle 56 / 177
-// us, 32 particles 162 / 217, 64 particles 256 / 431; at 90 px, +-2 BF16 64
-// particles (10 tile pairs per CU) 167 / 161.
+// per particle, 256 CUs), unpruned against pruned: FP32 8 particles 144 / 241
+// us, 16 particles 288 / 284, 24 particles 509 / 403; BF16 32 particles 158 /
+// 316 us, 64 particles 258 / 246; at 90 px, +-2 BF16 64 particles (10 tile pairs
+// per CU) 165 / 161; at 64 px, +-2, 20 references FP32 50 particles 154 / 162.
 bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N) {
   const int64_t tiles = (N * p.S + kRowTile - 1) / kRowTile * rs.n_kt;
   return tiles <= (rs.g.precision == kFP32 ? 5 : 12) * (int64_t)c->n_cu;
@@ -513,14 +536,6 @@ FineArgs fine_args(mra_ctx* c, const Refset& rs, const Plan& p, const CorrArgs& 
   return fa;
 }
 
-// Whether FP32 bounds are tightened before the evaluation of n particles.  It
-// saves the evaluation's second group of rows, whose resampling keeps the
-// CUs busy; when the particles do not fill the CUs' workgroups, its own
-// latency costs more.
-bool tighten(const mra_ctx* c, const Refset& rs, int64_t n) {
-  return rs.g.precision == kFP32 && n > fine_grid(kFP32, INT32_MAX, c->n_cu);
-}
-
 // One chunk of the alignment pass, pruned: resample + FFT -> bounds ->
 // evaluation (-> FP32 re-score for 16-bit contractions).
 void run_chunk(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, int64_t n0, int nc,
@@ -535,16 +550,16 @@ void run_chunk(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, 
   timed(c, "polar", [&] { hip_check(c, launch_polar(0, pa, st), "polar"); });
   CorrArgs ca = corr_args(c, rs, p, nc, kRingPerm16, b);
   const int items = bound_items(ca, c->n_cu);
-  timed(c, "bound", [&] { hip_check(c, launch_bound(prec, ca, items, st), "bound"); });
+  timed(c, "bound", [&] { hip_check(c, launch_bound(prec, ca, items, b.over.count, st), "bound"); });
   FineArgs fa = fine_args(c, rs, p, ca, src, n0, nc, out, b);
-  if (tighten(c, rs, nc)) {
+  if (prec == kFP32) {
     FineArgs ta = fa;
     ta.c.A = b.A;
     timed(c, "tighten", [&] {
-      hip_check(c, launch_fine(prec, kFineTighten, ta, fine_grid(kFP16, nc, c->n_cu), st), "tighten");
+      hip_check(c, launch_fine(prec, kFineTighten, ta, b.over, fine_grid(kFP16, nc, c->n_cu), st), "tighten");
     });
   }
-  timed(c, "fine", [&] { hip_check(c, launch_fine(prec, kFineArgmax, fa, b.grid, st), "fine"); });
+  timed(c, "fine", [&] { hip_check(c, launch_fine(prec, kFineArgmax, fa, prec == kFP32 ? FineOver{} : b.over, b.grid, st), "fine"); });
   if (prec != kFP32)
     timed(c, "rescore", [&] { hip_check(c, launch_rescore(rescore_args(rs, p, src, n0, nc, out, b), st), "rescore"); });
   if (out->cc2) {
@@ -554,7 +569,9 @@ void run_chunk(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, 
     fa.m.win = nullptr;
     fa.m.runner_up = 1;
     fa.margin = 0.f;
-    timed(c, "fine2", [&] { hip_check(c, launch_fine(prec, kFineRunnerUp, fa, b.grid, st), "fine2"); });
+    FineOver over = prec == kFP32 ? FineOver{} : b.over;
+    if (over.cap) over.count += 1;
+    timed(c, "fine2", [&] { hip_check(c, launch_fine(prec, kFineRunnerUp, fa, over, b.grid, st), "fine2"); });
   }
   if (out->psi_frac) refine_chunk(c, rs, p, parts, n0, nc, out);
 }
@@ -702,12 +719,15 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
   }
   const int prec = w[0].rs->g.precision, np = (int)w.size();
   size_t a_bytes = 0, ub_floats = 0, rows = 0, parts = 0, tile = 0;
+  int max_S = 0, units = 0;
   for (const Piece& pc : w) {
     const size_t r = (size_t)pc.nc * pc.p.S;
     a_bytes += (r + kRowTile - 1) / kRowTile * tile_bytes_of(*pc.rs, true);
     ub_floats += r * ub_pitch(*pc.rs);
     rows += r;
     parts += pc.nc;
+    max_S = std::max(max_S, pc.p.S);
+    units = std::max(units, fine_units(pc.p.S, pc.rs->K));
     tile = std::max(tile, scratch_tile_bytes(*pc.rs));
   }
   const int grid = fine_grid(prec, (int64_t)parts, c->n_cu);
@@ -717,6 +737,8 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
   unsigned long long* rowkey = (unsigned long long*)ws_get(c, "rowkey", (rows + 1) * sizeof(unsigned long long));
   float* rownorm = prec == kFP32 ? (float*)ws_get(c, "rownorm", 2 * rows * sizeof(float)) : nullptr;
   float* scratch = prec == kFP32 ? (float*)ws_get(c, "scratch", grid * tile) : nullptr;
+  const FineOver over = take_over((int64_t)parts, max_S, units, c->n_cu,
+                                  [&](const char* name, size_t bytes) { return ws_get(c, name, bytes); });
   float* rcc = prec != kFP32 ? (float*)ws_get(c, "row_cc", rows * sizeof(float)) : nullptr;
   int* ridx = prec != kFP32 ? (int*)ws_get(c, "row_idx", rows * sizeof(int)) : nullptr;
   float* maxabs = prec != kBF16 ? (float*)ws_get(c, "maxabs", parts * sizeof(float)) : nullptr;
@@ -739,6 +761,7 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     b.ub_hi = ub_hi;
     b.rowkey = rowkey;
     b.rownorm = rownorm;
+    b.over = over;
     b.scratch = scratch;
     b.grid = grid;
     b.maxabs = maxabs ? maxabs + part : nullptr;
@@ -775,14 +798,14 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
   fb.start[np] = rb.start[np] = part;
   cb.start[np] = items;
   timed(c, "polar", [&] { hip_check(c, launch_polar_batch(pb, st), "polar batch"); });
-  timed(c, "bound", [&] { hip_check(c, launch_bound_batch(prec, cb, st), "bound batch"); });
-  if (tighten(c, *w[0].rs, (int64_t)parts)) {
+  timed(c, "bound", [&] { hip_check(c, launch_bound_batch(prec, cb, over.count, st), "bound batch"); });
+  if (prec == kFP32) {
     FineBatch tb = fb;
     for (int i = 0; i < np; ++i) tb.piece[i].c.A = cb.piece[i].A;
     const int tgrid = fine_grid(kFP16, (int64_t)parts, c->n_cu);
-    timed(c, "tighten", [&] { hip_check(c, launch_fine_batch(prec, kFineTighten, tb, tgrid, st), "tighten batch"); });
+    timed(c, "tighten", [&] { hip_check(c, launch_fine_batch(prec, kFineTighten, tb, over, tgrid, st), "tighten batch"); });
   }
-  timed(c, "fine", [&] { hip_check(c, launch_fine_batch(prec, kFineArgmax, fb, grid, st), "fine batch"); });
+  timed(c, "fine", [&] { hip_check(c, launch_fine_batch(prec, kFineArgmax, fb, prec == kFP32 ? FineOver{} : over, grid, st), "fine batch"); });
   if (prec != kFP32) timed(c, "rescore", [&] { hip_check(c, launch_rescore_batch(rb, st), "rescore batch"); });
 }
 

@@ -159,6 +159,21 @@ struct CorrBatch {
   CorrArgs piece[kMaxBatchPieces];
 };
 
+constexpr int kFineOverCap = 1024;  // (8 (1 + S) bytes each)
+// Particles with many pairs to evaluate, left to the whole chip: how many, and
+// for each its item number in the launch, its best candidate so far and its
+// rows'.
+struct FineOver {
+  int* count;                // zeroed by the bounds' sum
+  int* item;                 // [cap]
+  unsigned long long* best;  // [cap]
+  unsigned long long* row;   // [cap][pitch]
+  int cap, pitch;            // cap 0: none is left over
+  int steps;                 // steps after which a particle is left over
+  int units;                 // units of work per particle
+  int grid;                  // workgroups of that launch
+};
+
 // Where a chunk's particles' results go.
 struct ResultArgs {
   int n_part, S, S1, T, M;
@@ -255,15 +270,19 @@ hipError_t launch_corr(int prec, int variant, bool table, const CorrArgs& a, hip
 hipError_t launch_corr_runner_up(int prec, int variant, const CorrArgs& a, hipStream_t st);
 // 16-bit ring buckets (R4 <= 8, 9..10, 11..12, 13..16): the pieces of a batched launch share one
 constexpr int ring_bucket(int R4) { return R4 <= 8 ? 0 : (R4 <= 10 ? 1 : (R4 <= 12 ? 2 : 3)); }
-// work items of a bound launch over a's rows; sets a.kt_per_wg
+// work items of a bound launch over a's rows; sets a.kt_per_wg.  The launch also
+// zeroes over_count[0 .. 1], the counters of FineOver (arg-max, runner-up), if not null.
 int bound_items(CorrArgs& a, int n_cu);
-hipError_t launch_bound(int prec, const CorrArgs& a, int n_items, hipStream_t st);
-hipError_t launch_bound_batch(int prec, const CorrBatch& b, hipStream_t st);
+hipError_t launch_bound(int prec, const CorrArgs& a, int n_items, int* over_count, hipStream_t st);
+hipError_t launch_bound_batch(int prec, const CorrBatch& b, int* over_count, hipStream_t st);
 // workgroups of an evaluation launch over n particles (FP32: also its scratch tiles)
 int fine_grid(int prec, int64_t n, int n_cu);
 enum FineMode { kFineArgmax = 0, kFineRunnerUp = 2, kFineTighten = 3 };
-hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, int grid, hipStream_t st);
-hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, int grid, hipStream_t st);
+hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, const FineOver& over, int grid, hipStream_t st);
+hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, const FineOver& over, int grid,
+                             hipStream_t st);
+int fine_units(int S, int K);                         // FineOver::units of a piece
+int fine_over_steps(int64_t n, int units, int n_cu);  // FineOver::steps of a launch over n particles
 // launches of few particles: workgroups of `waves` waves per particle (of
 // n_items 8-row ring items) that fill n_cu CUs with 16 waves each, and reference parts of a launch of `tiles`
 // row tiles that give every CU a workgroup

@@ -196,38 +196,70 @@ __device__ __forceinline__ void sample_ring(const float* img, const CosSin* cs, 
   wave_sync();  // before the FFT's transposes reuse the scratch
 }
 
-// One angle at the rows (shifts) J0 .. J1 - 1 of 8, consecutive in an image
-// row: the taps of one shift are the left taps of the next, so the run reads
-// J1 - J0 + 1 columns instead of twice their number.  at: byte address of the
-// first shift's top-left tap.  Row j's sample goes to tr[17 j] (written here:
-// handed back, the values are copied where the patterns' branches meet).
-template <int J0, int J1>
-__device__ __forceinline__ void sample_run(const char* at, int Lp4, float w00, float w10, float w01, float w11, float* tr) {
-  constexpr int n = J1 - J0;
-  const float* p0 = reinterpret_cast<const float*>(at);
-  const float* p1 = reinterpret_cast<const float*>(at + Lp4);
-  float t0[n + 1], t1[n + 1];
-#pragma unroll
-  for (int i = 0; i <= n; ++i) {
-    t0[i] = p0[i];
-    t1[i] = p1[i];
+// An angle's bilinear sample: the byte offset of its top-left tap from a
+// shift's centre pixel, and its weights.
+struct Tap {
+  int off;
+  float w00, w10, w01, w11;
+  __device__ __forceinline__ void set(float rr, const CosSin& c, int Lp4) {
+    off = polar_offset(rr, c, Lp4);
+    polar_weights(rr, c, w00, w10, w01, w11);
   }
+  __device__ __forceinline__ float operator()(float i00, float i10, float i01, float i11) const {
+    return fmaf(w11, i11, fmaf(w01, i01, fmaf(w10, i10, w00 * i00)));
+  }
+};
+
+// The taps of an angle at the rows (shifts) J0 .. J1 - 1 of 8, run K of the
+// pattern, consecutive in an image row: the taps of one shift are the left
+// taps of the next, so the run reads J1 - J0 + 1 columns instead of twice their
+// number.  at: byte address of the first shift's top-left tap.
+struct TapColumns {
+  float t0[12], t1[12];  // run after run: upper and lower pixel row
+  template <int J0, int J1, int K>
+  __device__ __forceinline__ void read(const char* at, int Lp4) {
+    const float* p0 = reinterpret_cast<const float*>(at);
+    const float* p1 = reinterpret_cast<const float*>(at + Lp4);
 #pragma unroll
-  for (int i = 0; i < n; ++i)
-    tr[17 * (J0 + i)] = fmaf(w11, t1[i + 1], fmaf(w01, t1[i], fmaf(w10, t0[i + 1], w00 * t0[i])));
-}
-// One angle at 8 consecutive rows: they wrap to the next image row of the
-// search grid after A rows and every S further ones.  at: byte address of the
-// angle's top-left tap at shift offset 0; o[k] the offset of run k's first shift.
+    for (int i = 0; i <= J1 - J0; ++i) {
+      t0[J0 + K + i] = p0[i];
+      t1[J0 + K + i] = p1[i];
+    }
+  }
+  // row j's sample goes to tr[17 j] (written here: handed back, the values
+  // are copied where the patterns' branches meet)
+  template <int J0, int J1, int K>
+  __device__ __forceinline__ void sample(const Tap& tap, float* tr) const {
+#pragma unroll
+    for (int i = J0 + K; i < J1 + K; ++i) tr[17 * (i - K)] = tap(t0[i], t0[i + 1], t1[i], t1[i + 1]);
+  }
+};
+// Two angles at 8 consecutive rows: they wrap to the next image row of the search
+// grid after A rows and every S further ones.  at: byte address of each
+// angle's top-left tap at shift offset 0; o[k] the offset of run k's first
+// shift.  All taps are read before the first sample is written: the compiler
+// does not move a read across a write to the same LDS (one angle's at a
+// time: 1 % slower).
 template <int A, int S>
-__device__ __forceinline__ void sample_pattern(const char* at, const int (&o)[4], int Lp4, float w00, float w10, float w01,
-                                               float w11, float* tr) {
+__device__ __forceinline__ void sample_pattern(const char* const (&at)[2], const int (&o)[4], int Lp4,
+                                               const Tap (&tap)[2], float* tr) {
   constexpr int e0 = A < 8 ? A : 8, e1 = A + S < 8 ? A + S : 8, e2 = A + 2 * S < 8 ? A + 2 * S : 8;
   static_assert(A + 3 * S >= 8, "at most four runs");
-  sample_run<0, e0>(at + o[0], Lp4, w00, w10, w01, w11, tr);
-  if constexpr (e0 < 8) sample_run<e0, e1>(at + o[1], Lp4, w00, w10, w01, w11, tr);
-  if constexpr (e1 < 8) sample_run<e1, e2>(at + o[2], Lp4, w00, w10, w01, w11, tr);
-  if constexpr (e2 < 8) sample_run<e2, 8>(at + o[3], Lp4, w00, w10, w01, w11, tr);
+  TapColumns t[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    t[e].template read<0, e0, 0>(at[e] + o[0], Lp4);
+    if constexpr (e0 < 8) t[e].template read<e0, e1, 1>(at[e] + o[1], Lp4);
+    if constexpr (e1 < 8) t[e].template read<e1, e2, 2>(at[e] + o[2], Lp4);
+    if constexpr (e2 < 8) t[e].template read<e2, 8, 3>(at[e] + o[3], Lp4);
+  }
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    t[e].template sample<0, e0, 0>(tap[e], tr + 8 * e);
+    if constexpr (e0 < 8) t[e].template sample<e0, e1, 1>(tap[e], tr + 8 * e);
+    if constexpr (e1 < 8) t[e].template sample<e1, e2, 2>(tap[e], tr + 8 * e);
+    if constexpr (e2 < 8) t[e].template sample<e2, 8, 3>(tap[e], tr + 8 * e);
+  }
 }
 
 // As sample_ring for 8 consecutive rows s0 .. s0 + 7 of the search grid (s =
@@ -251,45 +283,48 @@ __device__ __forceinline__ void sample_runs(const float* img, const CosSin* cs, 
   }
   // 8 S + A of sample_pattern; grids of more than 7 columns wrap as S = 7 does
   const int pattern = S1 == 1 ? 0 : (a >= 8 ? 64 : 8 * (S1 < 7 ? S1 : 7) + a);
-  const CosSin* cp = cs + 2 * l;
   float* tr = reinterpret_cast<float*>(my);  // [64 (l, row)][17]: row pitch 17 spreads the banks
 #pragma unroll
   for (int hf = 0; hf < 2; ++hf) {
     wave_sync();  // the scratch's earlier readers are done
+    Tap tap[2];
+    const char* at[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      const CosSin c = cp[16 * (2 * r + hf) + e];
-      const char* at = reinterpret_cast<const char*>(img) + polar_offset(rr, c, Lp4);
-      float w00, w10, w01, w11;
-      polar_weights(rr, c, w00, w10, w01, w11);
-      float* out = tr + l * 8 * 17 + 8 * e + r;
-      auto take = [&](auto a_c, auto s_c) {
-        sample_pattern<decltype(a_c)::value, decltype(s_c)::value>(at, o, Lp4, w00, w10, w01, w11, out);
-      };
-      switch (pattern) {  // wave-uniform
-        case 0: {  // one shift: the particle's own row is one of the 8, all take its sample
-          const float v = bilin4w(reinterpret_cast<const float*>(at + base4), 0, Lp4, w00, w10, w01, w11);
+      tap[e].set(rr, cs[16 * (2 * r + hf) + 2 * l + e], Lp4);
+      at[e] = reinterpret_cast<const char*>(img) + tap[e].off;
+    }
+    float* out = tr + l * 8 * 17 + r;
+    auto take = [&](auto a_c, auto s_c) {
+      sample_pattern<decltype(a_c)::value, decltype(s_c)::value>(at, o, Lp4, tap, out);
+    };
+    switch (pattern) {  // wave-uniform
+      case 0:  // one shift: the particle's own row is one of the 8, all take its sample
 #pragma unroll
-          for (int j = 0; j < 8; ++j) out[17 * j] = v;
-          break;
+        for (int e = 0; e < 2; ++e) {
+          const float* p0 = reinterpret_cast<const float*>(at[e] + base4);
+          const float* p1 = reinterpret_cast<const float*>(at[e] + base4 + Lp4);
+          const float v = tap[e](p0[0], p0[1], p1[0], p1[1]);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) out[17 * j + 8 * e] = v;
         }
-        case 25: take(std::integral_constant<int, 1>{}, std::integral_constant<int, 3>{}); break;
-        case 26: take(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{}); break;
-        case 27: take(std::integral_constant<int, 3>{}, std::integral_constant<int, 3>{}); break;
-        case 41: take(std::integral_constant<int, 1>{}, std::integral_constant<int, 5>{}); break;
-        case 42: take(std::integral_constant<int, 2>{}, std::integral_constant<int, 5>{}); break;
-        case 43: take(std::integral_constant<int, 3>{}, std::integral_constant<int, 5>{}); break;
-        case 44: take(std::integral_constant<int, 4>{}, std::integral_constant<int, 5>{}); break;
-        case 45: take(std::integral_constant<int, 5>{}, std::integral_constant<int, 5>{}); break;
-        case 57: take(std::integral_constant<int, 1>{}, std::integral_constant<int, 7>{}); break;
-        case 58: take(std::integral_constant<int, 2>{}, std::integral_constant<int, 7>{}); break;
-        case 59: take(std::integral_constant<int, 3>{}, std::integral_constant<int, 7>{}); break;
-        case 60: take(std::integral_constant<int, 4>{}, std::integral_constant<int, 7>{}); break;
-        case 61: take(std::integral_constant<int, 5>{}, std::integral_constant<int, 7>{}); break;
-        case 62: take(std::integral_constant<int, 6>{}, std::integral_constant<int, 7>{}); break;
-        case 63: take(std::integral_constant<int, 7>{}, std::integral_constant<int, 7>{}); break;
-        default: take(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
-      }
+        break;
+      case 25: take(std::integral_constant<int, 1>{}, std::integral_constant<int, 3>{}); break;
+      case 26: take(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{}); break;
+      case 27: take(std::integral_constant<int, 3>{}, std::integral_constant<int, 3>{}); break;
+      case 41: take(std::integral_constant<int, 1>{}, std::integral_constant<int, 5>{}); break;
+      case 42: take(std::integral_constant<int, 2>{}, std::integral_constant<int, 5>{}); break;
+      case 43: take(std::integral_constant<int, 3>{}, std::integral_constant<int, 5>{}); break;
+      case 44: take(std::integral_constant<int, 4>{}, std::integral_constant<int, 5>{}); break;
+      case 45: take(std::integral_constant<int, 5>{}, std::integral_constant<int, 5>{}); break;
+      case 57: take(std::integral_constant<int, 1>{}, std::integral_constant<int, 7>{}); break;
+      case 58: take(std::integral_constant<int, 2>{}, std::integral_constant<int, 7>{}); break;
+      case 59: take(std::integral_constant<int, 3>{}, std::integral_constant<int, 7>{}); break;
+      case 60: take(std::integral_constant<int, 4>{}, std::integral_constant<int, 7>{}); break;
+      case 61: take(std::integral_constant<int, 5>{}, std::integral_constant<int, 7>{}); break;
+      case 62: take(std::integral_constant<int, 6>{}, std::integral_constant<int, 7>{}); break;
+      case 63: take(std::integral_constant<int, 7>{}, std::integral_constant<int, 7>{}); break;
+      default: take(std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
     }
     wave_sync();
 #pragma unroll
