@@ -38,21 +38,17 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
+# profile groups of a pass (corr, merge: every pair evaluated)
+GROUPS = ("polar", "bound", "tighten", "fine", "corr", "merge", "rescore", "averages")
 METRIC = "aligned particles/s (L=76,K=100,±3px); FP32 vs BF16-MFMA; p50/p99 latency"
-FP32_MATRIX_PEAK = 157.3   # TFLOP/s, MI355X dense FP32 matrix
 BF16_MATRIX_PEAK = 2500.0  # TFLOP/s, dense
-FP32_VECTOR_PEAK = 157.3   # TFLOP/s, MI355X FP32 vector (published; counts packed FP32)
-# reachable without packed FP32 (which the library's compile flags disable): 256 CUs x 4 SIMDs
-# x 16 lanes x 2 (FMA) x 2.4 GHz
-FP32_VALU_PEAK = 78.6
 HBM_PEAK = 8000.0          # GB/s
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "mra_c1_hbm_traffic.md")
 CSRC = os.path.join(ROOT, "paper_2011_05755_amd", "csrc")
 # sources each kernel's code is built from (a change to any of them voids
 # counter figures taken before it)
 KERNEL_SOURCES = {
-    "k_corr": ["corr_impl.h", "k_corr.hip", "k_corr_fp32.hip", "k_corr_bf16.hip", "k_corr_fp16.hip", "mra_common.h",
-               "mra_fft.h"],
+    "k_bound": ["bound_impl.h", "corr_impl.h", "k_bound.hip", "mra_common.h", "mra_fft.h"],
     "k_polar_fft": ["k_polar.hip", "polar_impl.h", "mra_fft.h", "mra_common.h"],
     "k_avg": ["k_avg.hip", "mra_common.h"],
 }
@@ -90,12 +86,6 @@ def corr_flops_per_row_ref(R: int) -> float:
     # per (particle row, reference): 128 frequency slots x 4 real dot products
     # of length R (both mirrors), 2 flops per multiply-add
     return 128 * 4 * R * 2.0
-
-
-def ifft_flops_per_row_ref() -> float:
-    # 256-point complex inverse FFT as 16 x 16: 32 DFT16 (8 DFT4 = 128 adds,
-    # 7 general complex products = 42 flops) + 225 inter-pass complex products
-    return 32 * (128 + 42) + 225 * 6.0
 
 
 def run_serving(args, bench_ctx, dev) -> dict:
@@ -215,7 +205,7 @@ def main() -> int:
         torch.cuda.synchronize()
         dt = time.perf_counter() - t0
         per_step = [marks[k].elapsed_time(marks[k + 1]) for k in range(args.steps)]
-        kern = {name: ctx.profile_read(name) for name in ("polar", "corr", "merge", "rescore", "averages")}
+        kern = {name: ctx.profile_read(name) for name in GROUPS}
         ctx.profile(False)
         ms = dt * 1000.0 / args.steps
         log(f"{form}: {ms:.2f} ms/step (median {statistics.median(per_step):.2f}), {N / (ms / 1000):.4g} "
@@ -248,42 +238,45 @@ def main() -> int:
         log(f"fp32 with H2D: {dt * 1000:.1f} ms, {N / dt:.4g} particles/s")
         del host, staged
 
-    # ---- roofline of the dominant kernel (fused correlation, FP32 form) ----
+    # ---- roofline of the contraction of every (row, reference) pair (k_bound:
+    # 16-bit matrix cores in every form) ----
     head = "fp32" if "fp32" in results else forms[0]
-    corr_ms, corr_n = results[head]["kern"]["corr"]
-    corr_flops = corr_flops_per_row_ref(R) * N * S * K * args.steps
-    achieved = corr_flops / (corr_ms / 1000.0) / 1e12
-    peak = FP32_MATRIX_PEAK if head == "fp32" else BF16_MATRIX_PEAK
+    bound_flops = corr_flops_per_row_ref(R) * N * S * K * args.steps
     R4 = (R + 3) // 4
-    padded = corr_flops * (4 * R4) / R
-    roofline = dict(bound="mfma", achieved=round(achieved, 2), peak=peak, unit="TFLOP/s",
-                    frac=round(achieved / peak, 4),
-                    frac_padded=round(padded / (corr_ms / 1000.0) / 1e12 / peak, 4),
-                    traffic=traffic_from_profile("k_corr", head, args.workspace_gib),
+
+    def bound_roofline(form):
+        ms, n = results[form]["kern"]["bound"]
+        achieved = bound_flops / (ms / 1000.0) / 1e12
+        return dict(bound="mfma", achieved=round(achieved, 2), peak=BF16_MATRIX_PEAK, unit="TFLOP/s",
+                    frac=round(achieved / BF16_MATRIX_PEAK, 4),
+                    frac_padded=round(achieved * 4 * R4 / R / BF16_MATRIX_PEAK, 4),
+                    traffic=traffic_from_profile("k_bound", form, args.workspace_gib),
                     traffic_unit="bytes per launch (HBM, counter-measured)",
-                    kernel="k_corr", launches_per_step=corr_n // args.steps,
-                    avg_launch_ms=round(corr_ms / corr_n, 4),
+                    kernel="k_bound", launches_per_step=n // args.steps,
+                    avg_launch_ms=round(ms / n, 4),
                     flops_per_row_ref=corr_flops_per_row_ref(R))
+    roofline = bound_roofline(head)
+
+    # ring spectra are written as 2-byte values in every form
+    polar_bytes = N * L * L * 4 + N * S * 512 * R
+
+    def polar_gbps(form):
+        return polar_bytes * args.steps / (results[form]["kern"]["polar"][0] / 1000.0) / 1e9
 
     extra = {}
     for form in results:
         if form == head:
             continue
         r = results[form]
-        cms, cn = r["kern"]["corr"]
-        pms, _ = r["kern"]["polar"]
-        # 16-bit forms: ring spectra written as 2-byte values
-        pol16 = (N * L * L * 4 + N * S * 512 * R) * args.steps / (pms / 1000.0) / 1e9
-        alu = ifft_flops_per_row_ref() * N * S * K * args.steps / (cms / 1000.0) / 1e12
-        mf = corr_flops_per_row_ref(R) * N * S * K * args.steps / (cms / 1000.0) / 1e12
+        br = bound_roofline(form)
         extra[form] = dict(value=round(r["value"], 1), ms_per_step=round(r["ms"], 3),
                            median_ms_per_step=round(r["median_ms"], 3),
                            speedup_vs_fp32=round(results[head]["ms"] / r["ms"], 3) if head == "fp32" else None,
-                           corr_avg_launch_ms=round(cms / cn, 4),
-                           corr_matrix_tflops=round(mf, 2), corr_matrix_frac=round(mf / BF16_MATRIX_PEAK, 4),
-                           corr_ifft_valu_tflops=round(alu, 2), corr_ifft_valu_frac=round(alu / FP32_VALU_PEAK, 4),
-                           corr_traffic_bytes_per_launch=traffic_from_profile("k_corr", form, args.workspace_gib),
-                           polar_hbm_gbps=round(pol16, 1), polar_hbm_frac=round(pol16 / HBM_PEAK, 4))
+                           bound_avg_launch_ms=br["avg_launch_ms"],
+                           bound_matrix_tflops=br["achieved"], bound_matrix_frac=br["frac"],
+                           bound_traffic_bytes_per_launch=br["traffic"],
+                           polar_hbm_gbps=round(polar_gbps(form), 1),
+                           polar_hbm_frac=round(polar_gbps(form) / HBM_PEAK, 4))
 
     kernels = {form: {k: round(v[0] / args.steps, 3) for k, v in r["kern"].items() if v[1]}
                for form, r in results.items()}
@@ -292,18 +285,13 @@ def main() -> int:
     def gbps(nbytes, key):
         t, n = results[head]["kern"][key]
         return nbytes * args.steps / (t / 1000.0) / 1e9 if n else float("nan")
-    polar_bytes = N * L * L * 4 + N * S * 1024 * R        # images read + ring spectra written
     avg_bytes = N * L * L * 4 + 2 * K * L * L * 4         # images read + averages read and written
-    ifft = ifft_flops_per_row_ref() * N * S * K * args.steps / (corr_ms / 1000.0) / 1e12
     rooflines = {
-        "k_polar_fft": dict(bound="hbm", achieved=round(gbps(polar_bytes, "polar"), 1), peak=HBM_PEAK,
-                            unit="GB/s", frac=round(gbps(polar_bytes, "polar") / HBM_PEAK, 4),
+        "k_polar_fft": dict(bound="hbm", achieved=round(polar_gbps(head), 1), peak=HBM_PEAK,
+                            unit="GB/s", frac=round(polar_gbps(head) / HBM_PEAK, 4),
                             algorithmic_bytes_per_step=polar_bytes),
         "k_avg": dict(bound="hbm", achieved=round(gbps(avg_bytes, "averages"), 1), peak=HBM_PEAK, unit="GB/s",
                       frac=round(gbps(avg_bytes, "averages") / HBM_PEAK, 4), algorithmic_bytes_per_step=avg_bytes),
-        "k_corr_ifft": dict(bound="alu", achieved=round(ifft, 2), peak=FP32_VALU_PEAK, unit="TFLOP/s",
-                            frac=round(ifft / FP32_VALU_PEAK, 4), flops_per_row_ref=ifft_flops_per_row_ref(),
-                            note="inverse FFT share of the fused correlation kernel, same launches"),
     }
 
     # ---- serving: continuous batching on bounded Poisson traces (BF16) ----

@@ -7,7 +7,7 @@ blob references (random rotation, integer shift within +-3, mirror with
 p = 0.5, SNR 0.05), rings 1..36 x 256 angles, K in --refs.  For every K and
 form, one alignment pass plus the class-average update is timed (wall clock
 over --reps passes after a warm-up, references resident), with the
-correlation kernel's own time from HIP events.  One JSON line per (K, form).
+bound and evaluation kernels' own times from HIP events.  One JSON line per (K, form).
 
     python -m bench.ksweep --refs 10,20,50,100,200 --forms fp32,bf16
 """
@@ -63,16 +63,18 @@ def main(argv=None) -> int:
                 ctx.update_averages(rid, parts, out, avg)
             torch.cuda.synchronize()
             wall = (time.perf_counter() - t0) / args.reps
-            corr_ms, launches = ctx.profile_read("corr")
-            polar_ms, _ = ctx.profile_read("polar")
+            polar_ms, launches = ctx.profile_read("polar")
+            bound_ms, _ = ctx.profile_read("bound")
+            fine_ms = sum(ctx.profile_read(g)[0] for g in ("tighten", "fine"))
             ctx.profile(False)
             ctx.unload_refs(rid)
             print(json.dumps(dict(
                 workload=f"MRA pass + average update: {args.N} particles, L={L}, K={K}, shifts +-{T} (49), "
                          f"both mirrors, rings {r_min}..{r_max} x 256",
                 K=K, form=form, wall_s=round(wall, 4), particles_per_s=round(args.N / wall, 1),
-                corr_ms_per_pass=round(corr_ms / args.reps, 2), polar_ms_per_pass=round(polar_ms / args.reps, 2),
-                corr_launches_per_pass=launches // args.reps)), flush=True)
+                bound_ms_per_pass=round(bound_ms / args.reps, 2), fine_ms_per_pass=round(fine_ms / args.reps, 2),
+                polar_ms_per_pass=round(polar_ms / args.reps, 2),
+                chunks_per_pass=launches // args.reps)), flush=True)
             log(f"K={K} {form}: {wall * 1e3:.1f} ms per pass")
     ctx.close()
     return 0
