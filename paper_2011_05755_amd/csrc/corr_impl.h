@@ -172,18 +172,25 @@ struct Fp32Contract {
   static constexpr int LAYOUT = (NW == 8 && RES) ? kRingPerm : kSlotMajor;
   float areg[RES ? SPW : 1][RES ? MAXR : 1];
 
-  // the lane's reference operand of slot `slot` in reference tile kt
+  // the lane's reference operand of slot `slot` in reference tile kt, in
+  // 16-byte loads (with one load per element and none before the particle
+  // operand's, a launch of one tile pair per CU took 50 us instead of 29)
   __device__ __forceinline__ void load_b(const CorrArgs& a, int kt, int slot, int ln, float (&dst)[MAXR]) const {
-    const int R4 = EXACT ? MAXR : a.R4;
     const float* bp = b32_lane(a, kt * kRefTile + ((ln >> 1) & 7), slot, ln);
+    const int last = b32_pitch(a.R4) / 4 - 1;
 #pragma unroll
-    for (int t = 0; t < MAXR; ++t) dst[t] = bp[t < R4 ? t : R4 - 1];  // unconditional
+    for (int q = 0; q < (MAXR + 3) / 4; ++q) {  // unconditional, whole quads (elements t >= R4 are not used)
+      const f32x4 v = *reinterpret_cast<const f32x4*>(bp + 4 * (q < last ? q : last));
+#pragma unroll
+      for (int t = 4 * q; t < 4 * q + 4; ++t)
+        if (t < MAXR) dst[t] = v[t & 3];
+    }
   }
-  // PRE (8 waves, resident operand, ring count exact): the reference
+  // PRE (8 waves, resident operand): the reference
   // operand of the wave's first slot of reference tile kt is loaded before
   // the inverse FFT of the previous tile, so its latency passes under it
   // (one slot: the registers of two would spill in these forms)
-  static constexpr bool PRE = RES && NW == 8 && EXACT;
+  static constexpr bool PRE = RES && NW == 8;
   float bpre[PRE ? MAXR : 1];
   __device__ __forceinline__ void prefetch(const CorrArgs& a, int kt, int w, int ln) {
     if constexpr (PRE) load_b(a, kt, w, ln, bpre);

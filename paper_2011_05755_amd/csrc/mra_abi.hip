@@ -391,14 +391,14 @@ int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned
 
 // A call of few particles takes the unpruned way: with every pair of a few
 // row and reference tiles spread over the CUs it ends before the pruned way's
-// chain of dependent steps does.  At 76 px, 100 references, +-3 (91 tile pairs
-// per particle, 256 CUs), unpruned against pruned: FP32 8 particles 144 / 241
-// us, 16 particles 288 / 284, 24 particles 509 / 403; BF16 32 particles 158 /
-// 316 us, 64 particles 258 / 246; at 90 px, +-2 BF16 64 particles (10 tile pairs
-// per CU) 165 / 161; at 64 px, +-2, 20 references FP32 50 particles 154 / 162.
+// chain of dependent steps does.  Unpruned against pruned (us; tile pairs per
+// CU): FP32 76 px, 100 references, +-3 16 particles 134 / 283 (6), 40: 234 / 311
+// (14); 64 px, +-2, 20 references, 200 particles 234 / 242 (7); 90 px, +-2, 100
+// references, 32 particles 139 / 187 (5), 64: 229 / 204 (10).  BF16 76 px 32
+// particles 158 / 316 (11), 64: 258 / 246 (23); 90 px 64 particles 165 / 161 (10).
 bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N) {
   const int64_t tiles = (N * p.S + kRowTile - 1) / kRowTile * rs.n_kt;
-  return tiles <= (rs.g.precision == kFP32 ? 5 : 12) * (int64_t)c->n_cu;
+  return tiles <= (rs.g.precision == kFP32 ? 8 : 12) * (int64_t)c->n_cu;
 }
 
 // Particles per chunk within the workspace cap on the pruned path, or 0 when
