@@ -654,6 +654,7 @@ __device__ __forceinline__ int excluded_at(int e, int k, int s, int S, int M) {
 // Particle n's outputs from its best CC and flat index (2^31 - 1: none).
 __device__ __forceinline__ void write_result(const ResultArgs& a, int n, float best, int bi) {
   const int64_t o = a.out_off + n;
+  if (!(best == best)) bi = 0x7fffffff;  // (FP16: the particle does not scale into it)
   if (a.runner_up) {  // second pass: the best over every candidate but the winner
     a.cc2[o] = bi == 0x7fffffff ? NAN : best;
     return;

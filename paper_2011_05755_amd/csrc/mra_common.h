@@ -77,16 +77,19 @@ __host__ __device__ constexpr int b32_pitch(int R4) { return (R4 + 3) & ~3; }
 
 // Power-of-two FP16 scale of a particle's operand: |a +- b| <= 2 * 256 *
 // max|pixel| is mapped below 2^14.
-__device__ __forceinline__ float fp16_operand_scale(float maxabs) {
+__device__ __forceinline__ int fp16_operand_exponent(float maxabs) {
   const float m = fmaxf(maxabs * 512.f, 1e-30f);
-  return ldexpf(1.f, 14 - (int)ceilf(log2f(m)));
+  return 14 - (int)ceilf(log2f(m));
 }
+__device__ __forceinline__ float fp16_operand_scale(float maxabs) { return ldexpf(1.f, fp16_operand_exponent(maxabs)); }
 
 // A value in the scaled units of a particle with max |pixel| mx against a
-// refset of scale b_scale, in its own: one power of two at a time (their
-// product may leave the float range).
+// refset of scale b_scale, in its own: by the sum of the exponents (either
+// power, or their product, may take a value out of the float range that is within it
+// at the end).  NaN where either does not scale into FP16: then v means nothing.
 __device__ __forceinline__ float fp16_value(float v, float mx, float b_scale) {
-  return v * (1.f / fp16_operand_scale(mx)) * (1.f / b_scale);
+  if (!(mx * 512.f < INFINITY && b_scale < INFINITY)) return NAN;
+  return ldexpf(v, -(fp16_operand_exponent(mx) + ilogbf(b_scale)));
 }
 
 // Entry of the particle sampling stencil for ring r and angle j (FP64
