@@ -37,6 +37,7 @@ void* g_scratch_ptr[kMaxDevices] = {};
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
+  bool keep = false;   // lives across the steps of the present call
 };
 
 struct Refset {
@@ -129,8 +130,10 @@ void* alloc(mra_ctx* c, size_t bytes, const char* what) {
   return p;
 }
 
-void* ws_get(mra_ctx* c, const std::string& name, size_t bytes) {
+// A workspace buffer, grown on demand.
+void* ws_get(mra_ctx* c, const std::string& name, size_t bytes, bool keep = false) {
   DevBuf& b = c->ws[name];
+  b.keep = keep;
   if (b.bytes < bytes) {
     uint64_t total = bytes;  // the workspace after this buffer grows
     for (const auto& kv : c->ws)
@@ -145,6 +148,36 @@ void* ws_get(mra_ctx* c, const std::string& name, size_t bytes) {
     b.bytes = bytes;
   }
   return b.p;
+}
+
+// Before a step (a reference preparation, an alignment chunk, a batched wave, an
+// average update) takes the buffers `need`: buffers stay for later steps as long as
+// the cap has room; where it has not, all but the kept ones are given back, so that
+// a step that fits the cap by itself is never refused for what others left.
+typedef std::vector<std::pair<std::string, size_t>> WsNeed;
+void ws_step(mra_ctx* c, const WsNeed& need) {
+  uint64_t total = 0;  // the workspace with the step's buffers grown
+  for (const auto& kv : c->ws) total += kv.second.bytes;
+  for (const auto& n : need) {
+    const auto it = c->ws.find(n.first);
+    const size_t have = it == c->ws.end() ? 0 : it->second.bytes;
+    if (n.second > have) total += n.second - have;
+  }
+  if (total <= c->cap) return;
+  hip_check(c, hipStreamSynchronize(c->stream), "sync");
+  for (auto& kv : c->ws) {
+    if (kv.second.keep || !kv.second.p) continue;
+    hip_check(c, hipFree(kv.second.p), "hipFree");
+    kv.second = DevBuf{};
+  }
+}
+
+// Workspace that no step gives back.
+uint64_t ws_kept(const mra_ctx* c) {
+  uint64_t total = 0;
+  for (const auto& kv : c->ws)
+    if (kv.second.keep) total += kv.second.bytes;
+  return total;
 }
 
 // Runs `launch` between two events on the context stream when profiling.
@@ -361,20 +394,14 @@ size_t carve_chunk(const Refset& rs, const Plan& p, int64_t nc, bool pruned, boo
 
 // Buffers of a chunk from the context's workspace (grown on demand).
 ChunkBufs ws_chunk(mra_ctx* c, const Refset& rs, const Plan& p, int64_t nc, bool pruned, const mra_result* out) {
+  WsNeed need;
+  layout_chunk(rs, p, nc, pruned, out && out->cc2, c->n_cu, [&](const char* name, size_t bytes) -> void* {
+    need.emplace_back(name, bytes);
+    return nullptr;
+  });
+  ws_step(c, need);
   return layout_chunk(rs, p, nc, pruned, out && out->cc2, c->n_cu,
                       [&](const char* name, size_t bytes) { return ws_get(c, name, bytes); });
-}
-
-// Workspace held by buffers that a chunk does not use (and so cannot reuse).
-uint64_t ws_other(mra_ctx* c) {
-  uint64_t total = 0;
-  for (const auto& kv : c->ws) {
-    bool chunk_buf = false;
-    for (const char* n : {"A", "ub", "ub_hi", "rowkey", "rownorm", "scratch", "row_cc", "row_idx", "maxabs", "over", "win"})
-      chunk_buf |= kv.first == n;
-    if (!chunk_buf) total += kv.second.bytes;
-  }
-  return total;
 }
 
 // bytes of operand and bounds per particle
@@ -401,18 +428,8 @@ bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N) {
   return tiles <= (rs.g.precision == kFP32 ? 8 : 12) * (int64_t)c->n_cu;
 }
 
-// Particles per chunk within the workspace cap on the pruned path, or 0 when
-// its bounds and scratch do not fit (the call then takes the unpruned one).
-int64_t pruned_chunk(mra_ctx* c, const Refset& rs, const Plan& p, int64_t N, bool cc2) {
-  if (!rs.prune || few_pairs(c, rs, p, N)) return 0;
-  int64_t n = std::min<int64_t>({chunk_particles(c, rs, p, true), (int64_t)(INT32_MAX / p.S / 2), N});
-  const uint64_t other = ws_other(c);
-  while (n > 0 && other + carve_chunk(rs, p, n, true, cc2, c->n_cu, nullptr, nullptr) > c->cap) n /= 2;
-  return n;
-}
-
-// Largest chunk whose buffers fit `bytes` of scratch (0 if not one particle).
-int64_t scratch_chunk(const Refset& rs, const Plan& p, bool pruned, bool cc2, int n_cu, size_t bytes) {
+// Largest chunk whose buffers fit `bytes` (0 if not one particle).
+int64_t fitting_chunk(const Refset& rs, const Plan& p, bool pruned, bool cc2, int n_cu, size_t bytes) {
   if (carve_chunk(rs, p, 1, pruned, cc2, n_cu, nullptr, nullptr) > bytes) return 0;
   // the buffers grow with the chunk: bisect for the largest that fits
   int64_t lo = 1, hi = std::min<int64_t>(INT32_MAX / p.S / 2, (int64_t)(bytes / ((size_t)p.S * 8)) + 1);
@@ -422,6 +439,20 @@ int64_t scratch_chunk(const Refset& rs, const Plan& p, bool pruned, bool cc2, in
     else hi = mid - 1;
   }
   return lo;
+}
+
+// Particles per chunk on the pruned path, or 0 when not one particle's bounds and
+// scratch fit (the call then takes the unpruned one).  All that a chunk holds
+// takes at most half the cap, as the unpruned operand does: the other half is left
+// to the steps beside it (reference preparation, averages).
+int64_t pruned_chunk(mra_ctx* c, const Refset& rs, const Plan& p, int64_t N, bool cc2) {
+  if (!rs.prune || few_pairs(c, rs, p, N)) return 0;
+  const int64_t most = std::min<int64_t>(INT32_MAX / p.S / 2, N);
+  const uint64_t room = c->cap - std::min(c->cap, ws_kept(c));
+  if (rs.chunk <= 0) return std::min(most, fitting_chunk(rs, p, true, cc2, c->n_cu, std::min(c->cap / 2, room)));
+  int64_t n = std::min<int64_t>(rs.chunk, most);
+  while (n > 0 && carve_chunk(rs, p, n, true, cc2, c->n_cu, nullptr, nullptr) > room) n /= 2;
+  return n;
 }
 
 // Sub-step angles of particles n0 .. n0 + nc - 1 from their final parameters.
@@ -649,14 +680,14 @@ void run_single(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts,
   if (out->psi_frac) refine_chunk(c, rs, p, parts, 0, N, out);
 }
 
-// A stack chunk by chunk, in the context's workspace.
-void align_stack(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, int64_t N, const mra_result* out,
-                 float* table) {
+// Particles first .. first + N - 1 of a stack chunk by chunk, in the context's workspace.
+void align_stack(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, int64_t first, int64_t N,
+                 const mra_result* out, float* table) {
   int64_t step = table ? 0 : pruned_chunk(c, rs, p, N, out->cc2 != nullptr);
   const bool pruned = step > 0;
   if (!pruned) step = std::min<int64_t>(chunk_particles(c, rs, p, false), (int64_t)(INT32_MAX / p.S / 2));
-  for (int64_t n0 = 0; n0 < N; n0 += step) {
-    const int nc = (int)std::min<int64_t>(step, N - n0);
+  for (int64_t n0 = first; n0 < first + N; n0 += step) {
+    const int nc = (int)std::min<int64_t>(step, first + N - n0);
     const ChunkBufs b = ws_chunk(c, rs, p, nc, pruned, out);
     if (pruned)
       run_chunk(c, rs, p, parts, n0, nc, out, b);
@@ -681,13 +712,13 @@ void align_impl(mra_ctx* c, int32_t id, const float* parts, int64_t N, int T, co
     return;
   }
   if (!noalloc) {
-    align_stack(c, rs, p, parts, N, out, table);
+    align_stack(c, rs, p, parts, 0, N, out, table);
     return;
   }
   if (!c->scratch) throw Fail{MRA_E_DEVICE, "no-allocation scratch not resolved on this device"};
-  int64_t step = rs.prune && !few_pairs(c, rs, p, N) ? scratch_chunk(rs, p, true, out->cc2 != nullptr, c->n_cu, kScratchBytes) : 0;
+  int64_t step = rs.prune && !few_pairs(c, rs, p, N) ? fitting_chunk(rs, p, true, out->cc2 != nullptr, c->n_cu, kScratchBytes) : 0;
   const bool pruned = step > 0;
-  if (!pruned) step = scratch_chunk(rs, p, false, out->cc2 != nullptr, c->n_cu, kScratchBytes);
+  if (!pruned) step = fitting_chunk(rs, p, false, out->cc2 != nullptr, c->n_cu, kScratchBytes);
   if (step < 1)
     throw Fail{MRA_E_INVAL, "one particle's operand exceeds the " + std::to_string(kScratchBytes >> 20) +
                                 " MiB no-allocation scratch"};
@@ -709,8 +740,65 @@ struct Piece {
   int nc;
 };
 
+// Device buffers of a batched wave, those of the pieces end to end.
+struct WaveBufs {
+  size_t parts = 0, tile = 0;  // particles, largest scratch tile
+  int grid = 0;                // evaluation workgroups
+  char* A = nullptr;
+  float *ub = nullptr, *ub_hi = nullptr, *rownorm = nullptr, *scratch = nullptr, *rcc = nullptr, *maxabs = nullptr;
+  unsigned long long* rowkey = nullptr;
+  int* ridx = nullptr;
+  FineOver over{};
+};
+
+// Calls take(name, bytes) for every buffer of a wave.
+template <class Take>
+WaveBufs layout_wave(const std::vector<Piece>& w, int n_cu, Take take) {
+  WaveBufs b;
+  const int prec = w[0].rs->g.precision;
+  size_t a_bytes = 0, ub_floats = 0, rows = 0;
+  int max_S = 0, units = 0;
+  for (const Piece& pc : w) {
+    const size_t r = (size_t)pc.nc * pc.p.S;
+    a_bytes += (r + kRowTile - 1) / kRowTile * tile_bytes_of(*pc.rs, true);
+    ub_floats += r * ub_pitch(*pc.rs);
+    rows += r;
+    b.parts += pc.nc;
+    max_S = std::max(max_S, pc.p.S);
+    units = std::max(units, fine_units(pc.p.S, pc.rs->K));
+    b.tile = std::max(b.tile, scratch_tile_bytes(*pc.rs));
+  }
+  b.grid = fine_grid(prec, (int64_t)b.parts, n_cu);
+  b.A = (char*)take("A", a_bytes);
+  b.ub = (float*)take("ub", ub_floats * sizeof(float));
+  b.ub_hi = (float*)take("ub_hi", ub_floats * sizeof(float));
+  b.rowkey = (unsigned long long*)take("rowkey", (rows + 1) * sizeof(unsigned long long));
+  if (prec == kFP32) {
+    b.rownorm = (float*)take("rownorm", 2 * rows * sizeof(float));
+    b.scratch = (float*)take("scratch", b.grid * b.tile);
+  } else {
+    b.rcc = (float*)take("row_cc", rows * sizeof(float));
+    b.ridx = (int*)take("row_idx", rows * sizeof(int));
+  }
+  b.over = take_over((int64_t)b.parts, max_S, units, n_cu, take);
+  if (prec != kBF16) b.maxabs = (float*)take("maxabs", b.parts * sizeof(float));
+  return b;
+}
+
 void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& w) {
   hipStream_t st = c->stream;
+  uint64_t total = ws_kept(c);
+  WsNeed need;
+  layout_wave(w, c->n_cu, [&](const char* name, size_t bytes) -> void* {
+    total += bytes;
+    need.emplace_back(name, bytes);
+    return nullptr;
+  });
+  if (total > c->cap) {  // what a wave holds besides its operand and bounds does not fit: piece by piece
+    for (const Piece& pc : w)
+      align_stack(c, *pc.rs, pc.p, stacks[pc.stack].parts, pc.n0, pc.nc, &stacks[pc.stack].out, nullptr);
+    return;
+  }
   if (w.size() == 1) {  // one piece fills the chip by itself: the plain per-chunk launches
     const Piece& pc = w[0];
     const mra_stack& sk = stacks[pc.stack];
@@ -718,30 +806,16 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     return;
   }
   const int prec = w[0].rs->g.precision, np = (int)w.size();
-  size_t a_bytes = 0, ub_floats = 0, rows = 0, parts = 0, tile = 0;
-  int max_S = 0, units = 0;
-  for (const Piece& pc : w) {
-    const size_t r = (size_t)pc.nc * pc.p.S;
-    a_bytes += (r + kRowTile - 1) / kRowTile * tile_bytes_of(*pc.rs, true);
-    ub_floats += r * ub_pitch(*pc.rs);
-    rows += r;
-    parts += pc.nc;
-    max_S = std::max(max_S, pc.p.S);
-    units = std::max(units, fine_units(pc.p.S, pc.rs->K));
-    tile = std::max(tile, scratch_tile_bytes(*pc.rs));
-  }
-  const int grid = fine_grid(prec, (int64_t)parts, c->n_cu);
-  char* A = (char*)ws_get(c, "A", a_bytes);
-  float* ub = (float*)ws_get(c, "ub", ub_floats * sizeof(float));
-  float* ub_hi = (float*)ws_get(c, "ub_hi", ub_floats * sizeof(float));
-  unsigned long long* rowkey = (unsigned long long*)ws_get(c, "rowkey", (rows + 1) * sizeof(unsigned long long));
-  float* rownorm = prec == kFP32 ? (float*)ws_get(c, "rownorm", 2 * rows * sizeof(float)) : nullptr;
-  float* scratch = prec == kFP32 ? (float*)ws_get(c, "scratch", grid * tile) : nullptr;
-  const FineOver over = take_over((int64_t)parts, max_S, units, c->n_cu,
-                                  [&](const char* name, size_t bytes) { return ws_get(c, name, bytes); });
-  float* rcc = prec != kFP32 ? (float*)ws_get(c, "row_cc", rows * sizeof(float)) : nullptr;
-  int* ridx = prec != kFP32 ? (int*)ws_get(c, "row_idx", rows * sizeof(int)) : nullptr;
-  float* maxabs = prec != kBF16 ? (float*)ws_get(c, "maxabs", parts * sizeof(float)) : nullptr;
+  ws_step(c, need);
+  const WaveBufs wb = layout_wave(w, c->n_cu, [&](const char* name, size_t bytes) { return ws_get(c, name, bytes); });
+  const size_t parts = wb.parts, tile = wb.tile;
+  const int grid = wb.grid;
+  const FineOver over = wb.over;
+  char* A = wb.A;
+  float *ub = wb.ub, *ub_hi = wb.ub_hi, *rownorm = wb.rownorm, *scratch = wb.scratch, *rcc = wb.rcc;
+  float* maxabs = wb.maxabs;
+  unsigned long long* rowkey = wb.rowkey;
+  int* ridx = wb.ridx;
 
   PolarBatch pb{};
   CorrBatch cb{};
@@ -837,13 +911,10 @@ void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Pla
       run_single(c, rs, p, s.parts, s.N, &s.out);
       continue;
     }
-    // runner-up, refinement, no pruning, or a workspace too small for what a
-    // wave holds besides its operand and bounds (FP32: the scratch tiles, at
-    // most a quarter of it): the per-chunk path
-    if (s.out.cc2 || s.out.psi_frac || !rs.prune ||
-        (rs.g.precision == kFP32 && fine_grid(kFP32, INT32_MAX, c->n_cu) * scratch_tile_bytes(rs) > c->cap / 4) ||
-        ws_other(c) > c->cap / 8 || particle_bytes(rs, p, true) > budget / 2) {
-      align_stack(c, rs, p, s.parts, s.N, &s.out, nullptr);
+    // runner-up, refinement, no pruning or a workspace too small for the bounds:
+    // the per-chunk path
+    if (s.out.cc2 || s.out.psi_frac || !rs.prune || particle_bytes(rs, p, true) > budget / 2) {
+      align_stack(c, rs, p, s.parts, 0, s.N, &s.out, nullptr);
       continue;
     }
     const uint64_t per = particle_bytes(rs, p, true);
@@ -922,10 +993,16 @@ void load_refs_impl(mra_ctx* c, int32_t id, const float* refs, int32_t K, const 
     ra.K = K; ra.L = g->L; ra.r_min = g->r_min; ra.R = rs.R; ra.R4 = rs.R4; ra.NS = rs.NS;
     ra.n_ref_tiles = rs.n_kt; ra.normalize = g->normalize; ra.prec = g->precision;
     ra.cs64 = c->cs64;
-    ra.q64 = (double*)ws_get(c, "ref_q64", (size_t)K * rs.R * kNphi * sizeof(double));
-    ra.inv = (double*)ws_get(c, "ref_inv", (size_t)K * sizeof(double));
-    ra.Qs = (double2*)ws_get(c, "ref_Qs", (size_t)K * 129 * rs.R * sizeof(double2));
-    ra.info = (RefInfo*)ws_get(c, "ref_info", 256);
+    const WsNeed need = {{"ref_q64", (size_t)K * rs.R * kNphi * sizeof(double)},
+                         {"ref_inv", (size_t)K * sizeof(double)},
+                         {"ref_Qs", (size_t)K * 129 * rs.R * sizeof(double2)},
+                         {"ref_info", 256}};
+    ws_step(c, need);
+    auto take = [&](int i) { return ws_get(c, need[i].first, need[i].second); };
+    ra.q64 = (double*)take(0);
+    ra.inv = (double*)take(1);
+    ra.Qs = (double2*)take(2);
+    ra.info = (RefInfo*)take(3);
     buf(rs.norm, (size_t)K * sizeof(double), "norm");
     buf(rs.qhat, (size_t)K * rs.R * kNphi * sizeof(float), "qhat");
     ra.norm = rs.norm;
@@ -985,12 +1062,20 @@ void averages_core(mra_ctx* c, int K, int L, const float* parts, int64_t N, cons
   a.cs64 = c->cs64;
   a.n_blk = (int)((N + 1023) / 1024);
   a.max_chunks = (int)((N + kAvgChunk - 1) / kAvgChunk) + K;
-  a.blk_cnt = (int*)ws_get(c, "avg_blk_cnt", (size_t)a.n_blk * K * sizeof(int));
-  a.blk_off = (int*)ws_get(c, "avg_blk_off", (size_t)a.n_blk * K * sizeof(int));
-  a.cls_start = (int*)ws_get(c, "avg_cls", (size_t)(K + 1) * sizeof(int));
-  a.chunk_start = (int*)ws_get(c, "avg_chunk", (size_t)(K + 1) * sizeof(int));
-  a.order = (int*)ws_get(c, "avg_order", (size_t)N * sizeof(int));
-  a.partial = (float*)ws_get(c, "avg_partial", (size_t)a.max_chunks * L * L * sizeof(float));
+  const WsNeed need = {{"avg_blk_cnt", (size_t)a.n_blk * K * sizeof(int)},
+                       {"avg_blk_off", (size_t)a.n_blk * K * sizeof(int)},
+                       {"avg_cls", (size_t)(K + 1) * sizeof(int)},
+                       {"avg_chunk", (size_t)(K + 1) * sizeof(int)},
+                       {"avg_order", (size_t)N * sizeof(int)},
+                       {"avg_partial", (size_t)a.max_chunks * L * L * sizeof(float)}};
+  ws_step(c, need);
+  auto take = [&](int i) { return ws_get(c, need[i].first, need[i].second); };
+  a.blk_cnt = (int*)take(0);
+  a.blk_off = (int*)take(1);
+  a.cls_start = (int*)take(2);
+  a.chunk_start = (int*)take(3);
+  a.order = (int*)take(4);
+  a.partial = (float*)take(5);
   a.averages = averages;
   a.counts = counts;
   timed(c, "averages", [&] { hip_check(c, launch_averages(a, st), "averages"); });
@@ -1019,10 +1104,10 @@ void iterate_impl(mra_ctx* c, int32_t id, const mra_geom* g, const float* parts,
   }
   hipStream_t st = c->stream;
   mra_result o = *out;
-  if (by_flat && !o.flat_index) o.flat_index = (int32_t*)ws_get(c, "iter_flat", (size_t)N * sizeof(int32_t));
+  if (by_flat && !o.flat_index) o.flat_index = (int32_t*)ws_get(c, "iter_flat", (size_t)N * sizeof(int32_t), true);
   const int32_t* key = by_flat ? o.flat_index : o.ref;
-  int32_t* prev = (int32_t*)ws_get(c, "iter_prev", (size_t)N * sizeof(int32_t));
-  int* cnt = (int*)ws_get(c, "iter_count", 256);
+  int32_t* prev = (int32_t*)ws_get(c, "iter_prev", (size_t)N * sizeof(int32_t), true);
+  int* cnt = (int*)ws_get(c, "iter_count", 256, true);
   *n_iter = 0;
   for (int it = 1; it <= max_iter; ++it) {
     load_refs_impl(c, id, averages, K, g);
@@ -1073,6 +1158,7 @@ int guard(mra_ctx* c, F&& fn) {
   }
   try {
     hip_check(c, hipSetDevice(c->device), "hipSetDevice");
+    for (auto& kv : c->ws) kv.second.keep = false;
     fn();
     return MRA_OK;
   } catch (const Fail& f) {
@@ -1239,7 +1325,7 @@ int mra_rfa(mra_ctx* c, int32_t id, const mra_geom* g, const float* parts, int64
             int64_t* changed) {
   return guard(c, [&] {
     check_loop_args(g, parts, N, average, max_iter, max_changed_frac, out, n_iter);
-    int32_t* cnt = (int32_t*)ws_get(c, "rfa_count", 256);
+    int32_t* cnt = (int32_t*)ws_get(c, "rfa_count", 256, true);
     if (start_from_mean) {  // the plain mean: the average update with every parameter zero
       hipStream_t st = c->stream;
       for (int32_t* p : {out->ref, out->shift_x, out->shift_y, out->psi, out->mirror})
