@@ -404,7 +404,7 @@ struct Half16Contract {
   }
   // the same from the place pl (b16_lane) of a tile kt, `tile_off` elements
   // further (per lane: any reference)
-  __device__ __forceinline__ void load_b_at(const CorrArgs& a, int kt, int slot, int pl, uint32_t tile_off,
+  __device__ __forceinline__ void load_b_at(const CorrArgs& a, int kt, int slot, int pl, size_t tile_off,
                                             Frag& dst) const {
     const uint16_t* bp = a.B16 + (size_t)(kt * kSlots + slot) * SE;
     dst.f[0] = *reinterpret_cast<const u32x4*>(bp + (tile_off + pl * 8));

@@ -103,7 +103,7 @@ struct FineContract16 {
     constexpr int D = 4;  // reference operand kept D slots ahead
     Frag b[D];
     const int pl = b16_lane(ref & 7, ln);
-    const uint32_t tile_off = (uint32_t)(ref >> 3) * (uint32_t)(kSlots * Base::SE);
+    const size_t tile_off = (size_t)(ref >> 3) * (kSlots * Base::SE);
 #pragma unroll
     for (int i = 0; i < D; ++i) con.load_b_at(c, 0, slot_of(i, w), pl, tile_off, b[i]);
     const uint32_t lane_off = (uint32_t)((tile * 4 + (ln >> 4)) * c.R4) * (kSlots * 16 * 2) + k * 16;

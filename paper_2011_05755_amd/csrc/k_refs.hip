@@ -210,12 +210,13 @@ __device__ __forceinline__ void operand_norm(const RefArgs& a, int k) {
   if (threadIdx.x == 0) a.bnorm[k] = (float)(sqrt(((red[0] + red[1]) + red[2]) + red[3]) * (1.0 + 1e-6));
 }
 
-// Every operand the refset keeps, in one launch: block ranges of n.
+// Every operand the refset keeps, in one launch (from block `first` on): block
+// ranges of n.
 struct PackBlocks {
   unsigned single, f32, half, norm;
 };
-__global__ __launch_bounds__(256) void k_ref_pack(RefArgs a, PackBlocks n) {
-  unsigned b = blockIdx.x;
+__global__ __launch_bounds__(256) void k_ref_pack(RefArgs a, PackBlocks n, unsigned first) {
+  unsigned b = first + blockIdx.x;
   auto at = [&] { return b * (int64_t)256 + threadIdx.x; };
   if (b < n.single) return pack_single(a, at());
   b -= n.single;
@@ -241,7 +242,10 @@ hipError_t launch_ref_stage2(const RefArgs& a, hipStream_t st) {
   if (a.B32) n.f32 = blocks_for((int64_t)a.n_ref_tiles * kRefTile * kSlots * 8 * b32_pitch(a.R4), 256);
   if (a.B16) n.half = blocks_for((int64_t)a.n_ref_tiles * kSlots * b16_slot_elems(a.R4), 256);
   if (a.bnorm) n.norm = a.K;
-  hipLaunchKernelGGL(k_ref_pack, dim3(n.single + n.f32 + n.half + n.norm), dim3(256), 0, st, a, n);
+  // (a launch holds fewer than 2^32 work-items; FP32 sets pass that at 131 072 to 340 000 references)
+  const unsigned total = n.single + n.f32 + n.half + n.norm, most = 0xffffff;
+  for (unsigned first = 0; first < total; first += most)
+    hipLaunchKernelGGL(k_ref_pack, dim3(total - first < most ? total - first : most), dim3(256), 0, st, a, n, first);
   return hipGetLastError();
 }
 

@@ -84,3 +84,11 @@ def test_no_call_is_refused_for_what_others_left(run):
             assert code == want, (s["cap"] // M, c, err)
             refused += code != OK
     assert refused < sum(len(s["calls"]) for s in sequences) / 2   # (most calls do fit)
+
+
+@pytest.mark.parametrize("r,K", [(4, 350000), (8, 345000), (64, 131500)])
+def test_large_reference_sets_launch_within_the_grid_limit(run, r, K):
+    # (no launch may have 2^32 work-items; K as the FP32 operand alone is packed in one launch)
+    got = run([dict(cap=1 << 40, calls=[refs(160, r, 0, K, "fp32"), ["align", dict(N=3)]])])[0]
+    assert got["codes"] == [OK, OK], got["errors"]
+    assert got["most_items"] < 1 << 32
