@@ -944,13 +944,14 @@ uint64_t refset_bytes(const Refset& r) {
          (r.B16 ? (uint64_t)r.n_kt * kSlots * b16_slot_elems(r.R4) * sizeof(uint16_t) : 0);
 }
 
-void keep_spare(mra_ctx* c, Refset& old) {
-  Refset gone = refset_bytes(old) <= kSpareBytes ? c->spare : old;
-  if (refset_bytes(old) <= kSpareBytes) c->spare = old;
-  if (gone.stencil) {
-    hip_check(c, hipStreamSynchronize(c->stream), "sync");
-    free_refset(gone);
-  }
+// The set `old` becomes rs, and its buffers the spare ones or nobody's.  (The
+// wait, which can fail, comes before any buffer changes hands.)
+void replace_refset(mra_ctx* c, Refset& old, const Refset& rs) {
+  const bool keep = refset_bytes(old) <= kSpareBytes;
+  if ((keep ? c->spare : old).stencil) hip_check(c, hipStreamSynchronize(c->stream), "sync");
+  if (keep) std::swap(c->spare, old);
+  free_refset(old);
+  old = rs;
 }
 
 // rs (sizes set, no buffers yet) takes the spare set's buffers if they fit.
@@ -1029,16 +1030,13 @@ void load_refs_impl(mra_ctx* c, int32_t id, const float* refs, int32_t K, const 
     if (K == 1) buf(rs.G1, (size_t)rs.R * kSlots * sizeof(float2), "G1");
     ra.G1 = rs.G1;
     hip_check(c, launch_ref_stage2(ra, st), "ref stage 2");
+    const auto it = c->refs.find(id);
+    if (it == c->refs.end()) c->refs.emplace(id, rs);
+    else replace_refset(c, it->second, rs);
   } catch (...) {
     free_refset(rs);
     throw;
   }
-  auto it = c->refs.find(id);
-  if (it != c->refs.end()) {
-    keep_spare(c, it->second);
-    c->refs.erase(it);
-  }
-  c->refs[id] = rs;
 }
 
 void averages_core(mra_ctx* c, int K, int L, const float* parts, int64_t N, const mra_result* params,

@@ -12,13 +12,13 @@ typedef struct { uint32_t x, y, z; } dim3_t;
 enum { kMax = 4096 };
 static struct { void* p; size_t n; } live[kMax];
 static uint64_t held, most_items, launches, bad_frees;
-static int fail_syncs;
+static int sync_to_fail;
 
 uint64_t stub_held(void) { return held; }
 uint64_t stub_most_items(void) { return most_items; }
 uint64_t stub_launches(void) { return launches; }
 uint64_t stub_bad_frees(void) { return bad_frees; }
-void stub_fail_syncs(int n) { fail_syncs = n; }
+void stub_fail_sync(int n) { sync_to_fail = n; } /* the n-th from now on */
 void stub_reset(void) { most_items = launches = bad_frees = 0; }
 
 int hipGetDeviceCount(int* n) { *n = 1; return 0; }
@@ -58,7 +58,7 @@ int hipMemcpyAsync(void* d, const void* s, size_t n, int k, void* st) {
   return 0;
 }
 int hipMemsetAsync(void* d, int v, size_t n, void* st) { (void)d; (void)v; (void)n; (void)st; return 0; }
-int hipStreamSynchronize(void* st) { (void)st; return fail_syncs > 0 && fail_syncs-- ? 999 : 0; }
+int hipStreamSynchronize(void* st) { (void)st; return sync_to_fail > 0 && --sync_to_fail == 0 ? 999 : 0; }
 int hipGetSymbolAddress(void** p, const void* s) { (void)s; return hipMalloc(p, 1 << 20); }
 int hipEventCreate(void** e) { *e = malloc(1); return 0; }
 int hipEventDestroy(void* e) { free(e); return 0; }

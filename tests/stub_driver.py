@@ -70,14 +70,14 @@ def main(path, scenario):
             elif kind == "batch":
                 st = (Stack * len(a["stacks"]))(*[Stack(i, P, N, -1, result()) for i, N in a["stacks"]])
                 rc = lib.mra_align_batch(h, st, len(a["stacks"]))
-            elif kind == "fail_syncs":
-                stub.stub_fail_syncs(a["n"])
+            elif kind == "fail_sync":
+                stub.stub_fail_sync(a["n"])
                 rc = 0
             codes.append(rc)
             errors.append(lib.mra_last_error(h).decode() if rc else "")
         held = stub.stub_held()
         lib.mra_destroy(h)
-        out.append(dict(codes=codes, errors=errors, held=held, most_items=stub.stub_most_items(),
+        out.append(dict(codes=codes, errors=errors, held=held, left=stub.stub_held(), most_items=stub.stub_most_items(),
                         launches=stub.stub_launches(), bad_frees=stub.stub_bad_frees()))
     print(json.dumps(out))
 

@@ -92,3 +92,13 @@ def test_large_reference_sets_launch_within_the_grid_limit(run, r, K):
     got = run([dict(cap=1 << 40, calls=[refs(160, r, 0, K, "fp32"), ["align", dict(N=3)]])])[0]
     assert got["codes"] == [OK, OK], got["errors"]
     assert got["most_items"] < 1 << 32
+
+
+@pytest.mark.parametrize("n", [1, 2])
+def test_a_failed_wait_frees_every_buffer_once(run, n):
+    # sets of three sizes under one id: the third load frees the first set, after the second wait
+    loads = [refs(64, 28, 2, K, "fp32") for K in (5, 6, 7)]
+    fine, got = run([dict(cap=M << 10, calls=loads),
+                     dict(cap=M << 10, calls=loads[:2] + [["fail_sync", dict(n=n)], loads[2]])])
+    assert fine["codes"] == [OK] * 3 and got["codes"] == [OK] * 3 + [-4]
+    assert got["bad_frees"] == 0 and got["left"] == fine["left"]
