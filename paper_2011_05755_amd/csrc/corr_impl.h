@@ -128,8 +128,9 @@ __device__ __forceinline__ f32x2 a_pair(const CorrArgs& a, const float* ap, int 
 
 // FP32 reference operand of reference k and slot `slot`: the lane's R4
 // elements (ring group ln / 16, q = ln & 1) are contiguous.
+template <int RX = 0>
 __device__ __forceinline__ const float* b32_lane(const CorrArgs& a, int k, int slot, int ln) {
-  return a.B32 + ((size_t)(k * kSlots + slot) * 8 + (ln >> 4) * 2 + (ln & 1)) * b32_pitch(a.R4);
+  return a.B32 + ((size_t)(k * kSlots + slot) * 8 + (ln >> 4) * 2 + (ln & 1)) * b32_pitch(RX > 0 ? RX : a.R4);
 }
 // 16-bit reference operand: place of the lane's elements (reference r of
 // the tile, ring group ln / 16, q = ln & 1) in each step of a slot's block.
@@ -176,8 +177,8 @@ struct Fp32Contract {
   // 16-byte loads (with one load per element and none before the particle
   // operand's, a launch of one tile pair per CU took 50 us instead of 29)
   __device__ __forceinline__ void load_b(const CorrArgs& a, int kt, int slot, int ln, float (&dst)[MAXR]) const {
-    const float* bp = b32_lane(a, kt * kRefTile + ((ln >> 1) & 7), slot, ln);
-    const int last = b32_pitch(a.R4) / 4 - 1;
+    const float* bp = b32_lane<RX>(a, kt * kRefTile + ((ln >> 1) & 7), slot, ln);
+    const int last = b32_pitch(RX > 0 ? RX : a.R4) / 4 - 1;
 #pragma unroll
     for (int q = 0; q < (MAXR + 3) / 4; ++q) {  // unconditional, whole quads (elements t >= R4 are not used)
       const f32x4 v = *reinterpret_cast<const f32x4*>(bp + 4 * (q < last ? q : last));
