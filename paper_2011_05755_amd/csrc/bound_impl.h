@@ -176,15 +176,6 @@ struct BoundSmem {
   static constexpr size_t bytes() { return (2 * kBoundTiles * kTile * 2 + kBoundWaves * NT * 8) * sizeof(float); }
 };
 
-// What rounding both operands to FP16 can add to a pair's CC (see the file
-// comment), in their scaled units: sa = norm of the row's rounded operand,
-// nb = norm of the reference's (scaled) operand, R rings.
-__device__ __forceinline__ float fp16_error(float sa, float nb, int R) {
-  const float u = 1.f / 2048.f, eta = sqrtf(2.f * kSlots * R) / 16384.f;
-  const float Na = (sa + eta) * (1.f + 1.f / 1024.f), Da = u * Na + eta, Db = u * nb + eta;
-  return 1.41421363f * (1.f + 1.f / 64.f) * (Da * nb + Na * Db + Da * Db);
-}
-
 // Row blocks of a launch, padded so that every XCD gets both halves.
 __device__ __forceinline__ int bound_blocks(const CorrArgs& a, int nt) {
   return ((a.n_row_tiles + nt - 1) / nt + 7) & ~7;

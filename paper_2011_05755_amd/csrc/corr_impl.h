@@ -496,9 +496,45 @@ __device__ __forceinline__ int key_index(unsigned long long k) {
   return k == 0ull ? 0x7fffffff : (int)(0x7fffffffu - (uint32_t)k);
 }
 
-// What a tile computes: the per-row arg-max, the full CC table (debug), or
-// the arg-max with one candidate per particle left out (the runner-up pass).
-constexpr int kArgmax = 0, kTable = 1, kRunnerUp = 2;
+// What rounding both operands to FP16 can add to a pair's CC (see
+// bound_impl.h), in their scaled units: sa = norm of the row's rounded operand,
+// nb = norm of the reference's (scaled) operand, R rings.
+__device__ __forceinline__ float fp16_error(float sa, float nb, int R) {
+  const float u = 1.f / 2048.f, eta = sqrtf(2.f * kSlots * R) / 16384.f;
+  const float Na = (sa + eta) * (1.f + 1.f / 1024.f), Da = u * Na + eta, Db = u * nb + eta;
+  return 1.41421363f * (1.f + 1.f / 64.f) * (Da * nb + Na * Db + Da * Db);
+}
+
+// Tightens the bound of a pair of particle n (FP32 alignment) by the best CC of its
+// FP16 operands, which is within fp16_error of the FP32 one's, and within its own
+// rounding (2^-12 of the bound).  Returns a value that the FP32 one reaches,
+// or -inf.
+__device__ __forceinline__ float tighten_pair(const CorrArgs& c, int n, int row, int k, float cc) {
+  float* u = c.ub + (size_t)row * c.ldu + k;
+  const float err = fp16_error(c.rownorm[row], c.bnorm[k] * c.b_scale, c.R) + 1e-16f;
+  const float own = *u * (1.f / 4096.f), mx = c.maxabs[n];
+  const float hi = fp16_value(cc + err, mx, c.b_scale) + own + 1e-37f;
+  const float lo = fp16_value(cc - err, mx, c.b_scale) - own - 1e-37f;
+  if (hi < *u) *u = hi;
+  return lo > -INFINITY && lo < INFINITY ? lo : -INFINITY;
+}
+// The largest CC of a lane's 16 angles and both mirrors as ordered bits, any NaN as
+// infinite.
+__device__ __forceinline__ uint32_t largest_cc(const float2 (&x)[16], int M) {
+  float mx = -INFINITY;
+  bool nan = false;
+#pragma unroll
+  for (int n2 = 0; n2 < 16; ++n2) {
+    mx = fmaxf(mx, M == 2 ? fmaxf(x[n2].x, x[n2].y) : x[n2].x);
+    nan |= !(x[n2].x == x[n2].x) || !(x[n2].y == x[n2].y);
+  }
+  return (uint32_t)(cand_key(nan ? INFINITY : mx, 0) >> 32);
+}
+
+// What a tile computes: the per-row arg-max, the full CC table (debug),
+// the arg-max with one candidate per particle left out (the runner-up pass), or
+// the tightening of its pairs' bounds, with a value that each row's FP32 best reaches.
+constexpr int kArgmax = 0, kTable = 1, kRunnerUp = 2, kTighten = 3;
 
 constexpr size_t kStateFloats = (size_t)kSlots * 2 * 64 * 2;  // spectra of the 64 (row, ref) pairs
 
@@ -693,36 +729,39 @@ struct CorrSmem {
   unsigned long long* key;  // [8] best candidate of each row so far (ordered key, 0 = none)
   int* list;                // [NW][64] each wave's list of the pairs of the inverse FFT
   float2* tw;               // exp(-2 pi i e / 256)
+  uint32_t* pmax;           // [64] tightening: largest CC of each pair (ordered bits)
   __device__ __forceinline__ CorrSmem(float* smem) {
     stc = reinterpret_cast<float2*>(smem);
     key = reinterpret_cast<unsigned long long*>(smem + kStateFloats);
     list = reinterpret_cast<int*>(key + 8);
     tw = reinterpret_cast<float2*>(list + NW * 64);
+    pmax = reinterpret_cast<uint32_t*>(tw + kNphi);
   }
   static constexpr size_t bytes() {
     return kStateFloats * sizeof(float) + 8 * sizeof(unsigned long long) + NW * 64 * sizeof(int) +
-           kNphi * sizeof(float2);
+           kNphi * sizeof(float2) + 64 * sizeof(uint32_t);
   }
 };
 
-// One 8-row tile against the reference tiles kt0 .. kt1 - 1, every pair
-// evaluated; the rows' bests go to c.rowkey.
+// The rows of row tile `tile` (bit r of `rows`: its row r) against the reference
+// tiles kt0 .. kt1 - 1, every pair evaluated; the rows' bests go to a.rowkey.  The
+// operand is that of tile a_tile in a.A.
 template <int PREC, int NW, class Contract, int MODE, bool SPLIT>
-__device__ __forceinline__ void corr_tile(const CorrArgs& a, int tile, int kt0, int kt1, const CorrSmem<NW>& sm,
-                                          Contract& con) {
+__device__ __forceinline__ void corr_tile(const CorrArgs& a, int tile, int a_tile, uint32_t rows, int kt0, int kt1,
+                                          const CorrSmem<NW>& sm, Contract& con) {
   const int tid = threadIdx.x, ln = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (tid < 8) sm.key[tid] = 0ull;
+  if (MODE == kTighten && w == 0) sm.pmax[ln] = 0u;
   con.prefetch(a, kt0, w, ln);
   // (FP16: each particle's operand rows come scaled by a power of two of its
   // own, exact, so results do not depend on how particles are grouped)
-  con.load_a(a, tile, a_block_pos(ln & 15), w, ln);
+  con.load_a(a, a_tile, a_block_pos(ln & 15), w, ln);
   for (int kt = kt0; kt < kt1; ++kt) {
-    con.run(a, sm.stc, tile, kt, w, ln);
+    con.run(a, sm.stc, a_tile, kt, w, ln);
     con.prefetch(a, kt + 1 < kt1 ? kt + 1 : kt0, w, ln);
     __syncthreads();
-    const uint64_t live =
-        __ballot(tile * kRowTile + (ln >> 3) < a.rows && kt * kRefTile + (ln & 7) < a.K);
+    const uint64_t live = __ballot(((rows >> (ln >> 3)) & 1u) && kt * kRefTile + (ln & 7) < a.K);
     int* list = sm.list + w * 64;
     if ((live >> ln) & 1)
       list[__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0))] = ln;
@@ -739,6 +778,8 @@ __device__ __forceinline__ void corr_tile(const CorrArgs& a, int tile, int kt0, 
 #pragma unroll
           for (int n2 = 0; n2 < 16; ++n2) o[n1 + 16 * n2] = value(m ? x[n2].y : x[n2].x);
         }
+      } else if constexpr (MODE == kTighten) {
+        atomicMax(&sm.pmax[P], largest_cc(x, a.M));
       } else {
         const int ex = MODE == kRunnerUp ? excluded_at(a.excl[n], k, s, a.S, a.M) : -1;
         float bv;
@@ -751,11 +792,17 @@ __device__ __forceinline__ void corr_tile(const CorrArgs& a, int tile, int kt0, 
       }
     });
     __syncthreads();
+    if (MODE == kTighten && w == 0) {
+      if ((live >> ln) & 1) {
+        const int row = tile * kRowTile + (ln >> 3);
+        const float cc = key_value((unsigned long long)sm.pmax[ln] << 32);
+        const float lo = tighten_pair(a, row / a.S, row, kt * kRefTile + (ln & 7), cc);
+        if (lo > -INFINITY) atomicMax(&sm.key[ln >> 3], cand_key(lo, 0));
+      }
+      sm.pmax[ln] = 0u;
+    }
   }
-  if (MODE != kTable && tid < 8) {
-    const int r = tile * kRowTile + tid;
-    if (r < a.rows) atomicMax(&a.rowkey[r], sm.key[tid]);
-  }
+  if (MODE != kTable && tid < 8 && ((rows >> tid) & 1u)) atomicMax(&a.rowkey[tile * kRowTile + tid], sm.key[tid]);
 }
 
 template <int PREC, int NW, int MAXR, bool RES, bool EXACT>
@@ -770,9 +817,10 @@ __global__ __launch_bounds__(NW * 64) void k_corr(CorrArgs a) {
   CorrSmem<NW> sm(smem);
   if (threadIdx.x < kNphi) sm.tw[threadIdx.x] = w256c(a.cs32, threadIdx.x);
   typename ContractFor<PREC, NW, MAXR, RES, EXACT>::type con;
-  const int part = blockIdx.x / a.n_row_tiles, kt0 = part * a.kt_per_wg;
-  corr_tile<PREC, NW, decltype(con), MODE, NW == 8>(a, blockIdx.x - part * a.n_row_tiles, kt0,
-                                                    min(kt0 + a.kt_per_wg, a.n_ref_tiles), sm, con);
+  const int part = blockIdx.x / a.n_row_tiles, tile = blockIdx.x - part * a.n_row_tiles, kt0 = part * a.kt_per_wg;
+  const uint32_t rows = (1u << min(kRowTile, a.rows - tile * kRowTile)) - 1u;
+  corr_tile<PREC, NW, decltype(con), MODE, NW == 8>(a, tile, tile, rows, kt0, min(kt0 + a.kt_per_wg, a.n_ref_tiles), sm,
+                                                    con);
 }
 
 template <int P_, int NW_, int MR_, bool RES_, bool EXACT_>

@@ -38,6 +38,13 @@
 // units of work for every workgroup, the bests meet in memory, and k_fine_done
 // writes the result, or after tightening the rows' largest bounds.  The
 // arg-max is over the same pairs and more, so the result is the same.
+//
+// A particle of which the first step leaves more than a sixth of all pairs live
+// (references that are noisy images themselves, as in the first passes of a
+// classification) is not evaluated here: its row tiles go to k_dense, which
+// evaluates (FP32: tightens) every pair of theirs.  FP32 particles with many live
+// pairs left after tightening (blank images, whose candidates all tie) have their rows
+// evaluated there in FP32 too.
 #pragma once
 
 #include <climits>
@@ -50,6 +57,7 @@ namespace mra {
 constexpr int kFinePairs = 16;     // pairs evaluated at a time
 constexpr int kFineList = 512;     // entries of the list of live pairs
 constexpr int kFineRefs = kFineList / 8;  // references looked over at a time
+static_assert(kFineTighten == kTighten && kFineRunnerUp == kRunnerUp && kFineArgmax == kArgmax, "one set of modes");
 
 // The pruning threshold a particle's best so far imposes on its rows: the
 // best itself, or (re-ranked 16-bit forms) margin * |best| below it, so that
@@ -239,9 +247,12 @@ struct FineSmem {
 };
 static_assert(sizeof(FineStep) % 16 == 0 && FineSmem::fixed_bytes(49, 4) % 16 == 0, "the work area is 16-byte aligned");
 
-// FP32: the operand of the group's rows (shifts sh[0 .. 7]) into the scratch
-// tile, one ring per wave at a time (8 waves).
-__device__ __forceinline__ void fine_operand(const FineArgs& a, int n, const int* sh, float* work, float* tile) {
+// FP32: the operand of rows first .. last - 1 of a row tile, row r being particle n at
+// its shift shift_of(r) (any for the other rows), into the scratch tile, one ring per
+// wave at a time (8 waves).  PERM: layout kRingPerm, else kSlotMajor.
+template <bool PERM, class Shift>
+__device__ __forceinline__ void fine_operand(const FineArgs& a, int n, Shift shift_of, int first, int last, float* work,
+                                             float* tile) {
   float* img = work;
   float2* scr = reinterpret_cast<float2*>(work + ((a.Lp * a.Lp + 3) & ~3));
   CosSin* cs = reinterpret_cast<CosSin*>(scr + kPolarWaves * 64 * 9);
@@ -254,7 +265,7 @@ __device__ __forceinline__ void fine_operand(const FineArgs& a, int n, const int
   float* stage = reinterpret_cast<float*>(my);
   const int base = (a.cx + a.pad) * a.Lp + (a.cx + a.pad);
   const int s1m = (65536 + a.m.S1 - 1) / a.m.S1;
-  const int o4 = 4 * (base + shift_offset(sh[r_], a.m.S1, s1m, a.m.T, a.Lp));
+  const int o4 = 4 * (base + shift_offset(shift_of(r_), a.m.S1, s1m, a.m.T, a.Lp));
 #pragma unroll 1
   for (int ring = w; ring < a.c.R; ring += 8) {
     // opaque lane indices: addresses are recomputed per ring instead of
@@ -274,12 +285,12 @@ __device__ __forceinline__ void fine_operand(const FineArgs& a, int n, const int
     fft_ring(cs, my, l, r, k1a, k1b, z, Za, Zb);
     RingSlots rs;
     ring_slots(cs, l, Za, Zb, rs);
-    float* dst = tile + (size_t)ring * kSlots * 16;
+    float* dst = tile + (size_t)ring * (PERM ? kSlots * 16 : 16);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       stage_slots(stage, h, r, rs);
       wave_sync();
-      write_f32_half(stage, dst, h, ln, true, 16, 0, 8);
+      write_f32_half(stage, dst, h, ln, PERM, PERM ? 16 : a.c.R4 * 64, first, last);
       wave_sync();
     }
   }
@@ -301,7 +312,7 @@ __device__ __forceinline__ bool fine_steps(const FineArgs& a, const CorrArgs& c,
   const int tid = threadIdx.x, ln = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = at.n, row0 = at.row0, S = at.S, ex0 = at.ex0;
-  float* ub = const_cast<float*>(at.ub);
+  const float* ub = at.ub;
   float2* stc = reinterpret_cast<float2*>(sm.work);
   FineStep& st = sm.step[w];
   auto threshold = [&]() { return part_thr(key_value(*sm.pbest), a.margin); };
@@ -365,14 +376,7 @@ __device__ __forceinline__ bool fine_steps(const FineArgs& a, const CorrArgs& c,
     __syncthreads();
     inverse_pairs<NW, true, kFinePairs>(stc, sm.tw, nullptr, np, w, ln, [&](int i, int n1, const float2(&x)[16]) {
       if constexpr (MODE == kFineTighten) {
-        float mx = -INFINITY;
-        bool nan = false;
-#pragma unroll
-        for (int n2 = 0; n2 < 16; ++n2) {
-          mx = fmaxf(mx, c.M == 2 ? fmaxf(x[n2].x, x[n2].y) : x[n2].x);
-          nan |= !(x[n2].x == x[n2].x) || !(x[n2].y == x[n2].y);
-        }
-        atomicMax(&sm.pmax[i], (uint32_t)(cand_key(nan ? INFINITY : mx, 0) >> 32));
+        atomicMax(&sm.pmax[i], largest_cc(x, c.M));
       } else {
         const int s = sm.shift[st.j[i]], k = st.k[i];
         const int ex = MODE == kRunnerUp ? excluded_at(ex0, k, s, S, c.M) : -1;
@@ -388,18 +392,10 @@ __device__ __forceinline__ bool fine_steps(const FineArgs& a, const CorrArgs& c,
     });
     __syncthreads();
     if constexpr (MODE == kFineTighten) {
-      // the FP16 CC is within the rounding error of the FP32 one, and of
-      // its own evaluation (2^-12 of the bound)
       if (tid < np) {
-        const int s = sm.shift[st.j[tid]], k = st.k[tid];
         const float cc = key_value((unsigned long long)sm.pmax[tid] << 32);
-        float* u = ub + (size_t)s * c.ldu + k;
-        const float err = fp16_error(c.rownorm[row0 + s], c.bnorm[k] * c.b_scale, c.R) + 1e-16f;
-        const float own = *u * (1.f / 4096.f), mx = c.maxabs[n];
-        const float hi = fp16_value(cc + err, mx, c.b_scale) + own + 1e-37f;
-        const float lo = fp16_value(cc - err, mx, c.b_scale) - own - 1e-37f;
-        if (hi < *u) *u = hi;
-        if (lo > -INFINITY && lo < INFINITY) atomicMax(sm.pbest, cand_key(lo, 0));
+        const float lo = tighten_pair(c, n, row0 + sm.shift[st.j[tid]], st.k[tid], cc);
+        if (lo > -INFINITY) atomicMax(sm.pbest, cand_key(lo, 0));
         sm.pmax[tid] = 0u;
       }
       __syncthreads();
@@ -408,14 +404,17 @@ __device__ __forceinline__ bool fine_steps(const FineArgs& a, const CorrArgs& c,
   return true;
 }
 
-// A row's largest bound, after some have been tightened: one wave.
-__device__ __forceinline__ void largest_bound(const CorrArgs& c, int row, int ln) {
+// A row's largest bound, after some have been tightened: one wave.  Returns the
+// lane's bounds that reach thr.
+__device__ __forceinline__ int largest_bound(const CorrArgs& c, int row, float thr, int ln) {
   const float* ub = c.ub + (size_t)row * c.ldu;
   unsigned long long best = 0ull;
+  int live = 0;
   for (int k = ln; k < c.K; k += 64) {
     const float v = ub[k];
     const unsigned long long key = cand_key(v == v ? v : INFINITY, k);
     best = key > best ? key : best;
+    live += !(v < thr);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -423,6 +422,7 @@ __device__ __forceinline__ void largest_bound(const CorrArgs& c, int row, int ln
     best = other > best ? other : best;
   }
   if (ln == 0) c.rowkey[row] = best;
+  return live;
 }
 
 // A particle with many live pairs, left to the whole chip: its bests so far
@@ -443,9 +443,79 @@ __device__ __forceinline__ bool fine_spill(const FineSmem& sm, const FineOver& o
   return true;
 }
 
+// More live pairs than one in kDenseShare make a particle dense.  A step here takes
+// 13 us of a CU for 16 pairs, a row tile x reference tile of k_dense 7 to 9 us for 64:
+// even at one in 6 to 7.  kDenseShare32: the same after tightening, where a step takes
+// about 60 us (FP32 operands of which none is kept) and the row tile's operand is made
+// again.
+constexpr int kDenseShare = 6, kDenseShare32 = 12;
+
+// Whether a particle is dense at the threshold of its best so far: first by its
+// rows, then by its pairs.  Called by the whole workgroup, behind a barrier.
+template <int NW>
+__device__ __forceinline__ bool fine_dense(const CorrArgs& c, const FineSmem& sm, const float* ub, float thr) {
+  const int ln = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int rows = 0;
+  for (int s0 = 0; s0 < c.S; s0 += 64)
+    rows += __popcll(__ballot(s0 + ln < c.S && !(sm.rowmax[s0 + ln < c.S ? s0 + ln : 0] < thr)));
+  if (rows * kDenseShare <= c.S) return false;  // (the same in every wave)
+  int pairs = 0;
+  for (int s = w; s < c.S; s += NW) {
+    if (sm.rowmax[s] < thr) continue;
+    const float* u = ub + (size_t)s * c.ldu;
+    for (int k0 = 0; k0 < c.K; k0 += 64) {
+      const int k = k0 + ln;
+      pairs += __popcll(__ballot(k < c.K && !(u[k < c.K ? k : 0] < thr)));
+    }
+  }
+  if (ln == 0) atomicAdd(&sm.count[1], pairs);
+  __syncthreads();
+  return (int64_t)sm.count[1] * kDenseShare > (int64_t)c.S * c.K;
+}
+
+// Puts a dense particle and its row tiles (each once, by the particle that comes
+// first) on list LIST, and clears its rows' bests.
+template <int LIST>
+__device__ __forceinline__ void fine_list_dense(const CorrArgs& c, int row0, const FineDense& dense, int piece, int item) {
+  const int t = (row0 >> 3) + threadIdx.x;
+  if (8 * t < row0 + c.S) {
+    const int lo = max(row0 - 8 * t, 0), hi = min(row0 + c.S - 8 * t, 8);
+    const uint32_t bits = ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+    const uint32_t before = atomicOr(&dense_mask(c)[t], bits << (8 * LIST)) >> (8 * LIST);
+    if ((before & 0xffu) == 0u) dense.tile[LIST][atomicAdd(&dense.count[2 * LIST], 1)] = make_int2(piece, t);
+  }
+  if (threadIdx.x == 0) dense.item[LIST][atomicAdd(&dense.count[2 * LIST + 1], 1)] = item;
+  for (int s = threadIdx.x; s < c.S; s += blockDim.x) dense_rows(c)[row0 + s] = 0ull;
+  __syncthreads();  // before the next particle's keys
+}
+
+// Particle n's results from its rows' bests: one wave.  clear: the rows' bests are
+// zeroed, for the runner-up pass.
+template <int PREC>
+__device__ __forceinline__ void finish_rows(const FineArgs& a, int n, unsigned long long* rows, bool clear, int ln) {
+  const CorrArgs& c = a.c;
+  auto value = [&](float v) { return PREC == kFP16 ? fp16_value(v, c.maxabs[n], c.b_scale) : v; };
+  unsigned long long best = 0ull;
+  for (int s = ln; s < c.S; s += 64) {
+    const unsigned long long key = rows[s];
+    if (c.row_cc) {
+      c.row_cc[(size_t)n * c.S + s] = value(key_value(key));
+      c.row_idx[(size_t)n * c.S + s] = key_index(key);
+    }
+    if (clear) rows[s] = 0ull;
+    best = key > best ? key : best;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long other = __shfl_xor(best, o);
+    best = other > best ? other : best;
+  }
+  if (ln == 0) write_result(a.m, n, value(key_value(best)), key_index(best));
+}
+
 template <int PREC, int NW, class Contract, int MODE>
-__device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int n, const FineOver& over, int item,
-                                              float* smem) {
+__device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int n, const FineOver& over,
+                                              const FineDense& dense, int piece, int item, float* smem) {
   constexpr int kThreads = 64 * NW;
   const FineSmem sm(smem, c.S, NW);
   const int tid = threadIdx.x, ln = tid & 63;
@@ -458,8 +528,19 @@ __device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int
   const FineAt at{n, row0, S, MODE == kRunnerUp ? c.excl[n] : -1, ub};
   int steps = over.cap > 0 ? over.steps : INT_MAX;
   auto value = [&](float v) { return PREC == kFP16 ? fp16_value(v, c.maxabs[n], c.b_scale) : v; };
-  // (infinite bounds: the particle does not scale into FP16)
-  if (MODE == kFineTighten && !(c.maxabs[n] * 512.f < INFINITY)) return;
+  if constexpr (PREC == kFP32 || MODE == kRunnerUp) {
+    // a dense particle: k_dense has run (FP32), or will (16-bit runner-up; k_fine_done
+    // writes the result)
+    if ((dense_mask(c)[row0 >> 3] >> ((row0 & 7) + (PREC == kFP32 ? 8 : 0))) & 1u) {
+      if (PREC == kFP32 && w == 0) finish_rows<PREC>(a, n, dense_rows(c) + row0, true, ln);
+      return;
+    }
+  }
+  if constexpr (MODE == kFineTighten) {
+    // nothing to tighten: the particle does not scale into FP16, or is blank
+    const float mx = c.maxabs[n];
+    if (!(mx * 512.f < INFINITY) || mx == 0.f) return fine_list_dense<1>(c, row0, dense, piece, item);
+  }
 
   for (int i = tid; i < kNphi; i += kThreads) sm.tw[i] = w256c(c.cs32, i);
   for (int s = tid; s < S; s += kThreads) {
@@ -470,7 +551,10 @@ __device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int
     sm.key[s] = 0ull;
     sm.taken[s] = 0;
   }
-  if (tid == 0) *sm.pbest = 0ull;
+  if (tid == 0) {
+    *sm.pbest = 0ull;
+    sm.count[1] = 0;
+  }
   if (tid < kFinePairs) sm.pmax[tid] = 0u;
   __syncthreads();
   for (int s = tid; s < S; s += kThreads) {
@@ -522,7 +606,7 @@ __device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int
     if constexpr (PREC != kFP32)
       while (g0 < S && sm.taken[sm.order[g0]]) ++g0;
     if constexpr (PREC == kFP32) {
-      fine_operand(a, n, sm.shift, sm.work, const_cast<float*>(c.A));
+      fine_operand<true>(a, n, [&](int r) { return sm.shift[r]; }, 0, 8, sm.work, const_cast<float*>(c.A));
       __syncthreads();  // the tile is written and the work area is free for the state
     }
 
@@ -550,11 +634,13 @@ __device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int
         steps = INT_MAX;
       }
       if (base >= 0) __syncthreads();  // before the list is written again
+      if constexpr (MODE == kFineTighten || (PREC != kFP32 && MODE == kArgmax))
+        if (base < 0 && fine_dense<NW>(c, sm, ub, threshold())) return fine_list_dense<0>(c, row0, dense, piece, item);
     }
   }
   if constexpr (MODE == kFineTighten) {
     for (int s = w; s < S; s += NW)
-      if (sm.taken[s]) largest_bound(c, row0 + s, ln);  // the rows looked at
+      if (sm.taken[s]) largest_bound(c, row0 + s, 0.f, ln);  // the rows looked at
   } else {
     if (c.row_cc)
       for (int s = tid; s < S; s += kThreads) {
@@ -627,24 +713,6 @@ __device__ __forceinline__ void fine_unit(const FineArgs& a, CorrArgs c, int n, 
   __syncthreads();  // before the next unit's lists
 }
 
-// The results of entry e, particle n: one wave.
-template <int PREC, int MODE>
-__device__ __forceinline__ void fine_finish(const FineArgs& a, int n, const FineOver& over, int e, int ln) {
-  const CorrArgs& c = a.c;
-  if (MODE == kFineTighten) {
-    for (int s = 0; s < c.S; ++s) largest_bound(c, n * c.S + s, ln);
-    return;
-  }
-  auto value = [&](float v) { return PREC == kFP16 ? fp16_value(v, c.maxabs[n], c.b_scale) : v; };
-  if (c.row_cc)
-    for (int s = ln; s < c.S; s += 64) {
-      const unsigned long long key = over.row[(size_t)e * over.pitch + s];
-      c.row_cc[(size_t)n * c.S + s] = value(key_value(key));
-      c.row_idx[(size_t)n * c.S + s] = key_index(key);
-    }
-  if (ln == 0) write_result(a.m, n, value(key_value(over.best[e])), key_index(over.best[e]));
-}
-
 // 16-bit operands: 4 waves, FP32: 8 (as the resampler)
 constexpr int fine_waves(int prec) { return prec == kFP32 ? 8 : 4; }
 template <int PREC, int MAXR>
@@ -658,33 +726,37 @@ struct FineContract {
 struct FineOne {
   FineArgs a;
   __device__ __forceinline__ int items() const { return a.m.n_part; }
-  __device__ __forceinline__ const FineArgs& find(int item, int& n) const {
+  __device__ __forceinline__ int find(int item, int& n) const {
     n = item;
-    return a;
+    return 0;
   }
+  __device__ __forceinline__ const FineArgs& piece(int) const { return a; }
 };
-static_assert(sizeof(FineBatch) + sizeof(FineOver) <= 4096, "kernel arguments");
+static_assert(sizeof(FineBatch) + sizeof(FineOver) + sizeof(FineDense) <= 4096, "kernel arguments");
 struct FineMany {
   FineBatch b;
   __device__ __forceinline__ int items() const { return b.start[b.n]; }
-  __device__ __forceinline__ const FineArgs& find(int item, int& n) const {
+  __device__ __forceinline__ int find(int item, int& n) const {
     int p = 0;
     while (p + 1 < b.n && b.start[p + 1] <= item) ++p;
     n = item - b.start[p];
-    return b.piece[p];
+    return p;
   }
+  __device__ __forceinline__ const FineArgs& piece(int p) const { return b.piece[p]; }
 };
 
 // at most 128 registers: four waves per SIMD
 template <int PREC, int MAXR, int MODE, class Items>
-__global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine(Items it, FineOver over) {
+__global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine(Items it, FineOver over, FineDense dense) {
   extern __shared__ float smem[];
   for (int item = blockIdx.x; item < it.items(); item += gridDim.x) {
     int n;
-    const FineArgs& a = it.find(item, n);
+    const int p = it.find(item, n);
+    const FineArgs& a = it.piece(p);
     CorrArgs c = a.c;
     if (PREC == kFP32) c.A += (size_t)blockIdx.x * a.scratch_floats;
-    fine_particle<PREC, fine_waves(PREC), typename FineContract<PREC, MAXR>::type, MODE>(a, c, n, over, item, smem);
+    fine_particle<PREC, fine_waves(PREC), typename FineContract<PREC, MAXR>::type, MODE>(a, c, n, over, dense, p, item,
+                                                                                         smem);
   }
 }
 
@@ -698,7 +770,7 @@ __global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine_over(Items it
   for (int u = blockIdx.x; u < cnt * over.units; u += gridDim.x) {
     const int e = u % cnt;
     int n;
-    const FineArgs& a = it.find(over.item[e], n);
+    const FineArgs& a = it.piece(it.find(over.item[e], n));
     CorrArgs c = a.c;
     if (c.S != last) {  // the places of the table and of pmax depend on S
       const FineSmem sm(smem, c.S, fine_waves(PREC));
@@ -710,55 +782,149 @@ __global__ __launch_bounds__(64 * fine_waves(PREC), 4) void k_fine_over(Items it
     fine_unit<PREC, fine_waves(PREC), typename FineContract<PREC, MAXR>::type, MODE>(a, c, n, over, e, u / cnt, smem);
   }
 }
+// Their results, and those of the dense particles: a wave each.  After tightening:
+// the rows' largest bounds, a wave per row; what is still dense goes to list 1.
 template <int PREC, int MODE, class Items>
-__global__ __launch_bounds__(64) void k_fine_done(Items it, FineOver over) {
-  const int e = blockIdx.x;
-  if (e >= min(*over.count, over.cap)) return;
-  int n;
-  const FineArgs& a = it.find(over.item[e], n);
-  fine_finish<PREC, MODE>(a, n, over, e, threadIdx.x);
-}
-
-template <int PREC, int MAXR, int MODE, class Items>
-inline void fine_launch(const Items& it, const FineOver& over, int grid, size_t lds, hipStream_t st) {
-  const dim3 t(64 * fine_waves(PREC));
-  hipLaunchKernelGGL((k_fine<PREC, MAXR, MODE, Items>), dim3(grid), t, lds, st, it, over);
-  if constexpr (PREC != kFP32) {
-    if (over.cap > 0) {
-      hipLaunchKernelGGL((k_fine_over<PREC, MAXR, MODE, Items>), dim3(over.grid), t, lds, st, it, over);
-      hipLaunchKernelGGL((k_fine_done<PREC, MODE, Items>), dim3(over.cap), dim3(64), 0, st, it, over);
+__global__ __launch_bounds__(MODE == kFineTighten ? 256 : 64) void k_fine_done(Items it, FineOver over, FineDense dense) {
+  const int n_over = min(*over.count, over.cap), total = n_over + dense.count[1], ln = threadIdx.x & 63;
+  for (int e = blockIdx.x; e < total; e += gridDim.x) {
+    const int item = e < n_over ? over.item[e] : dense.item[0][e - n_over];
+    int n;
+    const int p = it.find(item, n);
+    const FineArgs& a = it.piece(p);
+    const CorrArgs& c = a.c;
+    const int row0 = n * c.S;
+    if constexpr (MODE == kFineTighten) {
+      __shared__ int pairs;
+      if (threadIdx.x == 0) pairs = 0;
+      __syncthreads();
+      unsigned long long best = 0ull;  // (of a particle left over its rows' are not kept, and not needed)
+      if (e >= n_over)
+        for (int s = 0; s < c.S; ++s) best = max(best, dense_rows(c)[row0 + s]);
+      int live = 0;
+      for (int s = threadIdx.x >> 6; s < c.S; s += 4) live += largest_bound(c, row0 + s, key_value(best), ln);
+      if (e >= n_over) {
+        atomicAdd(&pairs, live);
+        __syncthreads();
+        if ((int64_t)pairs * kDenseShare32 > (int64_t)c.S * c.K) fine_list_dense<1>(c, row0, dense, p, item);
+      }
+      __syncthreads();
+    } else {
+      unsigned long long* rows = e < n_over ? over.row + (size_t)e * over.pitch : dense_rows(c) + row0;
+      finish_rows<PREC>(a, n, rows, e >= n_over, ln);
     }
   }
 }
+
+// The dense particles: every pair of their rows, row tile by row tile, each
+// against all references or, where there are fewer row tiles than workgroups, a part
+// of them: the contraction and inverse FFTs of k_corr, 64 pairs at a time with the
+// rows' operand in registers.  16-bit forms read the operand of the bounds; FP32 makes
+// that of the tile's rows in the workgroup's scratch tile first.  One workgroup of 8
+// waves per CU (the state of 64 pairs takes 128 KiB of LDS), as many as CUs: a launch
+// that finds none ends at once (about 5 us).  76 px, 100 references that are particles,
+// +-3, 10 000 particles, whole call: FP32 171.7 ms with every pair in steps of 16,
+// 34.9 here; BF16 165.5 and 28.5 (every pair in k_corr, without bounds: 43.8 and 24.4).
+template <int PREC, class Contract, int MODE, class Items>
+__global__ __launch_bounds__(512) void k_dense(Items it, FineDense dense) {
+  extern __shared__ float smem[];
+  const CorrSmem<8> sm(smem);
+  constexpr int kList = PREC == kFP32 ? 1 : 0;
+  const int cnt = dense.count[2 * kList];
+  if (cnt == 0) return;
+  const int parts = max(1, (int)gridDim.x / cnt), tid = threadIdx.x;
+  for (int u = blockIdx.x; u < cnt * parts; u += gridDim.x) {
+    const int2 at = dense.tile[kList][u % cnt];
+    const FineArgs& a = it.piece(at.x);
+    CorrArgs c = a.c;
+    const int per = (c.n_ref_tiles + parts - 1) / parts, kt0 = u / cnt * per, kt1 = min(kt0 + per, c.n_ref_tiles);
+    if (kt0 >= kt1) continue;
+    const uint32_t rows = (dense_mask(c)[at.y] >> (8 * kList)) & 0xffu;
+    c.rowkey = dense_rows(c);
+    int a_tile = at.y;
+    if constexpr (PREC == kFP32) {
+      c.A += (size_t)blockIdx.x * a.scratch_floats;
+      a_tile = 0;
+      const int row0 = at.y * kRowTile;
+      for (int n = row0 / c.S; n * c.S < min(row0 + kRowTile, c.rows); ++n) {
+        const int first = max(n * c.S - row0, 0), last = min((n + 1) * c.S - row0, kRowTile);
+        if (!((rows >> first) & 1u)) continue;
+        const int S = c.S, s0 = row0 - n * S;
+        fine_operand<Contract::LAYOUT == kRingPerm>(a, n, [=](int r) { return min(max(s0 + r, 0), S - 1); }, first, last,
+                                                    smem, const_cast<float*>(c.A));
+        __syncthreads();  // the tile is written and the work area free
+      }
+    }
+    if (tid < kNphi) sm.tw[tid] = w256c(c.cs32, tid);
+    Contract con;
+    corr_tile<PREC, 8, Contract, MODE, true>(c, at.y, a_tile, rows, kt0, kt1, sm, con);
+    __syncthreads();  // before the next unit's work area
+  }
+}
+
+// A launch: one piece (a) or several (b).
+struct FineLaunch {
+  FineMode mode;
+  int R4max;             // largest ring count of the pieces (one ring bucket)
+  const FineArgs* a;
+  const FineBatch* b;
+  FineOver over;
+  FineDense dense;
+  int grid;
+  size_t lds, work;      // LDS of the evaluation; of the FP32 operand's preparation
+  hipStream_t st;
+};
+
+// The resident form of k_corr where there is one (FP32: up to 9 rings per lane group).
+template <int PREC, int MAXR>
+struct DenseContract {
+  typedef typename std::conditional<
+      PREC == kFP32, Fp32Contract<8, MAXR <= 9 ? 9 : 16, (MAXR <= 9), false>,
+      Half16Contract<PREC == kFP32 ? kBF16 : PREC, 8, MAXR == 9 ? 10 : MAXR, true>>::type type;
+};
+
+template <int PREC, int MAXR, int MODE, class Items>
+inline void fine_launch(const Items& it, const FineOver& over, const FineDense& dense, int grid, size_t lds, size_t work,
+                        hipStream_t st) {
+  const dim3 t(64 * fine_waves(PREC));
+  auto go_dense = [&] {
+    const size_t state = CorrSmem<8>::bytes();
+    hipLaunchKernelGGL((k_dense<PREC, typename DenseContract<PREC, MAXR>::type, MODE, Items>), dim3(dense.grid), dim3(512),
+                       state > work ? state : work, st, it, dense);
+  };
+  if constexpr (PREC == kFP32) go_dense();
+  hipLaunchKernelGGL((k_fine<PREC, MAXR, MODE, Items>), dim3(grid), t, lds, st, it, over, dense);
+  if constexpr (PREC != kFP32) {
+    hipLaunchKernelGGL((k_fine_over<PREC, MAXR, MODE, Items>), dim3(over.grid), t, lds, st, it, over);
+    go_dense();
+    hipLaunchKernelGGL((k_fine_done<PREC, MODE, Items>), dim3(over.cap), dim3(MODE == kFineTighten ? 256 : 64), 0, st, it,
+                       over, dense);
+  }
+}
 template <int PREC, int MAXR, int MODE>
-inline void fine_mode(const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds, hipStream_t st) {
-  if (b) fine_launch<PREC, MAXR, MODE>(FineMany{*b}, over, grid, lds, st);
-  else fine_launch<PREC, MAXR, MODE>(FineOne{*a}, over, grid, lds, st);
+inline void fine_mode(const FineLaunch& f) {
+  if (f.b) fine_launch<PREC, MAXR, MODE>(FineMany{*f.b}, f.over, f.dense, f.grid, f.lds, f.work, f.st);
+  else fine_launch<PREC, MAXR, MODE>(FineOne{*f.a}, f.over, f.dense, f.grid, f.lds, f.work, f.st);
 }
 // TIGHTEN: only the tightening of FP32 bounds, else every other mode
 template <int PREC, int MAXR, bool TIGHTEN>
-inline void fine_go(FineMode mode, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds, hipStream_t st) {
-  if constexpr (TIGHTEN) return fine_mode<PREC, MAXR, kFineTighten>(a, b, over, grid, lds, st);
-  else if (mode == kFineRunnerUp) return fine_mode<PREC, MAXR, kRunnerUp>(a, b, over, grid, lds, st);
-  else return fine_mode<PREC, MAXR, kArgmax>(a, b, over, grid, lds, st);
+inline void fine_go(const FineLaunch& f) {
+  if constexpr (TIGHTEN) return fine_mode<PREC, MAXR, kFineTighten>(f);
+  else if (f.mode == kFineRunnerUp) return fine_mode<PREC, MAXR, kRunnerUp>(f);
+  else return fine_mode<PREC, MAXR, kArgmax>(f);
 }
 
-// R4max: the largest ring count of the launch's pieces (one ring bucket).
-void fine_dispatch_fp32(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds,
-                        hipStream_t st);
-void fine_dispatch_bf16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds,
-                        hipStream_t st);
-void fine_dispatch_fp16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds,
-                        hipStream_t st);
-void fine_dispatch_tighten(int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds, hipStream_t st);
+void fine_dispatch_fp32(const FineLaunch& f);
+void fine_dispatch_bf16(const FineLaunch& f);
+void fine_dispatch_fp16(const FineLaunch& f);
+void fine_dispatch_tighten(const FineLaunch& f);
 
 template <int PREC, bool TIGHTEN>
-inline void fine_dispatch_16(FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, const FineOver& over, int grid, size_t lds,
-                             hipStream_t st) {
-  if (R4max <= 8) return fine_go<PREC, 8, TIGHTEN>(mode, a, b, over, grid, lds, st);
-  if (R4max <= 10) return fine_go<PREC, 10, TIGHTEN>(mode, a, b, over, grid, lds, st);
-  if (R4max <= 12) return fine_go<PREC, 12, TIGHTEN>(mode, a, b, over, grid, lds, st);
-  return fine_go<PREC, 16, TIGHTEN>(mode, a, b, over, grid, lds, st);
+inline void fine_dispatch_16(const FineLaunch& f) {
+  if (f.R4max <= 8) return fine_go<PREC, 8, TIGHTEN>(f);
+  if (f.R4max <= 10) return fine_go<PREC, 10, TIGHTEN>(f);
+  if (f.R4max <= 12) return fine_go<PREC, 12, TIGHTEN>(f);
+  return fine_go<PREC, 16, TIGHTEN>(f);
 }
 
 }  // namespace mra

@@ -62,17 +62,18 @@ __device__ __forceinline__ void bound_sum(const CorrArgs& a, int blk) {
   }
   if (c == 0) {
     a.rowkey[row] = best;
+    if (!(row & (kRowTile - 1))) dense_mask(a)[row / kRowTile] = 0u;
     if constexpr (ERR) a.rownorm[row] = err_s;
   }
 }
 template <bool ERR>
-__global__ __launch_bounds__(16 * kSumRows) void k_bound_sum(CorrArgs a, int* over_count) {
-  if (over_count && blockIdx.x == 0 && threadIdx.x < 2) over_count[threadIdx.x] = 0;
+__global__ __launch_bounds__(16 * kSumRows) void k_bound_sum(CorrArgs a, int* counts) {
+  if (blockIdx.x == 0 && threadIdx.x < kFineCounts) counts[threadIdx.x] = 0;
   bound_sum<ERR>(a, blockIdx.x);
 }
 template <bool ERR>
-__global__ __launch_bounds__(16 * kSumRows) void k_bound_sum_batch(CorrBatch b, int* over_count) {
-  if (over_count && blockIdx.x == 0 && threadIdx.x < 2) over_count[threadIdx.x] = 0;
+__global__ __launch_bounds__(16 * kSumRows) void k_bound_sum_batch(CorrBatch b, int* counts) {
+  if (blockIdx.x == 0 && threadIdx.x < kFineCounts) counts[threadIdx.x] = 0;
   const int item = blockIdx.x;
   if (item >= b.start[b.n]) return;
   int p = 0;
@@ -86,18 +87,19 @@ static void dispatch(int prec, int R4, const CorrArgs* a, const CorrBatch* b, in
   else bound_dispatch<kFP16, false>(R4, a, b, grid, st);
 }
 
-hipError_t launch_bound(int prec, const CorrArgs& a, int n_items, int* over_count, hipStream_t st) {
+hipError_t launch_bound(int prec, const CorrArgs& a, int n_items, int* counts, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
-  if (a.R4 < 1 || a.R4 > 16 || !a.ub || !a.ub_hi || !a.rowkey || a.rows <= 0 || (prec == kFP32 && (!a.bnorm || !a.maxabs))) return hipErrorInvalidValue;
+  if (a.R4 < 1 || a.R4 > 16 || !a.ub || !a.ub_hi || !a.rowkey || !counts || a.rows <= 0 || (prec == kFP32 && (!a.bnorm || !a.maxabs))) return hipErrorInvalidValue;
   dispatch(prec, a.R4, &a, nullptr, n_items, st);
   const dim3 grid((a.rows + kSumRows - 1) / kSumRows), block(16 * kSumRows);
-  if (prec == kFP32) hipLaunchKernelGGL(k_bound_sum<true>, grid, block, 0, st, a, over_count);
-  else hipLaunchKernelGGL(k_bound_sum<false>, grid, block, 0, st, a, over_count);
+  if (prec == kFP32) hipLaunchKernelGGL(k_bound_sum<true>, grid, block, 0, st, a, counts);
+  else hipLaunchKernelGGL(k_bound_sum<false>, grid, block, 0, st, a, counts);
   return hipGetLastError();
 }
 
-hipError_t launch_bound_batch(int prec, const CorrBatch& b, int* over_count, hipStream_t st) {
+hipError_t launch_bound_batch(int prec, const CorrBatch& b, int* counts, hipStream_t st) {
   if (b.n <= 0 || b.start[b.n] <= 0) return hipSuccess;
+  if (!counts) return hipErrorInvalidValue;
   const int bucket = ring_bucket(b.piece[0].R4);
   for (int i = 0; i < b.n; ++i)  // every piece in one ring bucket
     if (b.piece[i].R4 < 1 || ring_bucket(b.piece[i].R4) != bucket || !b.piece[i].ub || !b.piece[i].ub_hi ||
@@ -107,8 +109,8 @@ hipError_t launch_bound_batch(int prec, const CorrBatch& b, int* over_count, hip
   CorrBatch sum = b;
   for (int i = 0; i < b.n; ++i) sum.start[i + 1] = sum.start[i] + (b.piece[i].rows + kSumRows - 1) / kSumRows;
   const dim3 grid(sum.start[b.n]), block(16 * kSumRows);
-  if (prec == kFP32) hipLaunchKernelGGL(k_bound_sum_batch<true>, grid, block, 0, st, sum, over_count);
-  else hipLaunchKernelGGL(k_bound_sum_batch<false>, grid, block, 0, st, sum, over_count);
+  if (prec == kFP32) hipLaunchKernelGGL(k_bound_sum_batch<true>, grid, block, 0, st, sum, counts);
+  else hipLaunchKernelGGL(k_bound_sum_batch<false>, grid, block, 0, st, sum, counts);
   return hipGetLastError();
 }
 

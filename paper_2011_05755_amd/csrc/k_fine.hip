@@ -1,4 +1,6 @@
 // Launch of the evaluation kernel.
+#include <algorithm>
+
 #include "fine_impl.h"
 
 namespace mra {
@@ -16,12 +18,11 @@ static size_t lds_bytes(int prec, int S, int Lp) {
   return FineSmem::fixed_bytes(S, fine_waves(prec)) + (state > polar ? state : polar);
 }
 
-static void dispatch(int prec, FineMode mode, int R4max, const FineArgs* a, const FineBatch* b, int grid, size_t lds,
-                     const FineOver& over, hipStream_t st) {
-  if (mode == kFineTighten) fine_dispatch_tighten(R4max, a, b, over, grid, lds, st);
-  else if (prec == kFP32) fine_dispatch_fp32(mode, R4max, a, b, over, grid, lds, st);
-  else if (prec == kBF16) fine_dispatch_bf16(mode, R4max, a, b, over, grid, lds, st);
-  else fine_dispatch_fp16(mode, R4max, a, b, over, grid, lds, st);
+static void dispatch(int prec, const FineLaunch& f) {
+  if (f.mode == kFineTighten) fine_dispatch_tighten(f);
+  else if (prec == kFP32) fine_dispatch_fp32(f);
+  else if (prec == kBF16) fine_dispatch_bf16(f);
+  else fine_dispatch_fp16(f);
 }
 
 static bool accepts(int prec, FineMode mode, const FineArgs& a) {
@@ -52,32 +53,37 @@ int fine_over_steps(int64_t n, int units, int n_cu) {
   return 2 * n <= grid && units <= 16 ? 2 : (n <= 8 * grid ? 8 : 24);
 }
 
-static bool sound(const FineOver& o) {
-  return o.cap == 0 || (o.cap > 0 && o.count && o.item && o.best && o.row && o.pitch >= 1 && o.units >= 1 && o.grid >= 1);
+static bool sound(int prec, FineMode mode, const FineOver& o, const FineDense& d) {
+  const bool spills = prec != kFP32 || mode == kFineTighten;
+  const int list = prec == kFP32 ? 1 : 0;
+  return d.count && d.tile[list] && d.item[list] && d.grid >= 1 && (mode != kFineTighten || (d.tile[0] && d.item[0])) &&
+         (!spills || (o.cap > 0 && o.count && o.item && o.best && o.row && o.pitch >= 1 && o.units >= 1 && o.grid >= 1));
 }
 
-hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, const FineOver& over, int grid, hipStream_t st) {
+hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, const FineOver& over, const FineDense& dense, int grid,
+                       hipStream_t st) {
   if (a.m.n_part <= 0) return hipSuccess;
-  if (grid < 1 || !accepts(prec, mode, a) || !sound(over)) return hipErrorInvalidValue;
-  dispatch(prec, mode, a.c.R4, &a, nullptr, grid, lds_bytes(mode == kFineTighten ? kFP16 : prec, a.c.S, a.Lp), over, st);
+  if (grid < 1 || !accepts(prec, mode, a) || !sound(prec, mode, over, dense)) return hipErrorInvalidValue;
+  dispatch(prec, FineLaunch{mode, a.c.R4, &a, nullptr, over, dense, grid,
+                            lds_bytes(mode == kFineTighten ? kFP16 : prec, a.c.S, a.Lp),
+                            prec == kFP32 ? polar_lds_bytes(a.Lp) : 0, st});
   return hipGetLastError();
 }
 
-hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, const FineOver& over, int grid,
-                             hipStream_t st) {
+hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, const FineOver& over, const FineDense& dense,
+                             int grid, hipStream_t st) {
   if (b.n <= 0 || b.start[b.n] <= 0) return hipSuccess;
-  if (grid < 1 || !sound(over)) return hipErrorInvalidValue;
-  size_t lds = 0;
-  int r4 = 0;
+  if (grid < 1 || !sound(prec, mode, over, dense)) return hipErrorInvalidValue;
+  FineLaunch f{mode, 0, nullptr, &b, over, dense, grid, 0, 0, st};
   for (int i = 0; i < b.n; ++i) {
+    const FineArgs& a = b.piece[i];
     // (the 16-bit instantiations fix the operand's step count: one ring bucket)
-    if (!accepts(prec, mode, b.piece[i]) || ring_bucket(b.piece[i].c.R4) != ring_bucket(b.piece[0].c.R4))
-      return hipErrorInvalidValue;
-    r4 = b.piece[i].c.R4 > r4 ? b.piece[i].c.R4 : r4;
-    const size_t need = lds_bytes(mode == kFineTighten ? kFP16 : prec, b.piece[i].c.S, b.piece[i].Lp);
-    lds = need > lds ? need : lds;
+    if (!accepts(prec, mode, a) || ring_bucket(a.c.R4) != ring_bucket(b.piece[0].c.R4)) return hipErrorInvalidValue;
+    f.R4max = std::max(f.R4max, a.c.R4);
+    f.lds = std::max(f.lds, lds_bytes(mode == kFineTighten ? kFP16 : prec, a.c.S, a.Lp));
+    if (prec == kFP32) f.work = std::max(f.work, polar_lds_bytes(a.Lp));
   }
-  dispatch(prec, mode, r4, nullptr, &b, grid, lds, over, st);
+  dispatch(prec, f);
   return hipGetLastError();
 }
 

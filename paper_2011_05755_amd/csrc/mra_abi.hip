@@ -320,36 +320,45 @@ struct ChunkBufs {
   float* A = nullptr;        // particle operand, ceil(nc S / 8) row tiles
   float* ub = nullptr;       // pruned: [nc S][ub_pitch] bounds
   float* ub_hi = nullptr;    // pruned: a half of them before they are added
-  unsigned long long* rowkey = nullptr;  // [nc S] largest bound (pruned) or best CC per row
+  unsigned long long* rowkey = nullptr;  // [nc S] largest bound (pruned; then dense_rows, dense_mask) or best CC per row
   float* rownorm = nullptr;  // pruned FP32: [2][nc S] norm of the row's operand
   float* scratch = nullptr;  // pruned FP32: one operand tile per evaluation workgroup
   int grid = 0;              // evaluation workgroups
   FineOver over{};           // the particles left to the whole chip
+  FineDense dense{};         // those of which every pair is evaluated
   float* rcc = nullptr;      // [nc S] best CC per row
   int* ridx = nullptr;       // [nc S] its flat index
   float* maxabs = nullptr;   // FP16 operand: [nc] max |pixel|
   int32_t* win = nullptr;    // cc2: [nc] chunk-local winner copy
 };
 
-// The list of particles that an evaluation of nc particles (of at most S shifts
-// and `units` units of work each) leaves to the whole chip.
+// The lists of particles that an evaluation of nc particles (of at most S shifts
+// and `units` units of work each, in `tiles` row tiles) leaves to the whole chip,
+// and of those whose every pair is evaluated (their launch: dense.grid, set here).
 template <class Take>
-FineOver take_over(int64_t nc, int S, int units, int n_cu, Take take) {
-  FineOver o{};
+void take_lists(int64_t nc, size_t tiles, int S, int units, int n_cu, FineOver& o, FineDense& d, Take take) {
   o.cap = (int)std::min<int64_t>(nc, kFineOverCap);
   o.steps = fine_over_steps(nc, units, n_cu);
   o.pitch = S;
   o.units = units;
   o.grid = fine_grid(kFP16, INT32_MAX, n_cu);
-  const size_t keys = (size_t)o.cap * (1 + S) * sizeof(unsigned long long);
-  char* p = (char*)take("over", keys + (size_t)(o.cap + 2) * sizeof(int));
-  if (!p) return o;  // (only measured)
+  const size_t keys = (size_t)o.cap * (1 + S) * sizeof(unsigned long long), dtile = 2 * tiles * sizeof(int2);
+  char* p = (char*)take("over", keys + dtile + (size_t)(kFineCounts + o.cap + 2 * nc) * sizeof(int));
+  if (!p) return;  // (only measured)
   o.best = (unsigned long long*)p;
   o.row = o.best + o.cap;
-  o.item = (int*)(p + keys);
-  o.count = o.item + o.cap;
-  return o;
+  d.tile[0] = (int2*)(p + keys);
+  d.tile[1] = d.tile[0] + tiles;
+  o.count = (int*)(p + keys + dtile);
+  d.count = o.count + 2;
+  o.item = o.count + kFineCounts;
+  d.item[0] = o.item + o.cap;
+  d.item[1] = d.item[0] + nc;
 }
+
+// Workgroups of the evaluation of every pair of a launch's dense particles, one per
+// CU (FP32: each with a scratch tile; few particles, fewer tiles).
+int dense_grid(int prec, int grid, int n_cu) { return prec == kFP32 ? std::min(n_cu, 4 * grid) : n_cu; }
 
 // Calls take(name, bytes) for every buffer of an nc-particle chunk.
 template <class Take>
@@ -362,13 +371,14 @@ ChunkBufs layout_chunk(const Refset& rs, const Plan& p, int64_t nc, bool pruned,
     b.grid = fine_grid(rs.g.precision, nc, n_cu);
     b.ub = (float*)take("ub", rows * ub_pitch(rs) * sizeof(float));
     b.ub_hi = (float*)take("ub_hi", rows * ub_pitch(rs) * sizeof(float));
+    b.dense.grid = dense_grid(rs.g.precision, b.grid, n_cu);
     if (rs.g.precision == kFP32) {
       b.rownorm = (float*)take("rownorm", 2 * rows * sizeof(float));
-      b.scratch = (float*)take("scratch", b.grid * scratch_tile_bytes(rs));
+      b.scratch = (float*)take("scratch", std::max(b.grid, b.dense.grid) * scratch_tile_bytes(rs));
     }
-    b.over = take_over(nc, p.S, fine_units(p.S, rs.K), n_cu, take);
+    take_lists(nc, tiles, p.S, fine_units(p.S, rs.K), n_cu, b.over, b.dense, take);
   }
-  b.rowkey = (unsigned long long*)take("rowkey", (rows + 1) * sizeof(unsigned long long));
+  b.rowkey = (unsigned long long*)take("rowkey", rowkey_bytes(rows, pruned));
   if (row_results(rs)) {
     b.rcc = (float*)take("row_cc", rows * sizeof(float));
     b.ridx = (int*)take("row_idx", rows * sizeof(int));
@@ -587,10 +597,11 @@ void run_chunk(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, 
     FineArgs ta = fa;
     ta.c.A = b.A;
     timed(c, "tighten", [&] {
-      hip_check(c, launch_fine(prec, kFineTighten, ta, b.over, fine_grid(kFP16, nc, c->n_cu), st), "tighten");
+      hip_check(c, launch_fine(prec, kFineTighten, ta, b.over, b.dense, fine_grid(kFP16, nc, c->n_cu), st), "tighten");
     });
   }
-  timed(c, "fine", [&] { hip_check(c, launch_fine(prec, kFineArgmax, fa, prec == kFP32 ? FineOver{} : b.over, b.grid, st), "fine"); });
+  FineOver over = prec == kFP32 ? FineOver{} : b.over;
+  timed(c, "fine", [&] { hip_check(c, launch_fine(prec, kFineArgmax, fa, over, b.dense, b.grid, st), "fine"); });
   if (prec != kFP32)
     timed(c, "rescore", [&] { hip_check(c, launch_rescore(rescore_args(rs, p, src, n0, nc, out, b), st), "rescore"); });
   if (out->cc2) {
@@ -600,9 +611,8 @@ void run_chunk(mra_ctx* c, const Refset& rs, const Plan& p, const float* parts, 
     fa.m.win = nullptr;
     fa.m.runner_up = 1;
     fa.margin = 0.f;
-    FineOver over = prec == kFP32 ? FineOver{} : b.over;
     if (over.cap) over.count += 1;
-    timed(c, "fine2", [&] { hip_check(c, launch_fine(prec, kFineRunnerUp, fa, over, b.grid, st), "fine2"); });
+    timed(c, "fine2", [&] { hip_check(c, launch_fine(prec, kFineRunnerUp, fa, over, b.dense, b.grid, st), "fine2"); });
   }
   if (out->psi_frac) refine_chunk(c, rs, p, parts, n0, nc, out);
 }
@@ -749,18 +759,24 @@ struct WaveBufs {
   unsigned long long* rowkey = nullptr;
   int* ridx = nullptr;
   FineOver over{};
+  FineDense dense{};
 };
+
+// 8-byte words of a piece's row keys
+size_t wave_rowkeys(size_t rows) { return (rowkey_bytes(rows, true) + 7) / 8; }
 
 // Calls take(name, bytes) for every buffer of a wave.
 template <class Take>
 WaveBufs layout_wave(const std::vector<Piece>& w, int n_cu, Take take) {
   WaveBufs b;
   const int prec = w[0].rs->g.precision;
-  size_t a_bytes = 0, ub_floats = 0, rows = 0;
+  size_t a_bytes = 0, ub_floats = 0, rows = 0, keys = 0, tiles = 0;
   int max_S = 0, units = 0;
   for (const Piece& pc : w) {
-    const size_t r = (size_t)pc.nc * pc.p.S;
-    a_bytes += (r + kRowTile - 1) / kRowTile * tile_bytes_of(*pc.rs, true);
+    const size_t r = (size_t)pc.nc * pc.p.S, t = (r + kRowTile - 1) / kRowTile;
+    a_bytes += t * tile_bytes_of(*pc.rs, true);
+    keys += wave_rowkeys(r);
+    tiles += t;
     ub_floats += r * ub_pitch(*pc.rs);
     rows += r;
     b.parts += pc.nc;
@@ -772,15 +788,16 @@ WaveBufs layout_wave(const std::vector<Piece>& w, int n_cu, Take take) {
   b.A = (char*)take("A", a_bytes);
   b.ub = (float*)take("ub", ub_floats * sizeof(float));
   b.ub_hi = (float*)take("ub_hi", ub_floats * sizeof(float));
-  b.rowkey = (unsigned long long*)take("rowkey", (rows + 1) * sizeof(unsigned long long));
+  b.rowkey = (unsigned long long*)take("rowkey", keys * sizeof(unsigned long long));
+  b.dense.grid = dense_grid(prec, b.grid, n_cu);
   if (prec == kFP32) {
     b.rownorm = (float*)take("rownorm", 2 * rows * sizeof(float));
-    b.scratch = (float*)take("scratch", b.grid * b.tile);
+    b.scratch = (float*)take("scratch", std::max(b.grid, b.dense.grid) * b.tile);
   } else {
     b.rcc = (float*)take("row_cc", rows * sizeof(float));
     b.ridx = (int*)take("row_idx", rows * sizeof(int));
   }
-  b.over = take_over((int64_t)b.parts, max_S, units, n_cu, take);
+  take_lists((int64_t)b.parts, tiles, max_S, units, n_cu, b.over, b.dense, take);
   if (prec != kBF16) b.maxabs = (float*)take("maxabs", b.parts * sizeof(float));
   return b;
 }
@@ -835,7 +852,6 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     b.ub_hi = ub_hi;
     b.rowkey = rowkey;
     b.rownorm = rownorm;
-    b.over = over;
     b.scratch = scratch;
     b.grid = grid;
     b.maxabs = maxabs ? maxabs + part : nullptr;
@@ -860,7 +876,7 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     A += (r + kRowTile - 1) / kRowTile * tile_bytes_of(rs, true);
     ub += r * ub_pitch(rs);
     ub_hi += r * ub_pitch(rs);
-    rowkey += r;
+    rowkey += wave_rowkeys(r);
     if (rownorm) rownorm += 2 * r;
     if (rcc) {
       rcc += r;
@@ -877,9 +893,11 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     FineBatch tb = fb;
     for (int i = 0; i < np; ++i) tb.piece[i].c.A = cb.piece[i].A;
     const int tgrid = fine_grid(kFP16, (int64_t)parts, c->n_cu);
-    timed(c, "tighten", [&] { hip_check(c, launch_fine_batch(prec, kFineTighten, tb, over, tgrid, st), "tighten batch"); });
+    timed(c, "tighten", [&] { hip_check(c, launch_fine_batch(prec, kFineTighten, tb, over, wb.dense, tgrid, st), "tighten batch"); });
   }
-  timed(c, "fine", [&] { hip_check(c, launch_fine_batch(prec, kFineArgmax, fb, prec == kFP32 ? FineOver{} : over, grid, st), "fine batch"); });
+  timed(c, "fine", [&] {
+    hip_check(c, launch_fine_batch(prec, kFineArgmax, fb, prec == kFP32 ? FineOver{} : over, wb.dense, grid, st), "fine batch");
+  });
   if (prec != kFP32) timed(c, "rescore", [&] { hip_check(c, launch_rescore_batch(rb, st), "rescore batch"); });
 }
 

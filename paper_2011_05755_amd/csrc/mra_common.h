@@ -148,7 +148,7 @@ struct CorrArgs {
   int ldu;               // 8 * n_ref_tiles
   unsigned long long* rowkey;  // [rows] each row's largest bound and its reference, or (every pair evaluated) its
                                // best CC and flat index, in cand_key order; every pair evaluated: zeroed by
-                               // the resampler
+                               // the resampler.  With bounds, dense_rows and dense_mask follow
   float* rownorm;        // FP32 alignment: [2][rows], first the norm of the row's operand (FP16, scaled; bound
                          // error); scratch of the bounds: the halves' squares
   int kt_per_wg;         // reference tiles per workgroup (bounds, and the correlation of every pair)
@@ -176,6 +176,26 @@ struct FineOver {
   int units;                 // units of work per particle
   int grid;                  // workgroups of that launch
 };
+
+// Particles of which so many pairs are live that every pair is evaluated: their
+// row tiles and, for the results, their item numbers in the launch.  List 0: with
+// the 16-bit operand (FP32: the tightening), list 1: with the FP32 one.  The rows of
+// such particles have a bit in the mask of their row tile (dense_mask, zeroed by the
+// bounds' sum; list 1 eight bits up) and their best candidate in dense_rows.
+struct FineDense {
+  int* count;                // [4] row tiles and particles of either list; zeroed by the bounds' sum
+  int2* tile[2];             // (piece, row tile)
+  int* item[2];
+  int grid;                  // workgroups of a launch that evaluates them
+};
+constexpr int kFineCounts = 6;  // those of FineOver (arg-max, runner-up) and FineDense, end to end
+__host__ __device__ constexpr size_t rowkey_bytes(size_t rows, bool bounds) {
+  return bounds ? 16 * rows + 4 * ((rows + kRowTile - 1) / kRowTile + 1) : 8 * (rows + 1);
+}
+__device__ __forceinline__ unsigned long long* dense_rows(const CorrArgs& c) { return c.rowkey + c.rows; }
+__device__ __forceinline__ uint32_t* dense_mask(const CorrArgs& c) {
+  return reinterpret_cast<uint32_t*>(c.rowkey + 2 * (size_t)c.rows);
+}
 
 // Where a chunk's particles' results go.
 struct ResultArgs {
@@ -274,16 +294,17 @@ hipError_t launch_corr_runner_up(int prec, int variant, const CorrArgs& a, hipSt
 // 16-bit ring buckets (R4 <= 8, 9..10, 11..12, 13..16): the pieces of a batched launch share one
 constexpr int ring_bucket(int R4) { return R4 <= 8 ? 0 : (R4 <= 10 ? 1 : (R4 <= 12 ? 2 : 3)); }
 // work items of a bound launch over a's rows; sets a.kt_per_wg.  The launch also
-// zeroes over_count[0 .. 1], the counters of FineOver (arg-max, runner-up), if not null.
+// zeroes counts[0 .. kFineCounts - 1].
 int bound_items(CorrArgs& a, int n_cu);
-hipError_t launch_bound(int prec, const CorrArgs& a, int n_items, int* over_count, hipStream_t st);
-hipError_t launch_bound_batch(int prec, const CorrBatch& b, int* over_count, hipStream_t st);
+hipError_t launch_bound(int prec, const CorrArgs& a, int n_items, int* counts, hipStream_t st);
+hipError_t launch_bound_batch(int prec, const CorrBatch& b, int* counts, hipStream_t st);
 // workgroups of an evaluation launch over n particles (FP32: also its scratch tiles)
 int fine_grid(int prec, int64_t n, int n_cu);
 enum FineMode { kFineArgmax = 0, kFineRunnerUp = 2, kFineTighten = 3 };
-hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, const FineOver& over, int grid, hipStream_t st);
-hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, const FineOver& over, int grid,
-                             hipStream_t st);
+hipError_t launch_fine(int prec, FineMode mode, const FineArgs& a, const FineOver& over, const FineDense& dense, int grid,
+                       hipStream_t st);
+hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, const FineOver& over, const FineDense& dense,
+                             int grid, hipStream_t st);
 int fine_units(int S, int K);                         // FineOver::units of a piece
 int fine_over_steps(int64_t n, int units, int n_cu);  // FineOver::steps of a launch over n particles
 // launches of few particles: workgroups of `waves` waves per particle (of
