@@ -426,16 +426,24 @@ int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned
   return std::max<int64_t>(1, (int64_t)(budget / particle_bytes(rs, p, pruned)));
 }
 
-// A call of few particles takes the unpruned way: with every pair of a few
-// row and reference tiles spread over the CUs it ends before the pruned way's
-// chain of dependent steps does.  Unpruned against pruned (us; tile pairs per
-// CU): FP32 76 px, 100 references, +-3 16 particles 134 / 283 (6), 40: 234 / 311
-// (14); 64 px, +-2, 20 references, 200 particles 234 / 242 (7); 90 px, +-2, 100
-// references, 32 particles 139 / 187 (5), 64: 229 / 204 (10).  BF16 76 px 32
-// particles 158 / 316 (11), 64: 258 / 246 (23); 90 px 64 particles 165 / 161 (10).
+// A call of few pairs, or of few pairs per particle, takes the unpruned way: with
+// every pair of a few row and reference tiles spread over the CUs it ends before the
+// pruned way's chain of dependent steps does, and a particle costs the evaluation
+// about what four tile pairs do, however few it has.  The line was fitted to 2400 calls
+// (K 4 to 200, 30 to 3000 particles, +-0 to +-4, 3 to 62 rings, SNR 0.05 and 0.2; on average
+// 1 % above the faster way).  FP32: a tile pair costs more the more rings there are (7.6 us
+// of a CU at 3, 18 at 36, more where the operand is streamed), and the bounds
+// leave fewer pairs.  Pruned against unpruned (us; tile pairs per CU), SNR 0.05: FP32 64 px,
+// 28 rings, +-2, 20 references, 200 particles 263 / 203 (7), 1000: 666 / 761 (37); 8
+// references, 3000 particles 1672 / 1530 (37); +-0, 100 references, 3000 particles 911 / 502
+// (19); 24 px, 9 rings, +-2, 100 references, 400 particles 695 / 566 (63); 76 px, 35 rings, +-3,
+// 100 references, 30 particles 284 / 226 (9), 60: 347 / 429 (19); 96 px, 46 rings, +-2, 20
+// references, 200 particles 312 / 388 (7).  BF16 64 px, +-2, 20 references, 200 particles 209 /
+// 168 (7), 1000: 512 / 523 (37); 76 px, +-3, 100 references, 30 particles 224 / 167 (9).
 bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N) {
   const int64_t tiles = (N * p.S + kRowTile - 1) / kRowTile * rs.n_kt;
-  return tiles <= (rs.g.precision == kFP32 ? 8 : 12) * (int64_t)c->n_cu;
+  const int R4 = rs.R4, per_cu = rs.g.precision == kFP32 ? std::max(4, 4000 / (R4 * R4 * R4)) : (R4 <= 6 ? 20 : 12);
+  return tiles <= per_cu * (int64_t)c->n_cu + 4 * N;
 }
 
 // Largest chunk whose buffers fit `bytes` (0 if not one particle).
@@ -638,8 +646,7 @@ void run_chunk_unpruned(mra_ctx* c, const Refset& rs, const Plan& p, const float
   pa.out = b.A;
   timed(c, "polar", [&] { hip_check(c, launch_polar(0, pa, st), "polar"); });
   ca.table = table;
-  ca.kt_per_wg = (rs.n_kt + corr_parts(ca.n_row_tiles, rs.n_kt, c->n_cu) - 1) /
-                 corr_parts(ca.n_row_tiles, rs.n_kt, c->n_cu);
+  ca.kt_per_wg = corr_tiles_per_wg(ca.n_row_tiles, rs.n_kt, c->n_cu);
   timed(c, "corr", [&] { hip_check(c, launch_corr(prec, rs.variant, table != nullptr, ca, st), "corr"); });
   if (table) return;
   MergeArgs ma{};

@@ -308,15 +308,28 @@ hipError_t launch_fine_batch(int prec, FineMode mode, const FineBatch& b, const 
 int fine_units(int S, int K);                         // FineOver::units of a piece
 int fine_over_steps(int64_t n, int units, int n_cu);  // FineOver::steps of a launch over n particles
 // launches of few particles: workgroups of `waves` waves per particle (of
-// n_items 8-row ring items) that fill n_cu CUs with 16 waves each, and reference parts of a launch of `tiles`
-// row tiles that give every CU a workgroup
+// n_items 8-row ring items) that fill n_cu CUs with 16 waves each
 inline int polar_split(int n_part, int n_items, int n_cu, int waves) {
   const int want = n_part > 0 ? 2 * kPolarWaves * n_cu / waves / n_part : 1, most = (n_items + waves - 1) / waves;
   return want < 1 ? 1 : (want > most ? most : want);
 }
-inline int corr_parts(int tiles, int n_ref_tiles, int n_cu) {
-  const int want = tiles > 0 ? n_cu / tiles : 1;
-  return want < 1 ? 1 : (want > n_ref_tiles ? n_ref_tiles : want);
+// reference tiles per workgroup of a launch of `tiles` row tiles, one workgroup per CU
+// at a time: those that end the launch first, rounds of workgroups times their length
+// (a workgroup's prologue, which reads the operand of its rows, takes about a third of a
+// reference tile's time)
+inline int corr_tiles_per_wg(int tiles, int n_ref_tiles, int n_cu) {
+  int best = n_ref_tiles;
+  double least = 0;
+  for (int parts = 1; parts <= n_ref_tiles && (parts == 1 || (int64_t)tiles * parts <= 16 * (int64_t)n_cu); ++parts) {
+    const int per = (n_ref_tiles + parts - 1) / parts;
+    const int64_t wgs = (int64_t)tiles * ((n_ref_tiles + per - 1) / per);
+    const double time = (double)((wgs + n_cu - 1) / n_cu) * (per + 0.35);
+    if (parts == 1 || time < least) {
+      least = time;
+      best = per;
+    }
+  }
+  return best;
 }
 bool corr_variant_ok(int prec, int variant, int R4);
 int corr_default_variant(int prec, int R4);
