@@ -818,15 +818,11 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     need.emplace_back(name, bytes);
     return nullptr;
   });
-  if (total > c->cap) {  // what a wave holds besides its operand and bounds does not fit: piece by piece
+  // one piece is a call of its own (the way its size takes); so are all where what a
+  // wave holds besides its operand and bounds does not fit
+  if (w.size() == 1 || total > c->cap) {
     for (const Piece& pc : w)
       align_stack(c, *pc.rs, pc.p, stacks[pc.stack].parts, pc.n0, pc.nc, &stacks[pc.stack].out, nullptr);
-    return;
-  }
-  if (w.size() == 1) {  // one piece fills the chip by itself: the plain per-chunk launches
-    const Piece& pc = w[0];
-    const mra_stack& sk = stacks[pc.stack];
-    run_chunk(c, *pc.rs, pc.p, sk.parts, pc.n0, pc.nc, &sk.out, ws_chunk(c, *pc.rs, pc.p, pc.nc, true, &sk.out));
     return;
   }
   const int prec = w[0].rs->g.precision, np = (int)w.size();
@@ -936,9 +932,12 @@ void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Pla
       run_single(c, rs, p, s.parts, s.N, &s.out);
       continue;
     }
-    // runner-up, refinement, no pruning or a workspace too small for the bounds:
-    // the per-chunk path
-    if (s.out.cc2 || s.out.psi_frac || !rs.prune || particle_bytes(rs, p, true) > budget / 2) {
+    // runner-up, refinement, no pruning, a workspace too small for the bounds, or one
+    // reference tile, which the bounds cannot save much of (4 stacks of 1000 particles, 8
+    // references: FP32 3.60 ms in a wave, 3.30 alone; BF16 2.91, 2.37; with 10 references a
+    // wave is the faster), and rows that fill the chip: the per-chunk path
+    const bool alone = rs.n_kt == 1 && few_pairs(c, rs, p, s.N) && s.N * p.S >= 2 * kRowTile * (int64_t)c->n_cu;
+    if (s.out.cc2 || s.out.psi_frac || !rs.prune || alone || particle_bytes(rs, p, true) > budget / 2) {
       align_stack(c, rs, p, s.parts, 0, s.N, &s.out, nullptr);
       continue;
     }

@@ -1,7 +1,8 @@
 """Which way an alignment takes, read from the kernel groups that it launched: every
 pair evaluated (few pairs, pruning off), or bounds first.  Whatever the way, the
 results are bit for bit the same: at every ring bucket, noise-free and noisy,
-without mirrors or normalisation, and with reference sets replaced in between."""
+without mirrors or normalisation, with reference sets replaced in between, and in
+a batch of one stack."""
 
 import numpy as np
 import pytest
@@ -63,6 +64,7 @@ def both(ctx, precision, parts, expect):
     want, ran = run(ctx, lambda: ctx.align(0, parts, with_cc2=True))
     assert ran == every_pair(), ran
     same(got, want)
+    return want
 
 
 @pytest.mark.parametrize("precision", PRECISIONS)
@@ -85,7 +87,19 @@ def test_every_pair(ctx, precision, L, r_max, T, K, N):
     print(f"[gpu-routes] {precision} L={L} K={K} N={N}", flush=True)
     refs, parts = stack(L, K, T, N, r_max)
     ctx.load_refs(0, refs, r_min=1, r_max=r_max, shift_max=T, precision=precision)
-    both(ctx, precision, parts, every_pair())
+    want = both(ctx, precision, parts, every_pair())
+    # a batch of one stack is that stack's call
+    from paper_2011_05755_amd import mra
+    out = mra.AlignResult.empty(N, DEV)
+
+    def batch():
+        ctx.align_batch([(0, parts, -1, out)])
+        return out
+    for prune in (-1, 0):
+        ctx.set_tuning(0, prune=prune)
+        got, ran = run(ctx, batch)
+        assert ran == every_pair(cc2=False), ran
+        same(got, {f: want[f] for f in got})
 
 
 @pytest.mark.parametrize("precision", PRECISIONS)
