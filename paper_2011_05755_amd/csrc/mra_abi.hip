@@ -1041,7 +1041,12 @@ void load_refs_impl(mra_ctx* c, int32_t id, const float* refs, int32_t K, const 
       throw Fail{MRA_E_DEGENERATE,
                  "reference " + std::to_string(c->ref_info->bad) + " has zero weighted ring norm"};
     rs.b_scale = 1.f;
-    if (g->precision != kBF16 && bmax > 0.f && std::isfinite(bmax)) rs.b_scale = std::ldexp(1.f, 14 - (int)std::ceil(std::log2(bmax)));
+    if (g->precision != kBF16 && bmax > 0.f && std::isfinite(bmax)) {
+      // (FP32: only the bounds take it, and references below 2^-113 are better scaled
+      // by less than into an infinite scale)
+      const int e = 14 - (int)std::ceil(std::log2(bmax));
+      rs.b_scale = std::ldexp(1.f, g->precision == kFP32 ? std::min(e, 127) : e);
+    }
     ra.b_scale = rs.b_scale;
     // (FP32 with one reference: the fused kernel and the CC table need no bounds)
     if (g->precision == kFP32) buf(rs.B32, (size_t)rs.n_kt * kRefTile * kSlots * 8 * b32_pitch(rs.R4) * sizeof(float), "B32");

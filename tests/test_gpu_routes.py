@@ -129,3 +129,20 @@ def test_replaced_references(precision):
             got, ran = run(c, lambda: c.align(0, sets[i][1], with_cc2=True))
             assert ran == bounds_first(precision), ran
             same(got, want[i])
+
+
+def test_small_reference_sets_scale_into_the_bounds():
+    """FP32 references below 2^-113 (raw CC): the bounds' FP16 operand takes the largest finite scale."""
+    from paper_2011_05755_amd import mra
+    refs, parts = stack(76, 100, 3, 60, 35)
+    got = []
+    with mra.Context(0) as c:
+        for s in (1.0, 2.0 ** -118):
+            c.load_refs(0, (refs * s).contiguous(), r_min=1, r_max=35, shift_max=3, normalize=False)
+            r, ran = run(c, lambda: c.align(0, parts, with_cc2=True))
+            assert ran == bounds_first("fp32"), ran
+            c.set_tuning(0, prune=0)
+            same(r, c.align(0, parts, with_cc2=True).to_numpy())
+            got.append(r)
+    np.testing.assert_array_equal(got[0]["flat_index"], got[1]["flat_index"])
+    np.testing.assert_array_equal(np.ldexp(got[0]["cc"], -118), got[1]["cc"])
