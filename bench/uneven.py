@@ -1,4 +1,4 @@
-"""Uneven stacks in one batched call, with autotuned tile configurations.
+"""Uneven stacks in one batched call, with autotuned chunk sizes.
 
 64 stacks drawn from the uneven-stack size distribution (box L in
 {64, 76, 96, 128}, N uniform 2k..50k, K uniform 20..400, shifts +-2..+-5,
@@ -112,8 +112,7 @@ def main(argv=None) -> int:
         variants = {}
         for i in range(len(data)):
             v, c = ctx.get_tuning(base + i)
-            e = cache.get(autotune.refset_key(ctx, base + i)) or {}
-            k = f"{v}/{c}/run{e.get('run_tiles', 0)}"
+            k = f"{v}/{c}"
             variants[k] = variants.get(k, 0) + 1
         line = dict(workload=f"uneven stacks: {len(data)} stacks, L in {{64,76,96,128}}, N 2k..50k "
                              f"(x{args.n_scale}), K 20..400, shifts +-2..+-5, own refset each, seed {args.seed}",
@@ -121,7 +120,7 @@ def main(argv=None) -> int:
                     particles_per_s=round(n_total / t_batch, 1),
                     per_stack_calls_s=None if t_single is None else round(t_single, 4),
                     identical_to_per_stack_calls=None if same is None else f"{same}/{len(data)}",
-                    tuned_keys=len(tuned), tune_s=round(t_tune, 2), variant_chunk_run_counts=variants)
+                    tuned_keys=len(tuned), tune_s=round(t_tune, 2), variant_chunk_counts=variants)
         print(json.dumps(line), flush=True)
         for i in range(len(data)):
             ctx.unload_refs(base + i)

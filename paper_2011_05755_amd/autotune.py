@@ -1,27 +1,28 @@
-"""Autotuner for the tile configuration of the correlation kernel.
+"""Autotuner for the chunk size and the tile configuration of an alignment.
 
-A refset's tile configuration is (corr_variant, chunk_particles, run_tiles);
-see ``mra_tuning`` in include/mra.h.  No configuration changes any result,
-only speed, so the tuner may pick freely among the ones the library accepts.
-The tile itself (8 particle rows by 8 references) is fixed by the matrix-core
-block, whose 16 columns are the 8 references' two spectrum combinations, and
-by the LDS state of its 64 pairs; what a workgroup covers is tunable through
-run_tiles, the number of consecutive row tiles it takes (they share the
-particle thresholds of the pruning bound, and fewer, longer runs trade
-launch tail for pruning reach).
+A refset's tuning is (corr_variant, chunk_particles, run_tiles); see
+``mra_tuning`` in include/mra.h.  No configuration changes any result, only
+speed, so the tuner may pick freely among the ones the library accepts, and it
+times only what can change the time of the sample's call: a sample that takes
+the way with bounds first (most do) evaluates no pair in the correlation kernel,
+so its tile variants are not timed and the library's default stays; a sample of
+few pairs evaluates every pair there, and the variants are timed.  Run lengths
+(run_tiles) are accepted by the library and no longer used: they are timed
+only on a context that cannot tell which kernels it launched.
 
 Key:        (L, number of rings, K bucket, T, precision), where the K bucket is
             the smallest power of two >= K (at least 8, one reference tile).
-Candidates: every variant that ``mra_set_tuning`` accepts for the refset,
-            crossed with a few chunk sizes (0 = as large as the workspace
-            allows; small chunks keep the particle operand of a chunk within
-            the last-level cache), with the library's own run length; then,
-            at the winner, a few run lengths (0 = the library's choice).
+Candidates: the variants (see above; those that ``mra_set_tuning`` accepts for
+            the refset) crossed with a few chunk sizes (0 = as large as the
+            workspace allows; small chunks keep the particle operand of a chunk
+            within the last-level cache).
 Measure:    the median wall time of ``mra_align`` on a sample stack,
             synchronised, after one untimed call per candidate.
 Cache:      a JSON file, ``$MRA_AUTOTUNE_CACHE`` or
             ``~/.cache/paper_2011_05755_amd/autotune.json``; entries hold the
-            winner and every candidate's time.
+            winner, whether its variant was timed, and every candidate's time.
+            An entry that does not say so (written before the variants were
+            told apart) has its variant left at the default.
 
     python -m paper_2011_05755_amd.autotune --L 76 --rings 35 --K 100 --T 3 --precision fp32
 """
@@ -65,7 +66,7 @@ def default_cache_path() -> str:
 
 
 class Cache:
-    """Key -> {"corr_variant", "chunk_particles", "ms", "candidates"}."""
+    """Key -> {"corr_variant", "chunk_particles", "variant_timed", "ms", "candidates"}."""
 
     def __init__(self, path: str | None = None):
         self.path = path or default_cache_path()
@@ -127,6 +128,19 @@ def wall_ms(ctx, refset_id: int, parts, reps: int) -> float:
     return statistics.median(times)
 
 
+def evaluates_every_pair(ctx, refset_id: int, parts) -> bool | None:
+    """Whether aligning `parts` launches the correlation kernel, whose tile
+    variants a tuning chooses; None for a context that does not record its
+    launches."""
+    if not hasattr(ctx, "profile_read"):
+        return None
+    ctx.profile(True)
+    ctx.align(refset_id, parts)
+    launches = ctx.profile_read("corr")[1]
+    ctx.profile(False)
+    return launches > 0
+
+
 def tune(ctx, refset_id: int, parts, reps: int = 3, cache: Cache | None = None,
          chunks: Iterable[int] = DEFAULT_CHUNKS, runs: Iterable[int] = DEFAULT_RUNS,
          timer: Callable[[object, int, object, int], float] = wall_ms, log=None) -> dict:
@@ -135,6 +149,11 @@ def tune(ctx, refset_id: int, parts, reps: int = 3, cache: Cache | None = None,
     key = refset_key(ctx, refset_id)
     n = parts.shape[0]
     cand = [(v, c) for v, c in candidates(ctx, refset_id, chunks) if c == 0 or c < n]
+    ctx.set_tuning(refset_id)
+    every = evaluates_every_pair(ctx, refset_id, parts)
+    if every is False:  # the variants change nothing here: the default stays
+        default = ctx.get_tuning(refset_id)[0]
+        cand = [(v, c) for v, c in cand if v == default]
     times = {}
     for v, c in cand:
         ctx.set_tuning(refset_id, corr_variant=v, chunk_particles=c)
@@ -146,7 +165,7 @@ def tune(ctx, refset_id: int, parts, reps: int = 3, cache: Cache | None = None,
     # time already taken)
     run_times = {0: times[(bv, bc)]}
     for r in runs:
-        if r in run_times:
+        if r in run_times or every is not None:
             continue
         ctx.set_tuning(refset_id, corr_variant=bv, chunk_particles=bc, run_tiles=r)
         run_times[r] = timer(ctx, refset_id, parts, reps)
@@ -154,7 +173,8 @@ def tune(ctx, refset_id: int, parts, reps: int = 3, cache: Cache | None = None,
             log(f"{key}: variant {bv} chunk {bc} run {r}: {run_times[r]:.3f} ms")
     br = min(run_times, key=lambda r: (run_times[r], r))
     ctx.set_tuning(refset_id, corr_variant=bv, chunk_particles=bc, run_tiles=br)
-    entry = dict(corr_variant=bv, chunk_particles=bc, run_tiles=br, ms=run_times[br], n_sample=n,
+    entry = dict(corr_variant=bv, chunk_particles=bc, run_tiles=br, variant_timed=every is not False,
+                 ms=run_times[br], n_sample=n,
                  candidates={f"{v}/{c}": round(t, 4) for (v, c), t in sorted(times.items())},
                  runs={str(r): round(t, 4) for r, t in sorted(run_times.items())})
     if cache is not None:
@@ -167,8 +187,8 @@ def apply(ctx, refset_id: int, cache: Cache) -> bool:
     e = cache.get(refset_key(ctx, refset_id))
     if e is None:
         return False
-    ctx.set_tuning(refset_id, corr_variant=int(e["corr_variant"]), chunk_particles=int(e["chunk_particles"]),
-                   run_tiles=int(e.get("run_tiles", 0)))
+    ctx.set_tuning(refset_id, corr_variant=int(e["corr_variant"]) if e.get("variant_timed") else -1,
+                   chunk_particles=int(e["chunk_particles"]), run_tiles=int(e.get("run_tiles", 0)))
     return True
 
 
