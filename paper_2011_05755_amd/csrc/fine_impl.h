@@ -39,7 +39,7 @@
 // writes the result, or after tightening the rows' largest bounds.  The
 // arg-max is over the same pairs and more, so the result is the same.
 //
-// A particle of which the first step leaves more than a sixth of all pairs live
+// A particle of which the first step leaves more than an eighth of all pairs live
 // (references that are noisy images themselves, as in the first passes of a
 // classification) is not evaluated here: its row tiles go to k_dense, which
 // evaluates (FP32: tightens) every pair of theirs.  FP32 particles with many live
@@ -56,7 +56,6 @@ namespace mra {
 
 constexpr int kFinePairs = 16;     // pairs evaluated at a time
 constexpr int kFineList = 512;     // entries of the list of live pairs
-constexpr int kFineRefs = kFineList / 8;  // references looked over at a time
 static_assert(kFineTighten == kTighten && kFineRunnerUp == kRunnerUp && kFineArgmax == kArgmax, "one set of modes");
 
 // The pruning threshold a particle's best so far imposes on its rows: the
@@ -443,12 +442,14 @@ __device__ __forceinline__ bool fine_spill(const FineSmem& sm, const FineOver& o
   return true;
 }
 
-// More live pairs than one in kDenseShare make a particle dense.  A step here takes
-// 13 us of a CU for 16 pairs, a row tile x reference tile of k_dense 7 to 9 us for 64:
-// even at one in 6 to 7.  kDenseShare32: the same after tightening, where a step takes
-// about 60 us (FP32 operands of which none is kept) and the row tile's operand is made
-// again.
-constexpr int kDenseShare = 6, kDenseShare32 = 12;
+// More live pairs than one in kDenseShare make a particle dense.  A step here takes 13 us
+// of a CU for 16 pairs, a row tile x reference tile of k_dense 6.6 us (BF16) for 64: even at
+// one in 8 (76 px, 100 references, 3000 particles at SNR 0.02, BF16: 7.55, 7.24 and 6.83 ms
+// at one in 6, 8 and 12; 10 000 at SNR 0.05, FP32: 18.3, 18.5 and 19.0; 64 px, 50 references,
+// 200 particles, BF16: 309, 251, 248 and 246 us at one in 3, 8, 16 and 32).  After
+// tightening: than one in kDenseShare32, as a step takes about 60 us there (FP32 operands
+// of which none is kept), and the row tile's operand is made again.
+constexpr int kDenseShare = 8, kDenseShare32 = 12;
 
 // Whether a particle is dense at the threshold of its best so far: first by its
 // rows, then by its pairs.  Called by the whole workgroup, behind a barrier.
@@ -610,16 +611,18 @@ __device__ __forceinline__ void fine_particle(const FineArgs& a, CorrArgs c, int
       __syncthreads();  // the tile is written and the work area is free for the state
     }
 
-    // the references in windows of kFineRefs; before the first window of the
-    // first group (base = -kFineRefs) each row's best reference
-    for (int base = first_group ? -kFineRefs : 0; base < c.K; base += kFineRefs) {
+    // the references in windows, as many as the list holds for these rows (one row,
+    // 5000 references: 10 windows instead of the 79 that eight rows take); before the
+    // first window of the first group (base < 0) each row's best reference
+    const int lw = __builtin_ctz(kFineList) - (nrow > 4 ? 3 : (nrow > 2 ? 2 : nrow - 1)), refs = 1 << lw;
+    for (int base = first_group ? -refs : 0; base < c.K; base += refs) {
       int cnt = nrow;
       if (base >= 0) {
         if (tid == 0) *sm.count = 0;
         __syncthreads();
         const float thr = threshold();
-        for (int i = tid; i < 8 * kFineRefs; i += kThreads) {
-          const int j = i / kFineRefs, k = base + i % kFineRefs;
+        for (int i = tid; i < kFineList; i += kThreads) {
+          const int j = i >> lw, k = base + (i & (refs - 1));
           if (j >= nrow || k >= c.K) continue;
           const int s = sm.shift[j];
           const float u = ub[(size_t)s * c.ldu + k];
