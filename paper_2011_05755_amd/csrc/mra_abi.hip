@@ -358,7 +358,7 @@ void take_lists(int64_t nc, size_t tiles, int S, int units, int n_cu, FineOver& 
 
 // Workgroups of the evaluation of every pair of a launch's dense particles, one per
 // CU (FP32: each with a scratch tile; few particles, fewer tiles).
-int dense_grid(int prec, int grid, int n_cu) { return prec == kFP32 ? std::min(n_cu, 4 * grid) : n_cu; }
+int dense_grid(int prec, int grid, int n_cu) { return prec == kFP32 ? std::min(n_cu, 2 * grid) : n_cu; }
 
 // Calls take(name, bytes) for every buffer of an nc-particle chunk.
 template <class Take>
@@ -431,7 +431,7 @@ int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned
 // pruned way's chain of dependent steps does, and a particle costs the evaluation
 // about what four tile pairs do, however few it has.  The line was fitted to 2400 calls
 // (K 4 to 200, 30 to 3000 particles, +-0 to +-4, 3 to 62 rings, SNR 0.05 and 0.2; on average
-// 1 % above the faster way).  FP32: a tile pair costs more the more rings there are (7.6 us
+// 1 % above the faster way; where they cross, the less favourable data decides).  FP32: a tile pair costs more the more rings there are (7.6 us
 // of a CU at 3, 18 at 36, more where the operand is streamed), and the bounds
 // leave fewer pairs.  Pruned against unpruned (us; tile pairs per CU), SNR 0.05: FP32 64 px,
 // 28 rings, +-2, 20 references, 200 particles 263 / 203 (7), 1000: 666 / 761 (37); 8
@@ -440,17 +440,22 @@ int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned
 // 100 references, 30 particles 284 / 226 (9), 60: 347 / 429 (19); 96 px, 46 rings, +-2, 20
 // references, 200 particles 312 / 388 (7).  BF16 64 px, +-2, 20 references, 200 particles 209 /
 // 168 (7), 1000: 512 / 523 (37); 76 px, +-3, 100 references, 30 particles 224 / 167 (9).
+// Without shifts a step holds at most 8 pairs, of one row: 64 px, 5000 references, 2000
+// particles FP32 8.0 / 6.5 ms, BF16 6.7 / 4.3.
 bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N) {
+  if (p.S == 1) return true;
   const int64_t tiles = (N * p.S + kRowTile - 1) / kRowTile * rs.n_kt;
-  const int R4 = rs.R4, per_cu = rs.g.precision == kFP32 ? std::max(4, 4000 / (R4 * R4 * R4)) : (R4 <= 6 ? 20 : 12);
+  const int R4 = rs.R4, per_cu = rs.g.precision == kFP32 ? std::max(4, 5500 / (R4 * R4 * R4)) : (R4 <= 6 ? 20 : 12);
   return tiles <= per_cu * (int64_t)c->n_cu + 4 * N;
 }
 
-// Largest chunk whose buffers fit `bytes` (0 if not one particle).
-int64_t fitting_chunk(const Refset& rs, const Plan& p, bool pruned, bool cc2, int n_cu, size_t bytes) {
+// Largest chunk of at most N particles whose buffers fit `bytes` (0 if not one particle).
+int64_t fitting_chunk(const Refset& rs, const Plan& p, int64_t N, bool pruned, bool cc2, int n_cu, size_t bytes) {
+  const int64_t most = std::min<int64_t>(INT32_MAX / p.S / 2, N);
+  if (carve_chunk(rs, p, most, pruned, cc2, n_cu, nullptr, nullptr) <= bytes) return most;
   if (carve_chunk(rs, p, 1, pruned, cc2, n_cu, nullptr, nullptr) > bytes) return 0;
   // the buffers grow with the chunk: bisect for the largest that fits
-  int64_t lo = 1, hi = std::min<int64_t>(INT32_MAX / p.S / 2, (int64_t)(bytes / ((size_t)p.S * 8)) + 1);
+  int64_t lo = 1, hi = most;
   while (lo < hi) {
     const int64_t mid = lo + (hi - lo + 1) / 2;
     if (carve_chunk(rs, p, mid, pruned, cc2, n_cu, nullptr, nullptr) <= bytes) lo = mid;
@@ -459,18 +464,19 @@ int64_t fitting_chunk(const Refset& rs, const Plan& p, bool pruned, bool cc2, in
   return lo;
 }
 
-// Particles per chunk on the pruned path, or 0 when not one particle's bounds and
-// scratch fit (the call then takes the unpruned one).  All that a chunk holds
+// Particles per chunk on the pruned path, or 0 when a chunk is of few pairs or not one
+// particle's bounds and scratch fit (the call then takes the unpruned one).  All that a chunk holds
 // takes at most half the cap, as the unpruned operand does: the other half is left
 // to the steps beside it (reference preparation, averages).
 int64_t pruned_chunk(mra_ctx* c, const Refset& rs, const Plan& p, int64_t N, bool cc2) {
   if (!rs.prune || few_pairs(c, rs, p, N)) return 0;
   const int64_t most = std::min<int64_t>(INT32_MAX / p.S / 2, N);
   const uint64_t room = c->cap - std::min(c->cap, ws_kept(c));
-  if (rs.chunk <= 0) return std::min(most, fitting_chunk(rs, p, true, cc2, c->n_cu, std::min(c->cap / 2, room)));
   int64_t n = std::min<int64_t>(rs.chunk, most);
-  while (n > 0 && carve_chunk(rs, p, n, true, cc2, c->n_cu, nullptr, nullptr) > room) n /= 2;
-  return n;
+  if (rs.chunk <= 0) n = fitting_chunk(rs, p, N, true, cc2, c->n_cu, std::min(c->cap / 2, room));
+  else
+    while (n > 0 && carve_chunk(rs, p, n, true, cc2, c->n_cu, nullptr, nullptr) > room) n /= 2;
+  return few_pairs(c, rs, p, n) ? 0 : n;
 }
 
 // Sub-step angles of particles n0 .. n0 + nc - 1 from their final parameters.
@@ -733,9 +739,9 @@ void align_impl(mra_ctx* c, int32_t id, const float* parts, int64_t N, int T, co
     return;
   }
   if (!c->scratch) throw Fail{MRA_E_DEVICE, "no-allocation scratch not resolved on this device"};
-  int64_t step = rs.prune && !few_pairs(c, rs, p, N) ? fitting_chunk(rs, p, true, out->cc2 != nullptr, c->n_cu, kScratchBytes) : 0;
-  const bool pruned = step > 0;
-  if (!pruned) step = fitting_chunk(rs, p, false, out->cc2 != nullptr, c->n_cu, kScratchBytes);
+  int64_t step = rs.prune ? fitting_chunk(rs, p, N, true, out->cc2 != nullptr, c->n_cu, kScratchBytes) : 0;
+  const bool pruned = step > 0 && !few_pairs(c, rs, p, step);
+  if (!pruned) step = fitting_chunk(rs, p, N, false, out->cc2 != nullptr, c->n_cu, kScratchBytes);
   if (step < 1)
     throw Fail{MRA_E_INVAL, "one particle's operand exceeds the " + std::to_string(kScratchBytes >> 20) +
                                 " MiB no-allocation scratch"};

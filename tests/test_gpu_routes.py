@@ -69,7 +69,7 @@ def both(ctx, precision, parts, expect):
 
 @pytest.mark.parametrize("precision", PRECISIONS)
 @pytest.mark.parametrize("snr", [None, 0.05])
-@pytest.mark.parametrize("L,r_max,T,K,N", [(24, 9, 2, 400, 300), (64, 32, 3, 60, 171), (76, 35, 3, 100, 60),
+@pytest.mark.parametrize("L,r_max,T,K,N", [(24, 9, 2, 400, 400), (64, 32, 3, 60, 171), (76, 35, 3, 100, 60),
                                            (90, 40, 2, 80, 170), (110, 48, 2, 81, 170), (140, 64, 4, 17, 200)])
 def test_bounds_first(ctx, precision, snr, L, r_max, T, K, N):
     print(f"[gpu-routes] {precision} L={L} K={K} N={N} snr={snr}", flush=True)
