@@ -4,16 +4,15 @@
 A step is one pass of the hot path over the 100k-particle workload
 (N=100000, L=76, K=100 references, shifts +-3 px (49), both mirrors,
 rings 1..35 x 256 angles, SNR 0.05): mra_align (polar resampling + ring
-FFTs, correlation contraction on the matrix cores, inverse FFT over angle,
-arg-max) followed by mra_update_averages.  References are loaded once
+FFTs, a bound of every pair on the matrix cores, then contraction, inverse
+FFT over angle and arg-max of the pairs that can win) followed by
+mra_update_averages.  References are loaded once
 before timing; particles are resident in HBM when the timed region starts.
 
 Prints one JSON line.  `value` is the FP32 form's aligned particles/s; the
 BF16-matrix-core form (FP32 re-score of the winner) is reported beside it.
-`roofline` covers the dominant kernel (the fused correlation kernel), timed
-with HIP events on the library's stream; its `traffic` (HBM bytes per
-launch) comes from the counter summary under profiles/ when that summary was
-taken on the current kernel sources, else null.  `serving` runs the
+`roofline` covers the contraction of every (row, reference) pair (the bound
+kernel), timed with HIP events on the library's stream.  `serving` runs the
 continuous-batching server on a bounded trace (BF16, 8 resident refsets of
 the uneven-stack distribution, Poisson arrivals at 20/s and at a rate one
 GPU sustains) and reports p50/p99 latency and particles/s.  `cpu_baseline`
@@ -23,11 +22,9 @@ times the FP64 oracle on a sample of the same stack.
 from __future__ import annotations
 
 import argparse
-import hashlib
 import json
 import os
 import platform
-import re
 import statistics
 import sys
 import time
@@ -43,39 +40,6 @@ GROUPS = ("polar", "bound", "tighten", "fine", "corr", "merge", "rescore", "aver
 METRIC = "aligned particles/s (L=76,K=100,±3px); FP32 vs BF16-MFMA; p50/p99 latency"
 BF16_MATRIX_PEAK = 2500.0  # TFLOP/s, dense
 HBM_PEAK = 8000.0          # GB/s
-TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "mra_c1_hbm_traffic.md")
-CSRC = os.path.join(ROOT, "paper_2011_05755_amd", "csrc")
-# sources each kernel's code is built from (a change to any of them voids
-# counter figures taken before it)
-KERNEL_SOURCES = {
-    "k_bound": ["bound_impl.h", "corr_impl.h", "k_bound.hip", "mra_common.h", "mra_fft.h"],
-    "k_polar_fft": ["k_polar.hip", "polar_impl.h", "mra_fft.h", "mra_common.h"],
-    "k_avg": ["k_avg.hip", "mra_common.h"],
-}
-
-
-def kernel_sources_sha(kernel: str) -> str:
-    h = hashlib.sha256()
-    for name in KERNEL_SOURCES[kernel]:
-        with open(os.path.join(CSRC, name), "rb") as f:
-            h.update(name.encode() + b"\0" + f.read())
-    return h.hexdigest()[:16]
-
-
-def traffic_from_profile(kernel: str, form: str, workspace_gib: int):
-    """HBM bytes per launch of `kernel` in `form` from the committed counter
-    summary (FETCH_SIZE and WRITE_SIZE, calibrated on a plain copy), or None
-    when the summary is missing, was taken with another chunking, or on
-    other kernel sources."""
-    try:
-        with open(TRAFFIC_SUMMARY) as f:
-            m = re.search(r"<!-- traffic: (\{.*?\}) -->", f.read(), re.S)
-        e = json.loads(m.group(1))[kernel][form]
-    except (OSError, AttributeError, KeyError, ValueError):
-        return None
-    if e.get("sources_sha") != kernel_sources_sha(kernel) or e.get("workspace_gib") != workspace_gib:
-        return None
-    return float(e["bytes_per_launch"])
 
 
 def log(msg):
@@ -250,8 +214,6 @@ def main() -> int:
         return dict(bound="mfma", achieved=round(achieved, 2), peak=BF16_MATRIX_PEAK, unit="TFLOP/s",
                     frac=round(achieved / BF16_MATRIX_PEAK, 4),
                     frac_padded=round(achieved * 4 * R4 / R / BF16_MATRIX_PEAK, 4),
-                    traffic=traffic_from_profile("k_bound", form, args.workspace_gib),
-                    traffic_unit="bytes per launch (HBM, counter-measured)",
                     kernel="k_bound", launches_per_step=n // args.steps,
                     avg_launch_ms=round(ms / n, 4),
                     flops_per_row_ref=corr_flops_per_row_ref(R))
@@ -274,7 +236,6 @@ def main() -> int:
                            speedup_vs_fp32=round(results[head]["ms"] / r["ms"], 3) if head == "fp32" else None,
                            bound_avg_launch_ms=br["avg_launch_ms"],
                            bound_matrix_tflops=br["achieved"], bound_matrix_frac=br["frac"],
-                           bound_traffic_bytes_per_launch=br["traffic"],
                            polar_hbm_gbps=round(polar_gbps(form), 1),
                            polar_hbm_frac=round(polar_gbps(form) / HBM_PEAK, 4))
 

@@ -244,9 +244,8 @@ int mra_rfa(mra_ctx* ctx, int32_t refset_id, const mra_geom* g, const float* par
 
 /* Alignment of several stacks of uneven size (each against its own refset,
  * with its own shift range) in one call.  Stacks are cut into pieces that
- * fill the workspace; pieces with the same precision and tile variant share
- * one persistent correlation launch (workgroups pull (stack, row tile) work
- * items until all are done) and one launch of each per-particle kernel.
+ * fill the workspace; pieces of the same precision and range of ring counts (1..32,
+ * 33..40, 41..48, 49..64) share one launch of each kernel.
  * Each stack's results equal those of mra_align on it alone.  Errors as
  * mra_align, checked for every stack before anything is enqueued. */
 int mra_align_batch(mra_ctx* ctx, const mra_stack* stacks, int32_t n);
@@ -254,7 +253,7 @@ int mra_align_batch(mra_ctx* ctx, const mra_stack* stacks, int32_t n);
 /* Tile configuration of a refset's correlation kernel (chosen by the
  * autotuner in paper_2011_05755_amd/autotune.py, or left at the default).
  *  corr_variant  tile configuration of the evaluation of every pair (prune = 0,
- *                calls of few particles).  -1: default for the geometry.  FP32:
+ *                calls of few pairs).  -1: default for the geometry.  FP32:
  *                0 = 8 waves with the particle operand held in registers
  *                (R4 = ceil(n_rings/4) <= 9), 1 = 4 waves, operand in registers
  *                (R4 <= 12), 2 = 8 waves, operand streamed (any R4).  BF16/FP16:
@@ -267,8 +266,9 @@ int mra_align_batch(mra_ctx* ctx, const mra_stack* stacks, int32_t n);
  *                16-bit products (for FP32 raised by what their rounding can
  *                change), and only the pairs whose bound can still win are
  *                evaluated, in the refset's precision, best bound first; 0:
- *                evaluate every pair.  (A call of few particles, or with a
- *                workspace too small for the bounds, evaluates every pair.)
+ *                evaluate every pair.  (A call or chunk of few pairs, one without
+ *                shifts, or with a workspace too small for the bounds, evaluates every
+ *                pair.)
  *  run_tiles     0 .. 64, accepted and reported; no longer used.
  * Results do not depend on the tuning (bit for bit). */
 typedef struct mra_tuning {
@@ -296,7 +296,8 @@ int mra_debug_refs(mra_ctx* ctx, int32_t refset_id, float* qhat, double* norm);
  * recording a HIP event pair around every launch of the named kernel groups
  * ("polar", "bound", "tighten", "fine" and "fine2" for the resampling, the
  * bounds, the FP16 tightening of FP32 bounds, the evaluation of the pairs that
- * can win and its runner-up pass of cc2; "corr", "merge" and "corr2" where
+ * can win (of every pair, for particles of which nearly all can) and its runner-up
+ * pass of cc2; "corr", "merge" and "corr2" where
  * every pair is evaluated; "rescore", "averages", "rfa" for the fused K = 1
  * kernel and "refine" for psi_frac) on the context's stream;
  * mra_profile(ctx, 0) stops.  mra_profile_read synchronises the stream and

@@ -79,20 +79,12 @@ __device__ __forceinline__ int a_block_pos(int j) { return (j & 1) * 8 + (j >> 1
 // 2 (ln / 16) + q, ref (ln / 2) & 7, q = ln & 1.
 __device__ __forceinline__ int lane_pair(int ln) { return (2 * (ln >> 4) + (ln & 1)) * 8 + ((ln >> 1) & 7); }
 
-// Particle operand of lane ln for slot `slot`: ring g*R4 + t of lane group
-// g = ln/16 at element t * ring_stride(LAYOUT) (kRingMajor or kSlotMajor,
-// fixed per contraction form; the host has the resampler write the same
-// one; kRingPerm is read two slots at a time with a_pair).  Rings >= R are
-// padding that the polar kernel never writes: callers mask them.
-// RX > 0: R4 == RX is known at compile time.
-constexpr int ring_stride(int layout) { return layout == kSlotMajor ? 16 : kSlots * 16; }
-template <int LAYOUT, int RX = 0>
+// Particle operand of lane ln for slot `slot` in the slot-major layout: ring
+// g*R4 + t of lane group g = ln/16 at element 16 t (kRingPerm is read two slots at a
+// time with a_pair).  Rings >= R are padding that the polar kernel never writes:
+// callers mask them.
 __device__ __forceinline__ const float* a_lane(const CorrArgs& a, int tile, int slot, int ln) {
-  static_assert(LAYOUT != kRingPerm, "the paired layout is read with a_pair");
-  const int R4 = RX > 0 ? RX : a.R4;
-  if constexpr (LAYOUT == kSlotMajor)
-    return a.A + (size_t)(tile * kSlots + slot) * 64 * R4 + ((ln >> 4) * R4) * 16 + a_block_pos(ln & 15);
-  return a.A + ((size_t)(tile * 4 + (ln >> 4)) * R4 * kSlots + slot) * 16 + a_block_pos(ln & 15);
+  return a.A + (size_t)(tile * kSlots + slot) * 64 * a.R4 + ((ln >> 4) * a.R4) * 16 + a_block_pos(ln & 15);
 }
 // Element t of the lane's operand: ring (ln/16)*R4 + t.  The load is never
 // conditional (a conditional load waits for its data before the next one is
@@ -100,12 +92,10 @@ __device__ __forceinline__ const float* a_lane(const CorrArgs& a, int tile, int 
 // t >= R4 and padding rings >= R (which hold no data) are cleared by an AND
 // with a mask that is opaque to the optimiser, which would otherwise turn
 // the select back into a branch around the load.
-template <int LAYOUT, int RX = 0>
 __device__ __forceinline__ float a_elem(const CorrArgs& a, const float* ap, int ln, int t, bool nt) {
-  const int R4 = RX > 0 ? RX : a.R4;
-  const int tt = t < R4 ? t : R4 - 1;
-  const float x = nt ? __builtin_nontemporal_load(ap + tt * ring_stride(LAYOUT)) : ap[tt * ring_stride(LAYOUT)];
-  uint32_t keep = (t < R4 && (ln >> 4) * R4 + t < a.R) ? 0xffffffffu : 0u;
+  const int tt = t < a.R4 ? t : a.R4 - 1;
+  const float x = nt ? __builtin_nontemporal_load(ap + 16 * tt) : ap[16 * tt];
+  uint32_t keep = (t < a.R4 && (ln >> 4) * a.R4 + t < a.R) ? 0xffffffffu : 0u;
   asm("" : "+v"(keep));
   return __uint_as_float(__float_as_uint(x) & keep);
 }
@@ -217,9 +207,9 @@ struct Fp32Contract {
       } else {
 #pragma unroll
         for (int i = 0; i < SPW; ++i) {
-          const float* ap = a_lane<LAYOUT, RX>(a, tile, w + NW * i, ln);
+          const float* ap = a_lane(a, tile, w + NW * i, ln);
 #pragma unroll
-          for (int t = 0; t < MAXR; ++t) areg[i][t] = a_elem<LAYOUT, RX>(a, ap, ln, t, true);
+          for (int t = 0; t < MAXR; ++t) areg[i][t] = a_elem(a, ap, ln, t, true);
         }
       }
     }
@@ -260,9 +250,9 @@ struct Fp32Contract {
       // that the slot loop need not be unrolled)
       float b0[MAXR], a0[MAXR], b1[MAXR], a1[MAXR];
       auto loada = [&](int i, float (&dst)[MAXR]) {
-        const float* ap = a_lane<LAYOUT, RX>(a, tile, w + NW * i, ln);
+        const float* ap = a_lane(a, tile, w + NW * i, ln);
 #pragma unroll
-        for (int t = 0; t < MAXR; ++t) dst[t] = a_elem<LAYOUT, RX>(a, ap, ln, t, false);
+        for (int t = 0; t < MAXR; ++t) dst[t] = a_elem(a, ap, ln, t, false);
       };
       auto chain = [&](const float (&x)[MAXR], const float (&y)[MAXR], int slot) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};

@@ -5,8 +5,8 @@
 
 namespace mra {
 
-// As many workgroups as the CUs take at once (16 waves each, by registers),
-// each taking every grid-th particle.
+// As many workgroups as the CUs' registers take at once (16 waves each), each taking
+// every grid-th particle (where the LDS takes fewer, the others start as those end).
 int fine_grid(int prec, int64_t n, int n_cu) {
   const int64_t most = (int64_t)n_cu * 16 / fine_waves(prec);
   return (int)(n < most ? n : most);

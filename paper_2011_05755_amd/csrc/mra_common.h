@@ -15,7 +15,6 @@ constexpr int kRowTile = 8;         // particle rows (shift, particle) per corre
 constexpr int kMaxShifts = 289;     // shifts per particle at the largest search range (+-8)
 constexpr int kRefTile = 8;         // references per correlation tile
 constexpr int kPolarWaves = 8;      // resampling workgroup: 8 waves, 8 shifts x 8 FFT lanes each
-constexpr int kPolarThreads = 64 * kPolarWaves;
 constexpr int kMaxBatchPieces = 12; // stack pieces per batched launch (kernel-argument table)
 constexpr int kAvgChunk = 32;       // particles per partial class sum
 constexpr int kAvgThreads = 256;
@@ -32,10 +31,9 @@ __host__ __device__ constexpr float rerank_margin(int prec) {
 
 // Layouts of the particle operand A (per row tile of 8 rows, 16 floats per
 // (ring, slot): p*8 + row%8):
-//   kRingMajor  [ring < 4*R4][slot][16]: one (ring, row group) item of the
-//               resampler writes one contiguous 8 KB run
-//   kRingPerm   the same with slot s at position slot_pos(s), so that the
-//               slots s = w + 8 i of correlation wave w are contiguous, and
+//   kRingPerm   [ring < 4*R4][position][16], slot s at position slot_pos(s): one
+//               (ring, row group) item of the resampler writes one contiguous
+//               8 KB run, the slots s = w + 8 i of correlation wave w are contiguous, and
 //               positions 2m, 2m+1 interleaved element by element in one
 //               128-byte block (float 2k + (pos & 1) holds element k), so
 //               that one 8-byte load per lane reads both (FP32, 8 waves,
@@ -49,7 +47,7 @@ __host__ __device__ constexpr float rerank_margin(int prec) {
 //               16 w + i) and each run of 8 positions interleaved by element:
 //               element k of position 8 G + j at a16_index(8 G + j, k), so that
 //               one 16-byte load gives a lane element k of 8 of its wave's slots
-enum ALayout { kRingMajor = 0, kRingPerm = 1, kSlotMajor = 2, kRingPerm16 = 3 };
+enum ALayout { kRingPerm = 1, kSlotMajor = 2, kRingPerm16 = 3 };
 __host__ __device__ constexpr int slot_pos(int s) { return (s & 7) * 16 + (s >> 3); }
 // 16-bit index of element k of position pos within one (row tile, ring) block
 __host__ __device__ constexpr int a16_index(int pos, int k) { return (pos >> 3) * 128 + k * 8 + (pos & 7); }
