@@ -267,8 +267,8 @@ int mra_align_batch(mra_ctx* ctx, const mra_stack* stacks, int32_t n);
  *                change), and only the pairs whose bound can still win are
  *                evaluated, in the refset's precision, best bound first; 0:
  *                evaluate every pair.  (A call or chunk of few pairs, one without
- *                shifts, or with a workspace too small for the bounds, evaluates every
- *                pair.)
+ *                shifts or of up to 16 references in 16 bits, or with a workspace too
+ *                small for the bounds, evaluates every pair.)
  *  run_tiles     0 .. 64, accepted and reported; no longer used.
  * Results do not depend on the tuning (bit for bit). */
 typedef struct mra_tuning {

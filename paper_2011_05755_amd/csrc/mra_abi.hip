@@ -426,6 +426,15 @@ int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned
   return std::max<int64_t>(1, (int64_t)(budget / particle_bytes(rs, p, pruned)));
 }
 
+// One or two reference tiles in 16 bits, whatever the size: evaluating every pair costs
+// about what the bounds and their evaluation do on particles of these references, and less
+// on particles of others, of which more pairs stay live (4000 particles, 10 references,
+// bounds / every pair, ms, of these references and of 80: BF16 64 px, +-2 1.74 / 1.65
+// and 2.11 / 1.64; 90 px, 36 rings, +-3 3.20 / 3.52 and 4.43 / 3.74; 100 000 particles of 200:
+// 109 / 90).  Not with the runner-up, for which every pair is evaluated twice (90 px: 3.88 /
+// 5.24), nor for few rings, whose operand bounds little work (24 px, 9 rings, +-2: 0.77 / 1.01).
+bool few_refs(const Refset& rs, bool cc2) { return rs.g.precision != kFP32 && rs.n_kt <= 2 && rs.R4 > 6 && !cc2; }
+
 // A call of few pairs, or of few pairs per particle, takes the unpruned way: with
 // every pair of a few row and reference tiles spread over the CUs it ends before the
 // pruned way's chain of dependent steps does, and a particle costs the evaluation
@@ -441,9 +450,10 @@ int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned
 // references, 200 particles 312 / 388 (7).  BF16 64 px, +-2, 20 references, 200 particles 209 /
 // 168 (7), 1000: 512 / 523 (37); 76 px, +-3, 100 references, 30 particles 224 / 167 (9).
 // Without shifts a step holds at most 8 pairs, of one row: 64 px, 5000 references, 2000
-// particles FP32 8.0 / 6.5 ms, BF16 6.7 / 4.3.
-bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N) {
-  if (p.S == 1) return true;
+// particles FP32 8.0 / 6.5 ms, BF16 6.7 / 4.3.  Nor do the bounds save much of one or two
+// reference tiles (few_refs).
+bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N, bool cc2) {
+  if (p.S == 1 || few_refs(rs, cc2)) return true;
   const int64_t tiles = (N * p.S + kRowTile - 1) / kRowTile * rs.n_kt;
   const int R4 = rs.R4, per_cu = rs.g.precision == kFP32 ? std::max(4, 5500 / (R4 * R4 * R4)) : (R4 <= 6 ? 20 : 12);
   return tiles <= per_cu * (int64_t)c->n_cu + 4 * N;
@@ -469,14 +479,14 @@ int64_t fitting_chunk(const Refset& rs, const Plan& p, int64_t N, bool pruned, b
 // takes at most half the cap, as the unpruned operand does: the other half is left
 // to the steps beside it (reference preparation, averages).
 int64_t pruned_chunk(mra_ctx* c, const Refset& rs, const Plan& p, int64_t N, bool cc2) {
-  if (!rs.prune || few_pairs(c, rs, p, N)) return 0;
+  if (!rs.prune || few_pairs(c, rs, p, N, cc2)) return 0;
   const int64_t most = std::min<int64_t>(INT32_MAX / p.S / 2, N);
   const uint64_t room = c->cap - std::min(c->cap, ws_kept(c));
   int64_t n = std::min<int64_t>(rs.chunk, most);
   if (rs.chunk <= 0) n = fitting_chunk(rs, p, N, true, cc2, c->n_cu, std::min(c->cap / 2, room));
   else
     while (n > 0 && carve_chunk(rs, p, n, true, cc2, c->n_cu, nullptr, nullptr) > room) n /= 2;
-  return few_pairs(c, rs, p, n) ? 0 : n;
+  return few_pairs(c, rs, p, n, cc2) ? 0 : n;
 }
 
 // Sub-step angles of particles n0 .. n0 + nc - 1 from their final parameters.
@@ -740,7 +750,7 @@ void align_impl(mra_ctx* c, int32_t id, const float* parts, int64_t N, int T, co
   }
   if (!c->scratch) throw Fail{MRA_E_DEVICE, "no-allocation scratch not resolved on this device"};
   int64_t step = rs.prune ? fitting_chunk(rs, p, N, true, out->cc2 != nullptr, c->n_cu, kScratchBytes) : 0;
-  const bool pruned = step > 0 && !few_pairs(c, rs, p, step);
+  const bool pruned = step > 0 && !few_pairs(c, rs, p, step, out->cc2 != nullptr);
   if (!pruned) step = fitting_chunk(rs, p, N, false, out->cc2 != nullptr, c->n_cu, kScratchBytes);
   if (step < 1)
     throw Fail{MRA_E_INVAL, "one particle's operand exceeds the " + std::to_string(kScratchBytes >> 20) +
@@ -939,10 +949,12 @@ void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Pla
       continue;
     }
     // runner-up, refinement, no pruning, a workspace too small for the bounds, or one
-    // reference tile, which the bounds cannot save much of (4 stacks of 1000 particles, 8
-    // references: FP32 3.60 ms in a wave, 3.30 alone; BF16 2.91, 2.37; with 10 references a
-    // wave is the faster), and rows that fill the chip: the per-chunk path
-    const bool alone = rs.n_kt == 1 && few_pairs(c, rs, p, s.N) && s.N * p.S >= 2 * kRowTile * (int64_t)c->n_cu;
+    // reference tile (16 bits: two), which the bounds cannot save much of, and rows that
+    // fill the chip: the per-chunk path.  (4 stacks of 1000 particles, 8 references: FP32 3.60
+    // ms in a wave, 3.30 alone; BF16 2.91, 2.37; 10 references, BF16 3.11, 2.72; 12 of 300:
+    // 3.03 in a wave, 3.66 alone.)
+    const bool alone = few_pairs(c, rs, p, s.N, false) && (rs.n_kt == 1 || few_refs(rs, false)) &&
+                       s.N * p.S >= (rs.n_kt == 1 ? 2 : 8) * kRowTile * (int64_t)c->n_cu;
     if (s.out.cc2 || s.out.psi_frac || !rs.prune || alone || particle_bytes(rs, p, true) > budget / 2) {
       align_stack(c, rs, p, s.parts, 0, s.N, &s.out, nullptr);
       continue;

@@ -146,3 +146,35 @@ def test_small_reference_sets_scale_into_the_bounds():
             got.append(r)
     np.testing.assert_array_equal(got[0]["flat_index"], got[1]["flat_index"])
     np.testing.assert_array_equal(np.ldexp(got[0]["cc"], -118), got[1]["cc"])
+
+
+# sizes beyond the rule on pairs, in every row here
+@pytest.mark.parametrize("precision,K,r_max,cc2,every", [
+    ("bf16", 8, 28, False, True), ("bf16", 16, 28, False, True), ("fp16", 16, 46, False, True),
+    ("bf16", 17, 28, False, False), ("fp32", 16, 28, False, False), ("bf16", 16, 28, True, False),
+    ("fp16", 16, 24, False, False)])
+def test_few_references(ctx, precision, K, r_max, cc2, every):
+    from paper_2011_05755_amd import mra
+    N = 700 if K > 8 else 1600
+    print(f"[gpu-routes] {precision} K={K} r_max={r_max} cc2={cc2}", flush=True)
+    refs, parts = stack(2 * r_max + 8, K, 3, N, r_max)
+    ctx.load_refs(0, refs, r_min=1, r_max=r_max, shift_max=3, precision=precision)
+    expect = every_pair(cc2) if every else bounds_first(precision, cc2)
+    got, ran = run(ctx, lambda: ctx.align(0, parts, with_cc2=cc2))
+    assert ran == expect, ran
+    # the other way: with the runner-up bounds come first, without pruning they don't
+    ctx.set_tuning(0, prune=-1 if every else 0)
+    want, ran = run(ctx, lambda: ctx.align(0, parts, with_cc2=True))
+    assert ran == (bounds_first(precision) if every else every_pair()), ran
+    same(got, {f: want[f] for f in got})
+    if cc2:
+        return
+    ctx.set_tuning(0)
+    out = [mra.AlignResult.empty(N, DEV) for _ in range(2)]
+    ctx.profile(True)
+    ctx.align_batch([(0, parts, -1, o) for o in out])
+    torch.cuda.synchronize()
+    assert {g for g in GROUPS if ctx.profile_read(g)[1]} == expect
+    ctx.profile(False)
+    for o in out:
+        same(o.to_numpy(), {f: want[f] for f in got})
