@@ -245,7 +245,8 @@ int mra_rfa(mra_ctx* ctx, int32_t refset_id, const mra_geom* g, const float* par
 /* Alignment of several stacks of uneven size (each against its own refset,
  * with its own shift range) in one call.  Stacks are cut into pieces that
  * fill the workspace; pieces of the same precision and range of ring counts (1..32,
- * 33..40, 41..48, 49..64) share one launch of each kernel.
+ * 33..40, 41..48, 49..64) share one launch of each kernel, and apart from them those
+ * whose every pair is evaluated (see mra_tuning).
  * Each stack's results equal those of mra_align on it alone.  Errors as
  * mra_align, checked for every stack before anything is enqueued. */
 int mra_align_batch(mra_ctx* ctx, const mra_stack* stacks, int32_t n);

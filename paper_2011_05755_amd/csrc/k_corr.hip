@@ -42,13 +42,28 @@ hipError_t launch_corr_runner_up(int prec, int variant, const CorrArgs& a, hipSt
   return launch(prec, variant, kRunnerUp, a, st);
 }
 
+// One launch of the arg-max over the pieces of a batch, which take the same instance:
+// variant and ring bucket (FP32 variant 0: ring count).
+hipError_t launch_corr_batch(int prec, int variant, const CorrBatch& b, hipStream_t st) {
+  if (b.n <= 0 || b.start[b.n] <= 0) return hipSuccess;
+  const int R4 = b.piece[0].R4;
+  for (int i = 0; i < b.n; ++i) {
+    const CorrArgs& a = b.piece[i];
+    if (!corr_variant_ok(prec, variant, a.R4) || a.a_layout != a_layout_for(prec, variant) || a.kt_per_wg < 1 || !a.rowkey ||
+        corr_group(prec, variant, a.R4) != corr_group(prec, variant, R4) || b.start[i + 1] - b.start[i] != corr_items(a))
+      return hipErrorInvalidValue;
+  }
+  if (prec == kFP32) corr_dispatch_fp32(variant, b, st);
+  else if (prec == kBF16) corr_dispatch_bf16(variant, b, st);
+  else corr_dispatch_fp16(variant, b, st);
+  return hipGetLastError();
+}
+
 // Per-particle merge of its S row bests (the keys order them as the tie rule
 // does) and decoding of the flat index into alignment parameters; one wave
 // per particle.
-__global__ __launch_bounds__(256) void k_merge(MergeArgs m) {
+__device__ __forceinline__ void merge_particle(const MergeArgs& m, int n, int ln) {
   const ResultArgs& a = m.r;
-  const int n = (blockIdx.x * 256 + threadIdx.x) >> 6, ln = threadIdx.x & 63;
-  if (n >= a.n_part) return;
   auto value = [&](float v) { return m.maxabs ? fp16_value(v, m.maxabs[n], m.b_scale) : v; };
   unsigned long long best = 0ull;
   for (int s = ln; s < a.S; s += 64) {
@@ -67,9 +82,28 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs m) {
   if (ln == 0) write_result(a, n, value(key_value(best)), key_index(best));
 }
 
+__global__ __launch_bounds__(256) void k_merge(MergeArgs m) {
+  const int n = (blockIdx.x * 256 + threadIdx.x) >> 6;
+  if (n < m.r.n_part) merge_particle(m, n, threadIdx.x & 63);
+}
+
+__global__ __launch_bounds__(256) void k_merge_batch(MergeBatch b) {
+  const int item = __builtin_amdgcn_readfirstlane((blockIdx.x * 256 + threadIdx.x) >> 6);
+  if (item >= b.start[b.n]) return;
+  int p = 0;
+  while (p + 1 < b.n && b.start[p + 1] <= item) ++p;
+  merge_particle(b.piece[p], item - b.start[p], threadIdx.x & 63);
+}
+
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
   if (a.r.n_part <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_merge, dim3((a.r.n_part + 3) / 4), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_merge_batch(const MergeBatch& b, hipStream_t st) {
+  if (b.n <= 0 || b.start[b.n] <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_merge_batch, dim3((b.start[b.n] + 3) / 4), dim3(256), 0, st, b);
   return hipGetLastError();
 }
 

@@ -435,6 +435,11 @@ int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned
 // 5.24), nor for few rings, whose operand bounds little work (24 px, 9 rings, +-2: 0.77 / 1.01).
 bool few_refs(const Refset& rs, bool cc2) { return rs.g.precision != kFP32 && rs.n_kt <= 2 && rs.R4 > 6 && !cc2; }
 
+// Few pairs at any number of particles.
+bool few_each(const Refset& rs, const Plan& p, bool cc2) {
+  return p.S == 1 || few_refs(rs, cc2) || p.S * rs.n_kt <= 4 * kRowTile;
+}
+
 // A call of few pairs, or of few pairs per particle, takes the unpruned way: with
 // every pair of a few row and reference tiles spread over the CUs it ends before the
 // pruned way's chain of dependent steps does, and a particle costs the evaluation
@@ -453,7 +458,7 @@ bool few_refs(const Refset& rs, bool cc2) { return rs.g.precision != kFP32 && rs
 // particles FP32 8.0 / 6.5 ms, BF16 6.7 / 4.3.  Nor do the bounds save much of one or two
 // reference tiles (few_refs).
 bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N, bool cc2) {
-  if (p.S == 1 || few_refs(rs, cc2)) return true;
+  if (few_each(rs, p, cc2)) return true;
   const int64_t tiles = (N * p.S + kRowTile - 1) / kRowTile * rs.n_kt;
   const int R4 = rs.R4, per_cu = rs.g.precision == kFP32 ? std::max(4, 5500 / (R4 * R4 * R4)) : (R4 <= 6 ? 20 : 12);
   return tiles <= per_cu * (int64_t)c->n_cu + 4 * N;
@@ -584,6 +589,18 @@ RescoreArgs rescore_args(const Refset& rs, const Plan& p, const float* src, int6
   return ra;
 }
 
+// Merge of a chunk's rows, every pair evaluated.
+MergeArgs merge_args(const Refset& rs, const Plan& p, int64_t n0, int nc, const mra_result* out, const ChunkBufs& b) {
+  MergeArgs ma{};
+  ma.r = result_args(p, n0, nc, out, b);
+  ma.rowkey = b.rowkey;
+  ma.maxabs = rs.g.precision == kFP16 ? b.maxabs : nullptr;
+  ma.b_scale = rs.b_scale;
+  ma.row_cc = b.rcc;
+  ma.row_idx = b.ridx;
+  return ma;
+}
+
 // Evaluation of a chunk from its operand and bounds (ca, with b's buffers).
 FineArgs fine_args(mra_ctx* c, const Refset& rs, const Plan& p, const CorrArgs& ca, const float* src, int64_t n0,
                    int nc, const mra_result* out, const ChunkBufs& b) {
@@ -665,13 +682,7 @@ void run_chunk_unpruned(mra_ctx* c, const Refset& rs, const Plan& p, const float
   ca.kt_per_wg = corr_tiles_per_wg(ca.n_row_tiles, rs.n_kt, c->n_cu);
   timed(c, "corr", [&] { hip_check(c, launch_corr(prec, rs.variant, table != nullptr, ca, st), "corr"); });
   if (table) return;
-  MergeArgs ma{};
-  ma.r = result_args(p, n0, nc, out, b);
-  ma.rowkey = b.rowkey;
-  ma.maxabs = prec == kFP16 ? b.maxabs : nullptr;
-  ma.b_scale = rs.b_scale;
-  ma.row_cc = b.rcc;
-  ma.row_idx = b.ridx;
+  MergeArgs ma = merge_args(rs, p, n0, nc, out, b);
   timed(c, "merge", [&] { hip_check(c, launch_merge(ma, st), "merge"); });
   if (prec != kFP32)
     timed(c, "rescore", [&] { hip_check(c, launch_rescore(rescore_args(rs, p, src, n0, nc, out, b), st), "rescore"); });
@@ -771,6 +782,7 @@ struct Piece {
   Plan p;
   int64_t n0;
   int nc;
+  bool every;  // evaluate every pair
 };
 
 // Device buffers of a batched wave, those of the pieces end to end.
@@ -786,7 +798,7 @@ struct WaveBufs {
 };
 
 // 8-byte words of a piece's row keys
-size_t wave_rowkeys(size_t rows) { return (rowkey_bytes(rows, true) + 7) / 8; }
+size_t wave_rowkeys(size_t rows, bool pruned) { return (rowkey_bytes(rows, pruned) + 7) / 8; }
 
 // Calls take(name, bytes) for every buffer of a wave.
 template <class Take>
@@ -798,7 +810,7 @@ WaveBufs layout_wave(const std::vector<Piece>& w, int n_cu, Take take) {
   for (const Piece& pc : w) {
     const size_t r = (size_t)pc.nc * pc.p.S, t = (r + kRowTile - 1) / kRowTile;
     a_bytes += t * tile_bytes_of(*pc.rs, true);
-    keys += wave_rowkeys(r);
+    keys += wave_rowkeys(r, true);
     tiles += t;
     ub_floats += r * ub_pitch(*pc.rs);
     rows += r;
@@ -825,7 +837,105 @@ WaveBufs layout_wave(const std::vector<Piece>& w, int n_cu, Take take) {
   return b;
 }
 
+// The same for a wave whose every pair is evaluated.
+template <class Take>
+WaveBufs layout_every(const std::vector<Piece>& w, Take take) {
+  WaveBufs b;
+  size_t a_bytes = 0, keys = 0, rows = 0;
+  for (const Piece& pc : w) {
+    const size_t r = (size_t)pc.nc * pc.p.S;
+    a_bytes += (r + kRowTile - 1) / kRowTile * tile_bytes_of(*pc.rs, false);
+    keys += wave_rowkeys(r, false);
+    rows += r;
+    b.parts += pc.nc;
+  }
+  b.A = (char*)take("A", a_bytes);
+  b.rowkey = (unsigned long long*)take("rowkey", keys * sizeof(unsigned long long));
+  if (w[0].rs->g.precision != kFP32) {
+    b.rcc = (float*)take("row_cc", rows * sizeof(float));
+    b.ridx = (int*)take("row_idx", rows * sizeof(int));
+  }
+  if (w[0].rs->g.precision == kFP16) b.maxabs = (float*)take("maxabs", b.parts * sizeof(float));
+  return b;
+}
+
+// A wave with every pair evaluated: one launch each of resample + FFT, correlation,
+// merge and (16-bit forms) re-score.  Rows past a piece in its last tile keep what
+// is there: they take no part in any result.
+void launch_every(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& w) {
+  hipStream_t st = c->stream;
+  uint64_t total = ws_kept(c);
+  WsNeed need;
+  layout_every(w, [&](const char* name, size_t bytes) -> void* {
+    total += bytes;
+    need.emplace_back(name, bytes);
+    return nullptr;
+  });
+  if (w.size() == 1 || total > c->cap) {
+    for (const Piece& pc : w)
+      align_stack(c, *pc.rs, pc.p, stacks[pc.stack].parts, pc.n0, pc.nc, &stacks[pc.stack].out, nullptr);
+    return;
+  }
+  ws_step(c, need);
+  WaveBufs b = layout_every(w, [&](const char* name, size_t bytes) { return ws_get(c, name, bytes); });
+  const int prec = w[0].rs->g.precision, variant = w[0].rs->variant, np = (int)w.size();
+  const int layout = a_layout_for(prec, variant);
+  int64_t tiles = 0;
+  for (const Piece& pc : w) tiles += ((int64_t)pc.nc * pc.p.S + kRowTile - 1) / kRowTile;
+  PolarBatch pb{};
+  CorrBatch cb{};
+  MergeBatch mb{};
+  RescoreBatch rb{};
+  pb.n = cb.n = mb.n = rb.n = np;
+  int part = 0, items = 0, pitems = 0;
+  for (int i = 0; i < np; ++i) {
+    const Piece& pc = w[i];
+    const Refset& rs = *pc.rs;
+    const mra_stack& sk = stacks[pc.stack];
+    const size_t r = (size_t)pc.nc * pc.p.S;
+    const float* src = sk.parts + (size_t)pc.n0 * rs.g.L * rs.g.L;
+    ChunkBufs cbuf;
+    cbuf.A = (float*)b.A;
+    cbuf.rowkey = b.rowkey;
+    cbuf.maxabs = b.maxabs ? b.maxabs + part : nullptr;
+    if (row_results(rs)) {
+      cbuf.rcc = b.rcc;
+      cbuf.ridx = b.ridx;
+    }
+    PolarArgs& pa = pb.piece[i] = polar_args(c, rs, pc.p, src, pc.nc);
+    pa.split = polar_split((int)b.parts, rs.R * (pc.p.S / kRowTile + 1), c->n_cu, polar_waves(pa));
+    pa.a_layout = layout;
+    pa.maxabs = cbuf.maxabs;
+    pa.rowkey = cbuf.rowkey;
+    pa.out = cbuf.A;
+    CorrArgs& ca = cb.piece[i] = corr_args(c, rs, pc.p, pc.nc, layout, cbuf);
+    ca.kt_per_wg = corr_tiles_per_wg((int)std::min<int64_t>(tiles, INT32_MAX), rs.n_kt, c->n_cu);
+    mb.piece[i] = merge_args(rs, pc.p, pc.n0, pc.nc, &sk.out, cbuf);
+    rb.piece[i] = rescore_args(rs, pc.p, src, pc.n0, pc.nc, &sk.out, cbuf);
+    pb.start[i] = pitems;
+    pitems += pc.nc * pa.split;
+    cb.start[i] = items;
+    items += corr_items(ca);
+    mb.start[i] = rb.start[i] = part;
+    part += pc.nc;
+    b.A += (r + kRowTile - 1) / kRowTile * tile_bytes_of(rs, false);
+    b.rowkey += wave_rowkeys(r, false);
+    if (b.rcc) {
+      b.rcc += r;
+      b.ridx += r;
+    }
+  }
+  pb.start[np] = pitems;
+  cb.start[np] = items;
+  mb.start[np] = rb.start[np] = part;
+  timed(c, "polar", [&] { hip_check(c, launch_polar_batch(pb, st), "polar batch"); });
+  timed(c, "corr", [&] { hip_check(c, launch_corr_batch(prec, variant, cb, st), "corr batch"); });
+  timed(c, "merge", [&] { hip_check(c, launch_merge_batch(mb, st), "merge batch"); });
+  if (prec != kFP32) timed(c, "rescore", [&] { hip_check(c, launch_rescore_batch(rb, st), "rescore batch"); });
+}
+
 void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& w) {
+  if (w[0].every) return launch_every(c, stacks, w);
   hipStream_t st = c->stream;
   uint64_t total = ws_kept(c);
   WsNeed need;
@@ -895,7 +1005,7 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
     A += (r + kRowTile - 1) / kRowTile * tile_bytes_of(rs, true);
     ub += r * ub_pitch(rs);
     ub_hi += r * ub_pitch(rs);
-    rowkey += wave_rowkeys(r);
+    rowkey += wave_rowkeys(r, true);
     if (rownorm) rownorm += 2 * r;
     if (rcc) {
       rcc += r;
@@ -922,16 +1032,38 @@ void launch_wave(mra_ctx* c, const mra_stack* stacks, const std::vector<Piece>& 
 
 void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Plan>& plans) {
   const uint64_t budget = c->cap / 2;
-  // stacks that share the kernels' instantiations (precision and ring bucket)
-  // are packed into the same waves; within a group the caller's order holds
-  std::vector<int> order(n);
-  for (int i = 0; i < n; ++i) order[i] = i;
-  auto group = [](const Refset& rs) { return rs.g.precision * 4 + ring_bucket(rs.R4); };
+  // Stacks that share the kernels' instantiations are packed into the same waves; within a
+  // group the caller's order holds.  A group is of one precision and ring bucket, and of one
+  // instance of the correlation kernel if every pair is evaluated: with pruning off, or few
+  // pairs (in one reference tile, or per particle) of rows that together fill the chip; with
+  // fewer rows they join the others' waves, whose launches they need not repeat.
+  auto instance = [](const Refset& rs) {
+    return 8 + 64 * (rs.g.precision * 4 + rs.variant) + corr_group(rs.g.precision, rs.variant, rs.R4) * 1024;
+  };
+  auto few = [&](const Refset& rs, int i) {
+    return rs.K > 1 && (few_each(rs, plans[i], false) || (rs.n_kt == 1 && few_pairs(c, rs, plans[i], stacks[i].N, false)));
+  };
+  std::map<int, int64_t> rows;
+  for (int i = 0; i < n; ++i) {
+    if (stacks[i].N <= 0 || stacks[i].out.cc2 || stacks[i].out.psi_frac) continue;
+    const Refset& rs = get_refset(c, stacks[i].refset_id);
+    if (few(rs, i)) rows[instance(rs)] += stacks[i].N * plans[i].S;
+  }
+  auto every = [&](int i) {
+    const Refset& rs = get_refset(c, stacks[i].refset_id);
+    return !rs.prune || (few(rs, i) && rows[instance(rs)] >= 2 * kRowTile * (int64_t)c->n_cu);
+  };
   auto key = [&](int i) {
     if (stacks[i].N <= 0) return 0;
-    return group(get_refset(c, stacks[i].refset_id));
+    const Refset& rs = get_refset(c, stacks[i].refset_id);
+    return every(i) ? instance(rs) : 64 * rs.g.precision + ring_bucket(rs.R4);
   };
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return key(x) < key(y); });
+  std::vector<int> order(n), keys(n);
+  for (int i = 0; i < n; ++i) {
+    order[i] = i;
+    keys[i] = key(i);
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return keys[x] < keys[y]; });
   std::vector<Piece> wave;
   uint64_t used = 0;
   auto flush = [&] {
@@ -948,26 +1080,24 @@ void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Pla
       run_single(c, rs, p, s.parts, s.N, &s.out);
       continue;
     }
-    // runner-up, refinement, no pruning, a workspace too small for the bounds, or one
-    // reference tile (16 bits: two), which the bounds cannot save much of, and rows that
-    // fill the chip: the per-chunk path.  (4 stacks of 1000 particles, 8 references: FP32 3.60
-    // ms in a wave, 3.30 alone; BF16 2.91, 2.37; 10 references, BF16 3.11, 2.72; 12 of 300:
-    // 3.03 in a wave, 3.66 alone.)
-    const bool alone = few_pairs(c, rs, p, s.N, false) && (rs.n_kt == 1 || few_refs(rs, false)) &&
-                       s.N * p.S >= (rs.n_kt == 1 ? 2 : 8) * kRowTile * (int64_t)c->n_cu;
-    if (s.out.cc2 || s.out.psi_frac || !rs.prune || alone || particle_bytes(rs, p, true) > budget / 2) {
+    // runner-up, refinement, a workspace too small, or every pair of so many rows that
+    // a launch fills the chip by itself, with an operand that stays in the last-level cache
+    // (4 stacks of 1000 particles, 8 references, BF16: 2.61 ms in a wave, 2.36 one by one): the
+    // per-chunk path
+    const bool ev = every(i);
+    const uint64_t per = particle_bytes(rs, p, !ev);
+    if (s.out.cc2 || s.out.psi_frac || per > budget / 2 || (ev && s.N * p.S >= 8 * kRowTile * (int64_t)c->n_cu)) {
       align_stack(c, rs, p, s.parts, 0, s.N, &s.out, nullptr);
       continue;
     }
-    const uint64_t per = particle_bytes(rs, p, true);
     const int64_t cap_n = rs.chunk > 0 ? rs.chunk : std::max<int64_t>(1, (int64_t)(budget / per));
     for (int64_t n0 = 0; n0 < s.N;) {
-      const bool compatible = wave.empty() || group(*wave[0].rs) == group(rs);
+      const bool compatible = wave.empty() || keys[wave[0].stack] == keys[i];
       if (!compatible || (int)wave.size() == kMaxBatchPieces || used + per > budget) flush();
       const int64_t room = std::max<int64_t>(1, (int64_t)((budget - used) / per));
       const int nc = (int)std::min<int64_t>({s.N - n0, room, cap_n, (int64_t)(INT32_MAX / p.S / 2)});
-      wave.push_back(Piece{i, &rs, p, n0, nc});
-      used += (uint64_t)nc * per + tile_bytes_of(rs, true);
+      wave.push_back(Piece{i, &rs, p, n0, nc, ev});
+      used += (uint64_t)nc * per + tile_bytes_of(rs, !ev);
       n0 += nc;
     }
   }

@@ -215,6 +215,13 @@ struct MergeArgs {
   int* row_idx;
 };
 
+struct MergeBatch {
+  int n;
+  int start[kMaxBatchPieces + 1];
+  MergeArgs piece[kMaxBatchPieces];
+};
+static_assert(sizeof(CorrBatch) <= 4096 && sizeof(MergeBatch) <= 4096, "kernel arguments");
+
 // Evaluation of the pairs that can win, one workgroup per particle at a time.
 struct FineArgs {
   CorrArgs c;            // A: the rows' operand (16-bit forms) or the scratch tiles (FP32)
@@ -288,6 +295,7 @@ size_t polar_lds_bytes(int Lp);  // a resampler of 8 waves beside an Lp x Lp ima
 void polar_window(PolarArgs& a, int lo, int hi);
 int polar_waves(const PolarArgs& a);
 hipError_t launch_corr(int prec, int variant, bool table, const CorrArgs& a, hipStream_t st);
+hipError_t launch_corr_batch(int prec, int variant, const CorrBatch& b, hipStream_t st);
 hipError_t launch_corr_runner_up(int prec, int variant, const CorrArgs& a, hipStream_t st);
 // 16-bit ring buckets (R4 <= 8, 9..10, 11..12, 13..16): the pieces of a batched launch share one
 constexpr int ring_bucket(int R4) { return R4 <= 8 ? 0 : (R4 <= 10 ? 1 : (R4 <= 12 ? 2 : 3)); }
@@ -329,9 +337,16 @@ inline int corr_tiles_per_wg(int tiles, int n_ref_tiles, int n_cu) {
   }
   return best;
 }
+inline int corr_items(const CorrArgs& a) {
+  return a.n_row_tiles * ((a.n_ref_tiles + a.kt_per_wg - 1) / a.kt_per_wg);
+}
 bool corr_variant_ok(int prec, int variant, int R4);
+// stacks with the same value take the same instance of the correlation kernel (of one
+// precision and variant)
+constexpr int corr_group(int prec, int variant, int R4) { return prec == kFP32 && variant == 0 ? R4 : 16 + ring_bucket(R4); }
 int corr_default_variant(int prec, int R4);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st);
+hipError_t launch_merge_batch(const MergeBatch& b, hipStream_t st);
 hipError_t launch_rescore(const RescoreArgs& a, hipStream_t st);
 hipError_t launch_polar_batch(const PolarBatch& b, hipStream_t st);
 hipError_t launch_rescore_batch(const RescoreBatch& b, hipStream_t st);
