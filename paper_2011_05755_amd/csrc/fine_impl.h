@@ -13,7 +13,7 @@
 // barriers), not by their arithmetic: the state holds 16 pairs and both
 // operands are streamed through the registers, so that several workgroups
 // share a CU: by registers 4 of 4 waves (16-bit forms) or 2 of 8 (FP32); by LDS one less
-// of the former from 121 shifts on, and one of the latter from 90 px or so (its image).
+// of the former from 121 shifts on, and only one of the latter from 90 px or so (its image).
 // Lanes of rows or references that a step does not need repeat those it does,
 // and load nothing more.
 //

@@ -14,6 +14,9 @@
 //      FP32 registers;
 //   5. per class and pixel the chunk sums are added in chunk order and
 //      divided by the count; classes without members keep their image.
+// What bounds step 4 (50 000 particles of 76 px, 100 classes: 0.41 of the update's
+// 0.46 ms; a copy of the images 0.24): vector issue, 69 % of the busy cycles, and the
+// taps' LDS reads, 54 % (conflicts 30 %).
 #include "mra_common.h"
 
 namespace mra {

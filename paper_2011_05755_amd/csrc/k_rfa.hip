@@ -15,6 +15,9 @@
 // inverse DFT of each row gives the CC of the unmirrored (real part) and
 // mirrored (imaginary part) particle at every angle, and the best and
 // runner-up are kept per lane, then per workgroup.
+// What bounds it (8000 particles of 76 px, 7 x 7 shifts, 35 rings: 4.5 ms): vector
+// issue, 80 % of the busy cycles at two waves per SIMD, and LDS, 62 % (taps read with
+// bank conflicts, 27 %).
 #include <climits>
 
 #include "mra_common.h"
