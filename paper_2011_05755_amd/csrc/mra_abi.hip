@@ -426,42 +426,54 @@ int64_t chunk_particles(mra_ctx* c, const Refset& rs, const Plan& p, bool pruned
   return std::max<int64_t>(1, (int64_t)(budget / particle_bytes(rs, p, pruned)));
 }
 
-// One or two reference tiles in 16 bits, whatever the size: evaluating every pair costs
-// about what the bounds and their evaluation do on particles of these references, and less
-// on particles of others, of which more pairs stay live (4000 particles, 10 references,
-// bounds / every pair, ms, of these references and of 80: BF16 64 px, +-2 1.74 / 1.65
-// and 2.11 / 1.64; 90 px, 36 rings, +-3 3.20 / 3.52 and 4.43 / 3.74; 100 000 particles of 200:
-// 109 / 90).  Not with the runner-up, for which every pair is evaluated twice (90 px: 3.88 /
-// 5.24), nor for few rings, whose operand bounds little work (24 px, 9 rings, +-2: 0.77 / 1.01).
-bool few_refs(const Refset& rs, bool cc2) { return rs.g.precision != kFP32 && rs.n_kt <= 2 && rs.R4 > 6 && !cc2; }
+// Tile pairs (of 8 rows and 8 references) that cost what a particle's bounds and its steps of
+// evaluation do.  (The more rings, the shorter those steps are beside a tile pair: fewer pairs
+// stay live.  Up to 12 rings the bounds' own contraction is short; FP32 from 37 rings on,
+// a tile pair's operand is streamed; with the runner-up every pair is evaluated twice.)
+int particle_tiles(const Refset& rs, const Plan& p, bool cc2) {
+  if (rs.g.precision == kFP32) return cc2 ? 2 : (rs.R4 <= 9 ? 4 : 1);
+  if (cc2) return 2;
+  return p.S <= 9 ? 3 : (rs.R4 > 3 && rs.R4 <= 7 ? 12 : 5);
+}
 
-// Few pairs at any number of particles.
+// Few pairs per particle, at any number of particles.  In 16 bits one or two reference tiles
+// are, up to +-3: on particles of these references the two ways take about the same, on
+// others', which keep more pairs live, the bounds take longer (4000 particles, 10
+// references, bounds / every pair, ms, of these references and of 80: BF16 64 px, +-2 1.74 /
+// 1.65 and 2.11 / 1.64; 90 px, 36 rings, +-3 3.20 / 3.52 and 4.43 / 3.74; 100 000 particles of
+// 200: 109 / 90; FP32 146 / 147; with the runner-up 3.88 / 5.24; 24 px, 9 rings, +-2: 0.77 /
+// 1.01).  Without shifts a step holds at most 8 pairs, of one row: 64 px, 5000
+// references, 2000 particles FP32 8.0 / 6.5 ms, BF16 6.7 / 4.3.
 bool few_each(const Refset& rs, const Plan& p, bool cc2) {
-  return p.S == 1 || few_refs(rs, cc2) || p.S * rs.n_kt <= 4 * kRowTile;
+  const int pairs = p.S * rs.n_kt;
+  return p.S == 1 || pairs <= particle_tiles(rs, p, cc2) * kRowTile ||
+         (rs.g.precision != kFP32 && rs.R4 > 3 && !cc2 && rs.n_kt <= 2 && pairs <= 100);
 }
 
 // A call of few pairs, or of few pairs per particle, takes the unpruned way: with
 // every pair of a few row and reference tiles spread over the CUs it ends before the
-// pruned way's chain of dependent steps does, and a particle costs the evaluation
-// about what four tile pairs do, however few it has.  The line was fitted to 2400 calls
-// (K 4 to 200, 30 to 3000 particles, +-0 to +-4, 3 to 62 rings, SNR 0.05 and 0.2; on average
-// 1 % above the faster way; where they cross, the less favourable data decides).  FP32: a tile pair costs more the more rings there are (7.6 us
-// of a CU at 3, 18 at 36, more where the operand is streamed), and the bounds
-// leave fewer pairs.  Pruned against unpruned (us; tile pairs per CU), SNR 0.05: FP32 64 px,
-// 28 rings, +-2, 20 references, 200 particles 263 / 203 (7), 1000: 666 / 761 (37); 8
-// references, 3000 particles 1672 / 1530 (37); +-0, 100 references, 3000 particles 911 / 502
-// (19); 24 px, 9 rings, +-2, 100 references, 400 particles 695 / 566 (63); 76 px, 35 rings, +-3,
-// 100 references, 30 particles 284 / 226 (9), 60: 347 / 429 (19); 96 px, 46 rings, +-2, 20
-// references, 200 particles 312 / 388 (7).  BF16 64 px, +-2, 20 references, 200 particles 209 /
-// 168 (7), 1000: 512 / 523 (37); 76 px, +-3, 100 references, 30 particles 224 / 167 (9).
-// Without shifts a step holds at most 8 pairs, of one row: 64 px, 5000 references, 2000
-// particles FP32 8.0 / 6.5 ms, BF16 6.7 / 4.3.  Nor do the bounds save much of one or two
-// reference tiles (few_refs).
+// pruned way's chain of dependent steps does.  The lines were fitted to 4000 calls drawn over
+// boxes of 40 to 128 px, rings out to a third of the box up to all of it, +-1 to +-5, 5 to 300
+// references, SNR 0.05 and 0.1, particles of these references and (30 %) of others, 4 to
+// 250 tile pairs per CU (2 to 3 % above the faster way on the former, 5 on the latter), and
+// checked on 3000 with rings out to the box (1 to 2 %).  Fewer rings leave more pairs live
+// (and, FP32, a tile pair costs less).  Pruned over unpruned, geometric means at 8 to
+// 16, 32 to 64 and 128 to 260 tile pairs per CU: FP32 17 to 20 rings 2.4, 1.3, 0.92; 25 to
+// 28: 1.7, 0.93, 0.70; 33 to 36: 1.3, 0.75, 0.60; 45 to 48: 0.83, 0.46, 0.36; 16 bits 17 to 20
+// rings 1.8, 1.2, 1.1; 25 to 28: 1.4, 1.1, 0.80; 33 to 36: 1.2, 0.99, 0.75.  (Up to 12 rings:
+// 24 px, 9 rings, 100 references, 600 particles, 95 tile pairs per CU: FP32 1.1, BF16 0.54.)
+bool few_tiles(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t tiles, int64_t N, bool cc2) {
+  const int cube = rs.R4 * rs.R4 * rs.R4;
+  const int per_cu = rs.g.precision == kFP32
+                         ? (cc2 ? std::clamp(5500 / cube, 4, 150) : std::clamp(10000 / cube, 8, 150))
+                         : (rs.R4 <= 3 ? 20 : (cc2 ? std::clamp(7000 / cube, 12, 150) : std::clamp(20000 / cube, 20, 150)));
+  return tiles <= per_cu * (int64_t)c->n_cu + particle_tiles(rs, p, cc2) * N;
+}
+
+int64_t tile_pairs(const Refset& rs, const Plan& p, int64_t N) { return (N * p.S + kRowTile - 1) / kRowTile * rs.n_kt; }
+
 bool few_pairs(const mra_ctx* c, const Refset& rs, const Plan& p, int64_t N, bool cc2) {
-  if (few_each(rs, p, cc2)) return true;
-  const int64_t tiles = (N * p.S + kRowTile - 1) / kRowTile * rs.n_kt;
-  const int R4 = rs.R4, per_cu = rs.g.precision == kFP32 ? std::max(4, 5500 / (R4 * R4 * R4)) : (R4 <= 6 ? 20 : 12);
-  return tiles <= per_cu * (int64_t)c->n_cu + 4 * N;
+  return few_each(rs, p, cc2) || few_tiles(c, rs, p, tile_pairs(rs, p, N), N, cc2);
 }
 
 // Largest chunk of at most N particles whose buffers fit `bytes` (0 if not one particle).

@@ -149,14 +149,13 @@ def test_small_reference_sets_scale_into_the_bounds():
 
 
 # sizes beyond the rule on pairs, in every row here
-@pytest.mark.parametrize("precision,K,r_max,cc2,every", [
-    ("bf16", 8, 28, False, True), ("bf16", 16, 28, False, True), ("fp16", 16, 46, False, True),
-    ("bf16", 17, 28, False, False), ("fp32", 16, 28, False, False), ("bf16", 16, 28, True, False),
-    ("fp16", 16, 24, False, False)])
-def test_few_references(ctx, precision, K, r_max, cc2, every):
+@pytest.mark.parametrize("precision,K,r_max,N,cc2,every", [
+    ("bf16", 8, 28, 1600, False, True), ("bf16", 16, 28, 1300, False, True), ("fp16", 16, 46, 700, False, True),
+    ("bf16", 17, 28, 2600, False, False), ("fp32", 16, 28, 1100, False, False), ("bf16", 16, 28, 700, True, False),
+    ("fp16", 16, 12, 800, False, False)])
+def test_few_references(ctx, precision, K, r_max, N, cc2, every):
     from paper_2011_05755_amd import mra
-    N = 700 if K > 8 else 1600
-    print(f"[gpu-routes] {precision} K={K} r_max={r_max} cc2={cc2}", flush=True)
+    print(f"[gpu-routes] {precision} K={K} r_max={r_max} N={N} cc2={cc2}", flush=True)
     refs, parts = stack(2 * r_max + 8, K, 3, N, r_max)
     ctx.load_refs(0, refs, r_min=1, r_max=r_max, shift_max=3, precision=precision)
     expect = every_pair(cc2) if every else bounds_first(precision, cc2)
@@ -178,3 +177,18 @@ def test_few_references(ctx, precision, K, r_max, cc2, every):
     ctx.profile(False)
     for o in out:
         same(o.to_numpy(), {f: want[f] for f in got})
+
+
+# few rings keep many pairs live: more pairs than a box full of rings may have evaluate
+# all of them (R4 6 and 9; tile pairs per CU: 41)
+@pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("L,r_max,every", [(65, 21, True), (76, 36, False)])
+def test_few_rings(ctx, precision, L, r_max, every):
+    print(f"[gpu-routes] {precision} L={L} rings {r_max}", flush=True)
+    refs, parts = stack(L, 263, 2, 103, r_max)
+    ctx.load_refs(0, refs, r_min=1, r_max=r_max, shift_max=2, precision=precision)
+    got, ran = run(ctx, lambda: ctx.align(0, parts))
+    assert ran == (every_pair(False) if every else bounds_first(precision, False)), ran
+    ctx.set_tuning(0, prune=0)
+    want, _ = run(ctx, lambda: ctx.align(0, parts))
+    same(got, want)
