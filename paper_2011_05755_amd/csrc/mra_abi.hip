@@ -1047,28 +1047,51 @@ void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Pla
   // Stacks that share the kernels' instantiations are packed into the same waves; within a
   // group the caller's order holds.  A group is of one precision and ring bucket, and of one
   // instance of the correlation kernel if every pair is evaluated: with pruning off, or few
-  // pairs (in one reference tile, or per particle) of rows that together fill the chip; with
-  // fewer rows they join the others' waves, whose launches they need not repeat.
+  // pairs (per particle, or in all stacks of the bucket together).  Where the bucket has other
+  // stacks, whose waves can take those of few pairs, only if these are of so many rows
+  // that what they save is more than launches of their own cost (6 stacks of 100 to 150 particles,
+  // two of them of few references, BF16: 688 us in two waves, 506 in one).
+  auto bucket = [](const Refset& rs) { return 64 * rs.g.precision + ring_bucket(rs.R4); };
   auto instance = [](const Refset& rs) {
     return 8 + 64 * (rs.g.precision * 4 + rs.variant) + corr_group(rs.g.precision, rs.variant, rs.R4) * 1024;
   };
-  auto few = [&](const Refset& rs, int i) {
-    return rs.K > 1 && (few_each(rs, plans[i], false) || (rs.n_kt == 1 && few_pairs(c, rs, plans[i], stacks[i].N, false)));
+  struct Total {
+    int64_t tiles = 0, parts = 0;
+    bool others = false;
   };
-  std::map<int, int64_t> rows;
-  for (int i = 0; i < n; ++i) {
-    if (stacks[i].N <= 0 || stacks[i].out.cc2 || stacks[i].out.psi_frac) continue;
-    const Refset& rs = get_refset(c, stacks[i].refset_id);
-    if (few(rs, i)) rows[instance(rs)] += stacks[i].N * plans[i].S;
-  }
+  std::map<int, Total> total;       // by bucket
+  std::map<int, int64_t> few_rows;  // by instance
+  auto shares = [&](int i, const Refset& rs) {
+    return stacks[i].N > 0 && !stacks[i].out.cc2 && !stacks[i].out.psi_frac && rs.K > 1 && rs.prune;
+  };
+  auto few = [&](int i, const Refset& rs) {
+    const Total& b = total[bucket(rs)];
+    return few_each(rs, plans[i], false) || few_tiles(c, rs, plans[i], b.tiles, b.parts, false);
+  };
+  for (int pass = 0; pass < 2; ++pass)
+    for (int i = 0; i < n; ++i) {
+      if (stacks[i].N <= 0) continue;
+      const Refset& rs = get_refset(c, stacks[i].refset_id);
+      if (!shares(i, rs)) continue;
+      Total& b = total[bucket(rs)];
+      if (pass == 0) {
+        b.tiles += tile_pairs(rs, plans[i], stacks[i].N);
+        b.parts += stacks[i].N;
+      } else if (few(i, rs)) {
+        few_rows[instance(rs)] += stacks[i].N * plans[i].S;
+      } else {
+        b.others = true;
+      }
+    }
   auto every = [&](int i) {
     const Refset& rs = get_refset(c, stacks[i].refset_id);
-    return !rs.prune || (few(rs, i) && rows[instance(rs)] >= 2 * kRowTile * (int64_t)c->n_cu);
+    return !rs.prune || (shares(i, rs) && few(i, rs) &&
+                         (!total[bucket(rs)].others || few_rows[instance(rs)] >= 32 * kRowTile * (int64_t)c->n_cu));
   };
   auto key = [&](int i) {
     if (stacks[i].N <= 0) return 0;
     const Refset& rs = get_refset(c, stacks[i].refset_id);
-    return every(i) ? instance(rs) : 64 * rs.g.precision + ring_bucket(rs.R4);
+    return every(i) ? instance(rs) : bucket(rs);
   };
   std::vector<int> order(n), keys(n);
   for (int i = 0; i < n; ++i) {
@@ -1092,13 +1115,14 @@ void run_batch(mra_ctx* c, const mra_stack* stacks, int n, const std::vector<Pla
       run_single(c, rs, p, s.parts, s.N, &s.out);
       continue;
     }
-    // runner-up, refinement, a workspace too small, or every pair of so many rows that
-    // a launch fills the chip by itself, with an operand that stays in the last-level cache
-    // (4 stacks of 1000 particles, 8 references, BF16: 2.61 ms in a wave, 2.36 one by one): the
-    // per-chunk path
+    // runner-up, refinement, a workspace too small, or every pair of so many particles and
+    // rows that their launches fill the chip by themselves, with an operand that stays in the
+    // last-level cache (4 stacks of 1000 particles, 8 references, BF16: 2.61 ms in a wave, 2.36
+    // one by one): the per-chunk path
     const bool ev = every(i);
     const uint64_t per = particle_bytes(rs, p, !ev);
-    if (s.out.cc2 || s.out.psi_frac || per > budget / 2 || (ev && s.N * p.S >= 8 * kRowTile * (int64_t)c->n_cu)) {
+    if (s.out.cc2 || s.out.psi_frac || per > budget / 2 ||
+        (ev && s.N >= 2 * c->n_cu && s.N * p.S >= 8 * kRowTile * (int64_t)c->n_cu)) {
       align_stack(c, rs, p, s.parts, 0, s.N, &s.out, nullptr);
       continue;
     }

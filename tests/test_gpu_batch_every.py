@@ -48,3 +48,31 @@ def test_one_launch_of_each_kernel(precision, r_max, variant, cap):
                     x, y = (v.view(np.int32) if v.dtype.kind == "f" else v for v in (got[f], w[f]))
                     assert np.array_equal(x, y), (i, f, np.flatnonzero(x != y)[:5])
                 out.cc.zero_(), out.flat_index.zero_()
+
+
+# stacks of few pairs in all take every pair in one launch; a few of them beside stacks
+# that don't join those stacks' wave
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("sizes,every", [([(50, 8), (41, 8), (50, 5), (33, 1)], True), ([(8, 300), (200, 500)], False)])
+def test_way_of_a_batch(precision, sizes, every):
+    from paper_2011_05755_amd import mra, synth
+    print(f"[gpu-batch-every] {precision} {sizes}", flush=True)
+    stacks, want = [], []
+    with mra.Context(0) as ctx:
+        for i, (K, N) in enumerate(sizes):
+            blobs = synth.make_blobs(K, 64, seed=(i, K), rho_max=28.0)
+            parts, _ = synth.make_particles(blobs, N, 2, 0.1, seed=(i, 1), device=DEV)
+            ctx.load_refs(i, synth.render_refs(blobs).to(DEV), r_min=1, r_max=28, shift_max=2, precision=precision)
+            want.append(ctx.align(i, parts).to_numpy())
+            stacks.append((i, parts, -1, mra.AlignResult.empty(N, DEV)))
+        ctx.profile(True)
+        ctx.align_batch(stacks)
+        torch.cuda.synchronize()
+        ran = {g: ctx.profile_read(g)[1] for g in ("polar", "bound", "corr")}
+        ctx.profile(False)
+    assert ran == dict(polar=1, bound=int(not every), corr=int(every)), ran
+    for (i, _, _, out), w in zip(stacks, want):
+        got = out.to_numpy()
+        for f in got:
+            x, y = (v.view(np.int32) if v.dtype.kind == "f" else v for v in (got[f], w[f]))
+            assert np.array_equal(x, y), (i, f, np.flatnonzero(x != y)[:5])
