@@ -36,9 +36,9 @@ def same(a, b, what):
 
 
 @pytest.mark.parametrize("precision", PRECISIONS)
-@pytest.mark.parametrize("L,r_max,T,K,N", [(24, 9, 0, 200, 900), (64, 32, 1, 41, 400), (64, 28, 2, 41, 200),
-                                           (76, 35, 3, 33, 150), (90, 40, 2, 48, 180), (110, 48, 2, 43, 170),
-                                           (140, 64, 4, 17, 110), (160, 64, 8, 17, 60)])
+@pytest.mark.parametrize("L,r_max,T,K,N", [(24, 9, 0, 200, 900), (64, 32, 1, 41, 2800), (64, 28, 2, 41, 2300),
+                                           (76, 35, 3, 33, 300), (90, 40, 2, 48, 400), (110, 48, 2, 43, 400),
+                                           (140, 64, 4, 17, 220), (160, 64, 8, 17, 60)])
 def test_dense_particles(precision, L, r_max, T, K, N):
     from paper_2011_05755_amd import mra
     print(f"[gpu-dense] {precision} L={L} T={T} K={K} N={N}", flush=True)
@@ -59,8 +59,8 @@ def test_dense_particles_in_a_batch(precision):
     print(f"[gpu-dense] {precision} batch", flush=True)
     with mra.Context(0) as ctx:
         stacks, want = [], []
-        for i, (L, r_max, T, K, N) in enumerate([(64, 28, 2, 40, 150), (76, 32, 1, 60, 90), (64, 25, 3, 17, 70),
-                                                 (90, 33, 2, 30, 130), (96, 36, 2, 25, 50)]):
+        for i, (L, r_max, T, K, N) in enumerate([(64, 28, 2, 100, 300), (76, 32, 1, 150, 300), (64, 25, 3, 100, 150),
+                                                 (90, 33, 2, 100, 150), (96, 36, 2, 100, 150)]):
             refs, parts = stack(L, K, T, N, r_max, seed=20 + i)
             ctx.load_refs(i, refs, r_min=1, r_max=r_max, shift_max=T, precision=precision)
             ctx.set_tuning(i, prune=0)
